@@ -2,9 +2,11 @@
 
 Argument marshalling only: every step of the path runs inside the HIP library.  PyTorch is
 used for device memory and for the current stream, nothing else.  Importing this module
-without a built library raises: there is no fallback path.
+without a built library raises: there is no fallback path.  The calls of a serving loop
+(w3lr_gemm, MoELayer.forward, pack_w3) are marshalled in native code (csrc/torch_call.cpp).
 """
 import ctypes
+import importlib.util
 import os
 
 import numpy as np
@@ -56,6 +58,24 @@ class Expert(ctypes.Structure):
 
 
 _lib = None
+_native = None
+NATIVE_PATH = os.path.join(_HERE, "lib", "_milo_torch.so")
+# the entry points the native marshalling calls (csrc/torch_call.cpp)
+_NATIVE_ENTRIES = ("milo_w3_packed_bytes", "milo_pack_w3", "milo_pack_w3_sym", "milo_w3lr_gemm_workspace",
+                   "milo_w3lr_gemm_flags", "milo_workspace_init", "milo_moe_w3lr_workspace", "milo_moe_w3lr_forward_flags")
+
+
+def _load_native():
+    global _native
+    if _native is None:
+        if not os.path.exists(NATIVE_PATH):
+            raise ImportError(f"{NATIVE_PATH} is not built; run __graft_entry__.build() "
+                              "(or paper_2504_02658_amd/csrc/build.sh)")
+        spec = importlib.util.spec_from_file_location("_milo_torch", NATIVE_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _native = module
+    return _native
 
 
 def bind(path):
@@ -113,6 +133,7 @@ def bind(path):
     L.milo_moe_w3lr_forward.argtypes = [vp, i64, i64, i64, vp, ci, ci, vp, vp, ci, vp, vp, sz, vp]
     L.milo_moe_w3lr_routing_status.restype = ci
     L.milo_moe_w3lr_routing_status.argtypes = [vp, vp]
+    L.entries = _load_native().entries({n: ctypes.cast(getattr(L, n), vp).value for n in _NATIVE_ENTRIES})
     return L
 
 
@@ -191,13 +212,12 @@ def packed_bytes(N, K):
 
 def pack_w3(W, group_size=64, symmetric=False):
     """milo_pack_w3 (or milo_pack_w3_sym): fp32 CUDA weight [N, K] -> PackedWeight (no compensator)."""
-    W = _dev(W, torch.float32, "W")
+    entries = lib().entries
+    q3 = _native.pack(entries, W, group_size, symmetric)
+    if q3.__class__ is int:
+        raise MiloError(q3, "milo_pack_w3_sym" if symmetric else "milo_pack_w3")
     N, K = W.shape
-    nbytes = packed_bytes(N, K)
-    q3 = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=W.device)
-    fn, name = (lib().milo_pack_w3_sym, "milo_pack_w3_sym") if symmetric else (lib().milo_pack_w3, "milo_pack_w3")
-    _check(fn(_ptr(W), N, K, group_size, _ptr(q3), _stream()), name)
-    return PackedWeight(N, K, q3[:nbytes], flags=W3_SYMMETRIC if symmetric else 0)
+    return PackedWeight(N, K, q3, flags=W3_SYMMETRIC if symmetric else 0)
 
 
 def pack_lr3(U, V):
@@ -272,27 +292,11 @@ def gemm_workspace_bytes(M, N, K, r):
 
 def w3lr_gemm(X, pw, out=None, workspace=None):
     """milo_w3lr_gemm: Y = X dequant(Q3)^T + (X V^T) U^T."""
-    bf = isinstance(X, torch.Tensor) and X.dtype == torch.bfloat16
-    X = _dev(X, torch.bfloat16 if bf else torch.float16, "X")
-    M, K = X.shape
-    if K != pw.K:
-        raise ValueError("X and weight disagree on K")
-    if pw.U is not None and not (pw.flags & LR_INT3) and pw.U.dtype != X.dtype:
-        raise TypeError("the compensator and the activations must have the same 16-bit type")
-    if out is None:
-        out = torch.empty((M, pw.N), dtype=X.dtype, device=X.device)
-    need = gemm_workspace_bytes(M, pw.N, K, pw.r)
-    if workspace is None:
-        workspace = new_workspace(need, X.device)
-    flags = pw.flags | (ACT_BF16 if bf else 0)
-    if flags == 0:
-        _check(lib().milo_w3lr_gemm(_ptr(X), M, pw.N, K, _ptr(pw.q3), _ptr(pw.U), _ptr(pw.V), pw.r, _ptr(out),
-                                    _ptr(workspace), workspace.numel(), _stream()), "milo_w3lr_gemm")
-    else:
-        _check(lib().milo_w3lr_gemm_flags(_ptr(X), M, pw.N, K, _ptr(pw.q3), _ptr(pw.U), _ptr(pw.V), pw.r, flags,
-                                          _ptr(out), _ptr(workspace), workspace.numel(), _stream()),
-               "milo_w3lr_gemm_flags")
-    return out
+    entries = lib().entries
+    Y = _native.gemm(entries, X, pw.q3, pw.U, pw.V, pw.N, pw.K, pw._r, pw.flags, out, workspace)
+    if Y.__class__ is int:
+        raise MiloError(Y, "milo_w3lr_gemm")
+    return Y
 
 
 def w3lr_gemm_static(X, pw, out=None):
@@ -332,31 +336,18 @@ class MoELayer:
         return int(lib().milo_moe_w3lr_workspace(T, self.H, self.F, self.E, topk, self.r_max))
 
     def forward(self, X, ids, gates, out=None, workspace=None):
-        dt = torch.bfloat16 if self.flags & ACT_BF16 else torch.float16
-        X = _dev(X, dt, "X")
-        ids = _dev(ids, torch.int32, "ids")
-        gates = _dev(gates, torch.float32, "gates")
-        T, H = X.shape
-        topk = ids.shape[1]
-        need = self.workspace_bytes(T, topk)
-        if workspace is None:
-            if self._ws is None or self._ws.numel() < need:
-                self._ws = new_workspace(need, X.device)
-            workspace = self._ws
-        if out is None:
-            out = torch.empty((T, H), dtype=dt, device=X.device)
-        if self.flags:
-            _check(lib().milo_moe_w3lr_forward_flags(_ptr(X), T, H, self.F, _ptr(self.table), self.E,
-                                                     self.r_max, _ptr(ids), _ptr(gates), topk, self.flags, _ptr(out),
-                                                     _ptr(workspace), workspace.numel(), _stream()),
-                   "milo_moe_w3lr_forward_flags")
-        else:
-            _check(lib().milo_moe_w3lr_forward(_ptr(X), T, H, self.F, _ptr(self.table), self.E,
-                                               self.r_max, _ptr(ids), _ptr(gates), topk, _ptr(out),
-                                               _ptr(workspace), workspace.numel(), _stream()),
-                   "milo_moe_w3lr_forward")
-        self.last_workspace = workspace
-        return out
+        entries = lib().entries
+        ws = self._ws if workspace is None else workspace
+        Y = _native.moe(entries, X, ids, gates, self.table, self.H, self.F, self.E, self.r_max, self.flags, out, ws,
+                        workspace is None)
+        if Y.__class__ is int and Y < 0:            # no workspace of the layer's own yet, or too small a one
+            self._ws = ws = new_workspace(-Y, X.device)
+            Y = _native.moe(entries, X, ids, gates, self.table, self.H, self.F, self.E, self.r_max, self.flags, out, ws,
+                            False)
+        if Y.__class__ is int:
+            raise MiloError(Y, "milo_moe_w3lr_forward")
+        self.last_workspace = ws
+        return Y
 
     def routing_status(self):
         return int(lib().milo_moe_w3lr_routing_status(_ptr(self.last_workspace), _stream()))

@@ -15,6 +15,11 @@ hipcc $FLAGS $PRELOAD -c gemm_decode.hip -o _build/gemm_decode.o & pids+=($!)
 hipcc $FLAGS -c moe.hip -o _build/moe.o & pids+=($!)
 hipcc $FLAGS -c api.hip -o _build/api.o & pids+=($!)
 hipcc $FLAGS -c gemm_static.hip -o _build/gemm_static.o & pids+=($!)
+# the native marshalling of api.py (host code only, against the installed PyTorch)
+read -r TORCH_DIR CXX_ABI PY_INC < <(python3 -c "import os, sysconfig, torch; print(os.path.dirname(torch.__file__), int(torch._C._GLIBCXX_USE_CXX11_ABI), sysconfig.get_paths()['include'])")
+g++ -O2 -std=c++17 -fPIC -shared -D__HIP_PLATFORM_AMD__=1 -DUSE_ROCM=1 -D_GLIBCXX_USE_CXX11_ABI=$CXX_ABI \
+    -I"$TORCH_DIR/include" -I"$TORCH_DIR/include/torch/csrc/api/include" -I"$PY_INC" -I/opt/rocm/include torch_call.cpp \
+    -L"$TORCH_DIR/lib" -ltorch_python -ltorch -ltorch_cpu -ltorch_hip -lc10 -lc10_hip -o "$OUT/_milo_torch.so" & pids+=($!)
 # the same two GEMM kernels with every hand-counted wait replaced by a wait for everything
 hipcc $FLAGS -DMILO_FULL_WAITS -c gemm_tiled.hip -o _build/gemm_tiled_fw.o & pids+=($!)
 hipcc $FLAGS $PRELOAD -DMILO_FULL_WAITS -c gemm_decode.hip -o _build/gemm_decode_fw.o & pids+=($!)
@@ -102,4 +107,4 @@ for lib in libmilo.so libmilo_fullwaits.so; do
         exit 1
     fi
 done
-echo "built $OUT/libmilo.so and $OUT/libmilo_fullwaits.so"
+echo "built $OUT/libmilo.so, $OUT/libmilo_fullwaits.so and $OUT/_milo_torch.so"
