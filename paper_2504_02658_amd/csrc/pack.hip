@@ -10,91 +10,89 @@
 
 namespace milo {
 
-// SYM = false: asymmetric quantizer (Eq. wq).  SYM = true: the symmetric INT3 quantizer (Eq.
-// symm_int3) in the same storage: the scale word holds the step 2 * max|w| / 7, the zero word 4.
-// The source is element (n, k) = W[n * row_stride + k * col_stride] for n < n_valid and zero for the
-// rows from n_valid up to N (a plain row-major weight has row_stride = K, col_stride = 1, n_valid = N;
-// the compensator factors of milo_pack_lr3 come transposed or with padded rows).
+// One quantization group: scale, zero-point and codes (as whole floats).  SYM = false: asymmetric quantizer
+// (Eq. wq).  SYM = true: the symmetric INT3 quantizer (Eq. symm_int3) in the same storage: the scale word
+// holds the step 2 * max|w| / 7, the zero word 4.
 template <bool SYM>
-__global__ __launch_bounds__(kPackThreads) void pack_w3_kernel(
-    const float* __restrict__ W, int64_t N, int64_t K, int64_t row_stride, int64_t col_stride, int64_t n_valid,
-    uint32_t* __restrict__ planeA, uint32_t* __restrict__ planeB) {
-    const int64_t G = K / kGroup;
-    const int64_t total = N * G;
-    const int64_t gu = (int64_t)blockIdx.x * kUnitsPerBlock + (threadIdx.x >> 4);
-    const int l16 = threadIdx.x & 15;
-    if (gu >= total) return;          // whole 16-lane groups leave together
-    const int64_t n = gu / G;
-    const int64_t g = gu - n * G;
-
-    float4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (n < n_valid) {
-        const float* src = W + n * row_stride + (g * kGroup + 4 * l16) * col_stride;
-        if (col_stride == 1) {
-            v = *reinterpret_cast<const float4*>(src);
-        } else {
-            v.x = src[0];
-            v.y = src[col_stride];
-            v.z = src[2 * col_stride];
-            v.w = src[3 * col_stride];
-        }
-    }
-    float mn = fminf(fminf(v.x, v.y), fminf(v.z, v.w));
-    float mx = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
+__device__ __forceinline__ uint32_t quantize_group(float (&v)[64]) {
+    float mn = v[0], mx = v[0];
 #pragma unroll
-    for (int m = 1; m < 16; m <<= 1) {
-        mn = fminf(mn, shfl_xor16(mn, m));
-        mx = fmaxf(mx, shfl_xor16(mx, m));
+    for (int i = 1; i < 64; ++i) {
+        mn = fminf(mn, v[i]);
+        mx = fmaxf(mx, v[i]);
     }
-
-    f16 s16, z16;
-    uint32_t q[4];
-    const float in[4] = {v.x, v.y, v.z, v.w};
+    const float span = SYM ? fmaxf(mx, -mn) + fmaxf(mx, -mn) : mx - mn;      // (SYM: twice the largest magnitude)
+    f16 s16 = (f16)(span / 7.0f), z16;
+    float sf = (float)s16;
+    float lift;                             // what is added to w / s before rounding
+    const bool degenerate = !(sf > 0.0f && sf <= 65504.0f);                  // zero, NaN or overflowed scale
+    if (degenerate) s16 = (f16)1.0f;
     if (SYM) {
-        const float amax = fmaxf(mx, -mn);              // largest magnitude of the group
-        const float s32 = (amax + amax) / 7.0f;
-        s16 = (f16)s32;
-        const float sf = (float)s16;
         z16 = (f16)4.0f;
-        if (!(sf > 0.0f && sf <= 65504.0f)) {           // zero, NaN or overflowed step: all codes 4
-            s16 = (f16)1.0f;
-            q[0] = q[1] = q[2] = q[3] = 4u;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float t = in[i] / sf;
-                t = __builtin_rintf(t);
-                t = t + 4.0f;
-                t = fminf(fmaxf(t, 0.0f), 7.0f);
-                q[i] = (uint32_t)t;
-            }
-        }
+        lift = 4.0f;
     } else {
-        const float s32 = (mx - mn) / 7.0f;
-        s16 = (f16)s32;
-        const float sf = (float)s16;
-        const bool degenerate = !(sf > 0.0f && sf <= 65504.0f);   // zero, NaN or overflowed scale
-        if (degenerate) {
-            s16 = (f16)1.0f;
-            z16 = (f16)(-mn);
-            q[0] = q[1] = q[2] = q[3] = 0u;
-        } else {
-            float z = __builtin_rintf((-mn) / sf);
-            z = fminf(fmaxf(z, -65504.0f), 65504.0f);
-            z16 = (f16)z;
-            const float zf = (float)z16;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float t = in[i] / sf;
-                t = t + zf;
-                t = __builtin_rintf(t);
-                t = fminf(fmaxf(t, 0.0f), 7.0f);
-                q[i] = (uint32_t)t;
-            }
-        }
+        float z = __builtin_rintf((-mn) / sf);
+        z = fminf(fmaxf(z, -65504.0f), 65504.0f);
+        z16 = degenerate ? (f16)(-mn) : (f16)z;
+        lift = (float)z16;
     }
+    const float inv = 1.0f / sf;
+#pragma unroll
+    for (int i = 0; i < 64; ++i) {
+        float t = div_by(v[i], sf, inv);
+        if (SYM) {                          // rounded before the shift, so that it is exact
+            t = __builtin_rintf(t);
+            t = t + 4.0f;
+        } else {
+            t = t + lift;
+            t = __builtin_rintf(t);
+        }
+        t = fminf(fmaxf(t, 0.0f), 7.0f);
+        v[i] = degenerate ? (SYM ? 4.0f : 0.0f) : t;
+    }
+    return scale_zero_word(s16, z16);
+}
 
-    store_unit(q, l16, s16, z16, unit_index(n, g, G), planeA, planeB);
+// Row n of the source is W + n * row_stride for n < n_valid and zeros for the rows from n_valid up to N.
+template <bool SYM>
+__global__ __launch_bounds__(kRowBlockThreads) void pack_w3_kernel(const float* __restrict__ W, int64_t N, int64_t K,
+                                                                   int64_t row_stride, int64_t n_valid,
+                                                                   uint32_t* __restrict__ planeA, uint32_t* __restrict__ planeB) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[kRowBlockWaves * kRowBlockBytes];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t G = K / kGroup;
+    int64_t n0, g0;
+    if (!row_block_item(N, G, wave, &n0, &g0)) return;
+    unsigned char* const area = lds + wave * kRowBlockBytes;
+    stage_row_block(W, row_stride, n0, n_valid, g0, K, area, lane);
+    wait_vmem();
+    float v[64];
+    read_unit64(area, lane, v);
+    if (g0 + (lane >> 4) >= G) return;
+    const uint32_t sz = quantize_group<SYM>(v);
+    uint32_t d[6];
+    unit_words(v, d);
+    store_row_block_unit(d, sz, ((n0 >> 4) * G + g0) * 16 + lane, planeA, planeB);
+}
+
+// The transposed factor of milo_pack_lr3 (symmetric quantizer): element (n, k) = W[n + k * col_stride] for
+// n < n_valid, zero above.  A few rows, small: one lane per unit, straight from memory (neighbouring lanes
+// are neighbouring rows, which are adjacent here).
+__global__ __launch_bounds__(256) void pack_w3_transposed_kernel(const float* __restrict__ W, int64_t N, int64_t K,
+                                                                 int64_t col_stride, int64_t n_valid,
+                                                                 uint32_t* __restrict__ planeA, uint32_t* __restrict__ planeB) {
+    const int64_t G = K / kGroup;
+    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= N * G) return;
+    const int64_t rest = u >> 4, n = (rest / G) * 16 + (u & 15), g = rest % G;
+    float v[64];
+#pragma unroll
+    for (int i = 0; i < 64; ++i) v[i] = n < n_valid ? W[n + (g * kGroup + i) * col_stride] : 0.0f;
+    const uint32_t sz = quantize_group<true>(v);
+    uint32_t d[6];
+    unit_words(v, d);
+    store_row_block_unit(d, sz, u, planeA, planeB);
 }
 
 // One thread per unit: unpack to bytes / dequantize to fp16.  Test aids, not tuned.
@@ -161,13 +159,12 @@ static int pack_launch(const float* W, int64_t N, int64_t K, int group_size, voi
     if (group_size != kGroup) return MILO_ERR_GROUP;
     if (!weight_shape_ok(N, K)) return MILO_ERR_SHAPE;
     if (!aligned16(W) || !aligned16(q3)) return MILO_ERR_ALIGN;
-    const int64_t units = N * (K / kGroup);
-    const int64_t blocks = (units + kUnitsPerBlock - 1) / kUnitsPerBlock;
+    const int64_t blocks = row_block_grid(N, K);
     if (blocks > 0x7fffffff) return MILO_ERR_SHAPE;
     uint32_t* planeA = reinterpret_cast<uint32_t*>(q3);
     uint32_t* planeB = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(q3) + (N * K) / 4);
-    pack_w3_kernel<SYM><<<dim3((unsigned)blocks), dim3(kPackThreads), 0, (hipStream_t)stream>>>(W, N, K, K, 1, N, planeA,
-                                                                                               planeB);
+    pack_w3_kernel<SYM><<<dim3((unsigned)blocks), dim3(kRowBlockThreads), 0, (hipStream_t)stream>>>(W, N, K, K, N, planeA,
+                                                                                                   planeB);
     return launch_status();
 }
 
@@ -191,20 +188,19 @@ extern "C" int milo_pack_lr3(const float* U, const float* V, int64_t N, int64_t 
     const int64_t rp = rank_rows(r);
     // U^T: [rp x N], element (j, n) = U[n * r + j], groups of 64 along N
     {
-        const int64_t units = rp * (N / kGroup), blocks = (units + kUnitsPerBlock - 1) / kUnitsPerBlock;
+        const int64_t units = rp * (N / kGroup), blocks = (units + 255) / 256;
         uint32_t* planeA = reinterpret_cast<uint32_t*>(u3);
         uint32_t* planeB = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(u3) + (rp * N) / 4);
-        pack_w3_kernel<true><<<dim3((unsigned)blocks), dim3(kPackThreads), 0, (hipStream_t)stream>>>(U, rp, N, 1, r, r,
-                                                                                                planeA, planeB);
+        pack_w3_transposed_kernel<<<dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream>>>(U, rp, N, r, r, planeA, planeB);
         if (launch_status() != MILO_OK) return MILO_ERR_HIP;
     }
     // V: [rp x K], element (j, k) = V[j * K + k], groups of 64 along K
     {
-        const int64_t units = rp * (K / kGroup), blocks = (units + kUnitsPerBlock - 1) / kUnitsPerBlock;
+        const int64_t blocks = row_block_grid(rp, K);
         uint32_t* planeA = reinterpret_cast<uint32_t*>(v3);
         uint32_t* planeB = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(v3) + (rp * K) / 4);
-        pack_w3_kernel<true><<<dim3((unsigned)blocks), dim3(kPackThreads), 0, (hipStream_t)stream>>>(V, rp, K, K, 1, r,
-                                                                                                planeA, planeB);
+        pack_w3_kernel<true><<<dim3((unsigned)blocks), dim3(kRowBlockThreads), 0, (hipStream_t)stream>>>(V, rp, K, K, r, planeA,
+                                                                                                    planeB);
     }
     return launch_status();
 }

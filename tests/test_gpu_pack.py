@@ -106,3 +106,20 @@ def test_pack_sym_bit_exact():
     W[:, 256:320] = np.abs(W[:, 256:320])                 # one-sided group
     (q, s, z), _ = _assert_pack_equal(W, "symmetric edge groups", symmetric=True)
     assert np.all(q[:, 0:64] == 4) and np.all(s[:, 0] == np.float16(1))
+
+
+@pytest.mark.parametrize("N,K", [(16, 128), (32, 256), (64, 320), (16, 4160)])
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_pack_quotients_next_to_ties(N, K, symmetric):
+    # A lane quantizes a whole group and divides by its scale with a reciprocal and two corrections, which has
+    # to give the correctly rounded quotient: weights one unit in the last place around (integer + 1/2) scales
+    # turn any other rounding into another code.  Sizes: one to four groups in a wave's last column block.
+    rng = np.random.default_rng(N + K)
+    s = (2.0 ** rng.uniform(-12, 2, (N, K // 64, 1))).astype(np.float16).astype(np.float32)
+    half = (rng.integers(-4, 4, (N, K // 64, 64)) + np.float32(0.5)).astype(np.float32)
+    half[..., 0], half[..., 1] = -3.5, 3.5                # the extremes of the group: its scale is s
+    W = half * s
+    side = rng.integers(-1, 2, W.shape)
+    near = np.nextafter(W, np.where(side < 0, -np.inf, np.inf).astype(np.float32))
+    W[..., 2:] = np.where(side == 0, W, near)[..., 2:]
+    _assert_pack_equal(np.ascontiguousarray(W.reshape(N, K)), f"near ties {N}x{K}", symmetric)
