@@ -117,12 +117,12 @@ static bool gemm_shape_ok(int64_t M, int64_t N, int64_t K) {
 
 extern "C" size_t milo_w3lr_gemm_workspace(int64_t M, int64_t N, int64_t K, int r) {
     if (!gemm_shape_ok(M, N, K) || r < 0) return 0;
-    if (gemm_takes_decode(M, N, K, r)) return decode_workspace_bytes(r, K);
-    // control words | four flag words per 32-row tile | T = X V^T, fp16 [M x pad16(r)] | its fp32
+    if (gemm_takes_decode(M, N, K, r)) return decode_workspace_bytes(N, K, r);
+    // head (control words, hand-over area of the decode kernel) | four flag words per 32-row tile | T = X V^T, fp16 [M x pad16(r)] | its fp32
     // partials per part of K | with K splits, their fp32 partial sums [M x N] each
     const size_t parts = (size_t)gemm_t_parts(M, N, K, r);
     const int splits = gemm_splits(M, N, K, r);
-    return 256 + align_up((size_t)((M + 31) / 32) * 16, 256) +
+    return kGemmHeadBytes + align_up((size_t)((M + 31) / 32) * 16, 256) +
            align_up((size_t)M * (size_t)rank_pad(r) * 2 + 256, 256) +
            align_up(parts * (size_t)M * (size_t)rank_pad(r) * 4 + 256, 256) +
            (splits > 1 ? align_up((size_t)splits * (size_t)M * (size_t)N * 4, 256) : 0);
@@ -174,8 +174,8 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     }
     char* ws = reinterpret_cast<char*>(workspace);
     uint32_t* ctrl = reinterpret_cast<uint32_t*>(ws);
-    uint32_t* tile_flags = reinterpret_cast<uint32_t*>(ws + 256);
-    f16* T = reinterpret_cast<f16*>(ws + 256 + align_up((size_t)((M + 31) / 32) * 16, 256));
+    uint32_t* tile_flags = reinterpret_cast<uint32_t*>(ws + kGemmHeadBytes);
+    f16* T = reinterpret_cast<f16*>(ws + kGemmHeadBytes + align_up((size_t)((M + 31) / 32) * 16, 256));
     const int64_t ldt = rank_pad(r);
 
     const int mb = gemm_mb(M);

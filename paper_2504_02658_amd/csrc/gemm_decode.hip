@@ -24,14 +24,23 @@
 // converts while the later waves of its SIMD still queue.
 //
 // Low-rank term.  The first `nt` workgroups do no streaming: each computes whole blocks of 16
-// ranks of T = X V^T over a part of K (the parts are never added up across workgroups), writes
-// them as fp16 and is counted.  The streaming workgroups only need T in their epilogue, where
-// they add T U^T with a few more MFMAs.  Wave 0 of a streaming workgroup, whose requests are
-// accepted first and which is therefore done long before the others, fetches the U rows and,
-// once all workers have been counted, T into LDS.  The workers never wait for anything, they have
-// the lowest workgroup ids, and the grid never exceeds what the device keeps resident, so that
-// wait always ends.  Data that crosses workgroups is written and read with device-coherent
-// accesses, and worker 0 restores the control words to zero for the next launch.
+// ranks of T = X V^T over a part of K (the parts are never added up across workgroups).  The
+// streaming workgroups only need T in their epilogue, where they add T U^T with a few more MFMAs.
+// Wave 0 of a streaming workgroup, whose requests are accepted first and which is therefore done
+// long before the others, fetches the U rows and T into LDS.  The workers never wait for anything,
+// they have the lowest workgroup ids, and the grid never exceeds what the device keeps resident, so
+// that wait always ends.  Data that crosses workgroups is written and read with device-coherent
+// accesses.
+//
+// The hand-over of T (up to rank 128) takes one trip through memory: T travels in 8-byte granules of
+// two values and a 32-bit tag that names the launch, stored and polled as single 64-bit accesses, so
+// a consumer polls the data itself.  (Stores, their acknowledgement, a counter, a poll of the counter
+// and then the loads were five trips of 0.7 to 2 us, the longest chain of every decode launch, and
+// clearing the counter at the end waited for every consumer to sign off.)  The tag comes from
+// counters that only ever grow: each launch adds exactly 2^16 to every one of them, a consumer adds
+// its share after it has read T, so whoever reads a counter before that finds the number of launches
+// before this one in its upper bits.  Nothing has to be cleared between launches, in a replayed
+// graph neither.  M = 16, N = K = 2688, r = 32: 6.2 us, with a counter of finished workers 7.2.
 #include <stdlib.h>
 
 #include <type_traits>
@@ -110,8 +119,15 @@ __device__ __forceinline__ void read_bfrags(const unsigned char* slot, int j16, 
             f16x8, *reinterpret_cast<const u32x4*>(slot + j16 * 512 + (((8 * q + t) ^ j16) << 4)));
 }
 
-// T worker.  Work item (jb, h) = rank block jb (16 ranks) over K part h (kDecTWaves chunks of 256
-// columns, one per wave): T_h[m][j] = sum over the part of X[m][k] V[j][k].  The parts are NOT
+// The tag of this launch, from counter `group`: to be read before this workgroup's own contribution.
+__device__ __forceinline__ uint32_t decode_tag(const DecodeArgs& a, uint32_t group) {
+    const unsigned long long v =
+        __hip_atomic_load(a.epoch + group * kDecGroupStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return (uint32_t)(v >> 16) + 1u;
+}
+
+// T worker.  Work item (jb, h) = rank block jb (16 ranks) over K part h (kDecTWaves x t_chunks
+// chunks of 256 columns, t_chunks per wave): T_h[m][j] = sum over the part of X[m][k] V[j][k].  The parts are NOT
 // added up: the streaming workgroups multiply every T_h with U, which gives the same sum without
 // a reduction across workgroups.  Both operands are staged like the activations of the main
 // path (coalesced 1-KB buffer-to-LDS copies into a wave-private slot, xor-swizzled), and all
@@ -121,7 +137,9 @@ __device__ __forceinline__ void read_bfrags(const unsigned char* slot, int j16, 
 // the unit of rank 16 jb + lane % 16, group 4c + lane / 16, exactly as a streaming wave does for a
 // row block, and converts it with the zero-point-free conversion (the quantizer is symmetric).
 // BF: activations, V and T are bf16 (MILO_ACT_BF16).
-template <int XC, bool Q, bool BF>
+// TAG: T leaves as tagged granules (see the head of this file), else as plain 16-bit rows with a
+// counter of finished workers.
+template <int XC, bool Q, bool BF, bool TAG>
 __device__ __forceinline__ void decode_t_worker(const DecodeArgs& a, unsigned char* smem) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const bool active = wave < kDecTWaves;
@@ -131,6 +149,8 @@ __device__ __forceinline__ void decode_t_worker(const DecodeArgs& a, unsigned ch
     const BufRsrc xb = make_rsrc(a.X, (uint64_t)M * K * 2u);
     const BufRsrc vb = make_rsrc(a.w.V, (uint64_t)r * K * 2u);      // < 4 GiB (checked on the host)
     const BufRsrc tb = make_rsrc(a.T, (uint64_t)a.kh * 16u * (uint64_t)a.ldt * 2u);
+    uint32_t tag = 0u;
+    if (TAG && wave == 0) tag = decode_tag(a, 0u);
     unsigned char* const xs = smem + (wave & (kDecTWaves - 1)) * 2 * kDecSlotBytes;     // X chunk, then V chunk
     unsigned char* const vs = xs + kDecSlotBytes;
     f32x4* const red = reinterpret_cast<f32x4*>(smem);              // [wave][64 lanes], after a barrier
@@ -139,8 +159,9 @@ __device__ __forceinline__ void decode_t_worker(const DecodeArgs& a, unsigned ch
     for (int item = blockIdx.x; item < a.rblocks * a.kh; item += a.nt) {
         const int jb = item / a.kh, h = item - jb * a.kh;
         f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (active) {
-            const uint32_t c = (uint32_t)(h * kDecTWaves + wave), kc = c * 256u;
+        for (int ci = 0; active && ci < a.t_chunks; ++ci) {
+            const uint32_t c = (uint32_t)((h * a.t_chunks + ci) * kDecTWaves + wave), kc = c * 256u;
+            if (ci > 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the slots have been read
             xc.issue<XC>(xb, xs, kc, K, true);
             if (Q) {
                 const uint32_t G = K / kGroup;
@@ -186,9 +207,24 @@ __device__ __forceinline__ void decode_t_worker(const DecodeArgs& a, unsigned ch
                 for (int x = 0; x < 4; ++x) o[x] = (f16)sum[x];
                 ob = __builtin_bit_cast(u32x2, o);
             }
-            buf_store8_coherent(tb, (uint32_t)(((h * 16 + j16) * a.ldt + 16 * jb + 4 * q) * 2), ob);
+            if (TAG) {
+                // ranks 16 jb + 4 q + 0..3 = granules 2 (q % 2) and the next of lane (j16, 2 (jb % 2) + q / 2)
+                // in the fragment of k-step jb / 2
+                const uint32_t at = (((uint32_t)(h * a.nks + (jb >> 1)) * 4u + 2u * (q & 1u)) * 64u) +
+                                    ((2u * (jb & 1u) + ((uint32_t)q >> 1)) * 16u + j16);
+                __hip_atomic_store(a.tg + at, (uint64_t)tag << 32 | ob.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(a.tg + at + 64, (uint64_t)tag << 32 | ob.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                buf_store8_coherent(tb, (uint32_t)(((h * 16 + j16) * a.ldt + 16 * jb + 4 * q) * 2), ob);
+            }
         }
         __syncthreads();                                    // red is read before the slots are refilled
+    }
+    if (TAG) {
+        // counters without a consumer in this launch move on here
+        if (blockIdx.x == 0 && (uint32_t)tid < kDecGroups && (uint32_t)tid >= a.nmain)
+            atomicAdd(a.epoch + (uint32_t)tid * kDecGroupStride, 65536ull);
+        return;
     }
     // all T stores of this workgroup are complete before it is counted
     wait_vmem();
@@ -208,8 +244,50 @@ __device__ __forceinline__ void decode_wait_t(const DecodeArgs& a) {
     }
 }
 
-// LR: 0 = no low-rank term, 1 = rank a multiple of 8 and at most 128 (U and T fragments come
-// through LDS), 2 = any other rank (plain loads in the epilogue).
+// Fetches T into LDS as MFMA B fragments (K part h, k-step i -> fragment h * nks + i), polling each
+// granule until its tag is this launch's; a wait that gives up sets an error word.  Four fragments
+// are polled at a time.
+__device__ __forceinline__ void decode_fetch_t(const DecodeArgs& a, unsigned char* tlds, int lane, uint32_t group) {
+    asm volatile("" : "+v"(lane), "+s"(group));        // (what depends on them is formed here, not kept through the stream)
+    const uint32_t tag = decode_tag(a, group);
+    const uint32_t frags = (uint32_t)(a.kh * a.nks);
+#pragma unroll 1
+    for (uint32_t f0 = 0; f0 < frags; f0 += 4) {
+#pragma unroll 1
+        for (uint32_t spins = 0;; ++spins) {
+            unsigned long long g[4][4];
+#pragma unroll
+            for (uint32_t f = 0; f < 4; ++f)
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e)
+                    g[f][e] = __hip_atomic_load(a.tg + ((f0 + f < frags ? f0 + f : f0) * 4u + e) * 64u + lane,
+                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            bool ok = true;
+#pragma unroll
+            for (uint32_t f = 0; f < 4; ++f) {
+                // an odd number of 16-rank blocks leaves the upper half of the last k-step without ranks
+                const bool live = (int64_t)(((f0 + f) % (uint32_t)a.nks) * 32u + (lane >> 4) * 8u) < a.ldt;
+                u32x4 v = {0u, 0u, 0u, 0u};
+                if (live && f0 + f < frags) {
+#pragma unroll
+                    for (uint32_t e = 0; e < 4; ++e) {
+                        ok = ok && (uint32_t)(g[f][e] >> 32) == tag;
+                        v[e] = (uint32_t)g[f][e];
+                    }
+                }
+                if (f0 + f < frags) *reinterpret_cast<u32x4*>(tlds + (f0 + f) * 1024u + lane * 16) = v;
+            }
+            if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) break;
+            if (spins > (a.spin_limit >> 4)) {
+                if (lane == 0) atomicOr(a.ctrl + 3, 1u);
+                break;
+            }
+        }
+    }
+}
+
+// LR: 0 = no low-rank term, 1 = rank at most 128 (U and T fragments come through LDS), 2 = larger
+// ranks (plain loads in the epilogue).
 constexpr int kDecKS = 4;                                       // k-steps of 32 ranks, LR == 1
 constexpr int kDecULds = kDecLdsBytes;                          // U fragments [R][kDecKS][64] x 16 B
 constexpr int kDecTLds = kDecULds + 4 * kDecKS * 1024;          // T fragments [kDecTFrags][64] x 16 B
@@ -331,7 +409,7 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int nworkers = LR > 0 ? a.nt : 0;
     if (LR > 0 && (int)blockIdx.x < nworkers) {
-        decode_t_worker<XC, Q, BF>(a, smem);
+        decode_t_worker<XC, Q, BF, LR == 1>(a, smem);
     } else {
         const int j16 = lane & 15, q = lane >> 4;
         const int M = a.M;
@@ -414,37 +492,38 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
 #pragma unroll 1
                         for (int i = 0; i < ksu; ++i) {
                             const uint32_t k0 = 32u * i + 8u * q;
-                            const uint32_t off =
-                                (rb0 + b < NB && k0 < (uint32_t)r) ? (nrow * r + k0) * 2u : kOobOffset;
                             unsigned char* const dst = smem + kDecULds + (b * kDecKS + i) * 1024;
-                            __builtin_amdgcn_raw_ptr_buffer_load_lds(ub, (LdsPtr)dst, 16, off, 0, 0, 0);
+                            if ((r & 7) == 0) {
+                                const uint32_t off =
+                                    (rb0 + b < NB && k0 < (uint32_t)r) ? (nrow * r + k0) * 2u : kOobOffset;
+                                __builtin_amdgcn_raw_ptr_buffer_load_lds(ub, (LdsPtr)dst, 16, off, 0, 0, 0);
+                            } else {        // rows that are not 16-byte aligned: element by element
+                                uint32_t e[8];
+#pragma unroll
+                                for (uint32_t v = 0; v < 8; ++v)
+                                    e[v] = __builtin_amdgcn_raw_buffer_load_b16(
+                                        ub, (rb0 + b < NB && k0 + v < (uint32_t)r) ? (nrow * r + k0 + v) * 2u : kOobOffset, 0, 0);
+                                int l16 = lane * 16;
+                                asm volatile("" : "+v"(l16));
+                                *reinterpret_cast<u32x4*>(dst + l16) =
+                                    u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
+                            }
                         }
                     }
                 }
                 if (!t_ready) {
-                    decode_wait_t(a);
-                    if (LR == 1) {
-                        int f = 0;
-                        uint32_t ldt = (uint32_t)a.ldt;         // (offsets formed here, not kept from the top)
-                        asm volatile("" : "+s"(ldt));
-#pragma unroll 1
-                        for (int h = 0; h < a.kh; ++h) {
-#pragma unroll 1
-                            for (int i = 0; i < ksu; ++i, ++f) {
-                                const uint32_t k0 = 32u * i + 8u * q;
-                                const uint32_t off = (k0 < ldt) ? ((h * 16u + j16) * ldt + k0) * 2u : kOobOffset;
-                                unsigned char* const dst = smem + kDecTLds + f * 1024;
-                                __builtin_amdgcn_raw_ptr_buffer_load_lds(tb, (LdsPtr)dst, 16, off, 0, 0, 17);
-                            }
-                        }
-                    }
+                    if (LR == 1) decode_fetch_t(a, smem + kDecTLds, lane, (blockIdx.x - nworkers) % kDecGroups);
+                    else decode_wait_t(a);
                     t_ready = true;
                 }
                 wait_vmem();
                 __builtin_amdgcn_s_setprio(0);
-                // this workgroup needs the control words and (LR == 1) T in memory no more
-                if (LR == 1 && turn == 0 && lane == 0)
-                    __hip_atomic_store(a.done + (blockIdx.x - nworkers), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                // T has been read: this workgroup's share of its counter
+                if (LR == 1 && turn == 0 && lane == 0) {
+                    const uint32_t wg = blockIdx.x - nworkers;
+                    const uint32_t members = (nmain - wg % kDecGroups + kDecGroups - 1u) / kDecGroups;
+                    atomicAdd(a.epoch + (wg % kDecGroups) * kDecGroupStride, wg < kDecGroups ? 65537ull - members : 1ull);
+                }
             }
             __syncthreads();                                       // partial sums, U and T are in LDS
             if (wave < R) {
@@ -520,10 +599,9 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
     }
     // Worker 0 stays until every streaming workgroup has signed off (which each does only after
     // it has seen all workers counted), then restores the control words for the next launch.
-    // With LR == 1 the sign-offs come in the middle of the streaming work, so this wait ends
-    // before the kernel would have ended anyway.  No returning atomic on a shared word is
-    // involved: hundreds of those on one address serialize for several microseconds.
-    if (LR > 0 && blockIdx.x == 0 && wave == 0) {
+    // No returning atomic on a shared word is involved: hundreds of those on one address
+    // serialize for several microseconds.
+    if (LR == 2 && blockIdx.x == 0 && wave == 0) {
         const uint32_t nmain = a.nmain;
         bool all = false;
         for (uint32_t spins = 0; !all; ++spins) {
@@ -580,15 +658,26 @@ static DecodeKernel decode_variant_r(int R, int xc) {
         return decode_variant_xc<1, LR, SYM, Q>(xc);
     }
 }
-// bf16 activations: R x LR with all eight activation copies (no specialisation by M)
+// bf16 activations: R x LR x XC
+template <int R, int LR>
+static DecodeKernel decode_variant_bf_xc(int xc) {
+    if constexpr (LR == 2) {
+        return w3lr_decode_kernel<R, LR, 8, false, false, true>;
+    } else {
+        if (xc == 1) return w3lr_decode_kernel<R, LR, 1, false, false, true>;
+        if (xc == 2) return w3lr_decode_kernel<R, LR, 2, false, false, true>;
+        if (xc == 4) return w3lr_decode_kernel<R, LR, 4, false, false, true>;
+        return w3lr_decode_kernel<R, LR, 8, false, false, true>;
+    }
+}
 template <int LR>
-static DecodeKernel decode_variant_bf(int R) {
-    if (R == 4) return w3lr_decode_kernel<4, LR, 8, false, false, true>;
-    if (R == 2) return w3lr_decode_kernel<2, LR, 8, false, false, true>;
-    return w3lr_decode_kernel<1, LR, 8, false, false, true>;
+static DecodeKernel decode_variant_bf(int R, int xc) {
+    if (R == 4) return decode_variant_bf_xc<4, LR>(xc);
+    if (R == 2) return decode_variant_bf_xc<2, LR>(xc);
+    return decode_variant_bf_xc<1, LR>(xc);
 }
 static DecodeKernel decode_variant(int R, int lr, int xc, bool sym, bool q, bool bf = false) {
-    if (bf) return q ? nullptr : lr == 0 ? decode_variant_bf<0>(R) : lr == 1 ? decode_variant_bf<1>(R) : decode_variant_bf<2>(R);
+    if (bf) return q ? nullptr : lr == 0 ? decode_variant_bf<0>(R, xc) : lr == 1 ? decode_variant_bf<1>(R, xc) : decode_variant_bf<2>(R, xc);
     if (q) return lr == 1 ? decode_variant_r<1, false, true>(R, xc) : nullptr;
     if (sym && R == 4 && lr < 2) return lr == 0 ? decode_variant_r<0, true, false>(R, xc) : decode_variant_r<1, true, false>(R, xc);
     if (lr == 0) return decode_variant_r<0, false, false>(R, xc);
@@ -618,14 +707,36 @@ static int decode_capacity() {
     return cached[dev];
 }
 
-// K parts of the T workers: kDecTWaves chunks of 256 columns each.
-static int decode_k_parts(int64_t K) { return (int)((K + 256 * kDecTWaves - 1) / (256 * kDecTWaves)); }
+// K parts of the T workers: kDecTWaves chunks of 256 columns each, or twice that where the fragments of
+// T would not fit the consumers' LDS otherwise (rank 128 from K = 8192 on).
+static int decode_k_parts(int64_t K, int chunks) { return (int)((K + 256 * kDecTWaves * chunks - 1) / (256 * kDecTWaves * chunks)); }
+struct DecodeT {
+    bool staged;        // granules and the staged path (LR == 1)
+    int chunks, kh, nks;
+};
+static DecodeT decode_t_plan(int64_t N, int64_t K, int r) {
+    DecodeT t;
+    t.nks = (r + 31) / 32;
+    t.staged = false;
+    for (t.chunks = 1; t.chunks <= 2; ++t.chunks) {
+        t.kh = decode_k_parts(K, t.chunks);
+        if (r > 0 && r <= 32 * kDecKS && t.kh * t.nks <= kDecTFrags && (uint64_t)N * (uint64_t)r * 2u < 0xFFFFFFF0ull) {
+            t.staged = true;
+            return t;
+        }
+    }
+    t.chunks = 1;
+    t.kh = decode_k_parts(K, 1);
+    return t;
+}
 
-size_t decode_workspace_bytes(int r, int64_t K) {
+static_assert(kDecTFrags * 2048 == kDecGranuleBytes, "granules of all fragments");
+size_t decode_workspace_bytes(int64_t N, int64_t K, int r) {
     if (r <= 0) return 256;
     const size_t rblocks = ((size_t)r + 15) / 16;
-    // control words | sign-off words of the streaming workgroups | T fp16 [K parts][16 x ldt]
-    return 256 + kDecDoneBytes + align_up((size_t)decode_k_parts(K) * 16 * rblocks * 16 * 2, 256);
+    const DecodeT t = decode_t_plan(N, K, r);
+    // control words, sign-off words, counters, granules | T 16-bit [K parts][16 x ldt] of the other path
+    return kGemmHeadBytes + (t.staged ? 0 : align_up((size_t)t.kh * 16 * rblocks * 16 * 2, 256));
 }
 
 // Row blocks per workgroup (16 R rows).  Every workgroup stages all of X once per turn and streams
@@ -661,8 +772,13 @@ int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream) {
     char* ws = reinterpret_cast<char*>(workspace);
     a.ctrl = reinterpret_cast<uint32_t*>(ws);
     a.done = reinterpret_cast<uint32_t*>(ws + 256);
-    a.T = reinterpret_cast<f16*>(ws + 256 + kDecDoneBytes);
-    a.kh = decode_k_parts(a.K);
+    a.epoch = reinterpret_cast<unsigned long long*>(ws + 256 + kDecDoneBytes);
+    a.tg = reinterpret_cast<unsigned long long*>(ws + 256 + kDecDoneBytes + kDecGroups * kDecGroupStride * 8);
+    a.T = reinterpret_cast<f16*>(ws + kGemmHeadBytes);
+    const DecodeT tp = decode_t_plan(a.N, a.K, r);
+    a.kh = tp.kh;
+    a.nks = tp.nks;
+    a.t_chunks = tp.chunks;
     a.spin_limit = 1u << 24;
     // T workers: one per block of 16 ranks and K part, at most kDecMaxWorkers and never more than
     // a quarter of the resident workgroups (a worker then takes several items in turn)
@@ -682,10 +798,7 @@ int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream) {
     const int rows = 16 * R;
     const int64_t blocks = (a.N + rows - 1) / rows;
     const int grid = (int)(blocks < cap - workers ? blocks : cap - workers) + workers;
-    const bool int3 = (a.w.flags & MILO_LR_INT3) != 0;
-    const bool lds_path = ((r & 7) == 0 || int3) && r <= 32 * kDecKS && a.kh * ((r + 31) / 32) <= kDecTFrags &&
-                          (uint64_t)a.N * (uint64_t)r * 2u < 0xFFFFFFF0ull;
-    const int lr = r == 0 ? 0 : lds_path ? 1 : 2;
+    const int lr = r == 0 ? 0 : tp.staged ? 1 : 2;
     const int xc = a.M <= 2 ? 1 : a.M <= 4 ? 2 : a.M <= 8 ? 4 : 8;    // activation copies per chunk: rows 2i, 2i+1
     const bool q = r > 0 && (a.w.flags & MILO_LR_INT3) != 0;
     // an INT3 compensator only runs on the staged path: its T fragments must fit the workgroup's LDS

@@ -92,6 +92,12 @@ int tiled_t_parts(int64_t K);
 bool gemm_takes_decode(int64_t M, int64_t N, int64_t K, int r);
 
 constexpr int kDecDoneBytes = 8192;  // sign-off words: up to 2048 resident workgroups
+// Hand-over of T in the decode kernel (see gemm_decode.hip): launch counters, one per group of consumers
+// and each on a cache line of its own, and the granules.  The head of every GEMM workspace is set aside
+// for them, so that no other kernel that uses the same workspace writes there.
+constexpr uint32_t kDecGroups = 32, kDecGroupStride = 8;       // stride in 8-byte counters
+constexpr int kDecGranuleBytes = 32768;                         // 16 fragments of 2 KB
+constexpr size_t kGemmHeadBytes = 256 + kDecDoneBytes + kDecGroups * kDecGroupStride * 8 + kDecGranuleBytes;
 constexpr int kDecMaxWorkers = 32;  // workgroups forming T = X V^T in the decode kernel
 
 struct DecodeArgs {
@@ -101,13 +107,16 @@ struct DecodeArgs {
     WeightDev w;
     f16* Y;             // [M x N]
     // filled in by launch_decode from the workspace
-    uint32_t* ctrl;     // [0] T workers done, [3] a wait gave up; zero between launches
-    uint32_t* done;     // one sign-off word per streaming workgroup; zero between launches
-    f16* T;             // [kh][16 x ldt] fp16: X V^T per K part, zero beyond the rank
+    uint32_t* ctrl;     // [0] T workers done (ranks above 128), [3] a wait gave up; zero between launches
+    uint32_t* done;     // one sign-off word per streaming workgroup (ranks above 128); zero between launches
+    unsigned long long* epoch;  // counters of kDecGroups groups of consumers: 2^16 times the number of launches
+    unsigned long long* tg;     // granules of T, [kh][nks][4][64 lanes]
+    f16* T;             // ranks above 128: [kh][16 x ldt] fp16: X V^T per K part, zero beyond the rank
     int64_t ldt;
     int rblocks;        // ceil(r / 16)
     int nt;             // number of T workers (the first nt workgroups)
-    int kh;             // K parts of T (2048 columns each)
+    int kh;             // K parts of T (2048 * t_chunks columns each)
+    int nks, t_chunks;  // ceil(r / 32); chunks per wave of a T worker and part
     uint32_t spin_limit;    // polls after which a wait inside the kernel gives up
     // sizes and counts worked out on the host, so that a wave's first memory requests do not wait for
     // arithmetic (divisions, 64-bit products) or for further loads of launch parameters
@@ -119,7 +128,7 @@ struct DecodeArgs {
     uint32_t rot_mask;      // largest power of two not above 16 * chunks_per_wave, minus one
     uint32_t x_bytes, t_bytes, u_bytes;     // extents of X, T and (fp16) U
 };
-size_t decode_workspace_bytes(int r, int64_t K);
+size_t decode_workspace_bytes(int64_t N, int64_t K, int r);
 int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream);
 
 }  // namespace milo
