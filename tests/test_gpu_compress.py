@@ -166,6 +166,21 @@ def test_smallest_and_largest_shapes(N, K, r):
     _check_outputs(W, out, r, f"N{N} K{K} r{r}")
 
 
+@pytest.mark.parametrize("N,K,r,scale", [
+    (272, 704, 112, 1.0), (144, 448, 60, 1.0), (80, 128, 50, 1.0),     # 120, 68 and 58 basis vectors: each form of the factorizations
+    (64, 320, 8, 200.0), (64, 320, 8, 12.0),    # residuals that the shrinkage keeps: in every group, in some
+])
+def test_basis_widths_and_large_weights(N, K, r, scale):
+    # same bounds as above: nothing in the iteration depends on the width of the basis, and the oracle evaluates the
+    # shrinkage operator for every residual
+    W = (wl.gen_weight_lowrank(N, K, seed=3800 + r, modes=4) * scale).astype(np.float32)
+    ref = oracle.milo_compress(W, r, iters=3, tol=-1.0)
+    out = _compress(W, r, iters=3, tol=-1.0, power_iters=30, refine_iters=10)
+    rel = np.abs(np.array(out["eps"]) / np.array(ref["eps"]) - 1.0)
+    assert np.all(rel <= 5e-3), (out["eps"], ref["eps"])
+    _check_outputs(W, out, r, f"N{N} K{K} r{r} x{scale}")
+
+
 def test_constant_and_zero_groups():
     # groups without a range (scale 1, codes 0, z = -w) next to ordinary ones; an all-zero weight
     import torch
