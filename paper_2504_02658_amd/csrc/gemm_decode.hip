@@ -801,8 +801,9 @@ int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream) {
     const int lr = r == 0 ? 0 : tp.staged ? 1 : 2;
     const int xc = a.M <= 2 ? 1 : a.M <= 4 ? 2 : a.M <= 8 ? 4 : 8;    // activation copies per chunk: rows 2i, 2i+1
     const bool q = r > 0 && (a.w.flags & MILO_LR_INT3) != 0;
-    // an INT3 compensator only runs on the staged path: its T fragments must fit the workgroup's LDS
-    if (q && lr != 1) return MILO_ERR_SHAPE;
+    // an INT3 compensator only runs on the staged path, with one chunk per wave: its T fragments must fit
+    // the workgroup's LDS at that
+    if (q && (lr != 1 || tp.chunks != 1)) return MILO_ERR_SHAPE;
     const bool bf = (a.w.flags & MILO_ACT_BF16) != 0;
     if (bf && q) return MILO_ERR_SHAPE;
     const DecodeKernel kernel = decode_variant(R, lr, xc, (a.w.flags & MILO_W3_SYMMETRIC) != 0, q, bf);

@@ -165,6 +165,26 @@ def test_real_valued_zero_points():
         assert_close(_run(X, pw), oracle.w3lr_linear(X, q, s, z), f"real z, M={M}")
 
 
+def test_gpu_int3_compensator_limit():
+    # at decode sizes an INT3 compensator takes ceil(r / 32) * ceil(K / 2048) <= 16 fragments of T: rank 128 up
+    # to K = 8192, beyond that the call is refused before anything is launched
+    import torch
+    from paper_2504_02658_amd import api
+    rng = np.random.default_rng(7)
+    for K, taken in ((8192, True), (8256, False)):
+        X = rng.standard_normal((2, K)).astype(np.float16)
+        W = (rng.standard_normal((128, K)) * 0.02).astype(np.float32)
+        U, V = (rng.standard_normal(s).astype(np.float32) * 0.02 for s in ((128, 128), (128, K)))
+        u3, v3 = api.pack_lr3(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda())
+        pw = api.pack_w3(torch.from_numpy(W).cuda()).with_int3_compensator(u3, v3, 128)
+        if taken:
+            assert api.w3lr_gemm(torch.from_numpy(X).cuda(), pw).shape == (2, 128)
+        else:
+            with pytest.raises(api.MiloError) as ei:
+                api.w3lr_gemm(torch.from_numpy(X).cuda(), pw)
+            assert ei.value.status == 2
+
+
 def test_gpu_argument_errors():
     import torch
     from paper_2504_02658_amd import api
