@@ -242,9 +242,11 @@ int milo_compress_w3lr(const float* W, int64_t N, int64_t K, const milo_compress
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
  * result and errors as milo_w3lr_gemm, bit for bit, without `workspace`: the scratch memory is a
  * fixed array of MILO_STATIC_SCRATCH_BYTES inside the library's device image (every GPU the library
- * runs on holds its copy until the process ends).  The call allocates nothing; a problem whose
- * milo_w3lr_gemm_workspace(M, N, K, r) exceeds MILO_STATIC_SCRATCH_BYTES is refused with
- * MILO_ERR_WORKSPACE (all decode shapes fit; large M with a K split may not).  The control words
+ * runs on holds its copy until the process ends; the array has room for a fixed head of the workspace
+ * on top).  The call allocates nothing; a problem that needs more than MILO_STATIC_SCRATCH_BYTES
+ * besides that head is refused with MILO_ERR_WORKSPACE: all whose milo_w3lr_gemm_workspace(M, N, K, r)
+ * is within MILO_STATIC_SCRATCH_BYTES are taken (all decode shapes; large M with a K split may not fit).
+ * The control words
  * of the array are cleared by a small fill kernel at the start of every call (no memset, so the call
  * can be captured), then the kernels of milo_w3lr_gemm run on it.  All calls on one GPU share that
  * GPU's array: calls that overlap in time on one GPU (different streams) race; order them.  The

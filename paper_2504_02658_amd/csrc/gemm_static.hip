@@ -42,7 +42,11 @@ extern "C" int milo_w3lr_gemm_static(const milo_half* X, int64_t M, int64_t N, i
     if (!X || !q3 || !Y) return MILO_ERR_NULL;
     const size_t need = milo_w3lr_gemm_workspace(M, N, K, r);       // 0 for an invalid shape or rank
     if (need == 0) return (r < 0) ? MILO_ERR_RANK : MILO_ERR_SHAPE;
-    if (need > kStaticScratchBytes) return MILO_ERR_WORKSPACE;
+    // The array has room for the head of a GEMM workspace beyond MILO_STATIC_SCRATCH_BYTES: the limit applies
+    // to the control block, the flag or sign-off words and the scratch behind them.
+    const size_t flag_words = gemm_takes_decode(M, N, K, r) ? (size_t)kDecDoneBytes : 0;
+    const size_t counted = need > kGemmHeadBytes ? need - kGemmHeadBytes + 256 + flag_words : 256 + flag_words;
+    if (counted > (size_t)MILO_STATIC_SCRATCH_BYTES) return MILO_ERR_WORKSPACE;
     void* ws = nullptr;
     const int st = static_scratch(&ws);
     if (st != MILO_OK) return st;

@@ -65,6 +65,11 @@ def test_host_side_argument_errors(L):
     assert g(r=-1) == 4 and g(r=2048) == 4 and g(U=null) == 4
     assert g(ws=null) == 5 and g(wsb=16) == 5
     assert g(X=odd) == 7
+    # the fixed scratch array: 4 MiB of control words, flags (16 bytes per 32 rows), T and its fp32 partials.
+    # Each of these is one 256-byte step above it.
+    fixed = lambda M, K, r: L.milo_w3lr_gemm_static(p, M, 14336, K, p, p, p, r, p, st)
+    for M, K, r in ((3275, 1024, 128), (4366, 1024, 96), (5457, 64, 128), (8727, 1024, 48)):
+        assert fixed(M, K, r) == 5
     # MoE
     experts = (api.Expert * 2)()
     assert L.milo_moe_w3lr_check_experts(experts, 2, 256, 512, None) == 1      # NULL weight pointers
