@@ -172,8 +172,10 @@ PyObject* py_moe(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (!ws || have < need) return PyLong_FromLongLong(-(long long)(need > 256 ? need : 256));
         }
         at::Tensor out;
+        // X's own width goes to the call: nothing is read past a row, and a workspace made for the layer refuses a wider one
+        const int64_t width = X->size(1);
         if (a[10] == Py_None) {
-            out = at::empty({T, X->size(1)}, X->options());
+            out = at::empty({T, width}, X->options());
             Y = out.data_ptr();
         }
         void* const stream = current_stream();
@@ -182,7 +184,7 @@ PyObject* py_moe(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const float* gate = static_cast<const float*>(gates->data_ptr());
         int st;
         Py_BEGIN_ALLOW_THREADS
-        st = e->moe(x, T, H, F, static_cast<const milo_w3lr_expert*>(table), (int)E, (int)r_max, id, gate, (int)topk,
+        st = e->moe(x, T, width, F, static_cast<const milo_w3lr_expert*>(table), (int)E, (int)r_max, id, gate, (int)topk,
                     (unsigned)flags, static_cast<milo_half*>(Y), ws, have, stream);
         Py_END_ALLOW_THREADS
         if (st != MILO_OK) return status_object(st);

@@ -94,6 +94,19 @@ def test_many_tiles_take_the_xcd_placement_path():
     _check(case)
 
 
+def test_rows_wider_than_the_layer_are_refused():
+    """The call goes by the activations' own width, for which the layer's workspace is too small."""
+    import torch
+    from paper_2504_02658_amd import api
+    case = wl.MoECase("wide", T=64, H=256, F=384, E=4, topk=2, seed=13, rank_choices=(0, 8))
+    _, layer = build_moe(case)
+    ids, gates = (torch.from_numpy(a).cuda() for a in wl.moe_routing(case))
+    wide = torch.zeros((case.T, 4 * case.H), dtype=torch.float16, device="cuda")
+    with pytest.raises(api.MiloError) as e:
+        layer.forward(wide, ids, gates)
+    assert e.value.status == 5                                # MILO_ERR_WORKSPACE
+
+
 def test_graph_replay_of_a_layer():
     # routing, flags and partial buffers are re-initialised by the kernels themselves: a captured
     # layer replays bit for bit with eager work on the same workspace in between
