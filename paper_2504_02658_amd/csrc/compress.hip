@@ -691,6 +691,14 @@ __global__ __launch_bounds__(256) void random_basis_kernel(float* __restrict__ o
 }
 
 // ------------------------------------------------------------------ eigenvectors of the small Gram matrix
+// (p, q) turned by the angle with sine s and half-angle tangent h: cos = 1 - s h is not formed, so a small angle takes
+// nothing from the length of (p, q) by the rounding of its cosine.
+__device__ __forceinline__ void turn(float& p, float& q, float s, float h) {
+    const float p0 = p;
+    p = fmaf(-s, fmaf(h, p0, q), p0);
+    q = fmaf(s, fmaf(-h, q, p0), q);
+}
+
 // Gm = sum of the parts, [l x l] symmetric (B B^T) = Ub diag(lambda) Ub^T by cyclic Jacobi rotations, l / 2 disjoint
 // pairs per step in round-robin order, at most `sweeps` sweeps (fewer when they have converged).  With
 // sigma = sqrt(lambda) sorted descending it writes Vm [r x l] = sigma_r^(-1/2) Ub_r^T, Wm [l x l] = sigma^-1 Ub^T (rows
@@ -702,7 +710,7 @@ __global__ __launch_bounds__(256) void random_basis_kernel(float* __restrict__ o
 // a wave (of each of its `subs` parts) owns column pair m: it works out that pair's rotation itself, gets the one of
 // its row pair from another lane, and so nothing but the matrix itself crosses waves; with two copies of the
 // matrix (TWO, as long as they fit) a step costs one barrier.  PASSES: column pairs per lane (more than 64 pairs).
-// l = 40: 178 us; with three barriers per step (rotations, columns, rows) and scattered reads 555.
+// l = 40: 171 us; with three barriers per step (rotations, columns, rows) and scattered reads 555.
 // THREADS: a step is bound by instructions, many of them the same in every wave (the rotations), so up to three
 // row-pair rounds of a 40-wide matrix eight waves are faster than sixteen, and slower on larger ones.
 template <int THREADS, int PASSES, bool TWO>
@@ -748,7 +756,7 @@ __global__ __launch_bounds__(THREADS) void jacobi_factors_kernel(const float* __
     }
     for (int sweep = 0; sweep < sweeps; ++sweep) {
         for (int step = 0; step < n - 1; ++step) {
-            float c2[PASSES], s2[PASSES];
+            float s2[PASSES], h2[PASSES];               // sine, tangent of half the angle
 #pragma unroll
             for (int y = 0; y < PASSES; ++y) {
                 const float2 upper = *reinterpret_cast<const float2*>(A + at[y] * w + at[y]);
@@ -758,8 +766,8 @@ __global__ __launch_bounds__(THREADS) void jacobi_factors_kernel(const float* __
                 const float tau = (aqq - app) * 0.5f * __builtin_amdgcn_rcpf(apq);
                 const float t = copysignf(__builtin_amdgcn_rcpf(fabsf(tau) + __builtin_amdgcn_sqrtf(fmaf(tau, tau, 1.0f))), tau);
                 const float c = __builtin_amdgcn_rsqf(fmaf(t, t, 1.0f));
-                c2[y] = rotate ? c : 1.0f;
                 s2[y] = rotate ? t * c : 0.0f;
+                h2[y] = rotate ? s2[y] * __builtin_amdgcn_rcpf(1.0f + c) : 0.0f;
                 if (rotate && (fabsf(t) > 2e-4f || fabsf(apq) > 2e-4f * mean)) again[sweep & 1] = 1;
             }
             float blk[ROUNDS][PASSES][4];
@@ -767,21 +775,24 @@ __global__ __launch_bounds__(THREADS) void jacobi_factors_kernel(const float* __
             for (int k = 0; k < ROUNDS; ++k) {
                 if (wave * subs + k * stride >= half) break;
                 const int x = first + k * stride < half ? first + k * stride : half - 1;
-                float c1 = __shfl(c2[0], x & 63, 64), s1 = __shfl(s2[0], x & 63, 64);
+                float s1 = __shfl(s2[0], x & 63, 64), h1 = __shfl(h2[0], x & 63, 64);
                 if (PASSES == 2) {
-                    const float ch = __shfl(c2[PASSES - 1], x & 63, 64), sh = __shfl(s2[PASSES - 1], x & 63, 64);
-                    if (x >= 64) { c1 = ch; s1 = sh; }
+                    const float sh = __shfl(s2[PASSES - 1], x & 63, 64), hh = __shfl(h2[PASSES - 1], x & 63, 64);
+                    if (x >= 64) { s1 = sh; h1 = hh; }
                 }
 #pragma unroll
                 for (int y = 0; y < PASSES; ++y) {
                     const float2 u = *reinterpret_cast<const float2*>(A + 2 * x * w + at[y]);
                     const float2 v = *reinterpret_cast<const float2*>(A + (2 * x + 1) * w + at[y]);
-                    const float up = c1 * u.x - s1 * v.x, uq = c1 * u.y - s1 * v.y;      // rows: J1^T
-                    const float vp = s1 * u.x + c1 * v.x, vq = s1 * u.y + c1 * v.y;
-                    blk[k][y][0] = c2[y] * up - s2[y] * uq;
-                    blk[k][y][1] = s2[y] * up + c2[y] * uq;
-                    blk[k][y][2] = c2[y] * vp - s2[y] * vq;
-                    blk[k][y][3] = s2[y] * vp + c2[y] * vq;
+                    float up = u.x, uq = u.y, vp = v.x, vq = v.y;
+                    turn(up, vp, s1, h1);                       // rows: J1^T
+                    turn(uq, vq, s1, h1);
+                    turn(up, uq, s2[y], h2[y]);                 // columns: J2
+                    turn(vp, vq, s2[y], h2[y]);
+                    blk[k][y][0] = up;
+                    blk[k][y][1] = uq;
+                    blk[k][y][2] = vp;
+                    blk[k][y][3] = vq;
                 }
             }
             if (!TWO) __syncthreads();                  // everyone has read
@@ -809,8 +820,9 @@ __global__ __launch_bounds__(THREADS) void jacobi_factors_kernel(const float* __
 #pragma unroll
                 for (int y = 0; y < PASSES; ++y)
                     if (on && m + 64 * y < half) {
-                        ev[nu[y]] = c2[y] * e[y].x - s2[y] * e[y].y;
-                        ev[nl[y]] = s2[y] * e[y].x + c2[y] * e[y].y;
+                        turn(e[y].x, e[y].y, s2[y], h2[y]);
+                        ev[nu[y]] = e[y].x;
+                        ev[nl[y]] = e[y].y;
                     }
             }
             __syncthreads();
