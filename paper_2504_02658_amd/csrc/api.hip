@@ -111,6 +111,11 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict
     *reinterpret_cast<f16x4*>(Y + 4 * i) = o;
 }
 
+size_t milo::gemm_flags_behind(int64_t M) {
+    const int64_t bm = 32 * gemm_mb(M), tiles = (M + bm - 1) / bm;
+    return tiles > kTiledFlagTiles ? align_up((size_t)tiles * 16, 256) : 0;
+}
+
 static bool gemm_shape_ok(int64_t M, int64_t N, int64_t K) {
     return M >= 1 && M <= (int64_t)0x3fffffff && weight_shape_ok(N, K);
 }
@@ -118,11 +123,11 @@ static bool gemm_shape_ok(int64_t M, int64_t N, int64_t K) {
 extern "C" size_t milo_w3lr_gemm_workspace(int64_t M, int64_t N, int64_t K, int r) {
     if (!gemm_shape_ok(M, N, K) || r < 0) return 0;
     if (gemm_takes_decode(M, N, K, r)) return decode_workspace_bytes(N, K, r);
-    // head (control words, hand-over area of the decode kernel) | four flag words per 32-row tile | T = X V^T, fp16 [M x pad16(r)] | its fp32
-    // partials per part of K | with K splits, their fp32 partial sums [M x N] each
+    // head | flag words that do not fit in it | T = X V^T, fp16 [M x pad16(r)] | its fp32 partials per part of K | with K
+    // splits, their fp32 partial sums [M x N] each
     const size_t parts = (size_t)gemm_t_parts(M, N, K, r);
     const int splits = gemm_splits(M, N, K, r);
-    return kGemmHeadBytes + align_up((size_t)((M + 31) / 32) * 16, 256) +
+    return kGemmHeadBytes + gemm_flags_behind(M) +
            align_up((size_t)M * (size_t)rank_pad(r) * 2 + 256, 256) +
            align_up(parts * (size_t)M * (size_t)rank_pad(r) * 4 + 256, 256) +
            (splits > 1 ? align_up((size_t)splits * (size_t)M * (size_t)N * 4, 256) : 0);
@@ -174,8 +179,9 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     }
     char* ws = reinterpret_cast<char*>(workspace);
     uint32_t* ctrl = reinterpret_cast<uint32_t*>(ws);
-    uint32_t* tile_flags = reinterpret_cast<uint32_t*>(ws + kGemmHeadBytes);
-    f16* T = reinterpret_cast<f16*>(ws + kGemmHeadBytes + align_up((size_t)((M + 31) / 32) * 16, 256));
+    const size_t flags_behind = gemm_flags_behind(M);
+    uint32_t* tile_flags = reinterpret_cast<uint32_t*>(ws + (flags_behind ? kGemmHeadBytes : kGemmFlagsAt));
+    f16* T = reinterpret_cast<f16*>(ws + kGemmHeadBytes + flags_behind);
     const int64_t ldt = rank_pad(r);
 
     const int mb = gemm_mb(M);
@@ -220,6 +226,11 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     }
     ga.out = splits > 1 ? static_cast<void*>(partial) : static_cast<void*>(Y);
     ga.ldo = N; ga.out_split_stride = M * N; ga.out_rows = nullptr; ga.out_scale = nullptr;
+    if (flags_behind && r > 0) {
+        clear_kernel<<<dim3((unsigned)((flags_behind / 16 + 255) / 256)), dim3(256), 0, stream>>>(
+            reinterpret_cast<u32x4*>(tile_flags), flags_behind / 16);
+        if (launch_status() != MILO_OK) return MILO_ERR_HIP;
+    }
     int st = launch_tiled(ga, 1, mb, EPI_STORE, (int)m_tiles, stream);
     if (st != MILO_OK || splits == 1) return st;
     const int64_t n4 = M * N / 4;

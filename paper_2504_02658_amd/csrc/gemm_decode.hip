@@ -735,7 +735,7 @@ size_t decode_workspace_bytes(int64_t N, int64_t K, int r) {
     if (r <= 0) return 256;
     const size_t rblocks = ((size_t)r + 15) / 16;
     const DecodeT t = decode_t_plan(N, K, r);
-    // control words, sign-off words, counters, granules | T 16-bit [K parts][16 x ldt] of the other path
+    // head | T 16-bit [K parts][16 x ldt] of the other path
     return kGemmHeadBytes + (t.staged ? 0 : align_up((size_t)t.kh * 16 * rblocks * 16 * 2, 256));
 }
 
@@ -771,9 +771,9 @@ int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream) {
     if ((uint64_t)a.ldt * (uint64_t)a.K * 2u >= 0xFFFFFFF0ull) return MILO_ERR_SHAPE;
     char* ws = reinterpret_cast<char*>(workspace);
     a.ctrl = reinterpret_cast<uint32_t*>(ws);
-    a.done = reinterpret_cast<uint32_t*>(ws + 256);
-    a.epoch = reinterpret_cast<unsigned long long*>(ws + 256 + kDecDoneBytes);
-    a.tg = reinterpret_cast<unsigned long long*>(ws + 256 + kDecDoneBytes + kDecGroups * kDecGroupStride * 8);
+    a.done = reinterpret_cast<uint32_t*>(ws + kGemmDoneAt);
+    a.epoch = reinterpret_cast<unsigned long long*>(ws + kGemmCountersAt);
+    a.tg = reinterpret_cast<unsigned long long*>(ws + kGemmGranulesAt);
     a.T = reinterpret_cast<f16*>(ws + kGemmHeadBytes);
     const DecodeT tp = decode_t_plan(a.N, a.K, r);
     a.kh = tp.kh;

@@ -10,10 +10,9 @@ namespace milo {
 constexpr size_t kStaticScratchBytes = (size_t)MILO_STATIC_SCRATCH_BYTES + kGemmHeadBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
-// 16-byte words [0, head16) and [flags0, flags1)
-__global__ void scratch_clear_kernel(u32x4* p, size_t head16, size_t flags0, size_t flags1) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < flags1; i += (size_t)gridDim.x * blockDim.x)
-        if (i < head16 || i >= flags0) p[i] = u32x4{0u, 0u, 0u, 0u};
+__global__ void scratch_clear_kernel(u32x4* p, size_t n16) {
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (size_t)gridDim.x * blockDim.x)
+        p[i] = u32x4{0u, 0u, 0u, 0u};
 }
 }  // namespace milo
 
@@ -42,25 +41,22 @@ extern "C" int milo_w3lr_gemm_static(const milo_half* X, int64_t M, int64_t N, i
     if (!X || !q3 || !Y) return MILO_ERR_NULL;
     const size_t need = milo_w3lr_gemm_workspace(M, N, K, r);       // 0 for an invalid shape or rank
     if (need == 0) return (r < 0) ? MILO_ERR_RANK : MILO_ERR_SHAPE;
-    // The array has room for the head of a GEMM workspace beyond MILO_STATIC_SCRATCH_BYTES: the limit applies
-    // to the control block, the flag or sign-off words and the scratch behind them.
-    const size_t flag_words = gemm_takes_decode(M, N, K, r) ? (size_t)kDecDoneBytes : 0;
-    const size_t counted = need > kGemmHeadBytes ? need - kGemmHeadBytes + 256 + flag_words : 256 + flag_words;
-    if (counted > (size_t)MILO_STATIC_SCRATCH_BYTES) return MILO_ERR_WORKSPACE;
+    // The array has room for the head of a GEMM workspace beyond MILO_STATIC_SCRATCH_BYTES: the limit applies to the
+    // control block, the sign-off words (decode) or the flag words of 32-row tiles, and the scratch behind them.
+    const bool tiled = !gemm_takes_decode(M, N, K, r);
+    const size_t behind = tiled ? gemm_flags_behind(M) : 0;
+    const size_t words = tiled ? align_up((size_t)((M + 31) / 32) * 16, 256) : (size_t)kDecDoneBytes;
+    const size_t scratch_bytes = need > kGemmHeadBytes + behind ? need - kGemmHeadBytes - behind : 0;
+    if (256 + words + scratch_bytes > (size_t)MILO_STATIC_SCRATCH_BYTES) return MILO_ERR_WORKSPACE;
     void* ws = nullptr;
     const int st = static_scratch(&ws);
     if (st != MILO_OK) return st;
-    // The array keeps what the last call left.  The kernels leave their control words at zero,
-    // but a call that failed half-way may not have, and the flag words of another shape lie
-    // elsewhere: the control block, the sign-off words and the tiled kernel's flag words are cleared
-    // first, by a small fill kernel (not a memset, so that the call can be captured in a HIP graph).
-    // The launch counters and granules of the decode kernel are never reset: they stay valid from call to call.
-    const size_t head = need < 256 + (size_t)kDecDoneBytes ? need : 256 + (size_t)kDecDoneBytes;
-    const bool tiled = !gemm_takes_decode(M, N, K, r);
-    const size_t flags = tiled ? align_up((size_t)((M + 31) / 32) * 16, 256) : 0;
-    const size_t head16 = head / 16, flags0 = tiled ? kGemmHeadBytes / 16 : head16, flags1 = flags0 + flags / 16;
-    scratch_clear_kernel<<<dim3((unsigned)((flags1 + 255) / 256)), dim3(256), 0, (hipStream_t)stream>>>(
-        reinterpret_cast<u32x4*>(ws), head16, flags0, flags1);
+    // The array keeps what the last call left.  The kernels leave their control, sign-off and flag words at zero, but a
+    // call that failed half-way may not have, so they are cleared first, by a small fill kernel (not a memset, so that the
+    // call can be captured in a HIP graph).  The launch counters and granules of the decode kernel are never reset: they
+    // stay valid from call to call.
+    const size_t n16 = (tiled ? kGemmCountersAt : kGemmFlagsAt) / 16;
+    scratch_clear_kernel<<<dim3((unsigned)((n16 + 255) / 256)), dim3(256), 0, (hipStream_t)stream>>>(reinterpret_cast<u32x4*>(ws), n16);
     if (launch_status() != MILO_OK) return MILO_ERR_HIP;
     return milo_w3lr_gemm(X, M, N, K, q3, U, V, r, Y, ws, kStaticScratchBytes, stream);
 }

@@ -91,13 +91,22 @@ int tiled_t_parts(int64_t K);
 // Which of the two GEMM kernels milo_w3lr_gemm takes for a problem (true: the weight-streaming decode kernel).
 bool gemm_takes_decode(int64_t M, int64_t N, int64_t K, int r);
 
+// Head of every GEMM workspace with a compensator, the same for all shapes and both kernels: what has to keep its
+// value from one call to the next lies here and nowhere else, so that no scratch of one call lands on it in another.
+//   control words | sign-off words | flags of the tiled kernel's M-tiles | launch counters | granules
 constexpr int kDecDoneBytes = 8192;  // sign-off words: up to 2048 resident workgroups
+// Flag words of up to 1024 M-tiles (131072 rows at the tile height such an M takes).  A call with more keeps its
+// flags behind the head, where other calls have scratch, and clears them itself.
+constexpr int64_t kTiledFlagTiles = 1024;
+constexpr int kTiledFlagBytes = (int)kTiledFlagTiles * 16;
 // Hand-over of T in the decode kernel (see gemm_decode.hip): launch counters, one per group of consumers
-// and each on a cache line of its own, and the granules.  The head of every GEMM workspace is set aside
-// for them, so that no other kernel that uses the same workspace writes there.
+// and each on a cache line of its own, and the granules.
 constexpr uint32_t kDecGroups = 32, kDecGroupStride = 8;       // stride in 8-byte counters
 constexpr int kDecGranuleBytes = 32768;                         // 16 fragments of 2 KB
-constexpr size_t kGemmHeadBytes = 256 + kDecDoneBytes + kDecGroups * kDecGroupStride * 8 + kDecGranuleBytes;
+constexpr size_t kGemmDoneAt = 256, kGemmFlagsAt = kGemmDoneAt + kDecDoneBytes, kGemmCountersAt = kGemmFlagsAt + kTiledFlagBytes,
+                 kGemmGranulesAt = kGemmCountersAt + kDecGroups * kDecGroupStride * 8, kGemmHeadBytes = kGemmGranulesAt + kDecGranuleBytes;
+// Bytes of flag words behind the head (0: they fit in it).
+size_t gemm_flags_behind(int64_t M);
 constexpr int kDecMaxWorkers = 32;  // workgroups forming T = X V^T in the decode kernel
 
 struct DecodeArgs {

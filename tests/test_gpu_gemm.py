@@ -317,6 +317,40 @@ def test_workspace_status_reports_a_wait_that_gave_up():
         assert_close(Y.cpu().numpy(), oracle.w3lr_linear(X, **ow), "after re-init")
 
 
+def _shared_workspace_sequence(calls):
+    """Runs the calls (M, N, K, r) in order on one workspace large enough for all of them; each result has to be, bit for bit,
+    what the call gives on a fresh workspace of its own."""
+    import torch
+    from paper_2504_02658_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    made, jobs = {}, []
+    for M, N, K, r in calls:
+        if (N, K, r) not in made:
+            pw = api.pack_w3(randn(N, K) * 0.02)
+            if r:
+                pw = pw.with_compensator((randn(N, r) * 0.1).half(), (randn(r, K) * 0.1).half())
+            made[N, K, r] = pw
+        jobs.append((randn(M, K).half(), made[N, K, r]))
+    alone = [api.w3lr_gemm(X, pw, workspace=api.new_workspace(api.gemm_workspace_bytes(X.shape[0], pw.N, pw.K, pw.r)))
+             for X, pw in jobs]
+    ws = api.new_workspace(max(api.gemm_workspace_bytes(*c) for c in calls))
+    for (X, pw), ref, call in zip(jobs, alone, calls):
+        Y = api.w3lr_gemm(X, pw, workspace=ws)
+        assert torch.equal(Y, ref), f"{call} on a workspace that earlier calls used"
+    assert api.workspace_status(ws) == 0
+
+
+def test_calls_of_both_kernels_on_one_workspace():
+    # What a call leaves as scratch must not lie where another keeps words that have to be zero at launch: T of decode
+    # calls above rank 128, T, partials and split sums of tiled calls, flags of up to and beyond 1024 M-tiles.
+    _shared_workspace_sequence([
+        (4, 256, 1024, 256), (77, 256, 1024, 32), (4, 256, 1024, 256), (77, 256, 1024, 200), (4096, 256, 1024, 32),
+        (16, 256, 1024, 32), (20, 512, 4096, 8), (4096, 256, 1024, 32), (131072 + 40, 16, 64, 8), (96, 512, 4096, 16),
+        (131072 + 40, 16, 64, 8), (3, 256, 1024, 256), (131072, 16, 64, 8), (5, 256, 1024, 0), (300, 256, 1024, 72)])
+
+
 # ------------------------------------------------------------------ INT3 compensators, weight flags
 
 def _int3_case(M, N, K, r, seed, symmetric=False):
