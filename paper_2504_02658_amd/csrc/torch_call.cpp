@@ -164,6 +164,11 @@ PyObject* py_moe(PyObject*, PyObject* const* a, Py_ssize_t n) {
         if (!gates) return nullptr;
         if (X->dim() != 2 || ids->dim() != 2) return PyErr_Format(PyExc_ValueError, "X and ids must have two dimensions");
         const int64_t T = X->size(0), topk = ids->size(1);
+        // The kernels go by H and T alone: rows of another width would be multiplied with the experts' [F x H] weights at the
+        // wrong stride, wider ones past the weights' end, and missing ids or gates would be read past the end of theirs.
+        if (X->size(1) != H) return status_object(X->size(1) > H ? MILO_ERR_WORKSPACE : MILO_ERR_SHAPE);
+        if (ids->size(0) < T || gates->numel() < T * topk)
+            return PyErr_Format(PyExc_ValueError, "ids and gates must have a row for every row of X");
         void *table, *Y, *ws;
         if (!address(a[4], "table", &table) || !address(a[10], "out", &Y) || !address(a[11], "workspace", &ws)) return nullptr;
         const size_t have = a[11] == Py_None ? 0 : (size_t)THPVariable_Unpack(a[11]).numel();
@@ -172,10 +177,8 @@ PyObject* py_moe(PyObject*, PyObject* const* a, Py_ssize_t n) {
             if (!ws || have < need) return PyLong_FromLongLong(-(long long)(need > 256 ? need : 256));
         }
         at::Tensor out;
-        // X's own width goes to the call: nothing is read past a row, and a workspace made for the layer refuses a wider one
-        const int64_t width = X->size(1);
         if (a[10] == Py_None) {
-            out = at::empty({T, width}, X->options());
+            out = at::empty({T, H}, X->options());
             Y = out.data_ptr();
         }
         void* const stream = current_stream();
@@ -184,7 +187,7 @@ PyObject* py_moe(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const float* gate = static_cast<const float*>(gates->data_ptr());
         int st;
         Py_BEGIN_ALLOW_THREADS
-        st = e->moe(x, T, width, F, static_cast<const milo_w3lr_expert*>(table), (int)E, (int)r_max, id, gate, (int)topk,
+        st = e->moe(x, T, H, F, static_cast<const milo_w3lr_expert*>(table), (int)E, (int)r_max, id, gate, (int)topk,
                     (unsigned)flags, static_cast<milo_half*>(Y), ws, have, stream);
         Py_END_ALLOW_THREADS
         if (st != MILO_OK) return status_object(st);

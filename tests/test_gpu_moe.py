@@ -107,6 +107,31 @@ def test_rows_wider_than_the_layer_are_refused():
     assert e.value.status == 5                                # MILO_ERR_WORKSPACE
 
 
+def test_rows_of_another_width_are_refused_whatever_the_workspace_holds():
+    # a workspace that earlier, larger forwards have grown has room for a few rows of any width
+    import torch
+    from paper_2504_02658_amd import api
+    case = wl.MoECase("widths", T=512, H=256, F=384, E=4, topk=2, seed=14, rank_choices=(0, 8))
+    _, layer = build_moe(case)
+    ids, gates = (torch.from_numpy(a).cuda() for a in wl.moe_routing(case))
+    X = torch.randn((case.T, case.H), device="cuda").half()
+    ref = layer.forward(X, ids, gates)
+    assert layer._ws.numel() > layer.workspace_bytes(4, case.topk) * 8
+    for width, status in ((2 * case.H, 5), (case.H + 64, 5), (case.H - 64, 2)):
+        rows = torch.zeros((4, width), dtype=torch.float16, device="cuda")
+        for ws in (None, layer._ws):
+            with pytest.raises(api.MiloError) as e:
+                layer.forward(rows, ids[:4], gates[:4], workspace=ws)
+            assert e.value.status == status
+    with pytest.raises(ValueError):
+        layer.forward(X, ids[:-1].contiguous(), gates)
+    with pytest.raises(ValueError):
+        layer.forward(X, ids, gates[:-1].contiguous())
+    # more routing rows than tokens are fine: the first T count
+    assert torch.equal(layer.forward(X[:100], ids, gates), layer.forward(X[:100], ids[:100], gates[:100]))
+    assert torch.equal(layer.forward(X, ids, gates), ref)
+
+
 def test_graph_replay_of_a_layer():
     # routing, flags and partial buffers are re-initialised by the kernels themselves: a captured
     # layer replays bit for bit with eager work on the same workspace in between
