@@ -10,6 +10,7 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/milo.h"
@@ -61,15 +62,13 @@ bool whole(PyObject* o, int64_t* v) {
     return !(*v == -1 && PyErr_Occurred());
 }
 
-// at::Tensor calls throw C++ exceptions; they become a RuntimeError.
+// at::Tensor calls throw C++ exceptions; they become the Python exceptions that PyTorch's own calls raise
+// (torch.OutOfMemoryError from an allocation, for one).
 template <typename F>
 PyObject* guarded(F&& f) {
-    try {
-        return f();
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
-    }
+    HANDLE_TH_ERRORS
+    return f();
+    END_HANDLE_TH_ERRORS
 }
 PyObject* status_object(int st) { return PyLong_FromLong(st); }
 

@@ -201,6 +201,16 @@ def test_gpu_argument_errors():
         api.w3lr_gemm(torch.zeros((4, 64), dtype=torch.float16, device="cuda"), pw)
 
 
+def test_an_output_that_does_not_fit_raises_out_of_memory():
+    # the exception a caller can catch to retry with less; 2^51 bytes (the shape is refused too, but later)
+    import torch
+    from paper_2504_02658_amd import api
+    X = torch.zeros((1 << 20, 64), dtype=torch.float16, device="cuda")
+    pw = api.PackedWeight(1 << 30, 64, torch.zeros(448, dtype=torch.uint8, device="cuda"))
+    with pytest.raises(torch.OutOfMemoryError):
+        api.w3lr_gemm(X, pw)
+
+
 # ------------------------------------------------------------------ full-size configurations
 
 @pytest.fixture(scope="module")
