@@ -282,7 +282,7 @@ __global__ __launch_bounds__(256, 2) void resid_kernel(const float* __restrict__
                 const f16 z16 = (f16)fminf(fmaxf(z[gu], -65504.0f), 65504.0f);
 #pragma unroll
                 for (int e = 0; e < 64; ++e)
-                    q[e] = fminf(fmaxf(__builtin_rintf(div_by(q[e], sf, inv_s) + (float)z16), 0.0f), 7.0f);
+                    q[e] = fminf(fmaxf(__builtin_rintf(div_by_any(q[e], sf, inv_s) + (float)z16), 0.0f), 7.0f);
                 uint32_t d[6];
                 unit_words(q, d);
                 store_row_block_unit(d, scale_zero_word((f16)sf, z16), ((n0 >> 4) * G + g0) * 16 + lane, planeA, planeB);

@@ -107,6 +107,11 @@ __device__ __forceinline__ float div_by(float a, float b, float y) {
     const float q = a * y;
     return __builtin_fmaf(__builtin_fmaf(-q, b, a), y, q);
 }
+// The same for a quotient that may be infinite, which the remainder would turn into not-a-number.
+__device__ __forceinline__ float div_by_any(float a, float b, float y) {
+    const float q = a * y;
+    return fabsf(q) < __builtin_inff() ? __builtin_fmaf(__builtin_fmaf(-q, b, a), y, q) : q;
+}
 
 // The words of a unit from its 64 codes (whole numbers 0..7 as floats).
 __device__ __forceinline__ void unit_words(const float (&code)[64], uint32_t (&d)[6]) {

@@ -199,6 +199,17 @@ def test_constant_and_zero_groups():
     assert np.all(out["U"] @ out["V"] == 0.0)
 
 
+def test_infinite_weights_clamp():
+    # codes of infinite weights are the ends of the range, as of any weight beyond them
+    W = wl.gen_weight(32, 192, seed=3701)
+    W[3, 5], W[17, 130] = np.inf, -np.inf
+    out = _compress(W, 0, iters=1, hqq_iters=0)
+    with np.errstate(invalid="ignore"):
+        q, _ = oracle.quantize_with(W.astype(np.float64), out["scales"].astype(np.float64), out["zeros"].astype(np.float64))
+    assert out["codes"][3, 5] == 7 and out["codes"][17, 130] == 0
+    assert np.mean(q.astype(np.uint8) == out["codes"]) >= 0.999
+
+
 @pytest.mark.timeout(600)
 def test_mixtral_up_projection_size():
     # the full 14336 x 4096 weight, rank 32, three iterations: properties on the whole result, codes
