@@ -27,10 +27,10 @@
 // ranks of T = X V^T over a part of K (the parts are never added up across workgroups).  The
 // streaming workgroups only need T in their epilogue, where they add T U^T with a few more MFMAs.
 // Wave 0 of a streaming workgroup, whose requests are accepted first and which is therefore done
-// long before the others, fetches the U rows and T into LDS.  The workers never wait for anything,
-// they have the lowest workgroup ids, and the grid never exceeds what the device keeps resident, so
-// that wait always ends.  Data that crosses workgroups is written and read with device-coherent
-// accesses.
+// long before the others, fetches the U rows into LDS, the other waves fetch a fragment of T each as
+// they finish.  The workers never wait for anything, they have the lowest workgroup ids, and the grid
+// never exceeds what the device keeps resident, so that wait always ends.  Data that crosses
+// workgroups is written and read with device-coherent accesses.
 //
 // The hand-over of T (up to rank 128) takes one trip through memory: T travels in 8-byte granules of
 // two values and a 32-bit tag that names the launch, stored and polled as single 64-bit accesses, so
@@ -40,7 +40,16 @@
 // counters that only ever grow: each launch adds exactly 2^16 to every one of them, a consumer adds
 // its share after it has read T, so whoever reads a counter before that finds the number of launches
 // before this one in its upper bits.  Nothing has to be cleared between launches, in a replayed
-// graph neither.  M = 16, N = K = 2688, r = 32: 6.2 us, with a counter of finished workers 7.2.
+// graph neither.
+//
+// What the hand-over costs beside the poll is kept off the path to the output: one wave polling all fragments
+// took a trip through memory per four of them (eight in flight at once cost as much in instruction fetches: code that
+// a launch runs once comes from memory too), its share of the counter was waited for at the next barrier, and the
+// arguments of either branch were loaded before the first request of every wave (see late_args).  Against that
+// form and the one with a counter of finished workers, us: M = 16, N = 14336, K = 512, r = 32 8.4 and 8.0, now 7.9;
+// N = 2048, K = 8192, r = 128 10.7 and 8.8, now 8.3; M = 1, N = 1024, K = 14336, r = 64 10.7 and 9.1, now 8.8; M = 16,
+// N = K = 4096, r = 64 6.8 and 7.6, now 6.3.
+#include <stddef.h>
 #include <stdlib.h>
 
 #include <type_traits>
@@ -156,11 +165,12 @@ __device__ __forceinline__ void decode_t_worker(const DecodeArgs& a, unsigned ch
     f32x4* const red = reinterpret_cast<f32x4*>(smem);              // [wave][64 lanes], after a barrier
     const XCopy xc(lane, K);
 
+    const int chunks = a.t_chunks;
     for (int item = blockIdx.x; item < a.rblocks * a.kh; item += a.nt) {
         const int jb = item / a.kh, h = item - jb * a.kh;
         f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int ci = 0; active && ci < a.t_chunks; ++ci) {
-            const uint32_t c = (uint32_t)((h * a.t_chunks + ci) * kDecTWaves + wave), kc = c * 256u;
+        for (int ci = 0; active && ci < chunks; ++ci) {
+            const uint32_t c = (uint32_t)((h * chunks + ci) * kDecTWaves + wave), kc = c * 256u;
             if (ci > 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the slots have been read
             xc.issue<XC>(xb, xs, kc, K, true);
             if (Q) {
@@ -244,44 +254,38 @@ __device__ __forceinline__ void decode_wait_t(const DecodeArgs& a) {
     }
 }
 
-// Fetches T into LDS as MFMA B fragments (K part h, k-step i -> fragment h * nks + i), polling each
-// granule until its tag is this launch's; a wait that gives up sets an error word.  Four fragments
-// are polled at a time.
-__device__ __forceinline__ void decode_fetch_t(const DecodeArgs& a, unsigned char* tlds, int lane, uint32_t group) {
-    asm volatile("" : "+v"(lane), "+s"(group));        // (what depends on them is formed here, not kept through the stream)
+// Fetches the fragments f0, f0 + step, .. of T into LDS as MFMA B fragments (K part h, k-step i -> fragment
+// h * nks + i), polling each granule until its tag is this launch's; a wait that gives up sets an error word.
+// One wave, one fragment: at most 16 fragments over 15 waves, all on their way at once, in a few instructions.
+__device__ __forceinline__ void decode_fetch_t(const DecodeArgs& a, unsigned char* tlds, int lane, uint32_t group, uint32_t f0, uint32_t step) {
+    asm volatile("" : "+v"(lane), "+s"(group), "+s"(f0));      // (what depends on them is formed here, not kept through the stream)
+    const uint32_t nks = (uint32_t)a.nks, frags = (uint32_t)a.kh * nks;
+    if (f0 >= frags) return;
     const uint32_t tag = decode_tag(a, group);
-    const uint32_t frags = (uint32_t)(a.kh * a.nks);
 #pragma unroll 1
-    for (uint32_t f0 = 0; f0 < frags; f0 += 4) {
+    for (uint32_t f = f0; f < frags; f += step) {
+        // an odd number of 16-rank blocks leaves the upper half of a K part's last k-step without ranks
+        const bool none = (a.rblocks & 1) != 0 && lane >= 32 && f % nks == nks - 1u;
 #pragma unroll 1
         for (uint32_t spins = 0;; ++spins) {
-            unsigned long long g[4][4];
+            unsigned long long g[4];
 #pragma unroll
-            for (uint32_t f = 0; f < 4; ++f)
-#pragma unroll
-                for (uint32_t e = 0; e < 4; ++e)
-                    g[f][e] = __hip_atomic_load(a.tg + ((f0 + f < frags ? f0 + f : f0) * 4u + e) * 64u + lane,
-                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (uint32_t e = 0; e < 4; ++e)
+                g[e] = __hip_atomic_load(a.tg + (f * 4u + e) * 64u + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             bool ok = true;
+            u32x4 v;
 #pragma unroll
-            for (uint32_t f = 0; f < 4; ++f) {
-                // an odd number of 16-rank blocks leaves the upper half of the last k-step without ranks
-                const bool live = (int64_t)(((f0 + f) % (uint32_t)a.nks) * 32u + (lane >> 4) * 8u) < a.ldt;
-                u32x4 v = {0u, 0u, 0u, 0u};
-                if (live && f0 + f < frags) {
-#pragma unroll
-                    for (uint32_t e = 0; e < 4; ++e) {
-                        ok = ok && (uint32_t)(g[f][e] >> 32) == tag;
-                        v[e] = (uint32_t)g[f][e];
-                    }
-                }
-                if (f0 + f < frags) *reinterpret_cast<u32x4*>(tlds + (f0 + f) * 1024u + lane * 16) = v;
+            for (uint32_t e = 0; e < 4; ++e) {
+                ok = ok && (uint32_t)(g[e] >> 32) == tag;
+                v[e] = none ? 0u : (uint32_t)g[e];
             }
-            if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) break;
+            *reinterpret_cast<u32x4*>(tlds + f * 1024u + lane * 16) = v;
+            if (__builtin_amdgcn_ballot_w64(!(ok || none)) == 0ull) break;
             if (spins > (a.spin_limit >> 4)) {
                 if (lane == 0) atomicOr(a.ctrl + 3, 1u);
                 break;
             }
+            __builtin_amdgcn_s_sleep(1);
         }
     }
 }
@@ -391,6 +395,22 @@ __device__ __forceinline__ void scatter_u_rank(const uint32_t (&w)[32], unsigned
         }
 }
 
+// The argument block behind the kernel's leading scalar arguments, through an address the compiler knows nothing about:
+// its loads stay where the values are needed.  Read through the parameter itself, whatever any branch needs is loaded at
+// the kernel's first instructions, and every wave's first request to memory waits for it: 0.3 to 0.7 us of a launch
+// whose stream is short.  The other variants keep the parameter: without T there is little to load (K = 14336, M = 8
+// loses 1.5 % by the later loads), and with LR == 2 the longest chain is T itself.
+struct DecodeKernargs {         // (the kernel's parameters in order: the layout of the argument segment)
+    const void* q3; const f16* X; uint32_t units, K, nb; int M, nt; uint32_t nmain, cpw, rot_mask, x_bytes;
+    DecodeArgs args;
+};
+__device__ __forceinline__ const DecodeArgs& late_args() {
+    typedef const __attribute__((address_space(4))) char* Segment;
+    Segment p = (Segment)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(DecodeKernargs, args);
+    asm volatile("" : "+s"(p));
+    return *(const DecodeArgs*)p;
+}
+
 // SYM: the weight blob is symmetric (zero-point-free conversion).  Q (with LR == 1): the compensator
 // is the pair of INT3 blobs of milo_pack_lr3.
 template <int R, int LR, int XC, bool SYM, bool Q, bool BF>
@@ -401,45 +421,42 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
     // What a streaming wave needs for its first requests comes as leading scalar arguments, which the
     // hardware places in registers when it starts the wave (the build asks for that with
     // -amdgpu-kernarg-preload-count); everything else is read from the argument block when it is
-    // needed.  The values are the same as the block's.
-    DecodeArgs a = a_;
-    a.w.q3 = q3_; a.X = X_; a.units = units_; a.K = (int64_t)K_; a.nb = nb_; a.M = M_; a.nt = nt_; a.nmain = nmain_;
-    a.chunks_per_wave = cpw_; a.rot_mask = rot_mask_; a.x_bytes = x_bytes_;
+    // needed (LR == 1: late_args).  The values are the same as the block's.
+    DecodeArgs pa = a_;
+    pa.w.q3 = q3_; pa.X = X_; pa.units = units_; pa.K = (int64_t)K_; pa.nb = nb_; pa.M = M_; pa.nt = nt_; pa.nmain = nmain_;
+    pa.chunks_per_wave = cpw_; pa.rot_mask = rot_mask_; pa.x_bytes = x_bytes_;
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int nworkers = LR > 0 ? a.nt : 0;
+    const int nworkers = LR > 0 ? nt_ : 0;
     if (LR > 0 && (int)blockIdx.x < nworkers) {
+        DecodeArgs a = LR == 1 ? late_args() : pa;
+        a.X = X_; a.K = (int64_t)K_; a.M = M_; a.nt = nt_; a.nmain = nmain_;        // (in registers already)
         decode_t_worker<XC, Q, BF, LR == 1>(a, smem);
     } else {
         const int j16 = lane & 15, q = lane >> 4;
-        const int M = a.M;
-        const uint32_t K = (uint32_t)a.K;                   // < 2^27 (checked on the host)
+        const int M = M_;
+        const uint32_t K = K_;                              // < 2^27 (checked on the host)
         const uint32_t G = K / kGroup;
-        const uint32_t NB = a.nb;                           // 16-row blocks
-        const int r = a.w.r;
+        const uint32_t NB = nb_;                            // 16-row blocks
         W3Buf wb;
-        wb.a = make_rsrc(a.w.q3, (uint64_t)(a.units * 16u));                // (units <= 2^26)
-        wb.b = make_rsrc(reinterpret_cast<const char*>(a.w.q3) + (uint64_t)a.units * 16u, (uint64_t)(a.units * 12u));
-        const uint32_t nmain = a.nmain;
-        const BufRsrc tb = make_rsrc(a.T, (uint64_t)a.t_bytes);
-        const int ksu = (r + 31) >> 5;                  // k-steps of 32 ranks in use
-        // (T fragments in LDS: K part h, k-step i -> h * ksu + i)
-        bool t_ready = false;
+        wb.a = make_rsrc(q3_, (uint64_t)(units_ * 16u));                // (units <= 2^26)
+        wb.b = make_rsrc(reinterpret_cast<const char*>(q3_) + (uint64_t)units_ * 16u, (uint64_t)(units_ * 12u));
+        const uint32_t nmain = nmain_;
 
         const int wave_s = __builtin_amdgcn_readfirstlane(wave);        // known to be uniform
         DecodeStream<R, XC, SYM, BF> st{wb,
-                               make_rsrc(a.X, (uint64_t)a.x_bytes),
+                               make_rsrc(X_, (uint64_t)x_bytes_),
                                XCopy(lane, K),
                                smem + wave_s * kDecSlotBytes,
                                K, G, NB, 0u, 0u, 0u, (uint32_t)lane, (uint32_t)q, (uint32_t)j16};
-        st.C = a.chunks_per_wave;
+        st.C = cpw_;
         st.span = st.C * kDecWaves;
         // (rotation by a masked product instead of a remainder: no division before the first request)
-        st.first = (uint32_t)wave_s + ((blockIdx.x * 5u) & a.rot_mask);
+        st.first = (uint32_t)wave_s + ((blockIdx.x * 5u) & rot_mask_);
         if (st.first >= st.span) st.first -= st.span;
 
         // (every streaming workgroup has at least one turn: the number of turns is first looked at after it)
-        uint32_t turn = 0, blk = blockIdx.x - nworkers;
+        uint32_t turn = 0, turns, blk = blockIdx.x - nworkers;
         do {
             const uint32_t rb0 = blk * R;
             f32x4 acc[R];
@@ -453,12 +470,18 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
             // each wave leaves its partial sums in its own slot, which it has finished reading
 #pragma unroll
             for (int b = 0; b < R; ++b) red[wave * (kDecSlotBytes / 16) + b * 64 + lane] = acc[b];
+            const DecodeArgs& a = LR == 1 ? late_args() : pa;
+            const int r = a.w.r;
+            const int ksu = (r + 31) >> 5;                  // k-steps of 32 ranks in use
+            // (T fragments in LDS: K part h, k-step i -> h * ksu + i)
+            turns = a.turns;
+            int kh = a.kh;
+            const BufRsrc tb = make_rsrc(LR == 2 ? a.T : nullptr, LR == 2 ? (uint64_t)a.t_bytes : 0u);
             if (LR > 0 && wave == 0) {
                 // Everything the epilogue needs besides the partial sums, fetched by the wave that
                 // is done first, while the others still stream; its requests go ahead of theirs.
                 // U rows of the R row blocks as MFMA A fragments (k-step i, lane (j16, q) =
-                // U[n][32i + 8q ..]), then, once every T worker has been counted, T as B
-                // fragments with device-coherent reads: the workers wrote it during this launch.
+                // U[n][32i + 8q ..]); LR == 2: nothing but the wait for T.
                 __builtin_amdgcn_s_setprio(3);
                 if (LR == 1 && Q) {
                     // INT3 U: the blob holds U^T [ldt x N] with groups of 64 along N, and this
@@ -511,21 +534,26 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
                         }
                     }
                 }
-                if (!t_ready) {
-                    if (LR == 1) decode_fetch_t(a, smem + kDecTLds, lane, (blockIdx.x - nworkers) % kDecGroups);
-                    else decode_wait_t(a);
-                    t_ready = true;
-                }
+                if (LR == 2 && turn == 0) decode_wait_t(a);
                 wait_vmem();
                 __builtin_amdgcn_s_setprio(0);
-                // T has been read: this workgroup's share of its counter
-                if (LR == 1 && turn == 0 && lane == 0) {
-                    const uint32_t wg = blockIdx.x - nworkers;
-                    const uint32_t members = (nmain - wg % kDecGroups + kDecGroups - 1u) / kDecGroups;
-                    atomicAdd(a.epoch + (wg % kDecGroups) * kDecGroupStride, wg < kDecGroups ? 65537ull - members : 1ull);
-                }
             }
+            if (LR == 1 && turn == 0 && wave >= 1) {
+                __builtin_amdgcn_s_setprio(3);
+                decode_fetch_t(a, smem + kDecTLds, lane, (blockIdx.x - nworkers) % kDecGroups, (uint32_t)wave_s - 1u, kDecWaves - 1);
+                __builtin_amdgcn_s_setprio(0);
+            }
+            uint32_t n_out = (uint32_t)a.N;
+            f16* const y_out = a.Y;
+            if (LR == 1) asm volatile("" : "+s"(n_out), "+s"(turns), "+s"(kh) : "s"(y_out));       // (loaded before the barrier)
             __syncthreads();                                       // partial sums, U and T are in LDS
+            // T has been read: this workgroup's share of its counter, by a wave without a part in the epilogue and after
+            // the barrier, which would wait for the atomic's way to memory and back
+            if (LR == 1 && turn == 0 && wave == kDecWaves - 1 && lane == 0) {
+                const uint32_t wg = blockIdx.x - nworkers;
+                const uint32_t members = (nmain - wg % kDecGroups + kDecGroups - 1u) / kDecGroups;
+                atomicAdd(a.epoch + (wg % kDecGroups) * kDecGroupStride, wg < kDecGroups ? 65537ull - members : 1ull);
+            }
             if (wave < R) {
                 // wave b finishes row block b: sum of the waves' partials in wave order
                 const int b = wave;
@@ -543,7 +571,7 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
                 if (LR == 1) {
                     int f = 0;
 #pragma unroll 1
-                    for (int h = 0; h < a.kh; ++h) {
+                    for (int h = 0; h < kh; ++h) {
 #pragma unroll 1
                         for (int i = 0; i < ksu; ++i, ++f)
                             sum = BF ? mfma16_bf16(__builtin_bit_cast(bf16x8, ulds[(b * kDecKS + i) * 64 + lane]),
@@ -557,7 +585,7 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
                         const int k0 = ks + 8 * q;
                         f16x8 av = zero_f16x8();
                         if (nrow < a.N) av = load_row8(a.w.U + nrow * r, k0, r, (r & 7) == 0);
-                        for (int h = 0; h < a.kh; ++h) {
+                        for (int h = 0; h < kh; ++h) {
                             const f16x8 bv = __builtin_bit_cast(
                                 f16x8, buf_load16_coherent(tb, k0 < a.ldt ? (uint32_t)(((h * 16 + j16) * a.ldt + k0) * 2)
                                                                           : kOobOffset));
@@ -570,7 +598,7 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
                 // scalars the compiler cannot move: formed at the top of the kernel it would sit in
                 // registers through the whole stream, or in scratch memory, a round trip to memory
                 // right before the store.)
-                uint32_t n_out = (uint32_t)a.N, m_out = (uint32_t)M;
+                uint32_t m_out = (uint32_t)M;
                 asm volatile("" : "+s"(n_out), "+s"(m_out));
                 const uint32_t n = nb + 4u * q;
                 if ((uint32_t)j16 < m_out && n < n_out) {
@@ -583,26 +611,27 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
                         for (int e = 0; e < 4; ++e) o[e] = (f16)sum[e];
                         ob = __builtin_bit_cast(u32x2, o);
                     }
-                    *reinterpret_cast<u32x2*>(a.Y + ((uint64_t)j16 * n_out + n)) = ob;
+                    *reinterpret_cast<u32x2*>(y_out + ((uint64_t)j16 * n_out + n)) = ob;
                 }
             }
-            if (turn + 1 < a.turns) __syncthreads();      // slots, U and the partial sums are reused
+            if (turn + 1 < turns) __syncthreads();      // slots, U and the partial sums are reused
             blk += nmain;
-        } while (++turn < a.turns);
+        } while (++turn < turns);
     }
 
     // LR == 2: the streaming workgroups read T from memory in their epilogue, so they sign off last.
     if (LR == 2 && (int)blockIdx.x >= nworkers) {
         __syncthreads();
         if (tid == 0)
-            __hip_atomic_store(a.done + (blockIdx.x - nworkers), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(pa.done + (blockIdx.x - nworkers), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // Worker 0 stays until every streaming workgroup has signed off (which each does only after
     // it has seen all workers counted), then restores the control words for the next launch.
     // No returning atomic on a shared word is involved: hundreds of those on one address
     // serialize for several microseconds.
     if (LR == 2 && blockIdx.x == 0 && wave == 0) {
-        const uint32_t nmain = a.nmain;
+        const DecodeArgs& a = pa;
+        const uint32_t nmain = nmain_;
         bool all = false;
         for (uint32_t spins = 0; !all; ++spins) {
             all = true;
@@ -707,8 +736,11 @@ static int decode_capacity() {
     return cached[dev];
 }
 
-// K parts of the T workers: kDecTWaves chunks of 256 columns each, or twice that where the fragments of
-// T would not fit the consumers' LDS otherwise (rank 128 from K = 8192 on).
+// K parts of the T workers: kDecTWaves chunks of 256 columns each, or twice that.  Two chunks per wave cost a worker a
+// second round trip and halve the fragments every streaming workgroup fetches: from five fragments on that is
+// the faster side (M = 16, us: N = 4096, K = 14336, r = 32, 7 or 4 fragments, 16.3 -> 16.1; r = 64, 14 or 8, 17.1 -> 16.3;
+// N = 2048, K = 8192, r = 64, 8 or 4, 8.4 -> 8.0; N = K = 4096, r = 128, 8 or 4, 6.7 -> 6.6), with up to four there
+// is nothing to gain, and beyond 16, all that the LDS holds, it is the only one (r = 128 beyond K = 8192).
 static int decode_k_parts(int64_t K, int chunks) { return (int)((K + 256 * kDecTWaves * chunks - 1) / (256 * kDecTWaves * chunks)); }
 struct DecodeT {
     bool staged;        // granules and the staged path (LR == 1)
@@ -717,16 +749,13 @@ struct DecodeT {
 static DecodeT decode_t_plan(int64_t N, int64_t K, int r) {
     DecodeT t;
     t.nks = (r + 31) / 32;
-    t.staged = false;
-    for (t.chunks = 1; t.chunks <= 2; ++t.chunks) {
-        t.kh = decode_k_parts(K, t.chunks);
-        if (r > 0 && r <= 32 * kDecKS && t.kh * t.nks <= kDecTFrags && (uint64_t)N * (uint64_t)r * 2u < 0xFFFFFFF0ull) {
-            t.staged = true;
-            return t;
-        }
+    t.chunks = decode_k_parts(K, 1) * t.nks > 4 ? 2 : 1;
+    t.kh = decode_k_parts(K, t.chunks);
+    t.staged = r > 0 && r <= 32 * kDecKS && t.kh * t.nks <= kDecTFrags && (uint64_t)N * (uint64_t)r * 2u < 0xFFFFFFF0ull;
+    if (!t.staged) {
+        t.chunks = 1;
+        t.kh = decode_k_parts(K, 1);
     }
-    t.chunks = 1;
-    t.kh = decode_k_parts(K, 1);
     return t;
 }
 
@@ -801,9 +830,8 @@ int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream) {
     const int lr = r == 0 ? 0 : tp.staged ? 1 : 2;
     const int xc = a.M <= 2 ? 1 : a.M <= 4 ? 2 : a.M <= 8 ? 4 : 8;    // activation copies per chunk: rows 2i, 2i+1
     const bool q = r > 0 && (a.w.flags & MILO_LR_INT3) != 0;
-    // an INT3 compensator only runs on the staged path, with one chunk per wave: its T fragments must fit
-    // the workgroup's LDS at that
-    if (q && (lr != 1 || tp.chunks != 1)) return MILO_ERR_SHAPE;
+    // an INT3 compensator only runs on the staged path; the limit is the one of its fragments at one chunk per wave
+    if (q && (lr != 1 || decode_k_parts(a.K, 1) * tp.nks > kDecTFrags)) return MILO_ERR_SHAPE;
     const bool bf = (a.w.flags & MILO_ACT_BF16) != 0;
     if (bf && q) return MILO_ERR_SHAPE;
     const DecodeKernel kernel = decode_variant(R, lr, xc, (a.w.flags & MILO_W3_SYMMETRIC) != 0, q, bf);

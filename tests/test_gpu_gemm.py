@@ -61,6 +61,47 @@ def test_decode_block_loop_second_turn_with_staged_low_rank():
     _check_case(3, 16400, 4352, 24, seed=812)
 
 
+@pytest.mark.parametrize("N,K,r", [
+    (64, 8192, 32), (64, 8256, 32),         # four and five fragments of T: one and two chunks per wave of a T worker
+    (80, 10304, 96), (64, 14336, 96), (64, 16384, 128),     # only two chunks fit the LDS; 16 fragments, over 15 waves
+    (64, 16448, 128),                       # too many even so: plain rows of T
+    (48, 4160, 72),                         # an odd number of rank blocks, the last chunk nearly empty
+])
+@pytest.mark.parametrize("M", [1, 16])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16", "int3"])
+def test_decode_parts_of_t(N, K, r, M, dtype):
+    import torch
+    from paper_2504_02658_amd import api
+    if r > N:
+        N = (r + 63) // 64 * 64
+    if dtype == "int3":
+        N = (N + 63) // 64 * 64
+    g = torch.Generator()
+    g.manual_seed(N + K + r + M)
+    randn = lambda *shape: torch.randn(shape, generator=g)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    X, W = randn(M, K).to(dt), (randn(N, K) * 0.02).numpy()
+    U, V = randn(N, r) * 0.1, randn(r, K) * 0.1         # a low-rank term larger than the product: its errors show
+    q, s, z = oracle.quantize_rtn(W)
+    pw = api.pack_w3(torch.from_numpy(W).cuda())
+    if dtype == "int3":
+        pw = pw.with_int3_compensator(*api.pack_lr3(U.cuda(), V.cuda()), r)
+        Ud, Vd = oracle.dequantize_compensator(*oracle.quantize_compensator(U.numpy(), V.numpy()), r)
+        if (r + 31) // 32 * ((K + 2047) // 2048) > 16:      # the limit of INT3 compensators at decode sizes
+            with pytest.raises(api.MiloError) as e:
+                api.w3lr_gemm(X.cuda(), pw)
+            assert e.value.status == 2
+            return
+    else:
+        pw = pw.with_compensator(U.to(dt).cuda(), V.to(dt).cuda())
+        Ud, Vd = U.to(dt).double().numpy(), V.to(dt).double().numpy()
+    Y = api.w3lr_gemm(X.cuda(), pw).double().cpu().numpy()
+    ref = oracle.w3lr_linear(X.double().numpy(), q, s, z, Ud, Vd)
+    # One rounding to 16 bits in T per K part (their squares add up to one rounding of T), one in the output; fp16 2^-11 each at
+    # most, bf16 2^-8, a third of that in the mean.
+    assert np.linalg.norm(Y - ref) <= (8.0 if dtype == "bf16" else 1.0) * 2.0 ** -11 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("M", [17, 32, 33, 64, 100, 130, 257])
 def test_tiled_rows(M):
     _check_case(M, 272, 1408, 8, seed=60 + M)
