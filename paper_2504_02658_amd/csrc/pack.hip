@@ -77,8 +77,8 @@ __global__ __launch_bounds__(kRowBlockThreads) void pack_w3_kernel(const float* 
 }
 
 // The transposed factor of milo_pack_lr3 (symmetric quantizer): element (n, k) = W[n + k * col_stride] for
-// n < n_valid, zero above.  A few rows, small: one lane per unit, straight from memory (neighbouring lanes
-// are neighbouring rows, which are adjacent here).
+// n < n_valid, zero above.  One lane per unit, straight from memory (neighbouring lanes are neighbouring rows,
+// which are adjacent here).
 __global__ __launch_bounds__(256) void pack_w3_transposed_kernel(const float* __restrict__ W, int64_t N, int64_t K,
                                                                  int64_t col_stride, int64_t n_valid,
                                                                  uint32_t* __restrict__ planeA, uint32_t* __restrict__ planeB) {
@@ -93,6 +93,141 @@ __global__ __launch_bounds__(256) void pack_w3_transposed_kernel(const float* __
     uint32_t d[6];
     unit_words(v, d);
     store_row_block_unit(d, sz, u, planeA, planeB);
+}
+
+// For few units (kPackFewUnits): 16 lanes cooperate on one (64 weights, one float4 each), so that no lane walks 64 weights
+// in turn; a wave packs four units that are consecutive groups of one row.
+constexpr int kPackThreads = 256;
+constexpr int kUnitsPerBlock = kPackThreads / 16;
+
+__device__ __forceinline__ float shfl_xor16(float v, int m) { return __shfl_xor(v, m, 16); }
+__device__ __forceinline__ uint32_t shfl_xor16(uint32_t v, int m) {
+    return (uint32_t)__shfl_xor((int)v, m, 16);
+}
+
+// Lane l16 of the 16 holds the codes 4*l16 .. 4*l16+3 of unit u in q; lane 0 stores the unit.
+__device__ __forceinline__ void store_unit(const uint32_t (&q)[4], int l16, f16 s16, f16 z16, int64_t u,
+                                           uint32_t* __restrict__ planeA, uint32_t* __restrict__ planeB) {
+    // This lane owns code pairs P0 = 2*l16 (codes 4*l16, 4*l16+1) and P0+1.  Build its share of
+    // the six words, then OR the shares of the 16 lanes together.
+    uint32_t d[6] = {0u, 0u, 0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int P = 2 * l16 + h;
+        const uint32_t lo = q[2 * h], hi = q[2 * h + 1];
+        if (P < 30) {
+            const int j = P / 5, c = P - 5 * j;
+            const uint32_t bits = (lo << (3 * c)) | (hi << (16 + 3 * c));
+#pragma unroll
+            for (int jj = 0; jj < 6; ++jj)
+                if (jj == j) d[jj] |= bits;
+        } else {
+            const int base = (P == 30) ? 0 : 3;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const uint32_t bits = (((lo >> i) & 1u) << 15) | (((hi >> i) & 1u) << 31);
+#pragma unroll
+                for (int jj = 0; jj < 6; ++jj)
+                    if (jj == base + i) d[jj] |= bits;
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) {
+#pragma unroll
+        for (int jj = 0; jj < 6; ++jj) d[jj] |= shfl_xor16(d[jj], m);
+    }
+
+    if (l16 == 0) {
+        *reinterpret_cast<u32x4*>(planeA + 4 * u) = u32x4{d[0], d[1], d[2], d[3]};
+        planeB[3 * u] = d[4];
+        planeB[3 * u + 1] = d[5];
+        planeB[3 * u + 2] = (uint32_t)__builtin_bit_cast(unsigned short, s16) |
+                            ((uint32_t)__builtin_bit_cast(unsigned short, z16) << 16);
+    }
+}
+
+// Element (n, k) = W[n * row_stride + k * col_stride] for n < n_valid, zero for the rows from there up to N.
+template <bool SYM>
+__global__ __launch_bounds__(kPackThreads) void pack_w3_few_kernel(
+    const float* __restrict__ W, int64_t N, int64_t K, int64_t row_stride, int64_t col_stride, int64_t n_valid,
+    uint32_t* __restrict__ planeA, uint32_t* __restrict__ planeB) {
+    const int64_t G = K / kGroup;
+    const int64_t total = N * G;
+    const int64_t gu = (int64_t)blockIdx.x * kUnitsPerBlock + (threadIdx.x >> 4);
+    const int l16 = threadIdx.x & 15;
+    if (gu >= total) return;          // whole 16-lane groups leave together
+    const int64_t n = gu / G;
+    const int64_t g = gu - n * G;
+
+    float4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (n < n_valid) {
+        const float* src = W + n * row_stride + (g * kGroup + 4 * l16) * col_stride;
+        if (col_stride == 1) {
+            v = *reinterpret_cast<const float4*>(src);
+        } else {
+            v.x = src[0];
+            v.y = src[col_stride];
+            v.z = src[2 * col_stride];
+            v.w = src[3 * col_stride];
+        }
+    }
+    float mn = fminf(fminf(v.x, v.y), fminf(v.z, v.w));
+    float mx = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) {
+        mn = fminf(mn, shfl_xor16(mn, m));
+        mx = fmaxf(mx, shfl_xor16(mx, m));
+    }
+
+    f16 s16, z16;
+    uint32_t q[4];
+    const float in[4] = {v.x, v.y, v.z, v.w};
+    if (SYM) {
+        const float amax = fmaxf(mx, -mn);              // largest magnitude of the group
+        const float s32 = (amax + amax) / 7.0f;
+        s16 = (f16)s32;
+        const float sf = (float)s16;
+        z16 = (f16)4.0f;
+        if (!(sf > 0.0f && sf <= 65504.0f)) {           // zero, NaN or overflowed step: all codes 4
+            s16 = (f16)1.0f;
+            q[0] = q[1] = q[2] = q[3] = 4u;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float t = in[i] / sf;
+                t = __builtin_rintf(t);
+                t = t + 4.0f;
+                t = fminf(fmaxf(t, 0.0f), 7.0f);
+                q[i] = (uint32_t)t;
+            }
+        }
+    } else {
+        const float s32 = (mx - mn) / 7.0f;
+        s16 = (f16)s32;
+        const float sf = (float)s16;
+        const bool degenerate = !(sf > 0.0f && sf <= 65504.0f);   // zero, NaN or overflowed scale
+        if (degenerate) {
+            s16 = (f16)1.0f;
+            z16 = (f16)(-mn);
+            q[0] = q[1] = q[2] = q[3] = 0u;
+        } else {
+            float z = __builtin_rintf((-mn) / sf);
+            z = fminf(fmaxf(z, -65504.0f), 65504.0f);
+            z16 = (f16)z;
+            const float zf = (float)z16;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float t = in[i] / sf;
+                t = t + zf;
+                t = __builtin_rintf(t);
+                t = fminf(fmaxf(t, 0.0f), 7.0f);
+                q[i] = (uint32_t)t;
+            }
+        }
+    }
+
+    store_unit(q, l16, s16, z16, unit_index(n, g, G), planeA, planeB);
 }
 
 // One thread per unit: unpack to bytes / dequantize to fp16.  Test aids, not tuned.
@@ -153,6 +288,18 @@ extern "C" size_t milo_w3_packed_bytes(int64_t N, int64_t K) {
     return (size_t)(N * K / 64 * 28);
 }
 
+// Up to this many units sixteen lanes each are faster than one: the chip has lanes to spare, and what counts is the longest
+// chain.  us, sixteen lanes / one: 512 x 512 (4096 units) 3.3 / 3.8, 512 x 1024 (8192) 3.82 / 3.84, 512 x 1280 (10240) 4.1 / 3.8;
+// compensators of rank 32 and 48 with N = 14336 (7168 and 10752 units of U) 7.2 / 8.8 and 8.4 / 7.9.
+constexpr int64_t kPackFewUnits = 8192;
+template <bool SYM>
+static void launch_few(const float* W, int64_t N, int64_t K, int64_t row_stride, int64_t col_stride, int64_t n_valid, uint32_t* planeA,
+                       uint32_t* planeB, void* stream) {
+    const int64_t units = N * (K / kGroup), blocks = (units + kUnitsPerBlock - 1) / kUnitsPerBlock;
+    pack_w3_few_kernel<SYM><<<dim3((unsigned)blocks), dim3(kPackThreads), 0, (hipStream_t)stream>>>(W, N, K, row_stride, col_stride, n_valid,
+                                                                                                   planeA, planeB);
+}
+
 template <bool SYM>
 static int pack_launch(const float* W, int64_t N, int64_t K, int group_size, void* q3, void* stream) {
     if (!W || !q3) return MILO_ERR_NULL;
@@ -163,6 +310,10 @@ static int pack_launch(const float* W, int64_t N, int64_t K, int group_size, voi
     if (blocks > 0x7fffffff) return MILO_ERR_SHAPE;
     uint32_t* planeA = reinterpret_cast<uint32_t*>(q3);
     uint32_t* planeB = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(q3) + (N * K) / 4);
+    if (N * (K / kGroup) <= kPackFewUnits) {
+        launch_few<SYM>(W, N, K, K, 1, N, planeA, planeB, stream);
+        return launch_status();
+    }
     pack_w3_kernel<SYM><<<dim3((unsigned)blocks), dim3(kRowBlockThreads), 0, (hipStream_t)stream>>>(W, N, K, K, N, planeA,
                                                                                                    planeB);
     return launch_status();
@@ -191,7 +342,8 @@ extern "C" int milo_pack_lr3(const float* U, const float* V, int64_t N, int64_t 
         const int64_t units = rp * (N / kGroup), blocks = (units + 255) / 256;
         uint32_t* planeA = reinterpret_cast<uint32_t*>(u3);
         uint32_t* planeB = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(u3) + (rp * N) / 4);
-        pack_w3_transposed_kernel<<<dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream>>>(U, rp, N, r, r, planeA, planeB);
+        if (units <= kPackFewUnits) launch_few<true>(U, rp, N, 1, r, r, planeA, planeB, stream);
+        else pack_w3_transposed_kernel<<<dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream>>>(U, rp, N, r, r, planeA, planeB);
         if (launch_status() != MILO_OK) return MILO_ERR_HIP;
     }
     // V: [rp x K], element (j, k) = V[j * K + k], groups of 64 along K
@@ -199,8 +351,9 @@ extern "C" int milo_pack_lr3(const float* U, const float* V, int64_t N, int64_t 
         const int64_t blocks = row_block_grid(rp, K);
         uint32_t* planeA = reinterpret_cast<uint32_t*>(v3);
         uint32_t* planeB = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(v3) + (rp * K) / 4);
-        pack_w3_kernel<true><<<dim3((unsigned)blocks), dim3(kRowBlockThreads), 0, (hipStream_t)stream>>>(V, rp, K, K, r, planeA,
-                                                                                                    planeB);
+        if (rp * (K / kGroup) <= kPackFewUnits) launch_few<true>(V, rp, K, K, 1, r, planeA, planeB, stream);
+        else pack_w3_kernel<true><<<dim3((unsigned)blocks), dim3(kRowBlockThreads), 0, (hipStream_t)stream>>>(V, rp, K, K, r, planeA,
+                                                                                                         planeB);
     }
     return launch_status();
 }

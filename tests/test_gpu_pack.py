@@ -123,3 +123,30 @@ def test_pack_quotients_next_to_ties(N, K, symmetric):
     near = np.nextafter(W, np.where(side < 0, -np.inf, np.inf).astype(np.float32))
     W[..., 2:] = np.where(side == 0, W, near)[..., 2:]
     _assert_pack_equal(np.ascontiguousarray(W.reshape(N, K)), f"near ties {N}x{K}", symmetric)
+
+
+@pytest.mark.parametrize("N,K", [(1024, 512), (1024, 576), (2064, 320), (16, 33024), (8208, 64)])
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_pack_of_more_units_than_sixteen_lanes_each_are_for(N, K, symmetric):
+    # 8192 units and more, where a lane takes a whole group; one to four groups in a wave's last column block, weights next
+    # to ties as above
+    rng = np.random.default_rng(N + K)
+    s = (2.0 ** rng.uniform(-12, 2, (N, K // 64, 1))).astype(np.float16).astype(np.float32)
+    half = (rng.integers(-4, 4, (N, K // 64, 64)) + np.float32(0.5)).astype(np.float32)
+    half[..., 0], half[..., 1] = -3.5, 3.5
+    W = half * s
+    side = rng.integers(-1, 2, W.shape)
+    near = np.nextafter(W, np.where(side < 0, -np.inf, np.inf).astype(np.float32))
+    W[..., 2:] = np.where(side == 0, W, near)[..., 2:]
+    _assert_pack_equal(np.ascontiguousarray(W.reshape(N, K)), f"{N}x{K}", symmetric)
+
+
+@pytest.mark.parametrize("N,K,r", [(128, 64, 1), (10944, 16384, 48), (16384, 10944, 40)])
+def test_pack_lr3_on_both_sides_of_the_limit(N, K, r):
+    import torch
+    from paper_2504_02658_amd import api
+    rng = np.random.default_rng(N + r)
+    U, V = (rng.standard_normal(s).astype(np.float32) for s in ((N, r), (r, K)))
+    u3, v3 = api.pack_lr3(torch.from_numpy(U).cuda(), torch.from_numpy(V).cuda())
+    uq, vq = oracle.quantize_compensator(U, V)
+    assert np.array_equal(u3.cpu().numpy(), oracle.pack_w3(*uq)) and np.array_equal(v3.cpu().numpy(), oracle.pack_w3(*vq))
