@@ -118,10 +118,17 @@ int milo_dequant_w3(const void* q3, int64_t N, int64_t K, milo_half* W_dq, void*
  * all `workspace_bytes` with a small fill kernel on `stream` (the kernels synchronise through
  * counters and flags in it that must start at zero).  Call it once after allocating the workspace
  * and again after a call on it returned an error or milo_workspace_status reported MILO_ERR_WAIT;
- * the kernels leave their counters and flags cleared when they finish, so successive calls need no
- * further preparation and no memset (which makes them safe to capture in a HIP graph and replay).
+ * successive calls need no further preparation and no memset (which makes them safe to capture in a
+ * HIP graph and replay), for any mix of shapes and ranks that the workspace is large enough for.
+ * That holds while nothing else writes to the workspace: a GEMM workspace keeps state from call to
+ * call in its first MILO_WORKSPACE_STATE_BYTES (flags that the kernels leave at zero, counters that
+ * grow with every launch), so between calls those bytes are not scratch for the caller, and a
+ * workspace that milo_moe_w3lr_forward has used serves milo_w3lr_gemm only after another
+ * milo_workspace_init (and the other way round).  Without it later calls wait until their bound and
+ * report MILO_ERR_WAIT, call after call.  What lies behind those bytes may hold anything.
  * Errors: NULL, WORKSPACE (fewer than 256 bytes), ALIGN, HIP.
  */
+#define MILO_WORKSPACE_STATE_BYTES 59648u
 int milo_workspace_init(void* workspace, size_t workspace_bytes, void* stream);
 
 /*
@@ -144,7 +151,7 @@ int milo_workspace_status(const void* workspace, void* stream);
  *   X [M x K] fp16;  q3 as written by milo_pack_w3 (its zero-points may be any finite fp16,
  *   integer or not);  U [N x r], V [r x K] fp16 row-major, ignored when r == 0;  Y [M x N] fp16.
  *   workspace: at least milo_w3lr_gemm_workspace(M, N, K, r) bytes of device memory, prepared
- *   once with milo_workspace_init; beyond the control block its contents are scratch.  Calls that
+ *   once with milo_workspace_init (see there for what has to keep its value between calls).  Calls that
  *   share a workspace must be ordered on one stream (concurrent calls would race on it).
  * M <= 16 takes the weight-streaming decode kernel (a single launch that also forms X V^T),
  * larger M the tiled MFMA kernel (which also forms X V^T inside the launch; when the problem has
@@ -316,7 +323,8 @@ int milo_moe_w3lr_check_experts_flags(const milo_w3lr_expert* experts, int E, in
  *   topk_ids     [T x topk] int32, the ids of one token must be distinct
  *   topk_weights [T x topk] fp32
  *   Y            [T x H] fp16
- *   workspace    at least milo_moe_w3lr_workspace(T, H, F, E, topk, r_max) bytes
+ *   workspace    at least milo_moe_w3lr_workspace(T, H, F, E, topk, r_max) bytes, prepared once with
+ *                milo_workspace_init; not shared with milo_w3lr_gemm (see milo_workspace_init)
  * An id outside 0..E-1 contributes nothing and raises a flag that
  * milo_moe_w3lr_routing_status() reports; an expert with no tokens is legal.
  * Each routed pair's weighted expert output is kept as fp16 (per K split of the down projection,

@@ -105,6 +105,7 @@ constexpr uint32_t kDecGroups = 32, kDecGroupStride = 8;       // stride in 8-by
 constexpr int kDecGranuleBytes = 32768;                         // 16 fragments of 2 KB
 constexpr size_t kGemmDoneAt = 256, kGemmFlagsAt = kGemmDoneAt + kDecDoneBytes, kGemmCountersAt = kGemmFlagsAt + kTiledFlagBytes,
                  kGemmGranulesAt = kGemmCountersAt + kDecGroups * kDecGroupStride * 8, kGemmHeadBytes = kGemmGranulesAt + kDecGranuleBytes;
+static_assert(kGemmHeadBytes == MILO_WORKSPACE_STATE_BYTES, "stated in milo.h");
 // Bytes of flag words behind the head (0: they fit in it).
 size_t gemm_flags_behind(int64_t M);
 constexpr int kDecMaxWorkers = 32;  // workgroups forming T = X V^T in the decode kernel

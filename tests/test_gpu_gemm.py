@@ -402,6 +402,31 @@ def test_calls_of_both_kernels_on_one_workspace():
         (131072 + 40, 16, 64, 8), (3, 256, 1024, 256), (131072, 16, 64, 8), (5, 256, 1024, 0), (300, 256, 1024, 72)])
 
 
+def test_decode_calls_of_many_forms_on_one_workspace():
+    # every launch has to move all counters by the same amount, whatever its rank, its parts of T and the number of its
+    # streaming workgroups (one, fewer than the 32 counters, a full chip)
+    _shared_workspace_sequence([
+        (16, 16, 512, 8), (1, 14336, 512, 20), (4, 16, 14336, 16), (16, 1024, 14336, 128), (2, 16, 512, 0), (7, 14336, 512, 8),
+        (16, 16, 512, 16), (3, 272, 2048, 128), (8, 528, 4096, 200), (16, 1024, 14336, 128), (5, 14336, 512, 20), (16, 16, 512, 8)])
+
+
+def test_bytes_behind_the_state_of_a_workspace_may_hold_anything():
+    import torch
+    from paper_2504_02658_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    state = 59648                                       # MILO_WORKSPACE_STATE_BYTES
+    for M, N, K, r in ((4, 256, 1024, 256), (4, 256, 1024, 32), (96, 512, 4096, 24), (131072 + 40, 16, 64, 8)):
+        pw = api.pack_w3(randn(N, K) * 0.02).with_compensator((randn(N, r) * 0.1).half(), (randn(r, K) * 0.1).half())
+        X = randn(M, K).half()
+        ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, r))
+        ref = api.w3lr_gemm(X, pw, workspace=ws)
+        ws[state:].fill_(0xa5)
+        assert torch.equal(api.w3lr_gemm(X, pw, workspace=ws), ref), (M, N, K, r)
+        assert api.workspace_status(ws) == 0
+
+
 # ------------------------------------------------------------------ INT3 compensators, weight flags
 
 def _int3_case(M, N, K, r, seed, symmetric=False):
