@@ -219,8 +219,10 @@ int milo_pack_lr3(const float* U, const float* V, int64_t N, int64_t K, int r,
  *   U, V           out, device; may be NULL when rank == 0
  *   eps            out, HOST array of at least params->iters doubles: eps_t of the iterations run
  *   iters_run      out, HOST: how many iterations ran
- *   workspace      device, at least milo_compress_w3lr_workspace(N, K, rank) bytes (about 1.1 N K floats),
- *                  scratch; no preparation needed
+ *   workspace      device, at least milo_compress_w3lr_workspace(N, K, rank) bytes: N K floats and what the subspace
+ *                  iteration needs (1.15 N K floats at 14336 x 4096, rank 32; 3 N K at 1024 x 1024, rank 128), scratch; no
+ *                  preparation needed.  The size depends on the device (its number of compute units): query it with
+ *                  that device current
  * The call synchronizes `stream` once per iteration (the stop rule runs on the host), so it cannot be
  * captured in a graph; it is an offline tool, not part of the inference path.
  * Errors: NULL, SHAPE (also bad parameter values), RANK (rank < 0, > MILO_COMPRESS_MAX_RANK or

@@ -895,7 +895,7 @@ static CompressLayout compress_layout(int64_t N, int64_t K, int r) {
     L.groups = tiles > 0 ? (tiles + L.rb - 1) / L.rb : 1;
     // Four workgroups of the first pass fit on a CU, one of the second (whose launch has one more, see there): as
     // many parts as fill the chip that way, while a part keeps a few hundred columns (rows) to walk.
-    const int64_t cus = 256, wy = ((N + 63) / 64) * L.groups, wb = ((K + 255) / 256) * L.groups;
+    const int64_t cus = device_cus(), wy = ((N + 63) / 64) * L.groups, wb = ((K + 255) / 256) * L.groups;
     int64_t sy = 4 * cus / wy, sb = (cus - 1) / wb;
     if (sy > K / 256) sy = K / 256;
     if (sb > N / 256) sb = N / 256;
