@@ -32,7 +32,7 @@
 // never exceeds what the device keeps resident, so that wait always ends.  Data that crosses
 // workgroups is written and read with device-coherent accesses.
 //
-// The hand-over of T (up to rank 128) takes one trip through memory: T travels in 8-byte granules of
+// The hand-over of T (where it can be staged, see decode_t_plan) takes one trip through memory: T travels in 8-byte granules of
 // two values and a 32-bit tag that names the launch, stored and polled as single 64-bit accesses, so
 // a consumer polls the data itself.  (Stores, their acknowledgement, a counter, a poll of the counter
 // and then the loads were five trips of 0.7 to 2 us, the longest chain of every decode launch, and
@@ -65,9 +65,6 @@ constexpr int kDecTWaves = 8;                               // waves of a T work
 constexpr int kDecSlotBytes = 16 * 512;                     // one chunk of X: 16 rows x 256 k
 constexpr int kDecLdsBytes = kDecWaves * kDecSlotBytes;     // 128 KB
 
-__device__ __forceinline__ void buf_store16_coherent(BufRsrc r, uint32_t off, u32x4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 17);
-}
 __device__ __forceinline__ void buf_store8_coherent(BufRsrc r, uint32_t off, u32x2 v) {
     __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 17);
 }
@@ -290,8 +287,8 @@ __device__ __forceinline__ void decode_fetch_t(const DecodeArgs& a, unsigned cha
     }
 }
 
-// LR: 0 = no low-rank term, 1 = rank at most 128 (U and T fragments come through LDS), 2 = larger
-// ranks (plain loads in the epilogue).
+// LR: 0 = no low-rank term, 1 = U and T fragments come through LDS, 2 = more ranks or more parts of T than
+// that holds (plain loads in the epilogue).
 constexpr int kDecKS = 4;                                       // k-steps of 32 ranks, LR == 1
 constexpr int kDecULds = kDecLdsBytes;                          // U fragments [R][kDecKS][64] x 16 B
 constexpr int kDecTLds = kDecULds + 4 * kDecKS * 1024;          // T fragments [kDecTFrags][64] x 16 B

@@ -117,11 +117,11 @@ struct DecodeArgs {
     WeightDev w;
     f16* Y;             // [M x N]
     // filled in by launch_decode from the workspace
-    uint32_t* ctrl;     // [0] T workers done (ranks above 128), [3] a wait gave up; zero between launches
-    uint32_t* done;     // one sign-off word per streaming workgroup (ranks above 128); zero between launches
+    uint32_t* ctrl;     // [0] T workers done (T not staged), [3] a wait gave up; zero between launches
+    uint32_t* done;     // one sign-off word per streaming workgroup (T not staged); zero between launches
     unsigned long long* epoch;  // counters of kDecGroups groups of consumers: 2^16 times the number of launches
     unsigned long long* tg;     // granules of T, [kh][nks][4][64 lanes]
-    f16* T;             // ranks above 128: [kh][16 x ldt] fp16: X V^T per K part, zero beyond the rank
+    f16* T;             // T not staged: [kh][16 x ldt] fp16: X V^T per K part, zero beyond the rank
     int64_t ldt;
     int rblocks;        // ceil(r / 16)
     int nt;             // number of T workers (the first nt workgroups)

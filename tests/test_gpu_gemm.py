@@ -44,7 +44,7 @@ def test_decode_shapes(N, K, r):
 
 @pytest.mark.parametrize("N,K,r", [
     (256, 14336, 32),      # K > 4096: several pieces of 16 chunks per workgroup; staged low-rank path
-    (256, 14336, 64),      # the same with more T fragments than the staged path holds: plain loads
+    (256, 14336, 64),      # the same with more fragments of T
     (20480, 256, 16),      # more row blocks than resident workgroups: second turn of the block loop
     (272, 1408, 20),       # rank not a multiple of 8 at decode: element-wise U loads
     (4096, 14336, 32),     # Mixtral's own down projection at decode (Section 4 shapes)
@@ -63,7 +63,7 @@ def test_decode_block_loop_second_turn_with_staged_low_rank():
 
 @pytest.mark.parametrize("N,K,r", [
     (64, 8192, 32), (64, 8256, 32),         # four and five fragments of T: one and two chunks per wave of a T worker
-    (80, 10304, 96), (64, 14336, 96), (64, 16384, 128),     # only two chunks fit the LDS; 16 fragments, over 15 waves
+    (128, 8192, 128), (80, 10304, 96), (64, 14336, 96), (64, 16384, 128),    # the most fragments that fit the LDS, 16 over 15 waves
     (64, 16448, 128),                       # too many even so: plain rows of T
     (48, 4160, 72),                         # an odd number of rank blocks, the last chunk nearly empty
 ])
