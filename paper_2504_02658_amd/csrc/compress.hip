@@ -173,6 +173,64 @@ __global__ __launch_bounds__(kRowBlockThreads, 2) void hqq_kernel(const float* _
     }
 }
 
+// The same for few groups (kHqqFewUnits): 16 lanes per group, four targets each, the shrinkage always evaluated.  Bit for
+// bit the same: the mean is summed in the same order, and where the kernel above leaves the shrinkage out it is zero.
+constexpr int kHqqFewThreads = 256, kHqqFewPerBlock = kHqqFewThreads / 16;
+template <bool FIRST>
+__global__ __launch_bounds__(kHqqFewThreads) void hqq_few_kernel(const float* __restrict__ W, float* __restrict__ RE, float* __restrict__ s,
+                                                                 float* __restrict__ z, int64_t units, int iters, float pm1, float beta,
+                                                                 float kappa) {
+    const int64_t gu = (int64_t)blockIdx.x * kHqqFewPerBlock + (threadIdx.x >> 4);
+    const int l16 = threadIdx.x & 15;
+    if (gu >= units) return;                        // whole 16-lane groups leave together
+    const int64_t at = gu * kGroup + 4 * l16;
+    const float4 w4 = *reinterpret_cast<const float4*>(W + at);
+    const float4 r4 = FIRST ? w4 : *reinterpret_cast<const float4*>(RE + at);
+    const float w[4] = {w4.x, w4.y, w4.z, w4.w}, r[4] = {r4.x, r4.y, r4.z, r4.w};
+    float sf, zf;
+    if (FIRST) {
+        float mn = fminf(fminf(w[0], w[1]), fminf(w[2], w[3])), mx = fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3]));
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) {
+            mn = fminf(mn, __shfl_xor(mn, m, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, m, 16));
+        }
+        sf = (float)(f16)((mx - mn) / 7.0f);
+        if (!(sf > 0.0f && sf <= 65504.0f)) sf = 1.0f;
+        zf = (-mn) / sf;
+        if (l16 == 0) s[gu] = sf;
+    } else {
+        sf = s[gu];
+        zf = z[gu];
+    }
+    const float inv_s = 1.0f / sf;
+    auto code = [&](int i) { return fminf(fmaxf(__builtin_rintf(r[i] / sf + zf), 0.0f), 7.0f); };
+    for (int it = 0; it < iters; ++it) {
+        const float inv_beta = 1.0f / beta;
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float q = code(i), e = r[i] - sf * (q - zf), ae = fabsf(e);
+            const float thr = ae > 0.0f ? __builtin_amdgcn_exp2f(pm1 * __builtin_amdgcn_logf(ae)) * inv_beta : 0.0f;
+            const float m = copysignf(fmaxf(ae - thr, 0.0f), e);
+            v[i] = q - (r[i] - m) * inv_s;
+        }
+        float sum = ((v[0] + v[1]) + v[2]) + v[3];
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) sum += __shfl_xor(sum, m, 16);
+        zf = sum * (1.0f / 64.0f);
+        beta *= kappa;
+    }
+    float e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[i] = w[i] - sf * (code(i) - zf);
+    *reinterpret_cast<float4*>(RE + at) = float4{e[0], e[1], e[2], e[3]};
+    if (l16 == 0) z[gu] = zf;
+}
+// Up to here the chip has lanes to spare and the longest chain counts.  One outer iteration at rank 0, us, 16 lanes / one:
+// 512 x 512 (4096 groups) 39 / 50, 768 x 1024 (12288) 46 / 49, 1024 x 1024 (16384) 49.6 / 49.5, 1024 x 1536 57 / 53.
+constexpr int64_t kHqqFewUnits = 16384;
+
 // ------------------------------------------------------------------ In - U V: the new target, its norm, the codes
 // A wave computes 16 rows x 64 columns of U V with 16x16x4 fp32 MFMAs at a time.  Column tile c (of four) is
 // made of the columns 4 i + c, so that lane (i, k) of the result holds 4 consecutive columns of row 4 k + v and
@@ -1026,6 +1084,7 @@ extern "C" int milo_compress_w3lr(const float* W, int64_t N, int64_t K, const mi
         return MILO_ERR_HIP;
 
     const dim3 cols((unsigned)(K / 64));
+    const int64_t units = N * (K / kGroup);
     const unsigned hqq_grid = (unsigned)row_block_grid(N, K);
     const dim3 resid_grid((unsigned)(N / 16), (unsigned)L.norm_x);
     const int64_t part_b = (int64_t)ld * K;
@@ -1037,12 +1096,16 @@ extern "C" int milo_compress_w3lr(const float* W, int64_t N, int64_t K, const mi
     const float edge_step = (float)pow((double)prm->kappa, -1.0 / (2.0 - (double)prm->p));
     *iters_run = 0;
     for (int t = 0; t < prm->iters; ++t) {
-        if (t == 0) {
-            // (the first target is W itself)
+        if (t > 0)
+            resid_kernel<RESID_TARGET><<<resid_grid, dim3(256), resid_lds, st>>>(W, U, V, r, N, K, RE, nullptr, nullptr, nullptr, nullptr, nullptr);
+        if (units <= kHqqFewUnits) {
+            auto few = t == 0 ? hqq_few_kernel<true> : hqq_few_kernel<false>;       // (the first target is W itself)
+            few<<<dim3((unsigned)((units + kHqqFewPerBlock - 1) / kHqqFewPerBlock)), dim3(kHqqFewThreads), 0, st>>>(
+                W, RE, s, z, units, prm->hqq_iters, prm->p - 1.0f, prm->beta, prm->kappa);
+        } else if (t == 0) {
             hqq_kernel<true><<<dim3(hqq_grid), dim3(kRowBlockThreads), 0, st>>>(W, RE, s, z, N, K, prm->hqq_iters, prm->p - 1.0f, prm->beta,
                                                                                 prm->kappa, edge, edge_step);
         } else {
-            resid_kernel<RESID_TARGET><<<resid_grid, dim3(256), resid_lds, st>>>(W, U, V, r, N, K, RE, nullptr, nullptr, nullptr, nullptr, nullptr);
             hqq_kernel<false><<<dim3(hqq_grid), dim3(kRowBlockThreads), 0, st>>>(W, RE, s, z, N, K, prm->hqq_iters, prm->p - 1.0f, prm->beta,
                                                                                  prm->kappa, edge, edge_step);
         }

@@ -199,6 +199,19 @@ def test_constant_and_zero_groups():
     assert np.all(out["U"] @ out["V"] == 0.0)
 
 
+@pytest.mark.parametrize("scale", [1.0, 12.0])
+def test_zero_points_of_few_and_of_many_groups_agree(scale):
+    # at rank 0 rows do not see each other: a weight of more groups than sixteen lanes each are for (16384) against its row
+    # slices, which have fewer, bit for bit; at 12 times the size the shrinkage keeps some residuals and not others
+    W = (wl.gen_weight(1040, 1088, seed=3702, outlier_frac=0.01) * scale).astype(np.float32)
+    W[:8, :64], W[8:16, 64:128], W[600:616] = 0.25, 0.0, 0.0          # groups without a range
+    whole = _compress(W, 0, iters=3, tol=-1.0)
+    for lo, hi in ((0, 16), (16, 528), (528, 1040)):
+        part = _compress(np.ascontiguousarray(W[lo:hi]), 0, iters=3, tol=-1.0)
+        assert np.array_equal(part["codes"], whole["codes"][lo:hi])
+        assert np.array_equal(part["zeros"].view(np.uint16), whole["zeros"][lo:hi].view(np.uint16))
+
+
 def test_infinite_weights_clamp():
     # codes of infinite weights are the ends of the range, as of any weight beyond them
     W = wl.gen_weight(32, 192, seed=3701)
