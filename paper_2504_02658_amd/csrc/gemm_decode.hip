@@ -162,7 +162,7 @@ __device__ __forceinline__ void decode_t_worker(const DecodeArgs& a, unsigned ch
     f32x4* const red = reinterpret_cast<f32x4*>(smem);              // [wave][64 lanes], after a barrier
     const XCopy xc(lane, K);
 
-    const int chunks = a.t_chunks;
+    const int chunks = TAG ? a.t_chunks : 1;
     for (int item = blockIdx.x; item < a.rblocks * a.kh; item += a.nt) {
         const int jb = item / a.kh, h = item - jb * a.kh;
         f32x4 tacc = {0.0f, 0.0f, 0.0f, 0.0f};

@@ -119,14 +119,11 @@ struct DecodeArgs {
     // filled in by launch_decode from the workspace
     uint32_t* ctrl;     // [0] T workers done (T not staged), [3] a wait gave up; zero between launches
     uint32_t* done;     // one sign-off word per streaming workgroup (T not staged); zero between launches
-    unsigned long long* epoch;  // counters of kDecGroups groups of consumers: 2^16 times the number of launches
-    unsigned long long* tg;     // granules of T, [kh][nks][4][64 lanes]
     f16* T;             // T not staged: [kh][16 x ldt] fp16: X V^T per K part, zero beyond the rank
     int64_t ldt;
     int rblocks;        // ceil(r / 16)
     int nt;             // number of T workers (the first nt workgroups)
     int kh;             // K parts of T (2048 * t_chunks columns each)
-    int nks, t_chunks;  // ceil(r / 32); chunks per wave of a T worker and part
     uint32_t spin_limit;    // polls after which a wait inside the kernel gives up
     // sizes and counts worked out on the host, so that a wave's first memory requests do not wait for
     // arithmetic (divisions, 64-bit products) or for further loads of launch parameters
@@ -137,6 +134,10 @@ struct DecodeArgs {
     uint32_t chunks_per_wave;   // ceil(ceil(K / 256) / 16)
     uint32_t rot_mask;      // largest power of two not above 16 * chunks_per_wave, minus one
     uint32_t x_bytes, t_bytes, u_bytes;     // extents of X, T and (fp16) U
+    // of the staged hand-over; at the end, so that what the T workers of the other one read first stays on two cache lines
+    int nks, t_chunks;          // ceil(r / 32); chunks per wave of a T worker and part
+    unsigned long long* epoch;  // counters of kDecGroups groups of consumers: 2^16 times the number of launches
+    unsigned long long* tg;     // granules of T, [kh][nks][4][64 lanes]
 };
 size_t decode_workspace_bytes(int64_t N, int64_t K, int r);
 int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream);
