@@ -354,14 +354,14 @@ __device__ __forceinline__ void dequant_units2_steps(const RawUnit& r0, const Ra
 
 // ---------------------------------------------------------------------------------------------
 // bf16 variant of the conversion (activations, compensator and output in bf16; Section 3.3 names
-// FP16 only, this is the same idea on the other 16-bit format).  bf16 has seven mantissa bits, so a
-// 3-bit field reads as an integer in place only at bit 0 (exponent pattern 0x4300: 128 + e) and at
-// bit 3 (0x4180: 16 + e); the fields at bits 6, 9 and 12 are shifted down first.  bf16 has no packed
-// arithmetic here, and its eight significant bits could not hold s * (e - z) anyway: a bf16 is the
-// upper half of a binary32, so each value is widened with a shift or a mask, w = fma(B + e, s,
-// -(B + z) s) is formed in binary32 (the product is exact, the constant is exact for integer
-// zero-points), and two results are rounded to a bf16 pair with one conversion: one rounding per
-// weight, as in the fp16 path.
+// FP16 only).  bf16 has no packed arithmetic here, and its eight significant bits could not hold
+// s * (e - z) anyway, so a unit's eight possible weights v_e = bf16(fma(e, s, -z s)) are formed once in binary32 (the
+// products e s and z s are exact: one rounding to binary32 and one to bf16 per weight) and looked up: a byte
+// permute picks four bytes out of eight, so with the low bytes of v_0 .. v_7 in one register pair and the high
+// bytes in another, one selector of four codes gives the low and the high bytes of four weights, and two more
+// permutes interleave them to two bf16 pairs.  150 vector instructions per unit of 64 weights; converting every
+// weight by itself (field, widen, fma, round: the form before) took 224, and at decode the vector units, not HBM, set
+// the time of bf16 weights.
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -370,104 +370,97 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     const f32x2 v = {lo, hi};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
-// (B + e_lo, B + e_hi) as a bf16 pair in `h`  ->  bf16 pair of s * (e - z); c = -(B + z) * s
-__device__ __forceinline__ uint32_t bf16_pair(uint32_t h, float s, float c) {
-    const float lo = __builtin_bit_cast(float, h << 16), hi = __builtin_bit_cast(float, h & 0xffff0000u);
-    return pack_bf16(__builtin_fmaf(lo, s, c), __builtin_fmaf(hi, s, c));
+struct Bf16Table {
+    uint32_t lo[2], hi[2];      // bytes of v_0 .. v_3 and v_4 .. v_7
+};
+__device__ __forceinline__ Bf16Table bf16_table(const RawUnit& ru) {
+    const float s = (float)f16_bits(ru.sz), z = (float)f16_bits(ru.sz >> 16);
+    const float c = -z * s;
+    Bf16Table t;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t p = pack_bf16(__builtin_fmaf(4.0f * h, s, c), __builtin_fmaf(4.0f * h + 1.0f, s, c));
+        const uint32_t q = pack_bf16(__builtin_fmaf(4.0f * h + 2.0f, s, c), __builtin_fmaf(4.0f * h + 3.0f, s, c));
+        t.lo[h] = __builtin_amdgcn_perm(q, p, 0x06040200u);
+        t.hi[h] = __builtin_amdgcn_perm(q, p, 0x07050301u);
+    }
+    return t;
+}
+// Selector bytes 0 .. 3 = codes (low half of pair a, of pair b, high half of a, of b)  ->  pairs a and b
+__device__ __forceinline__ void bf16_lookup(const Bf16Table& t, uint32_t sel, uint32_t& a, uint32_t& b) {
+    const uint32_t lo = __builtin_amdgcn_perm(t.lo[1], t.lo[0], sel), hi = __builtin_amdgcn_perm(t.hi[1], t.hi[0], sel);
+    a = __builtin_amdgcn_perm(hi, lo, in_sgpr(0x06020400u));
+    b = __builtin_amdgcn_perm(hi, lo, in_sgpr(0x07030501u));
+}
+// Pairs 10 jj .. 10 jj + 9, those of words d0 = 2 jj and d1 = 2 jj + 1 (fields at bits 0, 3, 6, 9, 12 of both halves).
+__device__ __forceinline__ void bf16_words(const Bf16Table& t, uint32_t d0, uint32_t d1, uint32_t* w) {
+    const uint32_t MA = in_sgpr(0x00070007u), MB = in_sgpr(0x07000700u);
+    bf16_lookup(t, and_or(d0 << 5, MB, d0 & MA), w[0], w[1]);
+    bf16_lookup(t, and_or(d0 >> 1, MB, (d0 >> 6) & MA), w[2], w[3]);
+    bf16_lookup(t, and_or(d1 >> 4, MB, (d0 >> 12) & MA), w[4], w[9]);
+    bf16_lookup(t, and_or(d1 << 5, MB, d1 & MA), w[5], w[6]);
+    bf16_lookup(t, and_or(d1 >> 1, MB, (d1 >> 6) & MA), w[7], w[8]);
+}
+// Pairs 30 and 31: bits 15 / 31 of words 0 .. 2 and 3 .. 5 carry bits 0, 1, 2.
+__device__ __forceinline__ void bf16_spread(const Bf16Table& t, const uint32_t (&d)[6], uint32_t* w) {
+    uint32_t sel = (d[0] >> 15) & in_sgpr(0x00010001u);
+    sel = and_or(d[1] >> 14, in_sgpr(0x00020002u), sel);
+    sel = and_or(d[2] >> 13, in_sgpr(0x00040004u), sel);
+    sel = and_or(d[3] >> 7, in_sgpr(0x01000100u), sel);
+    sel = and_or(d[4] >> 6, in_sgpr(0x02000200u), sel);
+    sel = and_or(d[5] >> 5, in_sgpr(0x04000400u), sel);
+    bf16_lookup(t, sel, w[0], w[1]);
+}
+__device__ __forceinline__ bf16x8 bf16_frag(const uint32_t (&w)[32], int t) {
+    const u32x4 v = {w[4 * t + 0], w[4 * t + 1], w[4 * t + 2], w[4 * t + 3]};
+    return __builtin_bit_cast(bf16x8, v);
 }
 template <typename OnStep>
 __device__ __forceinline__ void dequant_unit_steps_bf16(const RawUnit& ru, OnStep&& on_step) {
-    const float s = (float)f16_bits(ru.sz);
-    const float z = (float)f16_bits(ru.sz >> 16);
-    const float c0 = -(128.0f + z) * s, c3 = -(16.0f + z) * s;
-    const uint32_t B0 = in_vgpr(0x43004300u), B3 = in_vgpr(0x41804180u);
-    const uint32_t M0 = in_sgpr(0x00070007u), M3 = in_sgpr(0x00380038u);
+    const Bf16Table tab = bf16_table(ru);
     const uint32_t d[6] = {ru.a.x, ru.a.y, ru.a.z, ru.a.w, ru.b.x, ru.b.y};
     uint32_t w[32];
     int next = 0;
+    // (the barriers keep the scheduler from working on several thirds of the unit at once: 128 registers hold the stream)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        const uint32_t s6 = d[j] >> 6, s12 = d[j] >> 12;
-        w[5 * j + 0] = bf16_pair(and_or(d[j], M0, B0), s, c0);
-        w[5 * j + 1] = bf16_pair(and_or(d[j], M3, B3), s, c3);
-        w[5 * j + 2] = bf16_pair(and_or(s6, M0, B0), s, c0);
-        w[5 * j + 3] = bf16_pair(and_or(s6, M3, B3), s, c3);
-        w[5 * j + 4] = bf16_pair(and_or(s12, M0, B0), s, c0);
+    for (int jj = 0; jj < 3; ++jj) {
+        bf16_words(tab, d[2 * jj], d[2 * jj + 1], w + 10 * jj);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < 7; ++t) {
-            if (t == next && 4 * t + 3 <= 5 * j + 4) {
-                const u32x4 v = {w[4 * t + 0], w[4 * t + 1], w[4 * t + 2], w[4 * t + 3]};
-                on_step(t, __builtin_bit_cast(bf16x8, v));
+            if (t == next && 4 * t + 3 <= 10 * jj + 9) {
+                on_step(t, bf16_frag(w, t));
                 ++next;
             }
         }
     }
-    // pairs 30 and 31: bits 15 / 31 of words 0..2 and 3..5 carry bits 0, 1, 2
-    const uint32_t S0 = in_sgpr(0x00010001u), S1 = in_sgpr(0x00020002u), S2 = in_sgpr(0x00040004u);
-    uint32_t t0 = and_or(d[0] >> 15, S0, B0), t1 = and_or(d[3] >> 15, S0, B0);
-    t0 = and_or(d[1] >> 14, S1, t0);
-    t1 = and_or(d[4] >> 14, S1, t1);
-    t0 = and_or(d[2] >> 13, S2, t0);
-    t1 = and_or(d[5] >> 13, S2, t1);
-    w[30] = bf16_pair(t0, s, c0);
-    w[31] = bf16_pair(t1, s, c0);
-    const u32x4 v = {w[28], w[29], w[30], w[31]};
-    on_step(7, __builtin_bit_cast(bf16x8, v));
+    bf16_spread(tab, d, w + 30);
+    on_step(7, bf16_frag(w, 7));
 }
 // Two units in lock step (the tiled kernel's two weight streams).  on_step(t, frag0, frag1).
 template <typename OnStep>
 __device__ __forceinline__ void dequant_units2_steps_bf16(const RawUnit& r0, const RawUnit& r1, OnStep&& on_step) {
-    const float s0 = (float)f16_bits(r0.sz), z0 = (float)f16_bits(r0.sz >> 16);
-    const float s1 = (float)f16_bits(r1.sz), z1 = (float)f16_bits(r1.sz >> 16);
-    const float c00 = -(128.0f + z0) * s0, c03 = -(16.0f + z0) * s0;
-    const float c10 = -(128.0f + z1) * s1, c13 = -(16.0f + z1) * s1;
-    const uint32_t B0 = in_vgpr(0x43004300u), B3 = in_vgpr(0x41804180u);
-    const uint32_t M0 = in_sgpr(0x00070007u), M3 = in_sgpr(0x00380038u);
+    const Bf16Table tab0 = bf16_table(r0), tab1 = bf16_table(r1);
     const uint32_t d0[6] = {r0.a.x, r0.a.y, r0.a.z, r0.a.w, r0.b.x, r0.b.y};
     const uint32_t d1[6] = {r1.a.x, r1.a.y, r1.a.z, r1.a.w, r1.b.x, r1.b.y};
     uint32_t w0[32], w1[32];
     int next = 0;
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        const uint32_t a6 = d0[j] >> 6, a12 = d0[j] >> 12, b6 = d1[j] >> 6, b12 = d1[j] >> 12;
-        w0[5 * j + 0] = bf16_pair(and_or(d0[j], M0, B0), s0, c00);
-        w1[5 * j + 0] = bf16_pair(and_or(d1[j], M0, B0), s1, c10);
-        w0[5 * j + 1] = bf16_pair(and_or(d0[j], M3, B3), s0, c03);
-        w1[5 * j + 1] = bf16_pair(and_or(d1[j], M3, B3), s1, c13);
-        w0[5 * j + 2] = bf16_pair(and_or(a6, M0, B0), s0, c00);
-        w1[5 * j + 2] = bf16_pair(and_or(b6, M0, B0), s1, c10);
-        w0[5 * j + 3] = bf16_pair(and_or(a6, M3, B3), s0, c03);
-        w1[5 * j + 3] = bf16_pair(and_or(b6, M3, B3), s1, c13);
-        w0[5 * j + 4] = bf16_pair(and_or(a12, M0, B0), s0, c00);
-        w1[5 * j + 4] = bf16_pair(and_or(b12, M0, B0), s1, c10);
+    for (int jj = 0; jj < 3; ++jj) {
+        bf16_words(tab0, d0[2 * jj], d0[2 * jj + 1], w0 + 10 * jj);
+        bf16_words(tab1, d1[2 * jj], d1[2 * jj + 1], w1 + 10 * jj);
 #pragma unroll
         for (int t = 0; t < 7; ++t) {
-            if (t == next && 4 * t + 3 <= 5 * j + 4) {
-                const u32x4 v0 = {w0[4 * t + 0], w0[4 * t + 1], w0[4 * t + 2], w0[4 * t + 3]};
-                const u32x4 v1 = {w1[4 * t + 0], w1[4 * t + 1], w1[4 * t + 2], w1[4 * t + 3]};
-                on_step(t, __builtin_bit_cast(bf16x8, v0), __builtin_bit_cast(bf16x8, v1));
+            if (t == next && 4 * t + 3 <= 10 * jj + 9) {
+                on_step(t, bf16_frag(w0, t), bf16_frag(w1, t));
                 ++next;
             }
         }
     }
-    const uint32_t S0 = in_sgpr(0x00010001u), S1 = in_sgpr(0x00020002u), S2 = in_sgpr(0x00040004u);
-    uint32_t p0 = and_or(d0[0] >> 15, S0, B0), q0 = and_or(d0[3] >> 15, S0, B0);
-    uint32_t p1 = and_or(d1[0] >> 15, S0, B0), q1 = and_or(d1[3] >> 15, S0, B0);
-    p0 = and_or(d0[1] >> 14, S1, p0);
-    q0 = and_or(d0[4] >> 14, S1, q0);
-    p1 = and_or(d1[1] >> 14, S1, p1);
-    q1 = and_or(d1[4] >> 14, S1, q1);
-    p0 = and_or(d0[2] >> 13, S2, p0);
-    q0 = and_or(d0[5] >> 13, S2, q0);
-    p1 = and_or(d1[2] >> 13, S2, p1);
-    q1 = and_or(d1[5] >> 13, S2, q1);
-    w0[30] = bf16_pair(p0, s0, c00);
-    w0[31] = bf16_pair(q0, s0, c00);
-    w1[30] = bf16_pair(p1, s1, c10);
-    w1[31] = bf16_pair(q1, s1, c10);
-    const u32x4 v0 = {w0[28], w0[29], w0[30], w0[31]};
-    const u32x4 v1 = {w1[28], w1[29], w1[30], w1[31]};
-    on_step(7, __builtin_bit_cast(bf16x8, v0), __builtin_bit_cast(bf16x8, v1));
+    bf16_spread(tab0, d0, w0 + 30);
+    bf16_spread(tab1, d1, w1 + 30);
+    on_step(7, bf16_frag(w0, 7), bf16_frag(w1, 7));
 }
 __device__ __forceinline__ f32x4 mfma16_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);

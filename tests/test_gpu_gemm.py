@@ -558,3 +558,27 @@ def test_bf16_integer_case_is_exact():
         Y = api.w3lr_gemm(_to_bf16(X).cuda(), pw).float().cpu().numpy().astype(np.float64)
         ref = oracle.w3lr_linear(X, q, s, z)
         assert np.array_equal(Y, np.asarray(_to_bf16(ref).float().numpy(), np.float64))
+
+
+@pytest.mark.parametrize("M", [16, 64, 128])
+def test_bf16_weights_are_rounded_once(M):
+    # One-hot rows read the converted weights out: every code at every position of a unit, integer and real-valued
+    # zero-points (as the compressor makes them), normal, tiny and large scales.  e s and z s are exact in binary32 (3 and
+    # 11 bits times 11), so the weight is the difference rounded to binary32 and then to bf16, bit for bit.
+    import torch
+    from paper_2504_02658_amd import api
+    N, K = 96, 192
+    rng = np.random.default_rng(83)
+    q = rng.integers(0, 8, size=(N, K)).astype(np.uint8)
+    s = (2.0 ** rng.uniform(-14, 6, size=(N, K // 64))).astype(np.float16)
+    z = np.where(rng.random((N, K // 64)) < 0.5, rng.integers(0, 8, size=(N, K // 64)), rng.uniform(-12, 20, size=(N, K // 64)))
+    z = z.astype(np.float16)
+    pw = api.PackedWeight(N, K, torch.from_numpy(oracle.pack_w3(q, s, z)).cuda())
+    grow = lambda a: np.repeat(a.astype(np.float64), 64, axis=1)
+    want = _to_bf16((q * grow(s) - grow(z) * grow(s)).astype(np.float32))
+    for k0 in range(0, K, M):
+        rows = torch.zeros(M, K)
+        cols = torch.arange(k0, min(k0 + M, K))
+        rows[torch.arange(len(cols)), cols] = 1.0
+        Y = api.w3lr_gemm(rows.to(torch.bfloat16).cuda(), pw).cpu()
+        assert torch.equal(Y[:len(cols)], want[:, cols].T), (M, k0)
