@@ -330,7 +330,7 @@ int milo_moe_w3lr_check_experts_flags(const milo_w3lr_expert* experts, int E, in
  * An id outside 0..E-1 contributes nothing and raises a flag that
  * milo_moe_w3lr_routing_status() reports; an expert with no tokens is legal.
  * Each routed pair's weighted expert output is kept as fp16 (per K split of the down projection,
- * when that is split); the combine adds a token's slots (and splits) in a fixed order in fp32 and
+ * when that is split) or, for batches of a few rows per expert, as fp32; the combine adds a token's slots (and splits) in a fixed order in fp32 and
  * rounds once, so two runs give bit-identical results.
  * Errors: NULL, SHAPE, RANK, WORKSPACE, ALIGN, HIP.
  */

@@ -13,6 +13,7 @@ hipcc $FLAGS -ffp-contract=off -c compress.hip -o _build/compress.o & pids+=($!)
 hipcc $FLAGS -c gemm_tiled.hip -o _build/gemm_tiled.o & pids+=($!)
 hipcc $FLAGS $PRELOAD -c gemm_decode.hip -o _build/gemm_decode.o & pids+=($!)
 hipcc $FLAGS -c moe.hip -o _build/moe.o & pids+=($!)
+hipcc $FLAGS -c gemm_few.hip -o _build/gemm_few.o & pids+=($!)
 hipcc $FLAGS -c api.hip -o _build/api.o & pids+=($!)
 hipcc $FLAGS -c gemm_static.hip -o _build/gemm_static.o & pids+=($!)
 # the native marshalling of api.py (host code only, against the installed PyTorch)
@@ -20,8 +21,9 @@ read -r TORCH_DIR CXX_ABI PY_INC < <(python3 -c "import os, sysconfig, torch; pr
 g++ -O2 -std=c++17 -fPIC -shared -D__HIP_PLATFORM_AMD__=1 -DUSE_ROCM=1 -D_GLIBCXX_USE_CXX11_ABI=$CXX_ABI \
     -I"$TORCH_DIR/include" -I"$TORCH_DIR/include/torch/csrc/api/include" -I"$PY_INC" -I/opt/rocm/include torch_call.cpp \
     -L"$TORCH_DIR/lib" -ltorch_python -ltorch -ltorch_cpu -ltorch_hip -lc10 -lc10_hip -o "$OUT/_milo_torch.so" & pids+=($!)
-# the same two GEMM kernels with every hand-counted wait replaced by a wait for everything
+# the same GEMM kernels with every hand-counted wait replaced by a wait for everything
 hipcc $FLAGS -DMILO_FULL_WAITS -c gemm_tiled.hip -o _build/gemm_tiled_fw.o & pids+=($!)
+hipcc $FLAGS -DMILO_FULL_WAITS -c gemm_few.hip -o _build/gemm_few_fw.o & pids+=($!)
 hipcc $FLAGS $PRELOAD -DMILO_FULL_WAITS -c gemm_decode.hip -o _build/gemm_decode_fw.o & pids+=($!)
 for p in "${pids[@]}"; do wait $p; done
 # The decode kernel counts outstanding memory operations by hand (see gemm_decode.hip): a streaming
@@ -29,15 +31,32 @@ for p in "${pids[@]}"; do wait $p; done
 # 16-byte and a 12-byte load of weights) and waits with "s_waitcnt vmcnt(N)".  The compiler must not
 # reorder these requests; memory operations of its own (register spills) after a counted request only
 # make a counted wait longer, never too short, but they must stay out of the streaming loop.
-hipcc $FLAGS $PRELOAD -S --cuda-device-only gemm_decode.hip -o _build/gemm_decode.s
+hipcc $FLAGS $PRELOAD -S --cuda-device-only gemm_decode.hip -o _build/gemm_decode.s & pids=($!)
+hipcc $FLAGS -S --cuda-device-only gemm_few.hip -o _build/gemm_few.s & pids+=($!)
+hipcc $FLAGS -S --cuda-device-only gemm_tiled.hip -o _build/gemm_tiled.s & pids+=($!)
+for p in "${pids[@]}"; do wait $p; done
 python3 - <<'PY'
 import re, sys
-txt = open("_build/gemm_decode.s").read()
+txt = open("_build/gemm_decode.s").read() + open("_build/gemm_few.s").read()
 VMEM = re.compile(r"\s+(buffer_|global_|scratch_|flat_)(\S+)")
-checked = 0
-for m in re.finditer(r"^(_ZN4milo18w3lr_decode_kernelILi(\d+)ELi(\d+)ELi(\d+)E\S*):[^\n]*\n(.*?)^\.Lfunc_end", txt, re.S | re.M):
+checked = {"decode": 0, "few": 0}
+def sequence(R, XC):
+    """The requests and waits of one streaming loop: R units and XC activation copies per chunk."""
+    unit = ["buffer_load_dwordx4", "buffer_load_dwordx3"]
+    xcp = ["buffer_load_dwordx4 lds"] * XC
+    nz = lambda seq: [x for x in seq if x != 0]
+    want = xcp + unit * R                                           # first chunk, up front
+    want += nz([2 * (R - 1)]) + xcp + unit                          # loop: unit 0, next activations, next unit 0
+    for b in range(1, R):
+        want += [2 * (R - 1) + XC] + unit                           #       unit b, next unit b
+    return want + nz([2 * (R - 1 - b) for b in range(R)])           # last chunk
+# decode kernel <R, LR, XC, ..>: one loop, R units per chunk; kernel of the few-row experts <NW, R, ..>: NW R units per
+# chunk, one loop for each number of activation copies
+for m in re.finditer(r"^(_ZN4milo\d+w3lr_(?:decode|few)_kernelILi(\d+)ELi(\d+)E(?:Li(\d+)E)?\S*):[^\n]*\n(.*?)^\.Lfunc_end", txt, re.S | re.M):
     name = m.group(1)
-    R, LR, XC = (int(m.group(i)) for i in (2, 3, 4))
+    kind = "few" if "w3lr_few" in name else "decode"
+    first, second, third = (int(m.group(i) or 0) for i in (2, 3, 4))
+    wanted = [sequence(first, third)] if kind == "decode" else [sequence(first * second, XC) for XC in (2, 4, 8)]
     body = m.group(5).split("\n")
     ev = []
     for i, line in enumerate(body):
@@ -49,30 +68,23 @@ for m in re.finditer(r"^(_ZN4milo18w3lr_decode_kernelILi(\d+)ELi(\d+)ELi(\d+)E\S
         v = VMEM.match(line)
         if v:
             ev.append(v.group(1) + v.group(2) + (" lds" if " lds" in line else ""))
-    unit = ["buffer_load_dwordx4", "buffer_load_dwordx3"]
-    xcp = ["buffer_load_dwordx4 lds"] * XC
-    nz = lambda seq: [x for x in seq if x != 0]
-    want = xcp + unit * R                                           # first chunk, up front
-    want += nz([2 * (R - 1)]) + xcp + unit                          # loop: unit 0, next activations, next unit 0
-    for b in range(1, R):
-        want += [2 * (R - 1) + XC] + unit                           #       unit b, next unit b
-    want += nz([2 * (R - 1 - b) for b in range(R)])                 # last chunk
-    # the streaming loop is the one place with counted waits: its whole sequence must appear as it is
-    # (what a T worker does before it, when it goes on to stream, is complete by then: it ends with a
+    # the streaming loops are the only places with counted waits: their whole sequences must appear as they are
+    # (what a T worker does before them, when it goes on to stream, is complete by then: it ends with a
     # wait for everything)
-    found = any(ev[i:i + len(want)] == want for i in range(len(ev) - len(want) + 1))
     counted = [e for e in ev if isinstance(e, int)]
-    if not found or counted != [e for e in want if isinstance(e, int)]:
-        sys.exit("%s: requests and waits of the streaming loop are not in the counted order:\n%r\nexpected\n%r" % (name, ev, want))
-    checked += 1
-if checked == 0:
-    sys.exit("decode kernel: nothing checked; the check is out of date")
-print("decode kernel: request order around the hand-counted waits verified in %d variants" % checked)
+    want_counted = [e for w in wanted for e in w if isinstance(e, int)]
+    for want in wanted:
+        at = [i for i in range(len(ev) - len(want) + 1) if ev[i:i + len(want)] == want]
+        if len(at) < 1 or sorted(counted) != sorted(want_counted):
+            sys.exit("%s: requests and waits of the streaming loop are not in the counted order:\n%r\nexpected\n%r" % (name, ev, want))
+    checked[kind] += 1
+if 0 in checked.values():
+    sys.exit("streaming kernels: nothing checked; the check is out of date")
+print("streaming kernels: request order around the hand-counted waits verified in %(decode)d + %(few)d variants" % checked)
 PY
 # The tiled kernel counts outstanding memory operations by hand too (in its K loop); that is safe as
 # long as the compiler adds none of its own there: no scratch access may sit between the barriers
 # around a hand-written wait for a non-zero count (a wait for zero assumes nothing).  (Its cold path that forms T may spill; it only waits for zero.)
-hipcc $FLAGS -S --cuda-device-only gemm_tiled.hip -o _build/gemm_tiled.s
 python3 - <<'PY'
 import re, sys
 txt = open("_build/gemm_tiled.s").read()
@@ -96,8 +108,8 @@ if bad or n == 0 or waits == 0:
     sys.exit("tiled kernel: scratch access inside the K loop (or nothing checked): %r" % bad[:4])
 print("tiled kernel: no scratch access around %d hand-counted waits in %d variants" % (waits, n))
 PY
-hipcc --offload-arch=gfx950 -shared -fPIC -o "$OUT/libmilo.so" _build/pack.o _build/gemm_tiled.o _build/gemm_decode.o _build/moe.o _build/api.o _build/gemm_static.o _build/compress.o
-hipcc --offload-arch=gfx950 -shared -fPIC -o "$OUT/libmilo_fullwaits.so" _build/pack.o _build/gemm_tiled_fw.o _build/gemm_decode_fw.o _build/moe.o _build/api.o _build/gemm_static.o _build/compress.o
+hipcc --offload-arch=gfx950 -shared -fPIC -o "$OUT/libmilo.so" _build/pack.o _build/gemm_tiled.o _build/gemm_decode.o _build/gemm_few.o _build/moe.o _build/api.o _build/gemm_static.o _build/compress.o
+hipcc --offload-arch=gfx950 -shared -fPIC -o "$OUT/libmilo_fullwaits.so" _build/pack.o _build/gemm_tiled_fw.o _build/gemm_decode_fw.o _build/gemm_few_fw.o _build/moe.o _build/api.o _build/gemm_static.o _build/compress.o
 # Every kernel the host code launches must have its launch stub in the library (a stub that the
 # compiler failed to emit only shows up as an undefined symbol when the library is loaded).
 for lib in libmilo.so libmilo_fullwaits.so; do

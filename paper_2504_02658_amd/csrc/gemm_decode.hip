@@ -56,29 +56,19 @@
 
 #include "milo_host.h"
 #include "milo_kernels.h"
+#include "stream_device.h"
 
 namespace milo {
 
 constexpr int kDecWaves = 16;                               // waves of a workgroup
 constexpr int kDecThreads = 64 * kDecWaves;
 constexpr int kDecTWaves = 8;                               // waves of a T worker that take a chunk each
-constexpr int kDecSlotBytes = 16 * 512;                     // one chunk of X: 16 rows x 256 k
+constexpr int kDecSlotBytes = kStreamSlotBytes;
 constexpr int kDecLdsBytes = kDecWaves * kDecSlotBytes;     // 128 KB
 
 __device__ __forceinline__ void buf_store8_coherent(BufRsrc r, uint32_t off, u32x2 v) {
     __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 17);
 }
-typedef __attribute__((address_space(3))) void* LdsPtr;
-
-// Compile-time loop: f(std::integral_constant<int, I>) for I in [B, E).
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
 // Staging of one chunk of X (16 rows x 256 columns, the B operand of every row block) in an
 // 8-KB LDS slot: copy i moves rows 2i, 2i+1 with one coalesced 1-KB buffer-to-LDS load, lane l ->
 // row 2i + l/32, slot position p = l%32, which receives segment p ^ row of the row's 32 segments of
@@ -116,14 +106,6 @@ struct XCopy {
         asm volatile("" ::: "memory");
     }
 };
-
-// B fragments of a staged chunk: step t, lane (j16, q) = X[j16][8 (8q + t) .. + 7] of the chunk.
-__device__ __forceinline__ void read_bfrags(const unsigned char* slot, int j16, int q, f16x8 (&bfrag)[8]) {
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-        bfrag[t] = __builtin_bit_cast(
-            f16x8, *reinterpret_cast<const u32x4*>(slot + j16 * 512 + (((8 * q + t) ^ j16) << 4)));
-}
 
 // The tag of this launch, from counter `group`: to be read before this workgroup's own contribution.
 __device__ __forceinline__ uint32_t decode_tag(const DecodeArgs& a, uint32_t group) {
@@ -289,7 +271,7 @@ __device__ __forceinline__ void decode_fetch_t(const DecodeArgs& a, unsigned cha
 
 // LR: 0 = no low-rank term, 1 = U and T fragments come through LDS, 2 = more ranks or more parts of T than
 // that holds (plain loads in the epilogue).
-constexpr int kDecKS = 4;                                       // k-steps of 32 ranks, LR == 1
+constexpr int kDecKS = kStreamKS;                               // k-steps of 32 ranks, LR == 1
 constexpr int kDecULds = kDecLdsBytes;                          // U fragments [R][kDecKS][64] x 16 B
 constexpr int kDecTLds = kDecULds + 4 * kDecKS * 1024;          // T fragments [kDecTFrags][64] x 16 B
 constexpr int kDecTFrags = 16;                                  // (K parts) x (k-steps used) at most, LR == 1
@@ -374,23 +356,6 @@ struct DecodeStream {
     }
 };
 
-
-// Scatters the dequantized unit of one rank (64 consecutive output features, w[P] = features 2P and
-// 2P + 1 of the group) into the U fragments of the R row blocks that start O16 blocks into the
-// group: feature 16 (O16 + b) + jj of rank j goes to fragment (b, j / 32), lane (jj, (j % 32) / 8),
-// element j % 8.  `frag0` points at that element of block 0's fragment for jj = 0.
-template <int R, int O16>
-__device__ __forceinline__ void scatter_u_rank(const uint32_t (&w)[32], unsigned char* frag0) {
-#pragma unroll
-    for (int b = 0; b < R; ++b)
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const int n = 16 * (O16 + b) + jj;
-            const uint32_t v = w[n >> 1];
-            *reinterpret_cast<unsigned short*>(frag0 + b * (kDecKS * 1024) + jj * 16) =
-                (unsigned short)((n & 1) ? (v >> 16) : v);
-        }
-}
 
 // The argument block behind the kernel's leading scalar arguments, through an address the compiler knows nothing about:
 // its loads stay where the values are needed.  Read through the parameter itself, whatever any branch needs is loaded at

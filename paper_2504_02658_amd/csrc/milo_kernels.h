@@ -139,6 +139,39 @@ struct DecodeArgs {
     unsigned long long* epoch;  // counters of kDecGroups groups of consumers: 2^16 times the number of launches
     unsigned long long* tg;     // granules of T, [kh][nks][4][64 lanes]
 };
+// One item of the grouped weight-streaming kernel (gemm_few.hip): up to sixteen rows of one expert, with the
+// tokens they come from and the expert's weight descriptors beside them, so that a workgroup's first requests wait for one load.
+struct FewItem {
+    int32_t expert, row0, rows, pad;        // rows [row0, row0 + rows) of the expert-sorted row space; rows 0: no item
+    int32_t token[16];                      // row of X of each row
+    WeightDev w[3];                         // w1, w3, w2
+};
+static_assert(sizeof(FewItem) % 16 == 0, "written in 16-byte pieces");
+constexpr int kFewRows = 16;
+constexpr int kFewTChunks = 16;             // 256-column chunks of a K part of T
+constexpr int kFewMaxFrags = 64;            // fragments of T a workgroup has LDS for
+int few_t_parts(int64_t K);                 // K parts of T
+constexpr int kFewMaxRank = 128;            // largest rank its epilogue holds
+struct FewArgs {
+    const FewItem* items;
+    uint32_t n_items;           // slots of the item list
+    uint32_t t_parts;           // K parts of T (set by launch_few)
+    uint32_t bands;             // workgroups per item that stream (set by launch_few)
+    uint32_t N, K;
+    const f16* X;               // rows of K elements
+    uint32_t x_bytes;           // < 2 GiB
+    unsigned long long* granules;   // T, [item][weight][t_parts][t_frags][4][64 lanes]
+    uint32_t t_frags;           // fragments of 32 ranks of the largest rank (0: no weight has a compensator)
+    uint32_t tag;               // of this launch (the granules were cleared to another value)
+    uint32_t spin_limit;
+    uint32_t* status;           // set non-zero if a wait gave up
+    void* out;                  // rows of N elements: 16-bit (gate and up), fp32 (down)
+    const int32_t* out_rows;    // down projection: output row of sorted row R, and the factor per output row
+    const float* out_scale;
+};
+// nw = 2: gate and up projection with SwiGLU, nw = 1: down projection (rows of X in the items' order).
+int launch_few(FewArgs a, int nw, bool bf, hipStream_t stream);
+
 size_t decode_workspace_bytes(int64_t N, int64_t K, int r);
 int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream);
 

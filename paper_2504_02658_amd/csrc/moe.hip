@@ -4,13 +4,17 @@
 //   route     group the (token, slot) pairs per expert: stable placement by counting and scans,
 //             and each expert's M-tiles in its own slots of a tile list
 //   order     work list = the filled slots, full tiles first, then the partly filled ones
+//             (batches of up to 512 pairs: both in one launch)
 //   gate/up   H = SiLU(lin_w1(x)) * lin_w3(x), both projections in one grouped launch, which
 //             also forms T1 = X V1^T and T3 = X V3^T (low-rank inputs) in its leading columns
-//   down      O[split][pair] = gate_weight * lin_w2(H) over the split's share of K (fp16, one row
+//   down      O[split][pair] = gate_weight * lin_w2(H) over the split's share of K (fp16, or fp32 from gemm_few.hip; one row
 //             per routed pair); T2 = H V2^T is formed inside this launch as well
+//             (a few rows per expert: the two launches are gemm_few.hip's, else gemm_tiled.hip's)
 //   combine   y_t = fp16( sum over the token's slots and the K splits, in a fixed order, of O )
 #include <math.h>
 #include <stdlib.h>
+
+#include <type_traits>
 
 #include "milo_host.h"
 #include "milo_kernels.h"
@@ -238,88 +242,112 @@ __global__ __launch_bounds__(kRouteThreads) void order_tiles_kernel(const TileDe
 
 // Routing and work list in one launch for decode-sized batches (at most kSmallPairs routed pairs and
 // kSmallExperts experts): with a handful of tokens the two kernels above are all latency, and so is
-// the launch between them.  One workgroup; thread p owns pair p.  The group of an expert starts at
-// the number of pairs with a smaller id, a pair's place inside it is the number of earlier pairs with
-// the same id (both counted from a copy of the ids in LDS), which is the same stable order as
+// the launch between them.  One workgroup routes; thread p owns pair p, thread e expert e.  The group of an expert
+// starts at the number of pairs with a smaller id, a pair's place inside it is the number of earlier pairs with
+// the same id (counted from a copy of the ids in LDS, four per read), which is the same stable order as
 // route_kernel's.  Tiles are written straight into the final list: tiles of experts with a rank
-// above 32 first, then the others, in expert order (order_tiles_kernel's order for 32-row tiles,
-// the only tile height such a batch gets).
-constexpr int kSmallPairs = 256, kSmallExperts = 256;
+// above 32 first, then the others, in expert order (order_tiles_kernel's order for tiles of one height class).
+// `items` given: the list is the weight-streaming kernel's, `n_items` slots with the expert's weights beside the rows and
+// no rows in those that stay empty, and the other workgroups of the launch clear the granules of T.
+// Latency-bound; every thread has its expert's ranks on the way before the ids arrive and no loop goes to memory:
+// 66 experts, 4 tokens 14.6 -> 6 us against a loop over the expert table by every thread.
+constexpr int kSmallPairs = 512, kSmallExperts = 512;
 __global__ __launch_bounds__(kSmallPairs) void route_small_kernel(const RouteArgs a, TileDesc* __restrict__ list,
-                                                                  const milo_w3lr_expert* __restrict__ experts) {
-    __shared__ int32_t s_id[kSmallPairs];
-    __shared__ int32_t s_cnt[kSmallExperts], s_start[kSmallExperts], s_tile0[kSmallExperts];
-    __shared__ int32_t s_bad, s_total;
-    const int tid = threadIdx.x;
-    if (tid == 0) s_bad = 0;
+                                                                  const milo_w3lr_expert* __restrict__ experts,
+                                                                  FewItem* __restrict__ items, int n_items,
+                                                                  u32x4* __restrict__ granules, uint32_t granules16) {
+    __shared__ __attribute__((aligned(16))) int32_t s_id[kSmallPairs];
+    __shared__ int32_t s_start[kSmallExperts], s_tile0[kSmallExperts];
+    __shared__ int32_t s_hi[kSmallPairs / 64], s_lo[kSmallPairs / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (blockIdx.x > 0) {
+        for (uint32_t i = (blockIdx.x - 1) * kSmallPairs + tid; i < granules16; i += (gridDim.x - 1) * kSmallPairs)
+            granules[i] = u32x4{0u, 0u, 0u, 0u};
+        return;
+    }
     int id = -1;
     if (tid < a.P) {
         id = a.ids[tid];
         if (id < 0 || id >= a.E) id = -1;
     }
+    const WeightDev* const ew = reinterpret_cast<const WeightDev*>(experts + (tid < a.E ? tid : 0));
+    const WeightDev w0 = ew[0], w1 = ew[1], w2 = ew[2];
     s_id[tid] = id;
-    __syncthreads();
-    if (tid < a.P && id < 0) s_bad = 1;
-    // expert e = tid: its pair count, the pairs before its group, and the tiles before its own in the list
-    if (tid < a.E) {
-        int cnt = 0, less = 0;
-        for (int p = 0; p < a.P; ++p) {
-            const int v = s_id[p];
-            cnt += v == tid;
-            less += v >= 0 && v < tid;
-        }
-        s_cnt[tid] = cnt;
-        s_start[tid] = less;
-    }
-    __syncthreads();
-    if (tid < a.E) {
-        const milo_w3lr_expert& me = experts[tid];
-        const bool low = me.w1.r <= 32 && me.w3.r <= 32 && me.w2.r <= 32;
-        int before = 0, high_tiles = 0;
-        for (int e = 0; e < a.E; ++e) {
-            const int nt = (s_cnt[e] + a.bm - 1) / a.bm;
-            if (nt == 0) continue;
-            const milo_w3lr_expert& ex = experts[e];
-            const bool elow = ex.w1.r <= 32 && ex.w3.r <= 32 && ex.w2.r <= 32;
-            high_tiles += elow ? 0 : nt;
-            if (elow == low && e < tid) before += nt;
-        }
-        s_tile0[tid] = low ? high_tiles + before : before;
-        const int nt = (s_cnt[tid] + a.bm - 1) / a.bm;
-        for (int i = 0; i < nt; ++i) {
-            TileDesc td;
-            td.expert = tid;
-            td.row0 = s_start[tid] + i * a.bm;
-            td.rows = s_cnt[tid] - i * a.bm < a.bm ? s_cnt[tid] - i * a.bm : a.bm;
-            td.pad = 0;
-            list[s_tile0[tid] + i] = td;
-        }
-        if (tid == 0) {
-            int total = 0;
-            for (int e = 0; e < a.E; ++e) total += (s_cnt[e] + a.bm - 1) / a.bm;
-            s_total = total;
+    const bool bad = __syncthreads_or(tid < a.P && id < 0) != 0;
+    // pair p = tid: earlier pairs of its expert; expert e = tid: its pairs and those before its group
+    int before = 0, cnt = 0, less = 0;
+#pragma unroll 4
+    for (int p = 0; p < a.P; p += 4) {
+        const int4 v4 = *reinterpret_cast<const int4*>(s_id + p);       // (entries from P on are -1)
+        const int v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            before += v[i] == id && p + i < tid;
+            cnt += v[i] == tid;
+            less += (uint32_t)v[i] < (uint32_t)tid;
         }
     }
-    if (tid < a.P && id >= 0) {
-        int before = 0;
-        for (int p = 0; p < tid; ++p) before += s_id[p] == id;
-        const int pos = s_start[id] + before;
+    // tiles of the experts before this one, those with a high rank ahead of all others
+    const bool low = w0.r <= 32 && w1.r <= 32 && w2.r <= 32;
+    const int nt = tid < a.E ? (cnt + a.bm - 1) / a.bm : 0;
+    int hi = low ? 0 : nt, lo = low ? nt : 0;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int h = __shfl_up(hi, d, 64), l = __shfl_up(lo, d, 64);
+        if (lane >= d) {
+            hi += h;
+            lo += l;
+        }
+    }
+    if (lane == 63) {
+        s_hi[wave] = hi;
+        s_lo[wave] = lo;
+    }
+    s_start[tid] = less;
+    __syncthreads();
+    int total_hi = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kSmallPairs / 64; ++w) {
+        if (w < wave) {
+            hi += s_hi[w];
+            lo += s_lo[w];
+        }
+        total_hi += s_hi[w];
+        total += s_hi[w] + s_lo[w];
+    }
+    const int tile0 = (low ? total_hi + lo : hi) - nt;
+    s_tile0[tid] = tile0;
+    for (int i = 0; i < nt; ++i) {
+        const int row0 = less + i * a.bm, rows = cnt - i * a.bm < a.bm ? cnt - i * a.bm : a.bm;
+        if (items) {
+            FewItem& it = items[tile0 + i];
+            it.expert = tid; it.row0 = row0; it.rows = rows; it.pad = 0;
+            it.w[0] = w0; it.w[1] = w1; it.w[2] = w2;
+        } else {
+            list[tile0 + i] = TileDesc{tid, row0, rows, 0};
+        }
+    }
+    if (items)
+        for (int i = total + tid; i < n_items; i += kSmallPairs) items[i].rows = 0;
+    if (items) __syncthreads();
+    if (id >= 0) {
+        const int pos = s_start[id] + before, token = tid / a.topk;
         a.sorted[pos] = tid;
-        a.sorted_token[pos] = tid / a.topk;
+        if (items) items[s_tile0[id] + before / kFewRows].token[before % kFewRows] = token;
+        else a.sorted_token[pos] = token;
     }
     for (int i = tid; i < a.n_flags; i += kSmallPairs) a.flags[i] = 0u;
-    __syncthreads();
     if (tid == 0) {
-        a.header[0] = s_bad ? MILO_ERR_ROUTING : MILO_OK;
-        a.header[1] = s_total;
+        a.header[0] = bad ? MILO_ERR_ROUTING : MILO_OK;
+        a.header[1] = total;
         a.header[3] = 0;
     }
 }
 
 // y[t, h..h+3] = fp16( sum_j O[t*topk + j, h..h+3] ), slots in order, invalid ids skipped.  BF: rows
-// and result are bfloat16.
-template <bool BF>
-__global__ __launch_bounds__(256) void combine_kernel(const f16* __restrict__ O, int splits,
+// and result are bfloat16.  WIDE: the rows are fp32 (decode-sized batches, where they are a few hundred KB).
+template <bool BF, bool WIDE>
+__global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ O, int splits,
                                                       int64_t split_stride,
                                                       const int32_t* __restrict__ ids, int E,
                                                       int topk, int64_t T, int64_t H,
@@ -331,7 +359,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const f16* __restrict__ O,
     f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
     const int total = topk * splits;
     for (int base = 0; base < total; base += 8) {
-        u32x2 v[8];
+        typename std::conditional<WIDE, f32x4, u32x2>::type v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int q = base + i;
@@ -341,12 +369,19 @@ __global__ __launch_bounds__(256) void combine_kernel(const f16* __restrict__ O,
                 const int id = ids[t * topk + j];
                 ok = id >= 0 && id < E;
             }
-            v[i] = u32x2{0u, 0u};
-            if (ok) v[i] = *reinterpret_cast<const u32x2*>(O + s * split_stride + (t * topk + j) * H + h);
+            const int64_t at = s * split_stride + (t * topk + j) * H + h;
+            v[i] = {};
+            if (ok) {
+                if constexpr (WIDE) v[i] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(O) + at);
+                else v[i] = *reinterpret_cast<const u32x2*>(static_cast<const f16*>(O) + at);
+            }
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            if (BF) {       // a bfloat16 is the upper half of the binary32 with the same value
+            if constexpr (WIDE) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += v[i][e];
+            } else if constexpr (BF) {       // a bfloat16 is the upper half of the binary32 with the same value
                 sum[0] += __builtin_bit_cast(float, v[i].x << 16);
                 sum[1] += __builtin_bit_cast(float, v[i].x & 0xffff0000u);
                 sum[2] += __builtin_bit_cast(float, v[i].y << 16);
@@ -378,7 +413,37 @@ struct MoeLayout {
     int splits_down;            // K splits of the down projection
     size_t off_header, off_flags, off_sorted, off_token, off_slots, off_tiles, off_t1, off_t3, off_tp1, off_tp3, off_h, off_o, total;
     int64_t max_tiles32;
+    // the weight-streaming kernel
+    int few_items;              // slots of its item list (0: the tiled kernel runs)
+    int few_frags;              // fragments of 32 ranks of T
+    size_t off_items, off_granules, granule_bytes;
 };
+
+// Tiles of b rows that P evenly spread pairs give E experts, on average: sum over the row counts n of ceil(n / b), n Poisson.
+static double expected_tiles(int64_t P, int E, int b) {
+    const double mean = (double)P / E;
+    double p = exp(-mean), tiles = 0.0;
+    for (int n = 1; n <= (int)P && (n <= mean || p > 1e-9); ++n) {
+        p *= mean / n;
+        tiles += p * ((n + b - 1) / b);
+    }
+    return tiles * E;
+}
+
+// Whether the weight-streaming kernel takes a batch (else the tiled one).  Both are measured per layer in us: the streaming one takes
+// 14 + 0.17 per MB of weight it reads, once per item of 16 rows, + 0.007 per workgroup; the tiled one 45 + 0.19 per MB, once per
+// 32-row tile.  So it is the number of rows per expert that decides, later where the weights are small:
+// 14336 x 4096, 8 experts, 12 rows each 145 against 164, 16 rows 221 / 168; 3584 x 1024, 16 experts, 16 rows 58 / 66, 24 rows 76 / 73;
+// 1408 x 2048, 64 + 2 experts, 0.5 rows 34 / 63, 8 rows 94 / 103; 1024 x 512, 8 experts, 24 rows 28 / 42.
+static bool moe_takes_few(int64_t T, int64_t H, int64_t F, int E, int topk, int r_max) {
+    const int64_t P = T * topk;
+    if (P > kSmallPairs || E > kSmallExperts || r_max > kFewMaxRank) return false;
+    // fragments of T that a workgroup holds in LDS
+    const int frags = (r_max + 31) / 32;
+    if (2 * few_t_parts(H) * frags > kFewMaxFrags || few_t_parts(F) * frags > kFewMaxFrags) return false;
+    const double mb = 3.0 * 0.4375e-6 * (double)H * (double)F, groups = (double)((F + 31) / 32 + (H + 63) / 64);
+    return 14.0 + expected_tiles(P, E, kFewRows) * (0.17 * mb + 0.007 * groups) < 45.0 + 0.19 * mb * expected_tiles(P, E, 32);
+}
 
 static bool moe_layout(int64_t T, int64_t H, int64_t F, int E, int topk, int r_max, MoeLayout* L) {
     if (T <= 0 || E <= 0 || topk <= 0 || r_max < 0) return false;
@@ -389,6 +454,27 @@ static bool moe_layout(int64_t T, int64_t H, int64_t F, int E, int topk, int r_m
     if (((uint64_t)r_max + 256) * (uint64_t)(H > F ? H : F) * 2 >= 0xFFFFFFF0ull) return false;
     // activations are addressed with 32-bit offsets inside the kernels
     if ((uint64_t)T * H * 2 >= 0x80000000ull || (uint64_t)P * F * 2 >= 0x80000000ull) return false;
+    L->few_items = 0;
+    if (moe_takes_few(T, H, F, E, topk, r_max)) {
+        // every expert with rows may have one item that is not full
+        const int64_t used = P < E ? P : E, items = used + P / kFewRows;
+        L->bm = kFewRows;
+        L->few_items = (int)(items < P ? items : P);
+        L->few_frags = (r_max + 31) / 32;
+        const int parts = few_t_parts(H) * 2 > few_t_parts(F) ? few_t_parts(H) * 2 : few_t_parts(F);   // gate and up, or down
+        L->granule_bytes = (size_t)L->few_items * parts * L->few_frags * 2048;
+        L->splits_down = 1;
+        size_t off = 0;
+        L->off_header = off; off = align_up(off + 64, 256);
+        L->off_sorted = off; off = align_up(off + (size_t)P * 4, 256);
+        L->off_token = 0;
+        L->off_items = off;  off = align_up(off + (size_t)L->few_items * sizeof(FewItem), 256);
+        L->off_granules = off; off = align_up(off + L->granule_bytes, 256);
+        L->off_h = off;      off = align_up(off + (size_t)P * F * 2, 256);
+        L->off_o = off;      off = align_up(off + (size_t)P * H * 4, 256);       // (fp32)
+        L->total = off;
+        return true;
+    }
     const int64_t avg = P / E;
     // Tile height: an expert whose rows do not fit one tile streams its weights once more, a
     // taller tile costs more activation copies and a shallower pipeline; measured on the Mixtral
@@ -415,7 +501,7 @@ static bool moe_layout(int64_t T, int64_t H, int64_t F, int E, int topk, int r_m
     int64_t est_tiles = (P + L->bm - 1) / L->bm;
     int split_cap = 64;
     if (L->bm == 32) {
-        // Decode-sized batches: nearly every tile is an expert's only, partly filled one, and it costs a
+        // Small batches: nearly every tile is an expert's only, partly filled one, and it costs a
         // full pass over the expert's weight whatever its rows, so the tiles to count are the experts
         // that receive anything: E (1 - (1 - 1/E)^P) for evenly spread pairs.  Measured on the Mixtral
         // shape (16, 4 and 1 tokens), splits beyond eight lose more to short workgroups than they gain.
@@ -447,6 +533,20 @@ static bool moe_layout(int64_t T, int64_t H, int64_t F, int E, int topk, int r_m
     L->off_o = off;      off = align_up(off + (size_t)L->splits_down * P * H * 2, 256);
     L->total = off;
     return true;
+}
+
+// Sums the rows of every token's pairs (and K splits) into Y.
+static int launch_combine(const void* O, bool wide, int splits, int64_t split_stride, const int32_t* ids, int E, int topk, int64_t T,
+                          int64_t H, f16* Y, bool bf, hipStream_t stream) {
+    const unsigned gx = (unsigned)((H / 4 + 255) / 256);
+    auto kern = wide ? (bf ? combine_kernel<true, true> : combine_kernel<false, true>)
+                     : (bf ? combine_kernel<true, false> : combine_kernel<false, false>);
+    for (int64_t t0 = 0; t0 < T; t0 += 65535) {         // (grid.y limit)
+        const int64_t nt = (T - t0) < 65535 ? (T - t0) : 65535;
+        kern<<<dim3(gx, (unsigned)nt), dim3(256), 0, stream>>>(static_cast<const char*>(O) + t0 * topk * H * (wide ? 4 : 2), splits, split_stride, ids + t0 * topk, E, topk, nt, H,
+                                                               Y + t0 * H);
+    }
+    return launch_status();
 }
 
 static int check_weight(const milo_w3lr_weight& w, int64_t N, int64_t K) {
@@ -533,25 +633,52 @@ extern "C" int milo_moe_w3lr_forward_flags(const milo_half* X, int64_t T, int64_
     int32_t* header = reinterpret_cast<int32_t*>(ws + L.off_header);
     int32_t* sorted = reinterpret_cast<int32_t*>(ws + L.off_sorted);
     int32_t* sorted_token = reinterpret_cast<int32_t*>(ws + L.off_token);
+    f16* Hbuf = reinterpret_cast<f16*>(ws + L.off_h);
+    void* O = ws + L.off_o;
+    const int P = (int)(T * topk);
+    RouteArgs ra;
+    ra.ids = topk_ids; ra.P = P; ra.E = E; ra.bm = L.bm;
+    ra.topk = topk; ra.sorted = sorted; ra.sorted_token = sorted_token; ra.header = header;
+    int st;
+    if (L.few_items > 0) {
+        FewItem* items = reinterpret_cast<FewItem*>(ws + L.off_items);
+        u32x4* granules = reinterpret_cast<u32x4*>(ws + L.off_granules);
+        ra.tiles = nullptr; ra.flags = nullptr; ra.n_flags = 0; ra.max_tiles = 0;
+        const size_t clear_blocks = (L.granule_bytes / 16 + 4 * kSmallPairs - 1) / (4 * kSmallPairs);
+        route_small_kernel<<<dim3(1u + (unsigned)(clear_blocks < 128 ? clear_blocks : 128)), dim3(kSmallPairs), 0, stream>>>(
+            ra, nullptr, experts, items, L.few_items, granules, (uint32_t)(L.granule_bytes / 16));
+        st = launch_status();
+        if (st != MILO_OK) return st;
+        FewArgs fa;
+        fa.items = items; fa.n_items = (uint32_t)L.few_items;
+        fa.t_parts = 0; fa.bands = 0;
+        fa.N = (uint32_t)F; fa.K = (uint32_t)H;
+        fa.X = reinterpret_cast<const f16*>(X); fa.x_bytes = (uint32_t)(T * H * 2);
+        fa.granules = reinterpret_cast<unsigned long long*>(granules); fa.t_frags = (uint32_t)L.few_frags; fa.tag = 1u;
+        fa.spin_limit = 1u << 20; fa.status = reinterpret_cast<uint32_t*>(header + 3);
+        fa.out = Hbuf; fa.out_rows = nullptr; fa.out_scale = nullptr;
+        st = launch_few(fa, 2, bf != 0, stream);
+        if (st != MILO_OK) return st;
+        fa.N = (uint32_t)H; fa.K = (uint32_t)F;
+        fa.X = Hbuf; fa.x_bytes = (uint32_t)((int64_t)P * F * 2);
+        fa.tag = 2u;
+        fa.out = O; fa.out_rows = sorted; fa.out_scale = topk_weights;
+        st = launch_few(fa, 1, bf != 0, stream);
+        if (st != MILO_OK) return st;
+        return launch_combine(O, true, 1, (int64_t)P * H, topk_ids, E, topk, T, H, reinterpret_cast<f16*>(Y), bf != 0, stream);
+    }
     TileDesc* slots = reinterpret_cast<TileDesc*>(ws + L.off_slots);
     TileDesc* tiles = reinterpret_cast<TileDesc*>(ws + L.off_tiles);
     f16* T1 = reinterpret_cast<f16*>(ws + L.off_t1);
     f16* T3 = reinterpret_cast<f16*>(ws + L.off_t3);
     float* Tp1 = reinterpret_cast<float*>(ws + L.off_tp1);
     float* Tp3 = reinterpret_cast<float*>(ws + L.off_tp3);
-    f16* Hbuf = reinterpret_cast<f16*>(ws + L.off_h);
-    f16* O = reinterpret_cast<f16*>(ws + L.off_o);
-    const int P = (int)(T * topk);
-
-    RouteArgs ra;
-    ra.ids = topk_ids; ra.P = P; ra.E = E; ra.bm = L.bm;
-    ra.topk = topk; ra.sorted = sorted; ra.sorted_token = sorted_token; ra.tiles = slots; ra.header = header;
     uint32_t* flags = reinterpret_cast<uint32_t*>(ws + L.off_flags);
+    ra.tiles = slots;
     ra.flags = flags; ra.n_flags = (int32_t)(2 * 4 * L.max_tiles32);
     ra.max_tiles = L.max_tiles;
-    int st;
     if (P <= kSmallPairs && E <= kSmallExperts && L.bm == 32) {
-        route_small_kernel<<<dim3(1), dim3(kSmallPairs), 0, stream>>>(ra, tiles, experts);
+        route_small_kernel<<<dim3(1), dim3(kSmallPairs), 0, stream>>>(ra, tiles, experts, nullptr, 0, nullptr, 0u);
         st = launch_status();
         if (st != MILO_OK) return st;
     } else {
@@ -607,25 +734,7 @@ extern "C" int milo_moe_w3lr_forward_flags(const milo_half* X, int64_t T, int64_
         st = launch_tiled(da, 1, mb, EPI_SCALE_SCATTER, L.max_tiles, stream);
         if (st != MILO_OK) return st;
     }
-    {
-        const unsigned gx = (unsigned)((H / 4 + 255) / 256);
-        if (T > 65535) {
-            // grid.y limit: split the token range
-            for (int64_t t0 = 0; t0 < T; t0 += 65535) {
-                const int64_t nt = (T - t0) < 65535 ? (T - t0) : 65535;
-                auto kern = bf ? combine_kernel<true> : combine_kernel<false>;
-                kern<<<dim3(gx, (unsigned)nt), dim3(256), 0, stream>>>(
-                    O + t0 * topk * H, L.splits_down, (int64_t)P * H, topk_ids + t0 * topk, E, topk, nt, H,
-                    reinterpret_cast<f16*>(Y) + t0 * H);
-            }
-        } else {
-            auto kern = bf ? combine_kernel<true> : combine_kernel<false>;
-            kern<<<dim3(gx, (unsigned)T), dim3(256), 0, stream>>>(
-                O, L.splits_down, (int64_t)P * H, topk_ids, E, topk, T, H, reinterpret_cast<f16*>(Y));
-        }
-        st = launch_status();
-    }
-    return st;
+    return launch_combine(O, false, L.splits_down, (int64_t)P * H, topk_ids, E, topk, T, H, reinterpret_cast<f16*>(Y), bf != 0, stream);
 }
 
 extern "C" int milo_moe_w3lr_routing_status(const void* workspace, void* stream) {

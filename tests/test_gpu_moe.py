@@ -246,3 +246,36 @@ def test_routing_of_small_batches_matches_the_general_kernels():
 @pytest.mark.timeout(900)
 def test_c4_deepseek_layer_full_size():
     _check(wl.C4)
+
+
+@pytest.mark.parametrize("H,F,E,topk,T,ranks", [
+    (64, 64, 2, 1, 1, (0,)),                    # one chunk for four waves, one band
+    (192, 128, 4, 2, 7, (8, 20)),               # a chunk that is not whole, elementwise U rows
+    (320, 1408, 3, 3, 16, (16, 40)),            # every expert sixteen rows: one full item each; odd numbers of rank blocks
+    (320, 320, 3, 3, 17, (8, 24)),              # seventeen: a second item of one row
+    (576, 4224, 5, 2, 9, (0, 64, 128)),         # K parts of T in the down projection, more fragments than waves
+    (4352, 256, 6, 2, 20, (32,)),               # K parts of T in the gate and up projections
+    (128, 192, 512, 1, 512, (8,)),              # largest batch and expert table of the single-launch routing
+    (128, 192, 40, 8, 64, (0, 8)),              # 512 pairs, a few items per expert
+])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16", "int3"])
+def test_few_rows_per_expert(H, F, E, topk, T, ranks, dtype):
+    # the weight-streaming kernel of decode-sized batches at the edges of its tiles
+    case = wl.MoECase("few", T=T, H=H, F=F, E=E, topk=topk, seed=H + F + T, rank_choices=ranks)
+    if dtype == "bf16":
+        _check_bf16(case)
+    else:
+        _check(case, int3=dtype == "int3")
+
+
+def test_few_rows_routing_rejects_and_repeats():
+    # ids out of range leave no item behind, and an expert named twice by a token gets both rows
+    case = wl.MoECase("few_ids", T=6, H=128, F=192, E=4, topk=3, seed=29, rank_choices=(8,))
+    o_experts, layer = build_moe(case)
+    X = wl.moe_activations(case)
+    _, gates = wl.moe_routing(case)
+    ids = np.array([[0, 0, 0], [1, 4, 1], [-1, 2, 2], [7, -3, 9], [2, 2, 2], [0, 1, 2]], np.int32)
+    good = (ids >= 0) & (ids < 4)
+    ref = oracle.moe_forward(X, o_experts, np.where(good, ids, 0), np.where(good, gates, 0).astype(np.float32))
+    assert_close(_forward(layer, X, ids, gates), ref, "repeated and bad ids")
+    assert layer.routing_status() == 6
