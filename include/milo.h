@@ -151,7 +151,8 @@ int milo_workspace_status(const void* workspace, void* stream);
  *   X [M x K] fp16;  q3 as written by milo_pack_w3 (its zero-points may be any finite fp16,
  *   integer or not);  U [N x r], V [r x K] fp16 row-major, ignored when r == 0;  Y [M x N] fp16.
  *   workspace: at least milo_w3lr_gemm_workspace(M, N, K, r) bytes of device memory, prepared
- *   once with milo_workspace_init (see there for what has to keep its value between calls).  Calls that
+ *   once with milo_workspace_init (see there for what has to keep its value between calls).  (At M <= 16 and a K
+ *   beyond 4096 that includes room for partial sums; a smaller workspace that holds the state is accepted, at less speed.)  Calls that
  *   share a workspace must be ordered on one stream (concurrent calls would race on it).
  * M <= 16 takes the weight-streaming decode kernel (a single launch that also forms X V^T),
  * larger M the tiled MFMA kernel (which also forms X V^T inside the launch; when the problem has

@@ -153,7 +153,8 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
         if (r > MILO_LR3_MAX_RANK) return MILO_ERR_RANK;
         if ((N % kGroup) != 0) return MILO_ERR_SHAPE;
     }
-    if (!workspace || workspace_bytes < milo_w3lr_gemm_workspace(M, N, K, r))
+    const bool decode = gemm_takes_decode(M, N, K, r);
+    if (!workspace || workspace_bytes < (decode ? decode_workspace_min(N, K, r) : milo_w3lr_gemm_workspace(M, N, K, r)))
         return MILO_ERR_WORKSPACE;
     if (!aligned16(X) || !aligned16(q3) ||
         !aligned16(Y) || !aligned16(workspace) || (r > 0 && (!aligned16(U) || !aligned16(V))))
@@ -166,7 +167,6 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     w.V = reinterpret_cast<const f16*>(V);
     w.r = r;
     w.flags = flags;
-    const bool decode = gemm_takes_decode(M, N, K, r);
     if (decode) {
         // 32-bit buffer offsets in the decode kernel
         if ((uint64_t)M * K * 2 >= 0xFFFFFFF0ull || ((uint64_t)r + 128) * K * 2 >= 0xFFFFFFF0ull ||
@@ -175,7 +175,7 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
         DecodeArgs da;
         da.X = reinterpret_cast<const f16*>(X); da.M = (int)M; da.N = N; da.K = K;
         da.w = w; da.Y = reinterpret_cast<f16*>(Y);
-        return launch_decode(da, workspace, stream);
+        return launch_decode(da, workspace, workspace_bytes, stream);
     }
     char* ws = reinterpret_cast<char*>(workspace);
     uint32_t* ctrl = reinterpret_cast<uint32_t*>(ws);

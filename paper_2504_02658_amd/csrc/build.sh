@@ -39,7 +39,7 @@ python3 - <<'PY'
 import re, sys
 txt = open("_build/gemm_decode.s").read() + open("_build/gemm_few.s").read()
 VMEM = re.compile(r"\s+(buffer_|global_|scratch_|flat_)(\S+)")
-checked = {"decode": 0, "few": 0}
+checked = {"decode": 0, "split": 0, "few": 0}
 def sequence(R, XC):
     """The requests and waits of one streaming loop: R units and XC activation copies per chunk."""
     unit = ["buffer_load_dwordx4", "buffer_load_dwordx3"]
@@ -50,13 +50,16 @@ def sequence(R, XC):
     for b in range(1, R):
         want += [2 * (R - 1) + XC] + unit                           #       unit b, next unit b
     return want + nz([2 * (R - 1 - b) for b in range(R)])           # last chunk
+def single(R):
+    """The one chunk of a wave of the long-K kernel, after its activation copies."""
+    return ["buffer_load_dwordx4", "buffer_load_dwordx3"] * R + [2 * (R - 1 - b) for b in range(R - 1)]
 # decode kernel <R, LR, XC, ..>: one loop, R units per chunk; kernel of the few-row experts <NW, R, ..>: NW R units per
 # chunk, one loop for each number of activation copies
-for m in re.finditer(r"^(_ZN4milo\d+w3lr_(?:decode|few)_kernelILi(\d+)ELi(\d+)E(?:Li(\d+)E)?\S*):[^\n]*\n(.*?)^\.Lfunc_end", txt, re.S | re.M):
+for m in re.finditer(r"^(_ZN4milo\d+w3lr_(?:decode|decode_split|few)_kernelILi(\d+)ELi(\d+)E(?:Li(\d+)E)?\S*):[^\n]*\n(.*?)^\.Lfunc_end", txt, re.S | re.M):
     name = m.group(1)
-    kind = "few" if "w3lr_few" in name else "decode"
+    kind = "few" if "w3lr_few" in name else "split" if "decode_split" in name else "decode"
     first, second, third = (int(m.group(i) or 0) for i in (2, 3, 4))
-    wanted = [sequence(first, third)] if kind == "decode" else [sequence(first * second, XC) for XC in (2, 4, 8)]
+    wanted = [sequence(first, third)] if kind == "decode" else [single(first)] if kind == "split" else [sequence(first * second, XC) for XC in (2, 4, 8)]
     body = m.group(5).split("\n")
     ev = []
     for i, line in enumerate(body):
@@ -80,7 +83,7 @@ for m in re.finditer(r"^(_ZN4milo\d+w3lr_(?:decode|few)_kernelILi(\d+)ELi(\d+)E(
     checked[kind] += 1
 if 0 in checked.values():
     sys.exit("streaming kernels: nothing checked; the check is out of date")
-print("streaming kernels: request order around the hand-counted waits verified in %(decode)d + %(few)d variants" % checked)
+print("streaming kernels: request order around the hand-counted waits verified in %(decode)d + %(split)d + %(few)d variants" % checked)
 PY
 # The tiled kernel counts outstanding memory operations by hand too (in its K loop); that is safe as
 # long as the compiler adds none of its own there: no scratch access may sit between the barriers

@@ -1,7 +1,8 @@
 // Weight-streaming kernel for the compensated W3A16 linear at M <= 16 (decode): ONE launch that
 // streams the packed weight once from HBM, forms T = X V^T cooperatively and adds T U^T.
 //
-// Weight stream.  A workgroup of sixteen waves owns 16*R output features over the whole K.  K is
+// Weight stream (w3lr_decode_kernel; for K beyond sixteen chunks see also w3lr_decode_split_kernel).  A workgroup of sixteen
+// waves owns 16*R output features over the whole K.  K is
 // cut into chunks of 256 columns; wave w takes chunks w, w + 16, ... for all R 16-row blocks.  For
 // a chunk a lane loads one unit per 16-row block (24 bytes of codes, fp16 scale and zero-point)
 // with fully coalesced 16- and 12-byte buffer loads and no branches (lanes without data read out
@@ -127,7 +128,9 @@ __device__ __forceinline__ uint32_t decode_tag(const DecodeArgs& a, uint32_t gro
 // BF: activations, V and T are bf16 (MILO_ACT_BF16).
 // TAG: T leaves as tagged granules (see the head of this file), else as plain 16-bit rows with a
 // counter of finished workers.
-template <int XC, bool Q, bool BF, bool TAG>
+// COUNT: the worker adds 1 to counter 0 once it has read the tag from it (the long-K kernel, where a streaming workgroup
+// may add its share without having waited for T).
+template <int XC, bool Q, bool BF, bool TAG, bool COUNT = false>
 __device__ __forceinline__ void decode_t_worker(const DecodeArgs& a, unsigned char* smem) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const bool active = wave < kDecTWaves;
@@ -139,6 +142,10 @@ __device__ __forceinline__ void decode_t_worker(const DecodeArgs& a, unsigned ch
     const BufRsrc tb = make_rsrc(a.T, (uint64_t)a.kh * 16u * (uint64_t)a.ldt * 2u);
     uint32_t tag = 0u;
     if (TAG && wave == 0) tag = decode_tag(a, 0u);
+    if (COUNT && tid == 0) {
+        asm volatile("" : "+v"(tag) :: "memory");           // (the tag has been read)
+        atomicAdd(a.epoch, 1ull);
+    }
     unsigned char* const xs = smem + (wave & (kDecTWaves - 1)) * 2 * kDecSlotBytes;     // X chunk, then V chunk
     unsigned char* const vs = xs + kDecSlotBytes;
     f32x4* const red = reinterpret_cast<f32x4*>(smem);              // [wave][64 lanes], after a barrier
@@ -236,11 +243,8 @@ __device__ __forceinline__ void decode_wait_t(const DecodeArgs& a) {
 // Fetches the fragments f0, f0 + step, .. of T into LDS as MFMA B fragments (K part h, k-step i -> fragment
 // h * nks + i), polling each granule until its tag is this launch's; a wait that gives up sets an error word.
 // One wave, one fragment: at most 16 fragments over 15 waves, all on their way at once, in a few instructions.
-__device__ __forceinline__ void decode_fetch_t(const DecodeArgs& a, unsigned char* tlds, int lane, uint32_t group, uint32_t f0, uint32_t step) {
-    asm volatile("" : "+v"(lane), "+s"(group), "+s"(f0));      // (what depends on them is formed here, not kept through the stream)
+__device__ __forceinline__ void decode_fetch_tagged(const DecodeArgs& a, unsigned char* tlds, int lane, uint32_t tag, uint32_t f0, uint32_t step) {
     const uint32_t nks = (uint32_t)a.nks, frags = (uint32_t)a.kh * nks;
-    if (f0 >= frags) return;
-    const uint32_t tag = decode_tag(a, group);
 #pragma unroll 1
     for (uint32_t f = f0; f < frags; f += step) {
         // an odd number of 16-rank blocks leaves the upper half of a K part's last k-step without ranks
@@ -267,6 +271,12 @@ __device__ __forceinline__ void decode_fetch_t(const DecodeArgs& a, unsigned cha
             __builtin_amdgcn_s_sleep(1);
         }
     }
+}
+// The same with the tag read from counter `group`.
+__device__ __forceinline__ void decode_fetch_t(const DecodeArgs& a, unsigned char* tlds, int lane, uint32_t group, uint32_t f0, uint32_t step) {
+    asm volatile("" : "+v"(lane), "+s"(group), "+s"(f0));      // (what depends on them is formed here, not kept through the stream)
+    if (f0 >= (uint32_t)a.kh * (uint32_t)a.nks) return;
+    decode_fetch_tagged(a, tlds, lane, decode_tag(a, group), f0, step);
 }
 
 // LR: 0 = no low-rank term, 1 = U and T fragments come through LDS, 2 = more ranks or more parts of T than
@@ -373,6 +383,64 @@ __device__ __forceinline__ const DecodeArgs& late_args() {
     return *(const DecodeArgs*)p;
 }
 
+// U rows of the R row blocks from rb0 on as MFMA A fragments to LDS (k-step i of block b, lane (j16, q) =
+// U[n][32i + 8q ..]), by one wave; its direct copies are still on their way when it returns.
+template <int R, bool Q>
+__device__ __forceinline__ void decode_fetch_u(const DecodeArgs& a, unsigned char* smem, uint32_t rb0, uint32_t NB, int r, int ksu,
+                                               int lane, int j16, int q) {
+    if (Q) {
+        // INT3 U: the blob holds U^T [ldt x N] with groups of 64 along N, and these
+        // 16 R rows lie inside one group.  Lane l takes rank l (then l +
+        // 64): one unit, converted, and scattered into the fragment layout the
+        // epilogue reads.  Ranks past the compensator's read as zero units, which
+        // also clears the rest of the last k-step.
+        const W3Buf uq = make_w3buf(a.w.U, a.ldt, a.N);
+        const uint32_t GN = (uint32_t)(a.N >> 6), g = rb0 >> 2, o16 = rb0 & 3u;
+        for (uint32_t j = (uint32_t)lane; j < 32u * (uint32_t)ksu; j += 64u) {
+            const bool ok = j < (uint32_t)a.ldt && rb0 < NB;
+            const RawUnit u = load_unit_buf(uq, ok ? ((j >> 4) * GN + g) * 16u + (j & 15u) : (1u << 27));
+            uint32_t w[32];
+            dequant_unit<true>(u, w);
+            unsigned char* const frag0 =
+                smem + kDecULds + (((j >> 5) * 64u + ((j & 31u) >> 3) * 16u) * 16u + (j & 7u) * 2u);
+            if (R == 4) scatter_u_rank<R, 0>(w, frag0);
+            else if (R == 2) { if (o16 == 0) scatter_u_rank<R, 0>(w, frag0); else scatter_u_rank<R, 2>(w, frag0); }
+            else {
+                if (o16 == 0) scatter_u_rank<R, 0>(w, frag0);
+                else if (o16 == 1) scatter_u_rank<R, 1>(w, frag0);
+                else if (o16 == 2) scatter_u_rank<R, 2>(w, frag0);
+                else scatter_u_rank<R, 3>(w, frag0);
+            }
+        }
+    } else {
+        const BufRsrc ub = make_rsrc(a.w.U, (uint64_t)a.u_bytes);
+#pragma unroll 1
+        for (int b = 0; b < R; ++b) {
+            const uint32_t nrow = (rb0 + b) * 16u + j16;
+#pragma unroll 1
+            for (int i = 0; i < ksu; ++i) {
+                const uint32_t k0 = 32u * i + 8u * q;
+                unsigned char* const dst = smem + kDecULds + (b * kDecKS + i) * 1024;
+                if ((r & 7) == 0) {
+                    const uint32_t off =
+                        (rb0 + b < NB && k0 < (uint32_t)r) ? (nrow * r + k0) * 2u : kOobOffset;
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(ub, (LdsPtr)dst, 16, off, 0, 0, 0);
+                } else {        // rows that are not 16-byte aligned: element by element
+                    uint32_t e[8];
+#pragma unroll
+                    for (uint32_t v = 0; v < 8; ++v)
+                        e[v] = __builtin_amdgcn_raw_buffer_load_b16(
+                            ub, (rb0 + b < NB && k0 + v < (uint32_t)r) ? (nrow * r + k0 + v) * 2u : kOobOffset, 0, 0);
+                    int l16 = lane * 16;
+                    asm volatile("" : "+v"(l16));
+                    *reinterpret_cast<u32x4*>(dst + l16) =
+                        u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
+                }
+            }
+        }
+    }
+}
+
 // SYM: the weight blob is symmetric (zero-point-free conversion).  Q (with LR == 1): the compensator
 // is the pair of INT3 blobs of milo_pack_lr3.
 template <int R, int LR, int XC, bool SYM, bool Q, bool BF>
@@ -445,57 +513,7 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
                 // U rows of the R row blocks as MFMA A fragments (k-step i, lane (j16, q) =
                 // U[n][32i + 8q ..]); LR == 2: nothing but the wait for T.
                 __builtin_amdgcn_s_setprio(3);
-                if (LR == 1 && Q) {
-                    // INT3 U: the blob holds U^T [ldt x N] with groups of 64 along N, and this
-                    // workgroup's 16 R rows lie inside one group.  Lane l takes rank l (then l +
-                    // 64): one unit, converted, and scattered into the fragment layout the
-                    // epilogue reads.  Ranks past the compensator's read as zero units, which
-                    // also clears the rest of the last k-step.
-                    const W3Buf uq = make_w3buf(a.w.U, a.ldt, a.N);
-                    const uint32_t GN = (uint32_t)(a.N >> 6), g = rb0 >> 2, o16 = rb0 & 3u;
-                    for (uint32_t j = (uint32_t)lane; j < 32u * (uint32_t)ksu; j += 64u) {
-                        const bool ok = j < (uint32_t)a.ldt && rb0 < NB;
-                        const RawUnit u = load_unit_buf(uq, ok ? ((j >> 4) * GN + g) * 16u + (j & 15u) : (1u << 27));
-                        uint32_t w[32];
-                        dequant_unit<true>(u, w);
-                        unsigned char* const frag0 =
-                            smem + kDecULds + (((j >> 5) * 64u + ((j & 31u) >> 3) * 16u) * 16u + (j & 7u) * 2u);
-                        if (R == 4) scatter_u_rank<R, 0>(w, frag0);
-                        else if (R == 2) { if (o16 == 0) scatter_u_rank<R, 0>(w, frag0); else scatter_u_rank<R, 2>(w, frag0); }
-                        else {
-                            if (o16 == 0) scatter_u_rank<R, 0>(w, frag0);
-                            else if (o16 == 1) scatter_u_rank<R, 1>(w, frag0);
-                            else if (o16 == 2) scatter_u_rank<R, 2>(w, frag0);
-                            else scatter_u_rank<R, 3>(w, frag0);
-                        }
-                    }
-                } else if (LR == 1) {
-                    const BufRsrc ub = make_rsrc(a.w.U, (uint64_t)a.u_bytes);
-#pragma unroll 1
-                    for (int b = 0; b < R; ++b) {
-                        const uint32_t nrow = (rb0 + b) * 16u + j16;
-#pragma unroll 1
-                        for (int i = 0; i < ksu; ++i) {
-                            const uint32_t k0 = 32u * i + 8u * q;
-                            unsigned char* const dst = smem + kDecULds + (b * kDecKS + i) * 1024;
-                            if ((r & 7) == 0) {
-                                const uint32_t off =
-                                    (rb0 + b < NB && k0 < (uint32_t)r) ? (nrow * r + k0) * 2u : kOobOffset;
-                                __builtin_amdgcn_raw_ptr_buffer_load_lds(ub, (LdsPtr)dst, 16, off, 0, 0, 0);
-                            } else {        // rows that are not 16-byte aligned: element by element
-                                uint32_t e[8];
-#pragma unroll
-                                for (uint32_t v = 0; v < 8; ++v)
-                                    e[v] = __builtin_amdgcn_raw_buffer_load_b16(
-                                        ub, (rb0 + b < NB && k0 + v < (uint32_t)r) ? (nrow * r + k0 + v) * 2u : kOobOffset, 0, 0);
-                                int l16 = lane * 16;
-                                asm volatile("" : "+v"(l16));
-                                *reinterpret_cast<u32x4*>(dst + l16) =
-                                    u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
-                            }
-                        }
-                    }
-                }
+                if (LR == 1) decode_fetch_u<R, Q>(a, smem, rb0, NB, r, ksu, lane, j16, q);
                 if (LR == 2 && turn == 0) decode_wait_t(a);
                 wait_vmem();
                 __builtin_amdgcn_s_setprio(0);
@@ -620,6 +638,221 @@ __global__ __launch_bounds__(kDecThreads) void w3lr_decode_kernel(const void* q3
     }
 }
 
+// Long K (more than sixteen chunks): the sixteen waves of a workgroup take sixteen consecutive (band, chunk) pairs of the
+// launch's list, band by band, one chunk each with everything requested up front.  A band of 16 R features so spreads over
+// several workgroups, every CU streams, and X is staged once per R row blocks and chunk by all of them together.  (In the
+// other kernel a row block belongs to one workgroup: 4096 x 14336 ran on half the CUs, four chunks per wave in turn.)
+//
+// The workgroup that holds a band's last chunk finishes it; the ones before hand their partial sums over as granules of 4 bytes of
+// value and 4 of mark, and the finisher adds its own and theirs in workgroup order.  It only waits for workgroups with
+// lower ids, which never wait for anything but T and lower ones before they publish.  The granules are scratch that may
+// hold anything, also this launch's mark, so their owner clears them first, while its later waves still stream, and says so with a
+// tagged word among the granules of T, whose contents the library owns; the finisher looks at that word, also
+// under the stream, before it looks at the granules.  So the path to the output has one trip through memory.
+//
+// 4096 x 14336, r = 32, us per launch, chunks in turn -> here: M = 16 15.5 -> 11.5, M = 1 12.2 -> 10.1, bf16 13.3 -> 10.7.
+template <int R, int LR, bool Q, bool BF>
+__global__ __launch_bounds__(kDecThreads) void w3lr_decode_split_kernel(const void* q3_, const f16* X_, uint32_t units_, uint32_t K_,
+                                                                        uint32_t nb_, int M_, int nt_, uint32_t nmain_, uint32_t nchunks_,
+                                                                        uint32_t magic_, uint32_t x_bytes_, const DecodeArgs) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int nworkers = LR > 0 ? nt_ : 0;
+    if (LR > 0 && (int)blockIdx.x < nworkers) {
+        DecodeArgs a = late_args();
+        a.X = X_; a.K = (int64_t)K_; a.M = M_; a.nt = nt_; a.nmain = nmain_;        // (in registers already)
+        decode_t_worker<8, Q, BF, true, true>(a, smem);
+        return;
+    }
+    const int j16 = lane & 15, q = lane >> 4;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t K = K_, NB = nb_, nchunks = nchunks_;
+    W3Buf wb;
+    wb.a = make_rsrc(q3_, (uint64_t)(units_ * 16u));                // (units <= 2^26)
+    wb.b = make_rsrc(reinterpret_cast<const char*>(q3_) + (uint64_t)units_ * 16u, (uint64_t)(units_ * 12u));
+    // pairs 16 wg .. 16 wg + 15: chunks from c0 of band `band0` on, and, past its last one, of the next band (there are
+    // more than sixteen chunks, so never of a third)
+    const uint32_t wg = blockIdx.x - (uint32_t)nworkers;
+    const uint32_t band0 = (uint32_t)(((uint64_t)(wg * kDecWaves) * magic_) >> 32), c0 = wg * kDecWaves - band0 * nchunks;
+    const uint32_t left = nchunks - c0;                             // waves from here on belong to the next band
+    const bool next = wave >= left;
+    const uint32_t rb0 = (band0 + (next ? 1u : 0u)) * R;            // (past the last band: no data, zero sums)
+    const DecodeStream<R, 8, false, BF> st{wb, make_rsrc(X_, (uint64_t)x_bytes_), XCopy(lane, K), smem + wave * kDecSlotBytes, K,
+                                           K / kGroup, NB, 1u, ~0u, next ? wave - left : c0 + wave, (uint32_t)lane, (uint32_t)q, (uint32_t)j16};
+    // (the number of activation copies does not enter the waits of a single chunk: they are older than every unit)
+    {
+        const uint32_t kc = st.first * 256u;
+        if (M_ <= 2) st.xc.template issue<1>(st.xb, st.slot, kc, K, true);
+        else if (M_ <= 4) st.xc.template issue<2>(st.xb, st.slot, kc, K, true);
+        else if (M_ <= 8) st.xc.template issue<4>(st.xb, st.slot, kc, K, true);
+        else st.xc.template issue<8>(st.xb, st.slot, kc, K, true);
+    }
+    f32x4 acc[R];
+    RawUnit u[R];
+#pragma unroll
+    for (int b = 0; b < R; ++b) {
+        acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        st.issue_w(0, rb0 + b, u[b]);
+    }
+    st.template chunk<true>(0, rb0, u, acc);
+    f32x4* const red = reinterpret_cast<f32x4*>(smem);              // wave w, block b at 512 w + 64 b
+#pragma unroll
+    for (int b = 0; b < R; ++b) red[wave * (kDecSlotBytes / 16) + b * 64 + lane] = acc[b];
+
+    const DecodeArgs& a = late_args();
+    const bool finishes = left <= kDecWaves;                        // the last chunk of band0 is here
+    const uint32_t group = wg % kDecGroups;
+    const bool hands_over = !finishes || (left < kDecWaves && (band0 + 1u) * R < NB);
+    const bool live = j16 < M_;                                     // this lane's token exists
+    const uint32_t first_wg = (band0 * nchunks) / kDecWaves;        // (the first one with a chunk of band0)
+    unsigned long long* const pg = a.pg;                            // [workgroup][R][4][64 lanes]
+    unsigned long long* const cleared = a.tg + kDecSplitFrags * 256;        // one word per workgroup, its tag in the upper half
+    constexpr uint32_t kTagWave = 5, kClearWave = 3;                // (waves that are done early)
+    uint32_t* const tag_lds = reinterpret_cast<uint32_t*>(smem + (kTagWave + 1) * kDecSlotBytes - 16);     // (its own slot, not read any more)
+    if (wave == kClearWave && hands_over) {
+        if (live)
+#pragma unroll
+            for (uint32_t i = 0; i < 4 * R; ++i)
+                __hip_atomic_store(pg + (size_t)wg * (R * 256u) + i * 64u + lane, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t t = decode_tag(a, group);
+        wait_vmem();
+        if (lane == 0) __hip_atomic_store(cleared + wg, (unsigned long long)t << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (wave == kTagWave) {
+        const uint32_t t = decode_tag(a, group);
+        if (lane == 0) *tag_lds = t;
+        if (finishes)
+#pragma unroll 1
+            for (uint32_t p0 = first_wg; p0 < wg; p0 += 64)
+#pragma unroll 1
+                for (uint32_t spins = 0;; ++spins) {
+                    const unsigned long long v = __hip_atomic_load(cleared + (p0 + lane < wg ? p0 + lane : wg - 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (__builtin_amdgcn_ballot_w64((uint32_t)(v >> 32) != t) == 0ull) break;
+                    if (spins > (a.spin_limit >> 4)) {
+                        if (lane == 0) atomicOr(a.ctrl + 3, 1u);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+    }
+    const int r = a.w.r, ksu = (r + 31) >> 5;
+    if (LR > 0 && finishes && wave == 0) {
+        __builtin_amdgcn_s_setprio(3);
+        decode_fetch_u<R, Q>(a, smem, band0 * R, NB, r, ksu, lane, j16, q);
+        wait_vmem();
+        __builtin_amdgcn_s_setprio(0);
+    }
+    __syncthreads();                                                // partial sums, the tag and U are in LDS; granules are clear
+    const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)*tag_lds);
+    // waves 0 .. R-1 finish the blocks of band0, waves R .. 2R-1 hand the other partial sums over (before anything is
+    // waited for: no finisher waits for T through another one), the rest fetch T
+    const bool fin = wave < R;
+    const uint32_t b = fin ? wave : wave - R;
+    if (wave >= 2 * R) {
+        if (LR > 0 && finishes) {
+            decode_fetch_tagged(a, smem + kDecTLds, lane, tag, wave - 2 * R, kDecWaves - 2 * R);
+            __syncthreads();
+        }
+        // the tag has been read: this workgroup's share of its counter (after the barrier, which would wait for the atomic)
+        if (wave == kDecWaves - 1 && lane == 0) {
+            const uint32_t members = (nmain_ - group + kDecGroups - 1u) / kDecGroups + (group == 0u ? (uint32_t)nworkers : 0u);
+            atomicAdd(a.epoch + group * kDecGroupStride, wg < kDecGroups ? 65537ull - members : 1ull);
+        }
+        return;
+    }
+    if (!finishes && fin) return;
+    if (!fin && !hands_over) {
+        if (LR > 0) __builtin_amdgcn_s_barrier();
+        return;
+    }
+    const uint32_t lo = !fin && finishes ? left : 0u, hi = fin ? left : (uint32_t)kDecWaves;
+    f32x4 part[kDecWaves];
+#pragma unroll
+    for (int pw = 0; pw < kDecWaves; ++pw) part[pw] = red[pw * (kDecSlotBytes / 16) + b * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int pw = 0; pw < kDecWaves; ++pw)
+        if ((uint32_t)pw >= lo && (uint32_t)pw < hi)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += part[pw][e];
+    const uint32_t mark = tag | 0x80000000u;                        // (never the zero of a cleared granule)
+    if (!fin) {
+        unsigned long long* const at = pg + (size_t)(wg * R + b) * 256u + lane;
+        if (live)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = sum[e];         // (a bit cast of the vector's element itself takes element 0)
+                __hip_atomic_store(at + e * 64, (unsigned long long)mark << 32 | __builtin_bit_cast(uint32_t, v), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+        if (LR > 0 && finishes) __builtin_amdgcn_s_barrier();       // (nothing of this wave's is behind it: no wait for the stores)
+        return;
+    }
+    // four workgroups' partial sums in one trip
+    constexpr uint32_t kBatch = 4;
+#pragma unroll 1
+    for (uint32_t p0 = first_wg; p0 < wg; p0 += kBatch) {
+        unsigned long long g[kBatch][4];
+#pragma unroll 1
+        for (uint32_t spins = 0;; ++spins) {
+            bool ok = true;
+            if (live)
+#pragma unroll
+                for (uint32_t i = 0; i < kBatch; ++i)
+#pragma unroll
+                    for (uint32_t e = 0; e < 4; ++e)                // (past the last one: the last one again)
+                        g[i][e] = __hip_atomic_load(pg + (size_t)((p0 + i < wg ? p0 + i : wg - 1u) * R + b) * 256u + e * 64u + lane, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+            if (live)
+#pragma unroll
+                for (uint32_t i = 0; i < kBatch; ++i)
+#pragma unroll
+                    for (uint32_t e = 0; e < 4; ++e) ok = ok && (uint32_t)(g[i][e] >> 32) == mark;
+            if (__builtin_amdgcn_ballot_w64(!ok) == 0ull) break;
+            if (spins > (a.spin_limit >> 4)) {
+                if (lane == 0) atomicOr(a.ctrl + 3, 1u);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kBatch; ++i)
+            if (p0 + i < wg)
+#pragma unroll
+                for (uint32_t e = 0; e < 4; ++e) sum[e] += live ? __builtin_bit_cast(float, (uint32_t)g[i][e]) : 0.0f;
+    }
+    if (LR > 0) {
+        __syncthreads();                                            // T is in LDS
+        const u32x4* const ulds = reinterpret_cast<const u32x4*>(smem + kDecULds);
+        const u32x4* const tbuf = reinterpret_cast<const u32x4*>(smem + kDecTLds);
+        const int kh = a.kh;
+        int f = 0;
+#pragma unroll 1
+        for (int h = 0; h < kh; ++h) {
+#pragma unroll 1
+            for (int i = 0; i < ksu; ++i, ++f)
+                sum = BF ? mfma16_bf16(__builtin_bit_cast(bf16x8, ulds[(b * kDecKS + i) * 64 + lane]),
+                                       __builtin_bit_cast(bf16x8, tbuf[f * 64 + lane]), sum)
+                         : mfma16(__builtin_bit_cast(f16x8, ulds[(b * kDecKS + i) * 64 + lane]),
+                                  __builtin_bit_cast(f16x8, tbuf[f * 64 + lane]), sum);
+        }
+    }
+    const uint32_t n_out = (uint32_t)a.N, n = (band0 * R + b) * 16u + 4u * q;
+    if (live && n < n_out) {
+        u32x2 ob;
+        if (BF) {
+            ob = u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+        } else {
+            f16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (f16)sum[e];
+            ob = __builtin_bit_cast(u32x2, o);
+        }
+        *reinterpret_cast<u32x2*>(a.Y + ((uint64_t)j16 * n_out + n)) = ob;
+    }
+}
+
 // Workgroups the device keeps resident at once (one 128-KB-LDS workgroup per CU), cached per
 // device; also raises the kernels' dynamic LDS limit once.
 typedef void (*DecodeKernel)(const void*, const f16*, uint32_t, uint32_t, uint32_t, int, int, uint32_t, uint32_t, uint32_t, uint32_t,
@@ -675,6 +908,15 @@ static DecodeKernel decode_variant(int R, int lr, int xc, bool sym, bool q, bool
     if (lr == 1) return decode_variant_r<1, false, false>(R, xc);
     return decode_variant_r<2, false, false>(R, xc);
 }
+template <int R>
+static DecodeKernel decode_split_variant_r(bool lr, bool q, bool bf) {
+    if (bf) return lr ? w3lr_decode_split_kernel<R, 1, false, true> : w3lr_decode_split_kernel<R, 0, false, true>;
+    if (q) return w3lr_decode_split_kernel<R, 1, true, false>;
+    return lr ? w3lr_decode_split_kernel<R, 1, false, false> : w3lr_decode_split_kernel<R, 0, false, false>;
+}
+static DecodeKernel decode_split_variant(int R, bool lr, bool q, bool bf) {
+    return R == 4 ? decode_split_variant_r<4>(lr, q, bf) : R == 2 ? decode_split_variant_r<2>(lr, q, bf) : decode_split_variant_r<1>(lr, q, bf);
+}
 static int decode_capacity() {
     static int cached[64] = {0};
     int dev = 0;
@@ -693,6 +935,11 @@ static int decode_capacity() {
                                                      kDecLdsTotal) != hipSuccess)
                             return 0;
                     }
+        for (int R = 1; R <= 4; R *= 2)
+            for (int v = 0; v < 5; ++v)                 // no compensator, plain, INT3; bf16 without and with
+                if (hipFuncSetAttribute(reinterpret_cast<const void*>(decode_split_variant(R, v == 1 || v == 2 || v == 4, v == 2, v >= 3)),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, kDecLdsTotal) != hipSuccess)
+                    return 0;
         cached[dev] = cus;
     }
     return cached[dev];
@@ -722,12 +969,51 @@ static DecodeT decode_t_plan(int64_t N, int64_t K, int r) {
 }
 
 static_assert(kDecTFrags * 2048 == kDecGranuleBytes, "granules of all fragments");
-size_t decode_workspace_bytes(int64_t N, int64_t K, int r) {
+
+// T workers of a launch: one per block of 16 ranks and K part, at most kDecMaxWorkers and never more than
+// a quarter of the resident workgroups (a worker then takes several items in turn).
+static int decode_workers(int rblocks, int kh, int cap) {
+    int nt = rblocks * kh;
+    if (nt > kDecMaxWorkers) nt = kDecMaxWorkers;
+    if (nt > cap / 4) nt = cap / 4 > 0 ? cap / 4 : 1;
+    return nt;
+}
+
+// Row blocks per wave with which the long-K kernel (w3lr_decode_split_kernel) can run a problem in one round: the fewest, so
+// that all CUs stream (0: it cannot).
+static int decode_split_rows(int64_t N, int64_t K, int r, int cap) {
+    const int64_t nchunks = (K + 255) / 256;
+    if (nchunks <= kDecWaves) return 0;
+    int64_t slots = cap < kDecSplitMax ? cap : kDecSplitMax;
+    if (r > 0) {
+        const DecodeT t = decode_t_plan(N, K, r);
+        if (!t.staged || t.kh * t.nks > kDecSplitFrags) return 0;
+        const int64_t room = cap - decode_workers((r + 15) / 16, t.kh, cap);
+        if (room < slots) slots = room;
+    }
+    for (int R = 1; R <= 4; R *= 2) {
+        const int64_t wgs = ((N + 16 * R - 1) / (16 * R) * nchunks + kDecWaves - 1) / kDecWaves;
+        if (wgs <= slots) return wgs >= (int64_t)kDecGroups ? R : 0;
+    }
+    return 0;
+}
+
+// Granules of the long-K kernel, behind the head.
+static size_t decode_split_bytes(int64_t N, int64_t K, int R) {
+    const int64_t nchunks = (K + 255) / 256;
+    return (size_t)(((N + 16 * R - 1) / (16 * R) * nchunks + kDecWaves - 1) / kDecWaves) * R * 2048;
+}
+
+size_t decode_workspace_min(int64_t N, int64_t K, int r) {
     if (r <= 0) return 256;
     const size_t rblocks = ((size_t)r + 15) / 16;
     const DecodeT t = decode_t_plan(N, K, r);
     // head | T 16-bit [K parts][16 x ldt] of the other path
     return kGemmHeadBytes + (t.staged ? 0 : align_up((size_t)t.kh * 16 * rblocks * 16 * 2, 256));
+}
+size_t decode_workspace_bytes(int64_t N, int64_t K, int r) {
+    const int split = decode_split_rows(N, K, r, device_cus());
+    return split > 0 ? kGemmHeadBytes + decode_split_bytes(N, K, split) : decode_workspace_min(N, K, r);
 }
 
 // Row blocks per workgroup (16 R rows).  Every workgroup stages all of X once per turn and streams
@@ -752,7 +1038,22 @@ static int decode_rows_per_workgroup(int64_t N, int64_t K, int slots) {
     return best;
 }
 
-int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream) {
+// Whether the long-K kernel, with Rs row blocks per wave, is the faster one for a problem that the other would walk with R
+// of them.  The other one walks ceil(chunks / 16) chunks per wave in turn, each with its XC activation copies; the long-K
+// kernel walks one, but hands partial sums over.  Both estimates (us) are fits to 69 shapes from 512 x 4160 to
+// 12000 x 4864 and 4096 x 14336 at M = 1 .. 16, off by 0.3 in the middle.  Measured, chunks in turn -> split: M = 16, r = 32,
+// 4096 x 14336 15.5 -> 11.5; 1024 x 14336 12.4 -> 7.4; 2816 x 11008 10.2 -> 8.2; 12000 x 4864 13.5 -> 11.8; 512 x 8192
+// 7.6 -> 6.4; M = 1, 4096 x 14336 12.2 -> 10.1.  Where it stays: M = 1, 3920 x 8128 6.6 -> 7.3, 1440 x 4608 5.5 -> 5.7; M = 8,
+// 4096 x 8192 8.6 -> 9.4; M = 6, 800 x 4544 6.5 -> 6.8; M = 16, 3008 x 6016 7.6 -> 7.8.
+static bool decode_split_faster(int64_t N, int64_t K, int xc, int R, int Rs, int slots) {
+    const int64_t nchunks = (K + 255) / 256, blocks = (N + 16 * R - 1) / (16 * R), bands = (N + 16 * Rs - 1) / (16 * Rs);
+    const double walk = (double)((blocks + slots - 1) / slots) * (double)((nchunks + kDecWaves - 1) / kDecWaves);
+    const double other = 3.0 + walk * (0.28 + 0.143 * xc + 0.88 * R);
+    const double split = 5.5 + 1.3 * (Rs - 1) + 0.12 * xc + 0.0035 * (double)(bands * nchunks) / kDecWaves;
+    return split + 0.3 < other;
+}
+
+int launch_decode(DecodeArgs a, void* workspace, size_t workspace_bytes, hipStream_t stream) {
     const int cap = decode_capacity();
     if (cap <= 0) return MILO_ERR_HIP;
     const int r = a.w.r;
@@ -771,11 +1072,7 @@ int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream) {
     a.nks = tp.nks;
     a.t_chunks = tp.chunks;
     a.spin_limit = 1u << 24;
-    // T workers: one per block of 16 ranks and K part, at most kDecMaxWorkers and never more than
-    // a quarter of the resident workgroups (a worker then takes several items in turn)
-    int nt = a.rblocks * a.kh;
-    if (nt > kDecMaxWorkers) nt = kDecMaxWorkers;
-    if (nt > cap / 4) nt = cap / 4 > 0 ? cap / 4 : 1;
+    const int nt = decode_workers(a.rblocks, a.kh, cap);
     a.nt = nt;
     const int workers = r > 0 ? nt : 0;
     if (cap <= workers || (size_t)cap * 4 > kDecDoneBytes) return MILO_ERR_HIP;
@@ -786,30 +1083,45 @@ int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream) {
         return (v == 1 || v == 2 || v == 4) ? v : 0;
     }();
     if (r_override) R = r_override;
+    const int xc = a.M <= 2 ? 1 : a.M <= 4 ? 2 : a.M <= 8 ? 4 : 8;    // activation copies per chunk: rows 2i, 2i+1
+    int split_rows = r_override ? 0 : decode_split_rows(a.N, a.K, r, cap);
+    // (a workspace that has no room for the granules is one for the other kernel)
+    if (split_rows > 0 && (!decode_split_faster(a.N, a.K, xc, R, split_rows, cap - workers) ||
+                           workspace_bytes < kGemmHeadBytes + decode_split_bytes(a.N, a.K, split_rows)))
+        split_rows = 0;
+    if (split_rows > 0) R = split_rows;
     const int rows = 16 * R;
     const int64_t blocks = (a.N + rows - 1) / rows;
     const int grid = (int)(blocks < cap - workers ? blocks : cap - workers) + workers;
     const int lr = r == 0 ? 0 : tp.staged ? 1 : 2;
-    const int xc = a.M <= 2 ? 1 : a.M <= 4 ? 2 : a.M <= 8 ? 4 : 8;    // activation copies per chunk: rows 2i, 2i+1
     const bool q = r > 0 && (a.w.flags & MILO_LR_INT3) != 0;
     // an INT3 compensator only runs on the staged path; the limit is the one of its fragments at one chunk per wave
     if (q && (lr != 1 || decode_k_parts(a.K, 1) * tp.nks > kDecTFrags)) return MILO_ERR_SHAPE;
     const bool bf = (a.w.flags & MILO_ACT_BF16) != 0;
     if (bf && q) return MILO_ERR_SHAPE;
-    const DecodeKernel kernel = decode_variant(R, lr, xc, (a.w.flags & MILO_W3_SYMMETRIC) != 0, q, bf);
-    if (!kernel) return MILO_ERR_HIP;
-    const uint32_t nchunks = (uint32_t)((a.K + 255) / 256);
     a.units = (uint32_t)(a.N * (a.K / kGroup));
     a.nb = (uint32_t)(a.N >> 4);
+    a.x_bytes = (uint32_t)((uint64_t)a.M * (uint64_t)a.K * 2u);            // (< 2^32: checked by the caller)
+    a.t_bytes = (uint32_t)((uint64_t)a.kh * 16u * (uint64_t)a.ldt * 2u);
+    a.u_bytes = (uint32_t)((uint64_t)a.N * (uint64_t)(r > 0 ? r : 0) * 2u);   // (fp16 U; < 2^32 on the staged path)
+    const uint32_t nchunks = (uint32_t)((a.K + 255) / 256);
+    if (split_rows > 0) {
+        a.nmain = (uint32_t)((blocks * nchunks + kDecWaves - 1) / kDecWaves);
+        a.pg = reinterpret_cast<unsigned long long*>(ws + kGemmHeadBytes);
+        // quotient by nchunks as the upper half of a product: exact while dividend x divisor stays below 2^32
+        const uint32_t magic = (uint32_t)((uint64_t(1) << 32) / nchunks) + 1u;
+        decode_split_variant(R, r > 0, q, bf)<<<dim3(a.nmain + (uint32_t)workers), dim3(kDecThreads), kDecLdsTotal, stream>>>(
+            a.w.q3, a.X, a.units, (uint32_t)a.K, a.nb, a.M, a.nt, a.nmain, nchunks, magic, a.x_bytes, a);
+        return launch_status();
+    }
+    const DecodeKernel kernel = decode_variant(R, lr, xc, (a.w.flags & MILO_W3_SYMMETRIC) != 0, q, bf);
+    if (!kernel) return MILO_ERR_HIP;
     a.nmain = (uint32_t)(grid - workers);
     a.turns = (uint32_t)((blocks + a.nmain - 1) / a.nmain);
     a.chunks_per_wave = (nchunks + kDecWaves - 1) / kDecWaves;
     uint32_t pow2 = kDecWaves;
     while (pow2 * 2u <= a.chunks_per_wave * kDecWaves) pow2 *= 2u;
     a.rot_mask = pow2 - 1u;
-    a.x_bytes = (uint32_t)((uint64_t)a.M * (uint64_t)a.K * 2u);            // (< 2^32: checked by the caller)
-    a.t_bytes = (uint32_t)((uint64_t)a.kh * 16u * (uint64_t)a.ldt * 2u);
-    a.u_bytes = (uint32_t)((uint64_t)a.N * (uint64_t)(r > 0 ? r : 0) * 2u);   // (fp16 U; < 2^32 on the staged path)
     kernel<<<dim3((unsigned)grid), dim3(kDecThreads), lr == 1 ? kDecLdsTotal : kDecLdsBytes, stream>>>(
         a.w.q3, a.X, a.units, (uint32_t)a.K, a.nb, a.M, a.nt, a.nmain, a.chunks_per_wave, a.rot_mask, a.x_bytes, a);
     return launch_status();

@@ -103,6 +103,9 @@ constexpr int kTiledFlagBytes = (int)kTiledFlagTiles * 16;
 // and each on a cache line of its own, and the granules.
 constexpr uint32_t kDecGroups = 32, kDecGroupStride = 8;       // stride in 8-byte counters
 constexpr int kDecGranuleBytes = 32768;                         // 16 fragments of 2 KB
+// The long-K decode kernel: workgroups that stream at most, each with a tagged word in the place of the last fragment.
+constexpr int kDecSplitMax = 256, kDecSplitFrags = 15;
+static_assert((kDecSplitFrags * 256 + kDecSplitMax) * 8 <= kDecGranuleBytes, "the tagged words fit");
 constexpr size_t kGemmDoneAt = 256, kGemmFlagsAt = kGemmDoneAt + kDecDoneBytes, kGemmCountersAt = kGemmFlagsAt + kTiledFlagBytes,
                  kGemmGranulesAt = kGemmCountersAt + kDecGroups * kDecGroupStride * 8, kGemmHeadBytes = kGemmGranulesAt + kDecGranuleBytes;
 static_assert(kGemmHeadBytes == MILO_WORKSPACE_STATE_BYTES, "stated in milo.h");
@@ -138,6 +141,7 @@ struct DecodeArgs {
     int nks, t_chunks;          // ceil(r / 32); chunks per wave of a T worker and part
     unsigned long long* epoch;  // counters of kDecGroups groups of consumers: 2^16 times the number of launches
     unsigned long long* tg;     // granules of T, [kh][nks][4][64 lanes]
+    unsigned long long* pg;     // granules of partial sums (long-K kernel), scratch
 };
 // One item of the grouped weight-streaming kernel (gemm_few.hip): up to sixteen rows of one expert, with the
 // tokens they come from and the expert's weight descriptors beside them, so that a workgroup's first requests wait for one load.
@@ -172,7 +176,8 @@ struct FewArgs {
 // nw = 2: gate and up projection with SwiGLU, nw = 1: down projection (rows of X in the items' order).
 int launch_few(FewArgs a, int nw, bool bf, hipStream_t stream);
 
-size_t decode_workspace_bytes(int64_t N, int64_t K, int r);
-int launch_decode(DecodeArgs a, void* workspace, hipStream_t stream);
+size_t decode_workspace_bytes(int64_t N, int64_t K, int r);    // what a call is to bring
+size_t decode_workspace_min(int64_t N, int64_t K, int r);      // what it has to (without room for the long-K kernel's granules)
+int launch_decode(DecodeArgs a, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 }  // namespace milo

@@ -102,6 +102,56 @@ def test_decode_parts_of_t(N, K, r, M, dtype):
     assert np.linalg.norm(Y - ref) <= (8.0 if dtype == "bf16" else 1.0) * 2.0 ** -11 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("M,N,K,r", [
+    (16, 512, 4352, 0),         # 17 chunks: the fewest that are spread over workgroups; 34 of those
+    (9, 528, 4160, 20),         # the last chunk has 64 columns, the last workgroup's waves past the last pair have none
+    (5, 1040, 8256, 128),       # eight fragments of T, each band ends in the middle of a workgroup
+    (3, 2816, 11008, 24),       # chunks in turn (the rule's other side)
+    (16, 2816, 11008, 24),      # two row blocks per wave
+    (2, 12016, 4864, 8),        # four, and a band of three at the end
+    (1, 1024, 14336, 64), (7, 528, 65536, 16),      # three and fifteen partial sums per band
+    (4, 512, 6144, 32),         # every other band starts with a workgroup
+])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16", "int3"])
+def test_decode_chunks_spread_over_workgroups(M, N, K, r, dtype):
+    if r == 0:
+        if dtype == "fp16":
+            _check_case(M, N, K, r, seed=N + K)
+    elif dtype != "int3" or r <= 64:
+        test_decode_parts_of_t(N, K, r, M, dtype)
+
+
+def test_decode_partial_sums_on_a_shared_workspace():
+    # partial sums and T carry the launch's number: calls with and without them, other shapes' scratch in between
+    _shared_workspace_sequence([
+        (16, 1024, 8192, 32), (16, 1024, 8192, 32), (96, 512, 4096, 16), (16, 1024, 8192, 32), (1, 2048, 14336, 0), (4, 256, 1024, 256),
+        (1, 2048, 14336, 0), (16, 1024, 8192, 0), (16, 512, 512, 8), (16, 1024, 8192, 32), (300, 256, 1024, 72), (2, 2048, 14336, 0)])
+
+
+def test_decode_partial_sums_in_scratch_that_looks_like_theirs():
+    # every granule holds a value and the mark of the launch that follows; a workspace without room for granules is accepted
+    import torch
+    from paper_2504_02658_amd import api
+    M, N, K, r, state = 16, 1024, 8192, 32, 59648
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    pw = api.pack_w3(randn(N, K) * 0.02).with_compensator((randn(N, r) * 0.1).half(), (randn(r, K) * 0.1).half())
+    X = randn(M, K).half()
+    ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, r))
+    assert ws.numel() > state
+    ref = api.w3lr_gemm(X, pw, workspace=ws)
+    for launches in range(1, 5):
+        ws[state:].view(torch.int32)[0::2] = 0x42f60000                         # 123.0
+        ws[state:].view(torch.int32)[1::2] = launches + 1 - (1 << 31)
+        assert torch.equal(api.w3lr_gemm(X, pw, workspace=ws), ref)
+    assert api.workspace_status(ws) == 0
+    small = api.new_workspace(state)
+    Y = api.w3lr_gemm(X, pw, workspace=small)
+    assert float((Y.double() - ref.double()).norm() / ref.double().norm()) < 2.0 ** -11       # (another order of the same sums)
+    assert api.workspace_status(small) == 0
+
+
 @pytest.mark.parametrize("M", [17, 32, 33, 64, 100, 130, 257])
 def test_tiled_rows(M):
     _check_case(M, 272, 1408, 8, seed=60 + M)

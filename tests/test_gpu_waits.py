@@ -27,7 +27,7 @@ def _gemm(L, X, q3, U, V, r, N):
 
 @pytest.mark.parametrize("M,N,K,r", [
     (16, 1024, 4096, 32), (1, 528, 2112, 16), (4, 272, 14336, 32), (7, 20480, 256, 16), (16, 272, 1408, 20),
-    (48, 512, 4096, 24), (130, 528, 1024, 64), (512, 1024, 2048, 8),
+    (48, 512, 4096, 24), (130, 528, 1024, 64), (512, 1024, 2048, 8), (16, 1040, 8256, 32), (2, 4096, 14336, 24),
 ])
 def test_counted_waits_equal_full_waits(M, N, K, r):
     import torch
