@@ -327,7 +327,8 @@ int milo_moe_w3lr_check_experts_flags(const milo_w3lr_expert* experts, int E, in
  *   topk_weights [T x topk] fp32
  *   Y            [T x H] fp16
  *   workspace    at least milo_moe_w3lr_workspace(T, H, F, E, topk, r_max) bytes, prepared once with
- *                milo_workspace_init; not shared with milo_w3lr_gemm (see milo_workspace_init)
+ *                milo_workspace_init (a batch of a few rows per expert is also accepted with
+ *                the fewer that the kernels of larger batches take, at less speed); not shared with milo_w3lr_gemm (see milo_workspace_init)
  * An id outside 0..E-1 contributes nothing and raises a flag that
  * milo_moe_w3lr_routing_status() reports; an expert with no tokens is legal.
  * Each routed pair's weighted expert output is kept as fp16 (per K split of the down projection,

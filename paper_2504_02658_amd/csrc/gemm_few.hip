@@ -16,11 +16,12 @@
 // 39.5 against 17 at 4 tokens of a layer of 66 experts of 1408 x 2048.
 //
 // Low-rank term.  T = X V^T of an item is formed inside the launch by the first workgroups of the grid, one per block of
-// 16 ranks and K part of 16 chunks, and handed over in tagged
-// granules: 8 bytes of two values and a tag, polled as single 64-bit accesses, so that the data is its own flag.  The
-// routing kernel clears the granules of a forward, the two launches use different tags.  The parts are not added up:
-// the streaming workgroups multiply each with U.  Workers never wait and
-// have the lowest workgroup ids.  (One workgroup per 32 ranks over the whole K was the longest chain of a launch: K = 14336,
+// 16 ranks (and, in the down projection, K part of 16 chunks), and handed over in tagged
+// granules: 8 bytes of values and a tag, polled as single 64-bit accesses, so that the data is its own flag.  The
+// routing kernel clears the granules of a forward, the two launches use different tags.  A T of one part is rounded by its
+// worker, two values to a granule; several parts travel as fp32 and the streaming workgroups add them, in
+// part order, before the one rounding.  Workers never wait and have the lowest workgroup ids.
+// (One workgroup per 32 ranks over the whole K was the longest chain of a launch: K = 14336,
 // rank 64, 62 -> 48 us.)
 #include "milo_host.h"
 #include "milo_kernels.h"
@@ -48,9 +49,9 @@ __device__ __forceinline__ u32x2 few_pack4(f32x4 v) {
 constexpr int kFewWaves = 4, kFewThreads = 64 * kFewWaves;
 constexpr int kFewTLds = kFewWaves * kStreamSlotBytes;         // T fragments behind the slots: [fragment][64 lanes] x 16 B
 
-// Granules of fragment i (32 ranks) of K part `part` of an item's weight: [4][64 lanes].
+// Granules of fragment i (32 ranks) of K part `part` of an item's weight: [4][64 lanes], or [8][64 lanes] with several parts.
 __device__ __forceinline__ unsigned long long* few_fragment(const FewArgs& a, uint32_t weight, int part, int i) {
-    return a.granules + ((size_t)(weight * a.t_parts + part) * a.t_frags + i) * 256u;
+    return a.granules + ((size_t)(weight * a.t_frags + i) * a.t_parts + part) * (a.t_parts > 1u ? 512u : 256u);
 }
 
 // Byte offset in X of the item's row j (kOobRow: no such row; stays past every buffer when a column is added).
@@ -61,7 +62,8 @@ __device__ __forceinline__ uint32_t few_row_offset(const FewArgs& a, const FewIt
     return j < it.rows ? (uint32_t)row * (2u * a.K) : kOobRow;
 }
 
-// T worker: block jb of 16 ranks of weight `w` of the item over K part `part` (kFewTChunks chunks); both operands go straight from
+// T worker: block jb of 16 ranks of weight `w` of the item over K part `part` (kFewTChunks chunks, or all: there is no room
+// for adding parts up beside the accumulators of two weights); both operands go straight from
 // memory to registers (16 rows x 64 contiguous bytes per load), and the partial sums of the waves are added in wave order.
 template <int NW, bool BF>
 __device__ __forceinline__ void few_t_worker(const FewArgs& a, const FewItem& it, const WeightDev& w, uint32_t item, int which,
@@ -69,7 +71,7 @@ __device__ __forceinline__ void few_t_worker(const FewArgs& a, const FewItem& it
     if (16 * jb >= w.r) return;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j16 = lane & 15, q = lane >> 4;
     const uint32_t K = a.K, G = K / kGroup;
-    const uint32_t c_lo = (uint32_t)(part * kFewTChunks), c_hi = c_lo + kFewTChunks;
+    const uint32_t c_lo = (uint32_t)(part * kFewTChunks), c_hi = NW == 2 ? (K + 255u) / 256u : c_lo + kFewTChunks;
     const BufRsrc xb = make_rsrc(a.X, a.x_bytes);
     const uint32_t xo = few_row_offset<NW>(a, it, j16);
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -111,8 +113,17 @@ __device__ __forceinline__ void few_t_worker(const FewArgs& a, const FewItem& it
 #pragma unroll
         for (int e = 0; e < 4; ++e) sum[e] += p[e];
     }
-    // element v = rank 16 jb + 4 q + v, row j16: granules 2 (q % 2) and the next of lane (j16, 2 (jb % 2) + q / 2) in the
-    // fragment of k-step jb / 2
+    // element v = rank 16 jb + 4 q + v, row j16: element 4 (q % 2) + v of lane (j16, 2 (jb % 2) + q / 2) in the fragment of
+    // k-step jb / 2
+    if (NW == 1 && a.t_parts > 1u) {
+        unsigned long long* const frag = few_fragment(a, item * NW + which, part, jb >> 1);
+        const uint32_t at = 4u * (q & 1) * 64u + (2u * (jb & 1) + (q >> 1)) * 16u + j16;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            __hip_atomic_store(frag + at + 64 * e, (unsigned long long)a.tag << 32 | __builtin_bit_cast(uint32_t, (float)sum[e]),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
     const u32x2 ob = few_pack4<BF>(sum);
     unsigned long long* const frag = few_fragment(a, item * NW + which, part, jb >> 1);
     const uint32_t at = 2u * (q & 1) * 64u + (2u * (jb & 1) + (q >> 1)) * 16u + j16;
@@ -122,7 +133,45 @@ __device__ __forceinline__ void few_t_worker(const FewArgs& a, const FewItem& it
 
 // One fragment of T (32 ranks x 16 rows) as an MFMA B fragment to LDS, polled until every granule carries the
 // launch's tag; a wait that gives up sets the status word.  `none`: this lane's ranks do not exist.
+template <int NW, bool BF>
 __device__ __forceinline__ void few_fetch_t(const FewArgs& a, const unsigned long long* frag, bool none, int lane, unsigned char* dst) {
+    if (NW == 1 && a.t_parts > 1u) {
+        constexpr int PT = 2;       // parts per trip to memory
+        f32x4 lo = {0.0f, 0.0f, 0.0f, 0.0f}, hi = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (uint32_t p = 0; p < a.t_parts; p += PT) {
+            const bool two = p + 1u < a.t_parts;
+            const unsigned long long* const f[2] = {frag + p * 512u, frag + (two ? p + 1u : p) * 512u};
+            for (uint32_t spins = 0;; ++spins) {
+                unsigned long long g[PT][8];
+                bool ok = true;
+#pragma unroll
+                for (int k = 0; k < PT; ++k)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        g[k][e] = __hip_atomic_load(f[k] + e * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int k = 0; k < PT; ++k)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) ok = ok && (uint32_t)(g[k][e] >> 32) == a.tag;
+                if (__builtin_amdgcn_ballot_w64(!(ok || none)) == 0ull || spins > a.spin_limit) {
+#pragma unroll
+                    for (int k = 0; k < PT; ++k)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (none || (k == 1 && !two)) continue;
+                            lo[e] += __builtin_bit_cast(float, (uint32_t)g[k][e]);
+                            hi[e] += __builtin_bit_cast(float, (uint32_t)g[k][4 + e]);
+                        }
+                    if (spins > a.spin_limit && lane == 0) atomicOr(a.status, 1u);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+        const u32x2 l = few_pack4<BF>(lo), h = few_pack4<BF>(hi);
+        *reinterpret_cast<u32x4*>(dst + lane * 16) = u32x4{l.x, l.y, h.x, h.y};
+        return;
+    }
     for (uint32_t spins = 0;; ++spins) {
         unsigned long long g[4];
 #pragma unroll
@@ -230,14 +279,13 @@ __global__ __launch_bounds__(kFewThreads, 4) void w3lr_few_kernel(const FewArgs 
         few_t_worker<NW, BF>(a, it, which == 0 ? w0 : w1, item, (int)which, (int)jb, (int)(r2 - jb * a.t_parts), smem);
         return;
     }
-    const int tid = threadIdx.x, lane = tid & 63, j16 = lane & 15, q = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t chunks = (a.K + 255u) / 256u;
     const uint32_t NB = a.N >> 4, rb0 = rest * R;
     W3Buf wb[NW];
     wb[0] = make_w3buf(w0.q3, a.N, a.K);
     wb[NW - 1] = make_w3buf(w1.q3, a.N, a.K);
-    const uint32_t my_row = few_row_offset<NW>(a, it, j16);
+    const uint32_t my_row = few_row_offset<NW>(a, it, threadIdx.x & 15);
     unsigned char* const slot = smem + wave * kStreamSlotBytes;
     f32x4 acc[U];
 #pragma unroll
@@ -246,7 +294,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void w3lr_few_kernel(const FewArgs 
     // slot held there only reaches output columns that are not stored).
     auto stream = [&](auto xc) {
         constexpr int XC = decltype(xc)::value;
-        FewStream<NW, R, XC, BF> st{wb, make_rsrc(a.X, a.x_bytes), {}, slot, a.K, a.K / kGroup, NB, rb0, (uint32_t)wave, (uint32_t)lane};
+        FewStream<NW, R, XC, BF> st{wb, make_rsrc(a.X, a.x_bytes), {}, slot, a.K, a.K / kGroup, NB, rb0, (uint32_t)wave, threadIdx.x & 63u};
 #pragma unroll
         for (int i = 0; i < 2 * XC; ++i) st.row[i] = (uint32_t)__builtin_amdgcn_readlane((int)my_row, i);
         if ((uint32_t)wave < chunks) st.run((chunks - wave + kFewWaves - 1u) / kFewWaves, acc);
@@ -254,6 +302,10 @@ __global__ __launch_bounds__(kFewThreads, 4) void w3lr_few_kernel(const FewArgs 
     if (it.rows <= 4) stream(std::integral_constant<int, 2>{});
     else if (it.rows <= 8) stream(std::integral_constant<int, 4>{});
     else stream(std::integral_constant<int, 8>{});
+    // the epilogue's lane number, counted anew: carried across the streaming loop, it and what is derived from it spill there
+    uint32_t every = ~0u;
+    asm volatile("" : "+s"(every));
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(every, __builtin_amdgcn_mbcnt_lo(every, 0u)), j16 = lane & 15, q = lane >> 4;
     f32x4* const red = reinterpret_cast<f32x4*>(smem);         // wave w, unit b at 512 w + 64 b
 #pragma unroll
     for (int b = 0; b < U; ++b) red[wave * (kStreamSlotBytes / 16) + b * 64 + lane] = acc[b];
@@ -261,13 +313,13 @@ __global__ __launch_bounds__(kFewThreads, 4) void w3lr_few_kernel(const FewArgs 
     // What the epilogue needs besides the partial sums: the fragments of T, dealt to the waves, and for wave b < R, which
     // finishes row block b, the U rows.  (Asked for before the last unit is converted they gained nothing.)
     const int r0 = w0.r, r1 = NW == 2 ? w1.r : 0;
-    const int ks0 = (r0 + 31) >> 5, ks1 = (r1 + 31) >> 5, parts = (int)a.t_parts, frags0 = ks0 * parts, frags = frags0 + ks1 * parts;
-    for (int f = wave; f < frags; f += kFewWaves) {
-        const bool second = f >= frags0;
-        const int f1 = f - (second ? frags0 : 0), i = f1 / parts;
+    const int ks0 = (r0 + 31) >> 5, ks1 = (r1 + 31) >> 5;
+    for (int f = wave; f < ks0 + ks1; f += kFewWaves) {
+        const bool second = f >= ks0;
+        const int i = f - (second ? ks0 : 0);
         // an odd number of 16-rank blocks leaves the upper half of the last k-step without ranks
         const bool none = ((((second ? r1 : r0) + 15) >> 4) & 1) != 0 && lane >= 32 && i == (second ? ks1 : ks0) - 1;
-        few_fetch_t(a, few_fragment(a, item * NW + (second ? 1u : 0u), f1 - i * parts, i), none, lane, smem + kFewTLds + f * 1024);
+        few_fetch_t<NW, BF>(a, few_fragment(a, item * NW + (second ? 1u : 0u), 0, i), none, lane, smem + kFewTLds + f * 1024);
     }
     const uint32_t blk = rb0 + (uint32_t)wave, nb16 = blk * 16u;
     const bool finish = wave < R && blk < NB;
@@ -330,16 +382,12 @@ __global__ __launch_bounds__(kFewThreads, 4) void w3lr_few_kernel(const FewArgs 
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             for (int i = 0; i < ks; ++i)
-                for (int p = 0; p < parts; ++p)
-                    sum[s] = few_mfma<BF>(reinterpret_cast<const u32x4*>(uf_lds)[i * 64 + lane], tl[((s ? frags0 : 0) + i * parts + p) * 64 + lane], sum[s]);
+                sum[s] = few_mfma<BF>(reinterpret_cast<const u32x4*>(uf_lds)[i * 64 + lane], tl[((s ? ks0 : 0) + i) * 64 + lane], sum[s]);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (read before the next weight's fragments land there)
         } else {
 #pragma unroll
             for (int i = 0; i < kStreamKS; ++i)
-                if (i < ks) {
-                    const u32x4 av = __builtin_bit_cast(u32x4, uf[s][i]);
-                    for (int p = 0; p < parts; ++p) sum[s] = few_mfma<BF>(av, tl[((s ? frags0 : 0) + i * parts + p) * 64 + lane], sum[s]);
-                }
+                if (i < ks) sum[s] = few_mfma<BF>(__builtin_bit_cast(u32x4, uf[s][i]), tl[((s ? ks0 : 0) + i) * 64 + lane], sum[s]);
         }
     }
     // element v: feature nb16 + 4 q + v, row j16
@@ -354,13 +402,13 @@ __global__ __launch_bounds__(kFewThreads, 4) void w3lr_few_kernel(const FewArgs 
 
 template <int NW, int R, bool BF>
 static int few_launch(const FewArgs& a, unsigned grid, hipStream_t stream) {
-    const int lds = kFewTLds + (int)(NW * a.t_frags * a.t_parts) * 1024;
+    const int lds = kFewTLds + (int)(NW * a.t_frags) * 1024;
     static bool raised[64] = {false};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MILO_ERR_HIP;
     if (!raised[dev]) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(w3lr_few_kernel<NW, R, BF>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kFewTLds + kFewMaxFrags * 1024) != hipSuccess)
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kFewTLds + 2 * kStreamKS * 1024) != hipSuccess)
             return MILO_ERR_HIP;
         raised[dev] = true;
     }
@@ -375,7 +423,7 @@ int launch_few(FewArgs a, int nw, bool bf, hipStream_t stream) {
     // items 97 -> 93 us per layer; at K = 1408 the two are equal).
     int R = 4 / nw;
     if (nw == 1 && a.K >= 4096u && (uint64_t)a.n_items * ((a.N + 63u) / 64u) < 2u * (uint32_t)device_cus()) R = 2;
-    a.t_parts = (uint32_t)few_t_parts(a.K);
+    a.t_parts = nw == 2 ? 1u : (uint32_t)few_t_parts(a.K);
     a.bands = (a.N + 16u * R - 1u) / (16u * R);
     const uint64_t grid = (uint64_t)a.n_items * ((uint64_t)nw * 2 * a.t_frags * a.t_parts + a.bands);
     if (grid > 0x7fffffffull) return MILO_ERR_SHAPE;

@@ -152,8 +152,8 @@ struct FewItem {
 };
 static_assert(sizeof(FewItem) % 16 == 0, "written in 16-byte pieces");
 constexpr int kFewRows = 16;
-constexpr int kFewTChunks = 16;             // 256-column chunks of a K part of T
-constexpr int kFewMaxFrags = 64;            // fragments of T a workgroup has LDS for
+constexpr int kFewTChunks = 16;             // 256-column chunks of a K part of T (down projection)
+constexpr int kFewMaxParts = 8;             // K parts of T (a workgroup fetches two per trip to memory; more were not measured)
 int few_t_parts(int64_t K);                 // K parts of T
 constexpr int kFewMaxRank = 128;            // largest rank its epilogue holds
 struct FewArgs {
@@ -164,7 +164,7 @@ struct FewArgs {
     uint32_t N, K;
     const f16* X;               // rows of K elements
     uint32_t x_bytes;           // < 2 GiB
-    unsigned long long* granules;   // T, [item][weight][t_parts][t_frags][4][64 lanes]
+    unsigned long long* granules;   // T, [item][weight][t_frags][t_parts][4, or 8 with several parts][64 lanes]
     uint32_t t_frags;           // fragments of 32 ranks of the largest rank (0: no weight has a compensator)
     uint32_t tag;               // of this launch (the granules were cleared to another value)
     uint32_t spin_limit;

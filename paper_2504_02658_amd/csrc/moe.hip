@@ -430,6 +430,10 @@ static double expected_tiles(int64_t P, int E, int b) {
     return tiles * E;
 }
 
+static bool moe_few_possible(int64_t H, int64_t F, int E, int r_max) {
+    return E <= kSmallExperts && r_max <= kFewMaxRank && few_t_parts(H) <= kFewMaxParts && few_t_parts(F) <= kFewMaxParts;
+}
+
 // Whether the weight-streaming kernel takes a batch (else the tiled one).  Both are measured per layer in us: the streaming one takes
 // 14 + 0.17 per MB of weight it reads, once per item of 16 rows, + 0.007 per workgroup; the tiled one 45 + 0.19 per MB, once per
 // 32-row tile.  So it is the number of rows per expert that decides, later where the weights are small:
@@ -437,15 +441,37 @@ static double expected_tiles(int64_t P, int E, int b) {
 // 1408 x 2048, 64 + 2 experts, 0.5 rows 34 / 63, 8 rows 94 / 103; 1024 x 512, 8 experts, 24 rows 28 / 42.
 static bool moe_takes_few(int64_t T, int64_t H, int64_t F, int E, int topk, int r_max) {
     const int64_t P = T * topk;
-    if (P > kSmallPairs || E > kSmallExperts || r_max > kFewMaxRank) return false;
-    // fragments of T that a workgroup holds in LDS
-    const int frags = (r_max + 31) / 32;
-    if (2 * few_t_parts(H) * frags > kFewMaxFrags || few_t_parts(F) * frags > kFewMaxFrags) return false;
+    if (P > kSmallPairs || !moe_few_possible(H, F, E, r_max)) return false;
     const double mb = 3.0 * 0.4375e-6 * (double)H * (double)F, groups = (double)((F + 31) / 32 + (H + 63) / 64);
     return 14.0 + expected_tiles(P, E, kFewRows) * (0.17 * mb + 0.007 * groups) < 45.0 + 0.19 * mb * expected_tiles(P, E, 32);
 }
 
-static bool moe_layout(int64_t T, int64_t H, int64_t F, int E, int topk, int r_max, MoeLayout* L) {
+// Layout of the weight-streaming kernel; grows with T.
+static void moe_few_layout(int64_t T, int64_t H, int64_t F, int E, int topk, int r_max, MoeLayout* L) {
+    const int64_t P = T * topk;
+    // every expert with rows may have one item that is not full
+    const int64_t used = P < E ? P : E, items = used + P / kFewRows;
+    L->bm = kFewRows;
+    L->few_items = (int)(items < P ? items : P);
+    L->few_frags = (r_max + 31) / 32;
+    // granules of a fragment of T: two values each, or one each of several parts
+    const int parts = few_t_parts(F), up = 2 * 256, down = parts > 1 ? 512 * parts : 256;
+    L->granule_bytes = (size_t)L->few_items * L->few_frags * (up > down ? up : down) * 8;
+    L->splits_down = 1;
+    size_t off = 0;
+    L->off_header = off; off = align_up(off + 64, 256);
+    L->off_sorted = off; off = align_up(off + (size_t)P * 4, 256);
+    L->off_token = 0;
+    L->off_items = off;  off = align_up(off + (size_t)L->few_items * sizeof(FewItem), 256);
+    L->off_granules = off; off = align_up(off + L->granule_bytes, 256);
+    L->off_h = off;      off = align_up(off + (size_t)P * F * 2, 256);
+    L->off_o = off;      off = align_up(off + (size_t)P * H * 4, 256);       // (fp32)
+    L->total = off;
+}
+
+// The layout of a call with a workspace of `have` bytes.  With too few for the weight-streaming kernel the call goes to the
+// tiled one, which for some shapes needs less (66 experts of 1408 x 2048, 62 tokens: 7.2 MB against 10.6).
+static bool moe_layout(int64_t T, int64_t H, int64_t F, int E, int topk, int r_max, size_t have, MoeLayout* L) {
     if (T <= 0 || E <= 0 || topk <= 0 || r_max < 0) return false;
     if (!weight_shape_ok(F, H) || !weight_shape_ok(H, F)) return false;
     if (H % 4 != 0) return false;
@@ -454,38 +480,22 @@ static bool moe_layout(int64_t T, int64_t H, int64_t F, int E, int topk, int r_m
     if (((uint64_t)r_max + 256) * (uint64_t)(H > F ? H : F) * 2 >= 0xFFFFFFF0ull) return false;
     // activations are addressed with 32-bit offsets inside the kernels
     if ((uint64_t)T * H * 2 >= 0x80000000ull || (uint64_t)P * F * 2 >= 0x80000000ull) return false;
-    L->few_items = 0;
-    if (moe_takes_few(T, H, F, E, topk, r_max)) {
-        // every expert with rows may have one item that is not full
-        const int64_t used = P < E ? P : E, items = used + P / kFewRows;
-        L->bm = kFewRows;
-        L->few_items = (int)(items < P ? items : P);
-        L->few_frags = (r_max + 31) / 32;
-        const int parts = few_t_parts(H) * 2 > few_t_parts(F) ? few_t_parts(H) * 2 : few_t_parts(F);   // gate and up, or down
-        L->granule_bytes = (size_t)L->few_items * parts * L->few_frags * 2048;
-        L->splits_down = 1;
-        size_t off = 0;
-        L->off_header = off; off = align_up(off + 64, 256);
-        L->off_sorted = off; off = align_up(off + (size_t)P * 4, 256);
-        L->off_token = 0;
-        L->off_items = off;  off = align_up(off + (size_t)L->few_items * sizeof(FewItem), 256);
-        L->off_granules = off; off = align_up(off + L->granule_bytes, 256);
-        L->off_h = off;      off = align_up(off + (size_t)P * F * 2, 256);
-        L->off_o = off;      off = align_up(off + (size_t)P * H * 4, 256);       // (fp32)
-        L->total = off;
-        return true;
-    }
-    const int64_t avg = P / E;
-    // Tile height: an expert whose rows do not fit one tile streams its weights once more, a
-    // taller tile costs more activation copies and a shallower pipeline; measured on the Mixtral
-    // shape the crossovers lie near 26 and 56 rows per expert.
-    L->bm = avg >= 56 ? 128 : (avg >= 26 ? 64 : 32);
     // tuning override, read once per process so that the workspace query and the call agree
     static const int bm_override = [] {
         const char* e = getenv("MILO_MOE_BM");
         const int v = e ? atoi(e) : 0;
         return (v == 32 || v == 64 || v == 128) ? v : 0;
     }();
+    if (!bm_override && moe_takes_few(T, H, F, E, topk, r_max)) {
+        moe_few_layout(T, H, F, E, topk, r_max, L);
+        if (have >= L->total) return true;
+    }
+    L->few_items = 0;
+    const int64_t avg = P / E;
+    // Tile height: an expert whose rows do not fit one tile streams its weights once more, a
+    // taller tile costs more activation copies and a shallower pipeline; measured on the Mixtral
+    // shape the crossovers lie near 26 and 56 rows per expert.
+    L->bm = avg >= 56 ? 128 : (avg >= 26 ? 64 : 32);
     if (bm_override) L->bm = bm_override;
     const int64_t max_tiles32 = (P + 31) / 32 + E;      // bound for the smallest tile height
     const int64_t max_tiles = (P + L->bm - 1) / L->bm + E;
@@ -600,8 +610,16 @@ extern "C" int milo_moe_w3lr_check_experts_flags(const milo_w3lr_expert* experts
 extern "C" size_t milo_moe_w3lr_workspace(int64_t T, int64_t H, int64_t F, int E, int topk,
                                           int r_max) {
     MoeLayout L;
-    if (!moe_layout(T, H, F, E, topk, r_max, &L)) return 0;
-    return L.total;
+    if (!moe_layout(T, H, F, E, topk, r_max, SIZE_MAX, &L)) return 0;
+    size_t bytes = L.total;
+    // A workspace sized for a batch that is tiled serves smaller, streamed ones at full speed as well: room for the
+    // largest of those.
+    if (L.few_items == 0 && moe_few_possible(H, F, E, r_max) && topk <= kSmallPairs) {
+        MoeLayout S;
+        moe_few_layout(T < kSmallPairs / topk ? T : kSmallPairs / topk, H, F, E, topk, r_max, &S);
+        if (S.total > bytes) bytes = S.total;
+    }
+    return bytes;
 }
 
 extern "C" int milo_moe_w3lr_forward(const milo_half* X, int64_t T, int64_t H, int64_t F,
@@ -622,7 +640,7 @@ extern "C" int milo_moe_w3lr_forward_flags(const milo_half* X, int64_t T, int64_
     if (call_flags & ~MILO_ACT_BF16) return MILO_ERR_SHAPE;
     const int bf = (call_flags & MILO_ACT_BF16) ? 1 : 0;
     MoeLayout L;
-    if (!moe_layout(T, H, F, E, topk, r_max, &L)) return MILO_ERR_SHAPE;
+    if (!moe_layout(T, H, F, E, topk, r_max, workspace_bytes, &L)) return MILO_ERR_SHAPE;
     if (r_max > H || r_max > F) return MILO_ERR_RANK;
     if (!workspace || workspace_bytes < L.total) return MILO_ERR_WORKSPACE;
     if (!aligned16(X) || !aligned16(Y) || !aligned16(workspace) || !aligned16(experts) ||

@@ -279,3 +279,52 @@ def test_few_rows_routing_rejects_and_repeats():
     ref = oracle.moe_forward(X, o_experts, np.where(good, ids, 0), np.where(good, gates, 0).astype(np.float32))
     assert_close(_forward(layer, X, ids, gates), ref, "repeated and bad ids")
     assert layer.routing_status() == 6
+
+
+def test_workspace_of_a_larger_batch_serves_smaller_ones():
+    # 250 tokens take the weight-streaming kernel and 260 the tiled one, which needs less room: a workspace sized for
+    # 260 has room for 250, one of two thirds of that is accepted (by the tiled kernel), and one too small for both is not
+    import torch
+    from paper_2504_02658_amd import api
+    case = wl.MoECase("ws", T=250, H=1024, F=512, E=8, topk=2, seed=37, rank_choices=(32,))
+    o_experts, layer = build_moe(case)
+    X, (ids, gates) = wl.moe_activations(case), wl.moe_routing(case)
+    args = [torch.from_numpy(a).cuda() for a in (X, ids, gates)]
+    need = layer.workspace_bytes(250, 2)
+    assert layer.workspace_bytes(260, 2) >= need
+    ws = api.new_workspace(2 * need // 3)
+    ref = oracle.moe_forward(X, o_experts, ids, gates)
+    for workspace in (ws, None, ws):
+        assert_close(layer.forward(*args, workspace=workspace).cpu().numpy(), ref, "workspace of a larger batch")
+        assert layer.routing_status() == 0
+    with pytest.raises(api.MiloError):
+        layer.forward(*args, workspace=api.new_workspace(65536))
+
+
+def test_few_rows_parts_of_t_are_added_in_fp32():
+    # Two K parts of T in the down projection that nearly cancel: the halves of H are equal and V's second half is the first
+    # one's negative, up to four columns, so |T| is about |part| / 32.  Rounding the parts to 16 bits would leave
+    # an error of about 32 * 2^-12 = 8e-3; rounding H, T and the output, 2^-11 at most each, is 1.5e-3, plus H's own
+    # products (16-bit weights, fp32 sums): 2e-3.
+    import torch
+    from paper_2504_02658_amd import api
+    H, F, T, r = 128, 8192, 5, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(41)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    w1, w3 = (api.pack_w3(torch.cat([w, w])) for w in (randn(F // 2, H) * 0.1, randn(F // 2, H) * 0.1))
+    v = randn(r, F // 2).half()
+    v2 = -v
+    v2[:, 5::1024] = 0
+    U, V = randn(H, r).half(), torch.cat([v, v2], dim=1).contiguous()
+    w2 = api.pack_w3(randn(H, F) * 1e-4)
+    X = randn(T, H).half()
+    ids, gates = torch.zeros(T, 1, dtype=torch.int32, device="cuda"), torch.ones(T, 1, device="cuda")
+    Y = api.MoELayer([(w1, w3, w2.with_compensator(U, V))], H, F).forward(X, ids, gates)
+    d = lambda pw: api.dequant_w3(pw).double().cpu()
+    a, b = X.double().cpu() @ d(w1).T, X.double().cpu() @ d(w3).T
+    h = a * torch.sigmoid(a) * b
+    low = (h @ V.double().cpu().T) @ U.double().cpu().T
+    ref = h @ d(w2).T + low
+    assert float(low.norm()) > 10 * float((ref - low).norm())
+    assert float((Y.double().cpu() - ref).norm() / ref.norm()) < 2e-3
