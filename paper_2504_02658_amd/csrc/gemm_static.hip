@@ -39,7 +39,7 @@ extern "C" int milo_w3lr_gemm_static(const milo_half* X, int64_t M, int64_t N, i
                                      const milo_half* U, const milo_half* V, int r, milo_half* Y,
                                      void* stream) {
     if (!X || !q3 || !Y) return MILO_ERR_NULL;
-    const size_t need = milo_w3lr_gemm_workspace(M, N, K, r);       // 0 for an invalid shape or rank
+    const size_t need = gemm_workspace_min(M, N, K, r);             // 0 for an invalid shape or rank
     if (need == 0) return (r < 0) ? MILO_ERR_RANK : MILO_ERR_SHAPE;
     // The array has room for the head of a GEMM workspace beyond MILO_STATIC_SCRATCH_BYTES: the limit applies to the
     // control block, the sign-off words (decode) or the flag words of 32-row tiles, and the scratch behind them.

@@ -111,6 +111,8 @@ constexpr size_t kGemmDoneAt = 256, kGemmFlagsAt = kGemmDoneAt + kDecDoneBytes, 
 static_assert(kGemmHeadBytes == MILO_WORKSPACE_STATE_BYTES, "stated in milo.h");
 // Bytes of flag words behind the head (0: they fit in it).
 size_t gemm_flags_behind(int64_t M);
+// Workspace bytes below which a milo_w3lr_gemm call is refused (0: invalid shape or rank).
+size_t gemm_workspace_min(int64_t M, int64_t N, int64_t K, int r);
 constexpr int kDecMaxWorkers = 32;  // workgroups forming T = X V^T in the decode kernel
 
 struct DecodeArgs {

@@ -43,6 +43,20 @@ def test_sizes(L):
     assert L.milo_moe_w3lr_workspace(512, 4096, 100, 8, 2, 64) == 0
 
 
+@pytest.mark.parametrize("N,K", [(1024, 1024), (4096, 14336), (4096, 4352), (2816, 11008), (512, 20480)])
+@pytest.mark.parametrize("r", [0, 16, 128])
+def test_gemm_workspace_of_more_rows_serves_a_decode(L, N, K, r):
+    # a serving program sizes one workspace for its largest prefill and decodes on it too
+    sizes = [L.milo_w3lr_gemm_workspace(M, N, K, r) for M in (1, 16, 17, 300, 4096)]
+    assert sizes[0] == sizes[1] <= min(sizes)
+    # a call for M > 16 itself needs no more than before: rows that the tiled kernel takes, without room for a decode
+    p, odd = ctypes.c_void_p(0x10000), ctypes.c_void_p(0x10008)
+    call = lambda M, have: L.milo_w3lr_gemm(odd, M, N, K, p, p, p, r, p, p, have, None)
+    assert call(4096, sizes[4]) == 7                            # (room enough: the next check, of X's alignment, refuses)
+    if (N, K, r) == (4096, 14336, 0):
+        assert call(4096, 65536) == 7 and call(16, 65536) == 7 and call(4096, 4096) == 5
+
+
 def test_host_side_argument_errors(L):
     p = ctypes.c_void_p(0x10000)       # never dereferenced: validation fails first
     null = ctypes.c_void_p(0)

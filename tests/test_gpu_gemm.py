@@ -152,6 +152,20 @@ def test_decode_partial_sums_in_scratch_that_looks_like_theirs():
     assert api.workspace_status(small) == 0
 
 
+def test_decode_on_a_prefill_workspace_is_the_decode_on_its_own():
+    # a workspace for 4096 rows without K splits: 16 rows on it take the kernel that they take with their own, bit for bit
+    import torch
+    from paper_2504_02658_amd import api
+    N, K = 4096, 14336
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    pw = api.pack_w3(torch.randn((N, K), generator=g, device="cuda") * 0.02)
+    X = torch.randn((16, K), generator=g, device="cuda").half()
+    own, prefill = (api.new_workspace(api.gemm_workspace_bytes(M, N, K, 0)) for M in (16, 4096))
+    assert torch.equal(api.w3lr_gemm(X, pw, workspace=own), api.w3lr_gemm(X, pw, workspace=prefill))
+    assert api.workspace_status(prefill) == 0
+
+
 @pytest.mark.parametrize("M", [17, 32, 33, 64, 100, 130, 257])
 def test_tiled_rows(M):
     _check_case(M, 272, 1408, 8, seed=60 + M)
