@@ -1011,10 +1011,6 @@ size_t decode_workspace_min(int64_t N, int64_t K, int r) {
     // head | T 16-bit [K parts][16 x ldt] of the other path
     return kGemmHeadBytes + (t.staged ? 0 : align_up((size_t)t.kh * 16 * rblocks * 16 * 2, 256));
 }
-size_t decode_workspace_bytes(int64_t N, int64_t K, int r) {
-    const int split = decode_split_rows(N, K, r, device_cus());
-    return split > 0 ? kGemmHeadBytes + decode_split_bytes(N, K, split) : decode_workspace_min(N, K, r);
-}
 
 // Row blocks per workgroup (16 R rows).  Every workgroup stages all of X once per turn and streams
 // R row blocks; a CU takes in activations (from L2) roughly five times as fast as weights (from
@@ -1053,6 +1049,35 @@ static bool decode_split_faster(int64_t N, int64_t K, int xc, int R, int Rs, int
     return split + 0.3 < other;
 }
 
+// Tuning override of the row blocks per workgroup, read once per process (it also keeps the long-K kernel out).
+static int decode_row_override() {
+    static const int rows = [] {
+        const char* e = getenv("MILO_DEC_R");
+        const int v = e ? atoi(e) : 0;
+        return (v == 1 || v == 2 || v == 4) ? v : 0;
+    }();
+    return rows;
+}
+
+// Row blocks per wave with which a launch of `xc` activation copies per chunk takes the long-K kernel (0: the other one), where
+// that one would take R and `slots` workgroups stream.
+static int decode_split_choice(int64_t N, int64_t K, int r, int xc, int R, int slots, int cap) {
+    const int rows = decode_row_override() ? 0 : decode_split_rows(N, K, r, cap);
+    return rows > 0 && decode_split_faster(N, K, xc, R, rows, slots) ? rows : 0;
+}
+
+// Room for the granules where any launch of up to sixteen rows takes the long-K kernel.  The more activation copies, the
+// further that one is ahead (a copy more costs it 0.12 us, the other kernel 0.143 us for each of two or more chunks), so
+// eight copies decide.
+size_t decode_workspace_bytes(int64_t N, int64_t K, int r) {
+    const size_t least = decode_workspace_min(N, K, r);
+    const int cap = device_cus();
+    const int slots = cap - (r > 0 ? decode_workers((r + 15) / 16, decode_t_plan(N, K, r).kh, cap) : 0);
+    if (slots <= 0) return least;
+    const int rows = decode_split_choice(N, K, r, 8, decode_rows_per_workgroup(N, K, slots), slots, cap);
+    return rows > 0 ? kGemmHeadBytes + decode_split_bytes(N, K, rows) : least;
+}
+
 int launch_decode(DecodeArgs a, void* workspace, size_t workspace_bytes, hipStream_t stream) {
     const int cap = decode_capacity();
     if (cap <= 0) return MILO_ERR_HIP;
@@ -1077,18 +1102,11 @@ int launch_decode(DecodeArgs a, void* workspace, size_t workspace_bytes, hipStre
     const int workers = r > 0 ? nt : 0;
     if (cap <= workers || (size_t)cap * 4 > kDecDoneBytes) return MILO_ERR_HIP;
     int R = decode_rows_per_workgroup(a.N, a.K, cap - workers);
-    static const int r_override = [] {                          // tuning override, read once per process
-        const char* e = getenv("MILO_DEC_R");
-        const int v = e ? atoi(e) : 0;
-        return (v == 1 || v == 2 || v == 4) ? v : 0;
-    }();
-    if (r_override) R = r_override;
+    if (decode_row_override()) R = decode_row_override();
     const int xc = a.M <= 2 ? 1 : a.M <= 4 ? 2 : a.M <= 8 ? 4 : 8;    // activation copies per chunk: rows 2i, 2i+1
-    int split_rows = r_override ? 0 : decode_split_rows(a.N, a.K, r, cap);
+    int split_rows = decode_split_choice(a.N, a.K, r, xc, R, cap - workers, cap);
     // (a workspace that has no room for the granules is one for the other kernel)
-    if (split_rows > 0 && (!decode_split_faster(a.N, a.K, xc, R, split_rows, cap - workers) ||
-                           workspace_bytes < kGemmHeadBytes + decode_split_bytes(a.N, a.K, split_rows)))
-        split_rows = 0;
+    if (split_rows > 0 && workspace_bytes < kGemmHeadBytes + decode_split_bytes(a.N, a.K, split_rows)) split_rows = 0;
     if (split_rows > 0) R = split_rows;
     const int rows = 16 * R;
     const int64_t blocks = (a.N + rows - 1) / rows;

@@ -57,6 +57,15 @@ def test_gemm_workspace_of_more_rows_serves_a_decode(L, N, K, r):
         assert call(4096, 65536) == 7 and call(16, 65536) == 7 and call(4096, 4096) == 5
 
 
+def test_gemm_workspace_has_room_for_partial_sums_only_where_some_decode_uses_it(L):
+    state = 59648                                               # MILO_WORKSPACE_STATE_BYTES
+    for r in (0, 32):
+        assert L.milo_w3lr_gemm_workspace(16, 4096, 14336, r) > state
+        # more than sixteen chunks of K, but up to sixteen rows walk them in turn
+        assert L.milo_w3lr_gemm_workspace(16, 4096, 8192, r) <= state
+        assert L.milo_w3lr_gemm_workspace(16, 7168, 6400, r) <= state
+
+
 def test_host_side_argument_errors(L):
     p = ctypes.c_void_p(0x10000)       # never dereferenced: validation fails first
     null = ctypes.c_void_p(0)
