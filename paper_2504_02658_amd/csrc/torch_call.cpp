@@ -128,7 +128,8 @@ PyObject* py_gemm(PyObject*, PyObject* const* a, Py_ssize_t n) {
             own = at::empty({(int64_t)(need > 256 ? need : 256)}, X->options().dtype(at::kByte));
             ws = own.data_ptr();
             ws_bytes = (size_t)own.numel();
-            const int st = e->workspace_init(ws, ws_bytes, stream);
+            // Only the state has to start at zero; what lies behind may hold anything.
+            const int st = e->workspace_init(ws, ws_bytes < MILO_WORKSPACE_STATE_BYTES ? ws_bytes : MILO_WORKSPACE_STATE_BYTES, stream);
             if (st != MILO_OK) return status_object(st);
         } else {
             ws_bytes = (size_t)THPVariable_Unpack(a[10]).numel();

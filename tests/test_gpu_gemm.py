@@ -152,6 +152,34 @@ def test_decode_partial_sums_in_scratch_that_looks_like_theirs():
     assert api.workspace_status(small) == 0
 
 
+@pytest.mark.parametrize("M,N,K,r", [(16, 4096, 14336, 32), (16, 512, 512, 0), (512, 1024, 4096, 8), (140000, 64, 64, 8)])
+def test_call_without_a_workspace_clears_its_state_and_no_more(M, N, K, r):
+    # partial sums and T lie behind the state (here in memory that holds 0x7f.. from before), also the flag words of 140000 rows
+    import ctypes
+    import torch
+    from paper_2504_02658_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(13)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    pw = api.pack_w3(randn(N, K) * 0.02)
+    if r:
+        pw = pw.with_compensator((randn(N, r) * 0.1).half(), (randn(r, K) * 0.1).half())
+    X = randn(M, K).half()
+    need = max(api.gemm_workspace_bytes(M, N, K, r), 256)
+    ref = api.w3lr_gemm(X, pw, workspace=api.new_workspace(need))
+    L, cleared = api.lib(), []
+    def init(ws, nbytes, stream):
+        cleared.append(nbytes)
+        return L.milo_workspace_init(ws, nbytes, stream)
+    recorder = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)(init)
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    entries = api._native.entries({n: address(recorder if n == "milo_workspace_init" else getattr(L, n)) for n in api._NATIVE_ENTRIES})
+    torch.full((need,), 0x7f, dtype=torch.uint8, device="cuda")                 # (freed at once: the call's own workspace is this memory)
+    Y = api._native.gemm(entries, X, pw.q3, pw.U, pw.V, N, K, None, 0, None, None)
+    assert torch.equal(Y, ref)
+    assert cleared == [min(need, 59648)]                                        # MILO_WORKSPACE_STATE_BYTES
+
+
 def test_decode_on_a_prefill_workspace_is_the_decode_on_its_own():
     # a workspace for 4096 rows without K splits: 16 rows on it take the kernel that they take with their own, bit for bit
     import torch
