@@ -23,6 +23,20 @@ def assert_close(Y_gpu, Y_ref, what=""):
     return rel, mx
 
 
+STREAMED = 16       # rows of an item of the weight-streaming kernel; tiles of the tiled one have 32, 64 or 128
+
+
+def assert_rows_per_tile(layer, ids, rows):
+    """Which kernel the last forward took, and at which tile height: the routing kernels leave the number of tiles in word 1
+    of the workspace, and the expert with the most rows has to make that number another one for every other height but (streaming
+    aside) greater ones."""
+    import torch
+    n = np.bincount(ids[(ids >= 0) & (ids < layer.E)], minlength=layer.E)
+    made = int(layer.last_workspace.view(torch.int32)[1])
+    heights = [b for b in (16, 32, 64, 128) if int(np.sum((n + b - 1) // b)) == made]
+    assert heights == [rows] or rows == 128 and heights[-1] == rows, (heights, rows, int(n.max()))
+
+
 def oracle_weight(W, r, seed=0, exact_svd_limit=1024 * 1024, symmetric=False):
     """Quantize W on the CPU and fit the rank-r compensator to the residual."""
     q, s, z = oracle.quantize_sym(W) if symmetric else oracle.quantize_rtn(W)

@@ -4,44 +4,72 @@ import pytest
 
 import oracle
 from paper_2504_02658_amd import workloads as wl
-from helpers import assert_close, build_moe
+from helpers import STREAMED, assert_close, assert_rows_per_tile, build_moe
 
 pytestmark = pytest.mark.gpu
 
 
-def _forward(layer, X, ids, gates):
+def _forward(layer, X, ids, gates, workspace=None):
     import torch
     Y = layer.forward(torch.from_numpy(X).cuda(), torch.from_numpy(ids).cuda(),
-                      torch.from_numpy(gates).cuda())
+                      torch.from_numpy(gates).cuda(), workspace=workspace)
     return Y.cpu().numpy()
 
 
-def _check(case, what=None, int3=False):
+def _check(case, what=None, int3=False, rows=None, less=0):
+    """rows: the tile height that the batch has to take.  less: bytes that its workspace is short of the size asked for."""
+    from paper_2504_02658_amd import api
     o_experts, layer = build_moe(case, int3=int3)
     X = wl.moe_activations(case)
     ids, gates = wl.moe_routing(case)
     ref = oracle.moe_forward(X, o_experts, ids, gates)
-    Y = _forward(layer, X, ids, gates)
+    ws = api.new_workspace(layer.workspace_bytes(case.T, ids.shape[1]) - less) if less else None
+    Y = _forward(layer, X, ids, gates, ws)
     res = assert_close(Y, ref, what or case.name)
     assert layer.routing_status() == 0
-    Y2 = _forward(layer, X, ids, gates)
+    if rows:
+        assert_rows_per_tile(layer, ids, rows)
+    Y2 = _forward(layer, X, ids, gates, ws)
     assert np.array_equal(Y.view(np.uint16), Y2.view(np.uint16)), "two runs differ"
     return res
 
 
 def test_tiny_layer_all_tile_heights():
     base = wl.MoECase("tiny", T=40, H=256, F=384, E=4, topk=2, seed=11, rank_choices=(0, 8, 16))
-    _check(base)                                              # ~20 rows per expert: 32-row tiles
-    _check(wl.scaled(base, T=80, name="tiny64"))             # ~40 rows: 64-row tiles
-    _check(wl.scaled(base, T=150, name="tiny128a"))          # ~75 rows: 128-row tiles, partly filled
-    _check(wl.scaled(base, T=400, name="tiny128"))           # ~200 rows: 128-row tiles, several per expert
+    _check(base, rows=STREAMED)                               # ~20 rows per expert
+    _check(wl.scaled(base, T=80, name="tiny40"))             # ~40 rows
+    _check(wl.scaled(base, T=150, name="tiny75"))            # ~75 rows, also streamed: a small layer's weights cost little
+    _check(wl.scaled(base, T=400, name="tiny128"), rows=128)  # ~200 rows: 128-row tiles, several per expert
+
+
+# The tiled kernel at 32- and 64-row tiles: layers that the weight-streaming kernel does not take (a rank above 128, more than
+# 512 pairs, or a workspace without room for it), with experts of no, one and several tiles.
+TILED = [
+    # T, H, F, E, topk, ranks, popularity skew, rows of a tile, bytes the workspace is short of
+    (80, 256, 384, 8, 2, (0, 40, 136), 2.5, 32, 0),         # routed by one launch; ranks on both sides of 32 and beyond 128
+    (40, 256, 3072, 4, 2, (136,), 2.5, 32, 0),              # K splits of the down projection
+    (140, 128, 2176, 24, 4, (0, 8, 40), 1.2, 32, 0),        # the same beyond 512 pairs: the general routing kernels
+    (160, 256, 384, 16, 4, (0, 8, 40), 1.2, 64, 0),
+    (160, 128, 2176, 16, 4, (0, 8, 40), 1.2, 64, 0),        # with K splits
+    (80, 256, 384, 8, 2, (0, 40, 128), 2.5, 32, 256),       # would stream, but for its workspace
+]
+
+
+@pytest.mark.parametrize("T,H,F,E,topk,ranks,zipf,rows,less,dtype", [
+    (*c, dtype) for c in TILED for dtype in ("fp16", "bf16", "int3") if dtype != "int3" or max(c[5]) <= 128])
+def test_tiled_layer_at_32_and_64_rows(T, H, F, E, topk, ranks, zipf, rows, less, dtype):
+    case = wl.MoECase("tiled", T=T, H=H, F=F, E=E, topk=topk, seed=51 + T, rank_choices=ranks, zipf_s=zipf)
+    if dtype == "bf16":
+        _check_bf16(case, rows=rows, less=less)
+    else:
+        _check(case, int3=dtype == "int3", rows=rows, less=less)
 
 
 def test_int3_compensators_in_a_layer():
     # every expert's U, V as INT3 blobs (Section 3.2.3): the grouped kernels unpack them like weights
     base = wl.MoECase("int3", T=40, H=256, F=384, E=4, topk=2, seed=21, rank_choices=(0, 8, 16, 40))
-    _check(base, int3=True)
-    _check(wl.scaled(base, T=400, name="int3_128", rank_choices=(16, 32, 128)), int3=True)
+    _check(base, int3=True, rows=STREAMED)
+    _check(wl.scaled(base, T=400, name="int3_128", rank_choices=(16, 32, 128)), int3=True, rows=128)
 
 
 # bfloat16 layer (MILO_ACT_BF16): on top of the single linear's roundings (every dequantized weight, T, the
@@ -51,15 +79,17 @@ def test_int3_compensators_in_a_layer():
 BF16_MOE_REL_FRO_TOL, BF16_MOE_MAX_ABS_TOL = 6e-3, 4e-2
 
 
-def _check_bf16(case):
+def _check_bf16(case, rows=None, less=0):
     import torch
     from helpers import to_bf16
+    from paper_2504_02658_amd import api
     o_experts, layer = build_moe(case, bf16=True)
     Xb = to_bf16(wl.moe_activations(case))
     ids, gates = wl.moe_routing(case)
     ref = oracle.moe_forward(Xb.float().numpy(), o_experts, ids, gates)
     args = (Xb.cuda(), torch.from_numpy(ids).cuda(), torch.from_numpy(gates).cuda())
-    Y = layer.forward(*args)
+    ws = api.new_workspace(layer.workspace_bytes(case.T, ids.shape[1]) - less) if less else None
+    Y = layer.forward(*args, workspace=ws)
     assert Y.dtype == torch.bfloat16
     Yf = Y.float().cpu().numpy().astype(np.float64)
     assert np.all(np.isfinite(Yf))
@@ -67,15 +97,17 @@ def _check_bf16(case):
     mx = np.max(np.abs(Yf - ref)) / np.max(np.abs(ref))
     assert rel <= BF16_MOE_REL_FRO_TOL and mx <= BF16_MOE_MAX_ABS_TOL, (case.name, rel, mx)
     assert layer.routing_status() == 0
-    assert torch.equal(Y, layer.forward(*args)), "two runs differ"
+    if rows:
+        assert_rows_per_tile(layer, ids, rows)
+    assert torch.equal(Y, layer.forward(*args, workspace=ws)), "two runs differ"
 
 
 def test_bf16_layer():
     base = wl.MoECase("bf16", T=40, H=256, F=384, E=4, topk=2, seed=31, rank_choices=(0, 8, 16, 40))
-    _check_bf16(base)                                                           # 32-row tiles
-    _check_bf16(wl.scaled(base, T=400, name="bf16_128"))                        # 128-row tiles, several per expert
-    _check_bf16(wl.scaled(base, T=3, name="bf16_small"))                        # single-launch routing
-    _check_bf16(wl.scaled(wl.C4, T=256, H=512, F=704, E=16, name="bf16_c4_reduced"))  # shared experts, K splits
+    _check_bf16(base, rows=STREAMED)
+    _check_bf16(wl.scaled(base, T=400, name="bf16_128"), rows=128)              # 128-row tiles, several per expert
+    _check_bf16(wl.scaled(base, T=3, name="bf16_small"))
+    _check_bf16(wl.scaled(wl.C4, T=256, H=512, F=704, E=16, name="bf16_c4_reduced"), rows=128)    # shared experts
 
 
 def test_bf16_layer_rejects_int3_compensators():
@@ -132,11 +164,17 @@ def test_rows_of_another_width_are_refused_whatever_the_workspace_holds():
     assert torch.equal(layer.forward(X, ids, gates), ref)
 
 
-def test_graph_replay_of_a_layer():
+@pytest.mark.parametrize("T,E,topk,ranks,zipf,rows", [
+    (150, 4, 2, (8, 16), 0.0, STREAMED),
+    (80, 8, 2, (8, 136), 2.5, 32),          # the tiled kernel's flags, single-launch routing
+    (160, 16, 4, (8, 16), 1.2, 64),         # and the general one
+    (300, 4, 2, (8, 16), 0.0, 128),
+])
+def test_graph_replay_of_a_layer(T, E, topk, ranks, zipf, rows):
     # routing, flags and partial buffers are re-initialised by the kernels themselves: a captured
     # layer replays bit for bit with eager work on the same workspace in between
     import torch
-    case = wl.MoECase("replay", T=150, H=256, F=384, E=4, topk=2, seed=15, rank_choices=(8, 16))
+    case = wl.MoECase("replay", T=T, H=256, F=384, E=E, topk=topk, seed=15, rank_choices=ranks, zipf_s=zipf)
     _, layer = build_moe(case)
     X = torch.from_numpy(wl.moe_activations(case)).cuda()
     ids_np, gates_np = wl.moe_routing(case)
@@ -145,6 +183,7 @@ def test_graph_replay_of_a_layer():
     ws = api.new_workspace(layer.workspace_bytes(case.T, case.topk), X.device)
     out = torch.empty((case.T, case.H), dtype=torch.float16, device=X.device)
     eager = layer.forward(X, ids, gates, workspace=ws).clone()
+    assert_rows_per_tile(layer, ids_np, rows)
     torch.cuda.synchronize()
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
@@ -217,11 +256,12 @@ def test_status_reports_a_wait_that_gave_up():
 
 @pytest.mark.timeout(900)
 def test_c3_mixtral_layer_full_size():
-    # the full layer at 512 tokens, then the same experts at decode-sized batches (16, 4 and 1 tokens:
-    # routing and work list come from the single-launch kernel, tiles are 32 rows high)
+    # the full layer at 512 tokens (128-row tiles), then the same experts at decode-sized batches (64 tokens:
+    # 32-row tiles with K splits of the down projection; 16, 4 and 1: the weight-streaming kernel)
     import dataclasses
+    import torch
     o_experts, layer = build_moe(wl.C3)
-    for T in (512, 16, 4, 1):
+    for T, rows in ((512, 128), (64, 32), (16, None), (4, None), (1, None)):
         case = dataclasses.replace(wl.C3, T=T)
         X = wl.moe_activations(case)
         ids, gates = wl.moe_routing(case)
@@ -229,18 +269,45 @@ def test_c3_mixtral_layer_full_size():
         Y = _forward(layer, X, ids, gates)
         assert_close(Y, ref, f"c3 at {T} tokens")
         assert layer.routing_status() == 0
+        if rows == 128:
+            assert_rows_per_tile(layer, ids, rows)
+        elif rows:                  # (no expert has more than 32 rows here: any height but the streamed items' fits)
+            n = np.bincount(ids.ravel(), minlength=layer.E)
+            assert int(layer.last_workspace.view(torch.int32)[1]) == int(np.sum((n + 31) // 32)) != int(np.sum((n + 15) // 16))
         Y2 = _forward(layer, X, ids, gates)
         assert np.array_equal(Y.view(np.uint16), Y2.view(np.uint16)), "two runs differ"
 
 
 def test_routing_of_small_batches_matches_the_general_kernels():
-    # up to 256 routed pairs the routing and the work list come from one single-workgroup kernel; from
-    # 257 on from the two general kernels: the same layer just below and just above the limit, many
-    # experts empty, several tiles per expert
+    # up to 512 routed pairs (and experts) the routing and the work list of 32-row tiles come from one single-workgroup
+    # kernel, from 513 on from the two general kernels: the same tokens below and above the limit give the same bits (a
+    # row's result does not depend on the tile it lands in), with many experts empty, several tiles per expert, ranks on
+    # both sides of 32 and ids out of range; the same layer's few-row batches beside it
+    import torch
     base = wl.MoECase("small_route", T=64, H=128, F=192, E=24, topk=4, seed=23, rank_choices=(0, 8, 40))
-    _check(base)                                              # 256 pairs
-    _check(wl.scaled(base, T=65, name="general_route"))      # 260 pairs
+    _check(base, rows=STREAMED)
     _check(wl.scaled(base, T=3, name="three_tokens"))
+    case = wl.MoECase("general_route", T=129, H=256, F=192, E=24, topk=4, seed=53, rank_choices=(0, 8, 40, 136), zipf_s=1.2)
+    o_experts, layer = build_moe(case)
+    X = wl.moe_activations(case)
+    ids, gates = wl.moe_routing(case)
+    ids = ids.copy()
+    ids[3, 1], ids[77, 0], ids[127, 3] = -1, case.E, 1 << 20
+    good = (ids >= 0) & (ids < case.E)
+    ref = oracle.moe_forward(X, o_experts, np.where(good, ids, 0), np.where(good, gates, 0).astype(np.float32))
+    general = _forward(layer, X, ids, gates)                  # 516 pairs
+    assert_close(general, ref, "general routing")
+    assert_rows_per_tile(layer, ids, 32)
+    assert layer.routing_status() == 6
+    small = _forward(layer, X[:128], ids[:128], gates[:128])  # 512
+    assert layer.routing_status() == 6
+    assert_rows_per_tile(layer, ids[:128], 32)
+    assert np.array_equal(general[:128].view(np.uint16), small.view(np.uint16))
+
+
+def test_single_launch_routing_of_many_tiles():
+    # 512 pairs over 220 experts: more than 128 tiles, whose list the tiled kernel reads as eight ranges
+    _check(wl.MoECase("many_small", T=128, H=256, F=192, E=220, topk=4, seed=56, rank_choices=(8, 136), zipf_s=0.4), rows=32)
 
 
 @pytest.mark.timeout(900)
@@ -283,7 +350,8 @@ def test_few_rows_routing_rejects_and_repeats():
 
 def test_workspace_of_a_larger_batch_serves_smaller_ones():
     # 250 tokens take the weight-streaming kernel and 260 the tiled one, which needs less room: a workspace sized for
-    # 260 has room for 250, one of two thirds of that is accepted (by the tiled kernel), and one too small for both is not
+    # 260 has room for 250, one of two thirds of that is accepted (by the tiled kernel, 128-row tiles), and one too small for
+    # both is not
     import torch
     from paper_2504_02658_amd import api
     case = wl.MoECase("ws", T=250, H=1024, F=512, E=8, topk=2, seed=37, rank_choices=(32,))
