@@ -6,6 +6,7 @@ import ctypes
 import numpy as np
 import pytest
 
+from helpers import STREAMED, assert_rows_per_tile
 from paper_2504_02658_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -45,24 +46,53 @@ def test_counted_waits_equal_full_waits(M, N, K, r):
     assert np.all(np.isfinite(a)) and np.any(a != 0)
 
 
-def test_moe_layer_counted_waits_equal_full_waits(monkeypatch):
-    # the grouped kernels of the MoE call share the K loop with its counted waits: the same layer through
-    # both builds, tile heights 32 and 128, must agree bit for bit
+@pytest.mark.parametrize("T,H,F,E,topk,ranks,zipf,rows", [
+    # the weight-streaming kernel, three and more chunks per wave in both projections: items of 16 and 4 rows, of 16 and 7,
+    # of 3 (the down projection at two row blocks per wave), and a layer whose loop never repeats
+    (20, 2304, 2112, 2, 2, (8, 40), 0.0, STREAMED), (23, 2304, 4416, 2, 2, (0, 128), 0.0, STREAMED),
+    (3, 4160, 4352, 4, 2, (24,), 0.0, None), (24, 256, 384, 4, 2, (0, 8, 40), 0.0, None),
+    # the tiled one at each of its heights, with and without K splits of the down projection
+    (80, 1024, 1152, 8, 2, (0, 40, 136), 2.5, 32), (140, 512, 2176, 24, 4, (0, 8, 40), 1.2, 32),
+    (160, 1024, 2304, 16, 4, (0, 8, 40), 1.2, 64), (400, 256, 384, 4, 2, (0, 8, 40), 0.0, 128),
+])
+@pytest.mark.parametrize("dtype", ["fp16", "bf16", "int3"])
+def test_moe_layer_counted_waits_equal_full_waits(monkeypatch, T, H, F, E, topk, ranks, zipf, rows, dtype):
+    # the grouped kernels of the MoE call count their waits too: the same layer through both builds must agree bit for bit
     import torch
     from paper_2504_02658_amd import api
-    from helpers import build_moe
-    for T in (24, 400):
-        case = wl.MoECase("waits", T=T, H=256, F=384, E=4, topk=2, seed=41, rank_choices=(0, 8, 40))
-        _, layer = build_moe(case)
-        X = torch.from_numpy(wl.moe_activations(case)).cuda()
-        ids_np, gates_np = wl.moe_routing(case)
-        ids, gates = torch.from_numpy(ids_np).cuda(), torch.from_numpy(gates_np).cuda()
-        Y1 = layer.forward(X, ids, gates).clone()
+    less = 0
+    if dtype == "int3" and max(ranks) > 128:        # (136 keeps the other types off the streaming kernel, here less room does)
+        less, ranks = 256, tuple(min(r, 128) for r in ranks)
+    case = wl.MoECase("waits", T=T, H=H, F=F, E=E, topk=topk, seed=41, rank_choices=ranks, zipf_s=zipf)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H + F + T)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+
+    def weight(N, K, r):
+        pw = api.pack_w3(randn(N, K) * 0.02)
+        U, V = randn(N, r) * 0.1, randn(r, K) * 0.1
+        if r == 0:
+            return pw
+        return pw.with_int3_compensator(*api.pack_lr3(U, V), r) if dtype == "int3" else pw.with_compensator(U.to(dt), V.to(dt))
+
+    experts = [tuple(weight(n, k, ranks[e % len(ranks)]) for n, k in ((F, H), (F, H), (H, F))) for e in range(E)]
+    X = torch.from_numpy(wl.moe_activations(case)).cuda().to(dt)
+    ids_np, gates_np = wl.moe_routing(case)
+    ids, gates = torch.from_numpy(ids_np).cuda(), torch.from_numpy(gates_np).cuda()
+
+    def forward():
+        layer = api.MoELayer(experts, H, F, bf16=dtype == "bf16")
+        ws = api.new_workspace(layer.workspace_bytes(T, topk) - less)
+        Y = layer.forward(X, ids, gates, workspace=ws).clone()
         assert layer.routing_status() == 0
-        with monkeypatch.context() as m:
-            m.setattr(api, "_lib", api.bind(api.FULLWAITS_LIB_PATH))
-            layer2 = api.MoELayer(layer.experts, case.H, case.F)
-            Y2 = layer2.forward(X, ids, gates).clone()
-            assert layer2.routing_status() == 0
-        assert torch.equal(Y1, Y2), f"the two builds differ at {T} tokens"
-        assert bool(torch.isfinite(Y1.float()).all()) and bool((Y1 != 0).any())
+        if rows:
+            assert_rows_per_tile(layer, ids_np, rows)
+        return Y
+
+    Y1 = forward()
+    with monkeypatch.context() as m:
+        m.setattr(api, "_lib", api.bind(api.FULLWAITS_LIB_PATH))
+        Y2 = forward()
+    assert torch.equal(Y1, Y2)
+    assert bool(torch.isfinite(Y1.float()).all()) and bool((Y1 != 0).any())
