@@ -1035,18 +1035,22 @@ static int decode_rows_per_workgroup(int64_t N, int64_t K, int slots) {
 }
 
 // Whether the long-K kernel, with Rs row blocks per wave, is the faster one for a problem that the other would walk with R
-// of them.  The other one walks ceil(chunks / 16) chunks per wave in turn, each with its XC activation copies; the long-K
-// kernel walks one, but hands partial sums over.  Both estimates (us) are fits to 69 shapes from 512 x 4160 to
-// 12000 x 4864 and 4096 x 14336 at M = 1 .. 16, off by 0.3 in the middle.  Measured, chunks in turn -> split: M = 16, r = 32,
-// 4096 x 14336 15.5 -> 11.5; 1024 x 14336 12.4 -> 7.4; 2816 x 11008 10.2 -> 8.2; 12000 x 4864 13.5 -> 11.8; 512 x 8192
-// 7.6 -> 6.4; M = 1, 4096 x 14336 12.2 -> 10.1.  Where it stays: M = 1, 3920 x 8128 6.6 -> 7.3, 1440 x 4608 5.5 -> 5.7; M = 8,
-// 4096 x 8192 8.6 -> 9.4; M = 6, 800 x 4544 6.5 -> 6.8; M = 16, 3008 x 6016 7.6 -> 7.8.
+// of them.  The other one walks ceil(chunks / 16) chunks per wave in turn and copies each workgroup's chunks of X; the long-K
+// kernel walks one, but hands partial sums over.  Both estimates (us) are fits to 37 shapes from 512 x 4160 to 12000 x 4864 and
+// 4096 x 14336 at M = 1 .. 16, and were checked on 69 drawn ones: of those 276 points one was spread although it is
+// slower, by 2 %, and 17 were not although they would be 2 to 13 % faster.  The copies count with the chunks there are, not
+// with whole rounds of sixteen: with seventeen to 24 chunks M = 5 .. 8 was spread at a loss (512 x 4160, M = 8, 5.5 in
+// turn against 5.8; 752 x 4160, M = 5, 5.9 / 6.3).  Measured, chunks in turn -> spread: M = 16, r = 32, 4096 x 14336 15.6 -> 11.4;
+// 1024 x 14336 12.1 -> 6.9; 2816 x 11008 10.3 -> 8.3; 12000 x 4864 13.5 -> 11.9; 512 x 8192 7.5 -> 6.4; M = 1, 4096 x 14336
+// 12.0 -> 10.2.  Where it stays: M = 1, 3920 x 8128 6.2 -> 7.2, 1440 x 4608 5.4 -> 6.0; M = 8, 4096 x 8192 8.6 -> 9.4;
+// M = 16, 3008 x 6016 7.6 -> 7.8.
 static bool decode_split_faster(int64_t N, int64_t K, int xc, int R, int Rs, int slots) {
     const int64_t nchunks = (K + 255) / 256, blocks = (N + 16 * R - 1) / (16 * R), bands = (N + 16 * Rs - 1) / (16 * Rs);
-    const double walk = (double)((blocks + slots - 1) / slots) * (double)((nchunks + kDecWaves - 1) / kDecWaves);
-    const double other = 3.0 + walk * (0.28 + 0.143 * xc + 0.88 * R);
-    const double split = 5.5 + 1.3 * (Rs - 1) + 0.12 * xc + 0.0035 * (double)(bands * nchunks) / kDecWaves;
-    return split + 0.3 < other;
+    const double turns = (double)((blocks + slots - 1) / slots), rounds = (double)((nchunks + kDecWaves - 1) / kDecWaves);
+    const double per_wave = (double)nchunks / kDecWaves;
+    const double other = 2.9 + turns * (rounds * (0.02 + 1.1 * R) + 0.179 * xc * per_wave);
+    const double split = 5.5 + 1.3 * (Rs - 1) + 0.05 * xc + 0.0013 * (double)bands * per_wave;
+    return split + 0.46 < other;
 }
 
 // Tuning override of the row blocks per workgroup, read once per process (it also keeps the long-K kernel out).
@@ -1067,8 +1071,8 @@ static int decode_split_choice(int64_t N, int64_t K, int r, int xc, int R, int s
 }
 
 // Room for the granules where any launch of up to sixteen rows takes the long-K kernel.  The more activation copies, the
-// further that one is ahead (a copy more costs it 0.12 us, the other kernel 0.143 us for each of two or more chunks), so
-// eight copies decide.
+// further that one is ahead (a copy more costs it 0.05 us, the other kernel 0.179 us for each chunk of a wave), so eight copies
+// decide.
 size_t decode_workspace_bytes(int64_t N, int64_t K, int r) {
     const size_t least = decode_workspace_min(N, K, r);
     const int cap = device_cus();

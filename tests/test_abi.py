@@ -62,7 +62,7 @@ def test_gemm_workspace_has_room_for_partial_sums_only_where_some_decode_uses_it
     for r in (0, 32):
         assert L.milo_w3lr_gemm_workspace(16, 4096, 14336, r) > state
         # more than sixteen chunks of K, but up to sixteen rows walk them in turn
-        assert L.milo_w3lr_gemm_workspace(16, 4096, 8192, r) <= state
+        assert L.milo_w3lr_gemm_workspace(16, 3008, 6016, r) <= state
         assert L.milo_w3lr_gemm_workspace(16, 7168, 6400, r) <= state
 
 

@@ -102,23 +102,45 @@ def test_decode_parts_of_t(N, K, r, M, dtype):
     assert np.linalg.norm(Y - ref) <= (8.0 if dtype == "bf16" else 1.0) * 2.0 ** -11 * np.linalg.norm(ref)
 
 
-@pytest.mark.parametrize("M,N,K,r", [
-    (16, 512, 4352, 0),         # 17 chunks: the fewest that are spread over workgroups; 34 of those
-    (9, 528, 4160, 20),         # the last chunk has 64 columns, the last workgroup's waves past the last pair have none
-    (5, 1040, 8256, 128),       # eight fragments of T, each band ends in the middle of a workgroup
-    (3, 2816, 11008, 24),       # chunks in turn (the rule's other side)
-    (16, 2816, 11008, 24),      # two row blocks per wave
-    (2, 12016, 4864, 8),        # four, and a band of three at the end
-    (1, 1024, 14336, 64), (7, 528, 65536, 16),      # three and fifteen partial sums per band
-    (4, 512, 6144, 32),         # every other band starts with a workgroup
+def _spreads(M, N, K, r, dt):
+    """Whether a decode goes to the kernel that hands partial sums over: it writes them behind the workspace's state."""
+    import torch
+    from paper_2504_02658_amd import api
+    zeros = lambda *shape: torch.zeros(shape, dtype=dt, device="cuda")
+    pw = api.PackedWeight(N, K, torch.zeros(N * K * 7 // 16, dtype=torch.uint8, device="cuda"))
+    if r:
+        pw = pw.with_compensator(zeros(N, r), zeros(r, K))
+    state = 59648                                               # MILO_WORKSPACE_STATE_BYTES
+    ws = api.new_workspace(state + (4 << 20))
+    ws[state:] = 0x55
+    api.w3lr_gemm(zeros(M, K), pw, workspace=ws)
+    assert api.workspace_status(ws) == 0
+    return bool((ws[state:] != 0x55).any())
+
+
+@pytest.mark.parametrize("M,N,K,r,spread", [
+    (16, 512, 4352, 0, True),           # 17 chunks: the fewest that are spread over workgroups; 34 of those
+    (9, 528, 4160, 20, True),           # the last chunk has 64 columns, the last workgroup's waves past the last pair have none
+    (5, 1040, 8256, 128, True),         # eight fragments of T, each band ends in the middle of a workgroup
+    (3, 2816, 11008, 24, False),        # chunks in turn (the rule's other side)
+    (16, 2816, 11008, 24, True),        # two row blocks per wave
+    (2, 12016, 4864, 8, True),          # four, and a band of three at the end
+    (1, 1024, 14336, 64, True),         # three partial sums per band
+    (7, 528, 65536, 0, True),           # fifteen
+    (7, 528, 65536, 16, False),         # T would take all sixteen fragments
+    (16, 512, 6144, 32, True),          # every other band starts with a workgroup
+    (8, 512, 4160, 0, False), (5, 752, 4160, 48, False),        # a second chunk for few waves only: not worth the hand-over
 ])
 @pytest.mark.parametrize("dtype", ["fp16", "bf16", "int3"])
-def test_decode_chunks_spread_over_workgroups(M, N, K, r, dtype):
+def test_decode_chunks_spread_over_workgroups(M, N, K, r, spread, dtype):
+    import torch
     if r == 0:
         if dtype == "fp16":
             _check_case(M, N, K, r, seed=N + K)
     elif dtype != "int3" or r <= 64:
         test_decode_parts_of_t(N, K, r, M, dtype)
+    if dtype != "int3":
+        assert _spreads(M, N, K, r, torch.bfloat16 if dtype == "bf16" else torch.float16) == spread
 
 
 def test_decode_partial_sums_on_a_shared_workspace():
