@@ -244,21 +244,28 @@ __global__ __launch_bounds__(kRouteThreads) void order_tiles_kernel(const TileDe
 // kSmallExperts experts): with a handful of tokens the two kernels above are all latency, and so is
 // the launch between them.  One workgroup routes; thread p owns pair p, thread e expert e.  The group of an expert
 // starts at the number of pairs with a smaller id, a pair's place inside it is the number of earlier pairs with
-// the same id (counted from a copy of the ids in LDS, four per read), which is the same stable order as
-// route_kernel's.  Tiles are written straight into the final list: tiles of experts with a rank
-// above 32 first, then the others, in expert order (order_tiles_kernel's order for tiles of one height class).
-// `items` given: the list is the weight-streaming kernel's, `n_items` slots with the expert's weights beside the rows and
-// no rows in those that stay empty, and the other workgroups of the launch clear the granules of T.
-// Latency-bound; every thread has its expert's ranks on the way before the ids arrive and no loop goes to memory:
-// 66 experts, 4 tokens 14.6 -> 6 us against a loop over the expert table by every thread.
-constexpr int kSmallPairs = 512, kSmallExperts = 512;
+// the same id, which is the same stable order as route_kernel's.  Tiles are written straight into the final list: tiles of
+// experts with a rank above 32 first, then the others, in expert order (order_tiles_kernel's order for tiles of one height
+// class).  `items` given: the list is the weight-streaming kernel's, `n_items` slots with the expert's weights beside the rows
+// and no rows in those that stay empty, and the other workgroups of the launch clear the granules of T.
+// Latency-bound; every thread has its expert's ranks on the way before the ids arrive and no loop goes to memory.
+// FEW (up to kFewPairs pairs): every thread counts from a copy of the ids in LDS, four per read.  That loop grows with the
+// pairs; more of them are counted per wave: the lanes whose ids agree in all nine bits come from one ballot per bit, the
+// lowest lane of each id writes the wave's count (nothing is added atomically), and scans over waves and experts do the rest.
+// us, all ids per thread / per wave: 2 pairs 4.1 / 5.0, 32 5.0 / 4.9, 60 6.2 / 5.3, 128 8.9 / 5.3, 512 22.0 / 5.4 (the two
+// general kernels take 12.9 for those).  In one kernel the two cost each other 0.5 us, code that is fetched and not run.
+constexpr int kSmallPairs = 512, kSmallExperts = 512, kFewPairs = 32;
+template <bool FEW>
 __global__ __launch_bounds__(kSmallPairs) void route_small_kernel(const RouteArgs a, TileDesc* __restrict__ list,
                                                                   const milo_w3lr_expert* __restrict__ experts,
                                                                   FewItem* __restrict__ items, int n_items,
                                                                   u32x4* __restrict__ granules, uint32_t granules16) {
-    __shared__ __attribute__((aligned(16))) int32_t s_id[kSmallPairs];
+    constexpr int kWaves = kSmallPairs / 64, kIdBits = 9;
+    static_assert(kSmallExperts == 1 << kIdBits && kSmallExperts == kSmallPairs, "a thread per expert, ids of kIdBits bits");
+    __shared__ __attribute__((aligned(16))) int32_t s_id[FEW ? kSmallPairs : 4];
+    __shared__ int32_t s_wave[FEW ? 1 : kWaves][kSmallExperts];     // pairs of a wave per expert, then those of the waves before it
     __shared__ int32_t s_start[kSmallExperts], s_tile0[kSmallExperts];
-    __shared__ int32_t s_hi[kSmallPairs / 64], s_lo[kSmallPairs / 64];
+    __shared__ int32_t s_hi[kWaves], s_lo[kWaves], s_cnt[kWaves];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (blockIdx.x > 0) {
         for (uint32_t i = (blockIdx.x - 1) * kSmallPairs + tid; i < granules16; i += (gridDim.x - 1) * kSmallPairs)
@@ -272,20 +279,52 @@ __global__ __launch_bounds__(kSmallPairs) void route_small_kernel(const RouteArg
     }
     const WeightDev* const ew = reinterpret_cast<const WeightDev*>(experts + (tid < a.E ? tid : 0));
     const WeightDev w0 = ew[0], w1 = ew[1], w2 = ew[2];
-    s_id[tid] = id;
-    const bool bad = __syncthreads_or(tid < a.P && id < 0) != 0;
     // pair p = tid: earlier pairs of its expert; expert e = tid: its pairs and those before its group
     int before = 0, cnt = 0, less = 0;
-#pragma unroll 4
-    for (int p = 0; p < a.P; p += 4) {
-        const int4 v4 = *reinterpret_cast<const int4*>(s_id + p);       // (entries from P on are -1)
-        const int v[4] = {v4.x, v4.y, v4.z, v4.w};
+    if constexpr (FEW) {
+        s_id[tid] = id;
+    } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            before += v[i] == id && p + i < tid;
-            cnt += v[i] == tid;
-            less += (uint32_t)v[i] < (uint32_t)tid;
+        for (int w = 0; w < kWaves; ++w) s_wave[w][tid] = 0;
+    }
+    const bool bad = __syncthreads_or(tid < a.P && id < 0) != 0;
+    if constexpr (FEW) {
+#pragma unroll 4
+        for (int p = 0; p < a.P; p += 4) {
+            const int4 v4 = *reinterpret_cast<const int4*>(s_id + p);       // (entries from P on are -1)
+            const int v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                before += v[i] == id && p + i < tid;
+                cnt += v[i] == tid;
+                less += (uint32_t)v[i] < (uint32_t)tid;
+            }
         }
+    } else {
+        unsigned long long same = __builtin_amdgcn_ballot_w64(id >= 0);
+#pragma unroll
+        for (int b = 0; b < kIdBits; ++b) {
+            const bool set = (id >> b & 1) != 0;
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(set);
+            same &= set ? m : ~m;
+        }
+        before = __popcll(same & ((1ull << lane) - 1ull));
+        if (id >= 0 && before == 0) s_wave[wave][id] = __popcll(same);
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const int n = s_wave[w][tid];
+            s_wave[w][tid] = cnt;
+            cnt += n;
+        }
+        less = cnt;                                         // (scanned over the wave's experts, then over the waves)
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int c = __shfl_up(less, d, 64);
+            if (lane >= d) less += c;
+        }
+        if (lane == 63) s_cnt[wave] = less;
+        less -= cnt;
     }
     // tiles of the experts before this one, those with a high rank ahead of all others
     const bool low = w0.r <= 32 && w1.r <= 32 && w2.r <= 32;
@@ -303,11 +342,16 @@ __global__ __launch_bounds__(kSmallPairs) void route_small_kernel(const RouteArg
         s_hi[wave] = hi;
         s_lo[wave] = lo;
     }
-    s_start[tid] = less;
+    if constexpr (FEW) s_start[tid] = less;
     __syncthreads();
+    if constexpr (!FEW) {
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) less += w < wave ? s_cnt[w] : 0;
+        s_start[tid] = less;
+    }
     int total_hi = 0, total = 0;
 #pragma unroll
-    for (int w = 0; w < kSmallPairs / 64; ++w) {
+    for (int w = 0; w < kWaves; ++w) {
         if (w < wave) {
             hi += s_hi[w];
             lo += s_lo[w];
@@ -329,8 +373,9 @@ __global__ __launch_bounds__(kSmallPairs) void route_small_kernel(const RouteArg
     }
     if (items)
         for (int i = total + tid; i < n_items; i += kSmallPairs) items[i].rows = 0;
-    if (items) __syncthreads();
+    if (!FEW || items) __syncthreads();
     if (id >= 0) {
+        if constexpr (!FEW) before += s_wave[wave][id];
         const int pos = s_start[id] + before, token = tid / a.topk;
         a.sorted[pos] = tid;
         if (items) items[s_tile0[id] + before / kFewRows].token[before % kFewRows] = token;
@@ -553,8 +598,8 @@ static int launch_combine(const void* O, bool wide, int splits, int64_t split_st
                      : (bf ? combine_kernel<true, false> : combine_kernel<false, false>);
     for (int64_t t0 = 0; t0 < T; t0 += 65535) {         // (grid.y limit)
         const int64_t nt = (T - t0) < 65535 ? (T - t0) : 65535;
-        kern<<<dim3(gx, (unsigned)nt), dim3(256), 0, stream>>>(static_cast<const char*>(O) + t0 * topk * H * (wide ? 4 : 2), splits, split_stride, ids + t0 * topk, E, topk, nt, H,
-                                                               Y + t0 * H);
+        kern<<<dim3(gx, (unsigned)nt), dim3(256), 0, stream>>>(static_cast<const char*>(O) + t0 * topk * H * (wide ? 4 : 2), splits,
+                                                               split_stride, ids + t0 * topk, E, topk, nt, H, Y + t0 * H);
     }
     return launch_status();
 }
@@ -663,7 +708,8 @@ extern "C" int milo_moe_w3lr_forward_flags(const milo_half* X, int64_t T, int64_
         u32x4* granules = reinterpret_cast<u32x4*>(ws + L.off_granules);
         ra.tiles = nullptr; ra.flags = nullptr; ra.n_flags = 0; ra.max_tiles = 0;
         const size_t clear_blocks = (L.granule_bytes / 16 + 4 * kSmallPairs - 1) / (4 * kSmallPairs);
-        route_small_kernel<<<dim3(1u + (unsigned)(clear_blocks < 128 ? clear_blocks : 128)), dim3(kSmallPairs), 0, stream>>>(
+        const auto route = P <= kFewPairs ? route_small_kernel<true> : route_small_kernel<false>;
+        route<<<dim3(1u + (unsigned)(clear_blocks < 128 ? clear_blocks : 128)), dim3(kSmallPairs), 0, stream>>>(
             ra, nullptr, experts, items, L.few_items, granules, (uint32_t)(L.granule_bytes / 16));
         st = launch_status();
         if (st != MILO_OK) return st;
@@ -696,7 +742,8 @@ extern "C" int milo_moe_w3lr_forward_flags(const milo_half* X, int64_t T, int64_
     ra.flags = flags; ra.n_flags = (int32_t)(2 * 4 * L.max_tiles32);
     ra.max_tiles = L.max_tiles;
     if (P <= kSmallPairs && E <= kSmallExperts && L.bm == 32) {
-        route_small_kernel<<<dim3(1), dim3(kSmallPairs), 0, stream>>>(ra, tiles, experts, nullptr, 0, nullptr, 0u);
+        const auto route = P <= kFewPairs ? route_small_kernel<true> : route_small_kernel<false>;
+        route<<<dim3(1), dim3(kSmallPairs), 0, stream>>>(ra, tiles, experts, nullptr, 0, nullptr, 0u);
         st = launch_status();
         if (st != MILO_OK) return st;
     } else {

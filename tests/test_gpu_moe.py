@@ -305,6 +305,35 @@ def test_routing_of_small_batches_matches_the_general_kernels():
     assert np.array_equal(general[:128].view(np.uint16), small.view(np.uint16))
 
 
+@pytest.mark.parametrize("rank", [8, 136])
+@pytest.mark.parametrize("E,topk,T", [(5, 2, 16), (5, 2, 17), (5, 1, 33), (3, 3, 21), (3, 3, 22), (200, 4, 127), (200, 4, 128), (511, 1, 512), (512, 8, 64)])
+def test_single_launch_routing_at_its_edges(E, topk, T, rank):
+    # 32 and 33 pairs (one count per thread, one per wave), 63 to 66 (one wave and a second), 508 and 512, the last expert ids;
+    # streamed items and tiles: each row against the row alone, which is routed by itself
+    import torch
+    from paper_2504_02658_amd import api
+    H, F = 192, 192
+    g = torch.Generator(device="cuda")
+    g.manual_seed(E + T + rank)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    kinds = [tuple(api.pack_w3(randn(n, k) * 0.05).with_compensator((randn(n, r) * 0.1).half(), (randn(r, k) * 0.1).half())
+                   for n, k in ((F, H), (F, H), (H, F))) for r in (8, rank, 40)]
+    layer = api.MoELayer([kinds[(7 * e) % 3] for e in range(E)], H, F)
+    X = randn(T, H).half()
+    ids = torch.rand((T, E), generator=g, device="cuda").argsort(dim=1)[:, :topk].to(torch.int32).contiguous()
+    ids[0, 0] = E - 1                                       # (may name an expert twice: both rows count)
+    ids[T - 1, topk - 1] = 0
+    gates = torch.rand((T, topk), generator=g, device="cuda")
+    Y = layer.forward(X, ids, gates).clone()
+    assert layer.routing_status() == 0
+    rows = layer.last_workspace.view(torch.int32)[1].item()
+    n = np.bincount(ids.cpu().numpy().ravel(), minlength=E)
+    assert rows == int(np.sum((n + (31 if rank > 128 else 15)) // (32 if rank > 128 else 16)))
+    for t in range(0, T, 1 if T < 64 else 29):
+        alone = layer.forward(X[t:t + 1].clone(), ids[t:t + 1].clone(), gates[t:t + 1].clone())
+        assert torch.equal(alone[0], Y[t]), t
+
+
 def test_single_launch_routing_of_many_tiles():
     # 512 pairs over 220 experts: more than 128 tiles, whose list the tiled kernel reads as eight ranges
     _check(wl.MoECase("many_small", T=128, H=256, F=192, E=220, topk=4, seed=56, rank_choices=(8, 136), zipf_s=0.4), rows=32)
