@@ -61,7 +61,8 @@ enum milo_status {
                                 array the kernels address with 32-bit offsets), bad top-k / E */
     MILO_ERR_GROUP = 3,      /* group_size != 64                                            */
     MILO_ERR_RANK = 4,       /* r < 0, r > min(N, K), or r > 0 with U or V NULL             */
-    MILO_ERR_WORKSPACE = 5,  /* workspace NULL or smaller than the *_workspace() size       */
+    MILO_ERR_WORKSPACE = 5,  /* workspace NULL or too small; the *_workspace() size always suffices,
+                                some calls accept less (see there)                          */
     MILO_ERR_ROUTING = 6,    /* an expert id outside 0..E-1 was met (reported after the run)*/
     MILO_ERR_ALIGN = 7,      /* a pointer is not 16-byte aligned                            */
     MILO_ERR_WAIT = 8,       /* a bounded wait inside a kernel gave up (see milo_workspace_status) */
@@ -122,10 +123,11 @@ int milo_dequant_w3(const void* q3, int64_t N, int64_t K, milo_half* W_dq, void*
  * HIP graph and replay), for any mix of shapes and ranks that the workspace is large enough for.
  * That holds while nothing else writes to the workspace: a GEMM workspace keeps state from call to
  * call in its first MILO_WORKSPACE_STATE_BYTES (flags that the kernels leave at zero, counters that
- * grow with every launch), so between calls those bytes are not scratch for the caller, and a
+ * grow with every launch, those of rank 0 at decode included), so between calls those bytes are not scratch for the caller, and a
  * workspace that milo_moe_w3lr_forward has used serves milo_w3lr_gemm only after another
  * milo_workspace_init (and the other way round).  Without it later calls wait until their bound and
- * report MILO_ERR_WAIT, call after call.  What lies behind those bytes may hold anything.
+ * report MILO_ERR_WAIT, call after call.  What lies behind those bytes may hold anything (so for a GEMM
+ * workspace that serves one call it is enough to prepare that many).
  * Errors: NULL, WORKSPACE (fewer than 256 bytes), ALIGN, HIP.
  */
 #define MILO_WORKSPACE_STATE_BYTES 59648u
@@ -134,10 +136,11 @@ int milo_workspace_init(void* workspace, size_t workspace_bytes, void* stream);
 /*
  * Waits for `stream`, then reports whether a kernel that used this workspace (of milo_w3lr_gemm or
  * of milo_moe_w3lr_forward) gave up a wait.  The kernels hand T = X V^T from the workgroups that form
- * it to the ones that use it inside one launch; the consumers' wait is bounded (about a second), and
- * one that runs out sets a word in the control block and goes on with whatever T holds, so the
+ * it to the ones that use it inside one launch, and at M <= 16 with K beyond 4096 (any rank, also 0) partial
+ * sums over K from workgroup to workgroup; the consumers' wait is bounded (about a second), and
+ * one that runs out sets a word in the control block and goes on with whatever is there, so the
  * output of that call is not to be used.  This needs the whole launch to make progress together: the
- * launches are sized for an otherwise idle device, and the producers have the lowest workgroup ids,
+ * launches are sized for an otherwise idle device, and a workgroup only waits for ones with lower ids,
  * which the hardware dispatches first; a device kept busy by other streams' kernels can break that.
  * MILO_ERR_WAIT: discard the outputs written since the last MILO_OK and call milo_workspace_init
  * before the next use (a GEMM workspace keeps the word until then; the MoE call clears its own at
@@ -151,9 +154,12 @@ int milo_workspace_status(const void* workspace, void* stream);
  *   X [M x K] fp16;  q3 as written by milo_pack_w3 (its zero-points may be any finite fp16,
  *   integer or not);  U [N x r], V [r x K] fp16 row-major, ignored when r == 0;  Y [M x N] fp16.
  *   workspace: at least milo_w3lr_gemm_workspace(M, N, K, r) bytes of device memory, prepared
- *   once with milo_workspace_init (see there for what has to keep its value between calls).  (At M <= 16 and a K
- *   beyond 4096 that includes room for partial sums; a smaller workspace that holds the state is accepted, at less speed.)  Calls that
+ *   once with milo_workspace_init (see there for what has to keep its value between calls).  The size for
+ *   some M also serves every M <= 16 of the same weight.  Calls that
  *   share a workspace must be ordered on one stream (concurrent calls would race on it).
+ *   At M <= 16 with K beyond 4096 the size may include room for partial sums over K.  A workspace without that room, but with
+ *   the state, is accepted: the sums are then formed by another kernel, slower and in another order, so the result
+ *   may differ in its last bits.  On workspaces of at least the size asked for, results do not depend on the size.
  * M <= 16 takes the weight-streaming decode kernel (a single launch that also forms X V^T),
  * larger M the tiled MFMA kernel (which also forms X V^T inside the launch; when the problem has
  * too few tiles to fill the device it splits K over workgroups and a second small kernel adds the
@@ -250,7 +256,8 @@ int milo_compress_w3lr(const float* W, int64_t N, int64_t K, const milo_compress
 /*
  * milo_w3lr_gemm for callers that cannot allocate and cannot bring a workspace: code that runs
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * result and errors as milo_w3lr_gemm, bit for bit, without `workspace`: the scratch memory is a
+ * result and errors as milo_w3lr_gemm on a workspace of at least milo_w3lr_gemm_workspace() bytes, bit for
+ * bit, without `workspace`: the scratch memory is a
  * fixed array of MILO_STATIC_SCRATCH_BYTES inside the library's device image (every GPU the library
  * runs on holds its copy until the process ends; the array has room for a fixed head of the workspace
  * on top).  The call allocates nothing; a problem that needs more than MILO_STATIC_SCRATCH_BYTES
@@ -327,13 +334,15 @@ int milo_moe_w3lr_check_experts_flags(const milo_w3lr_expert* experts, int E, in
  *   topk_weights [T x topk] fp32
  *   Y            [T x H] fp16
  *   workspace    at least milo_moe_w3lr_workspace(T, H, F, E, topk, r_max) bytes, prepared once with
- *                milo_workspace_init (a batch of a few rows per expert is also accepted with
- *                the fewer that the kernels of larger batches take, at less speed); not shared with milo_w3lr_gemm (see milo_workspace_init)
+ *                milo_workspace_init; not shared with milo_w3lr_gemm (see milo_workspace_init).  A batch of a
+ *                few rows per expert is also accepted with the fewer bytes that the kernels of larger
+ *                batches take: those then run, slower and with their rounding of the per-pair outputs
  * An id outside 0..E-1 contributes nothing and raises a flag that
  * milo_moe_w3lr_routing_status() reports; an expert with no tokens is legal.
  * Each routed pair's weighted expert output is kept as fp16 (per K split of the down projection,
- * when that is split) or, for batches of a few rows per expert, as fp32; the combine adds a token's slots (and splits) in a fixed order in fp32 and
- * rounds once, so two runs give bit-identical results.
+ * when that is split) or, for batches of a few rows per expert, as fp32; the combine adds a token's slots
+ * (and splits) in a fixed order in fp32 and rounds once, so two runs give bit-identical results, on any
+ * workspaces of at least the size asked for.
  * Errors: NULL, SHAPE, RANK, WORKSPACE, ALIGN, HIP.
  */
 size_t milo_moe_w3lr_workspace(int64_t T, int64_t H, int64_t F, int E, int topk, int r_max);

@@ -394,6 +394,8 @@ def test_workspace_of_a_larger_batch_serves_smaller_ones():
     for workspace in (ws, None, ws):
         assert_close(layer.forward(*args, workspace=workspace).cpu().numpy(), ref, "workspace of a larger batch")
         assert layer.routing_status() == 0
+    # (on any workspace of at least the size asked for the bits are the same)
+    assert torch.equal(layer.forward(*args), layer.forward(*args, workspace=api.new_workspace(layer.workspace_bytes(260, 2))))
     with pytest.raises(api.MiloError):
         layer.forward(*args, workspace=api.new_workspace(65536))
 
