@@ -10,10 +10,11 @@
 //
 // What bounds it: HBM and the vector units together (125 vector instructions convert 1.8 KB).  Every weight is read once
 // per sixteen rows of its expert.  Four small workgroups fit on a CU, so that while one starts (two round trips to
-// memory) or ends, others convert; with eight waves each, two on a CU, they did so in step: the gate/up launch of eight
-// experts of 14336 x 4096 at 16 tokens, 411 MB, took 93 us against 84 (4.9 TB/s; loads alone reach 7.0).  The tiled kernel, which took
-// such batches before, walks 32-row tiles with 128 columns a step and two steps of requests in flight: 105 us there, and
-// 39.5 against 17 at 4 tokens of a layer of 66 experts of 1408 x 2048.
+// memory) or ends, others convert; with eight waves each, two on a CU, they do so in step.  The gate/up launch of eight
+// experts of 14336 x 4096 at 16 tokens, 411 MB, us on average and at least: 86 / 80 against 92 / 85 with eight waves (the
+// down launch, whose waves hold one weight, 49 / 46 against 48 / 45).  Its loads alone take 68 / 66 (6.1 TB/s), and the vector
+// units are busy for 71 % of it.  The tiled kernel, which took such batches before, walks 32-row tiles with 128 columns a step
+// and two steps of requests in flight: 102 / 97 there, and 38 against 16 at 4 tokens of a layer of 66 experts of 1408 x 2048.
 //
 // Low-rank term.  T = X V^T of an item is formed inside the launch by the first workgroups of the grid, one per block of
 // 16 ranks (and, in the down projection, K part of 16 chunks), and handed over in tagged

@@ -464,7 +464,8 @@ struct MoeLayout {
     size_t off_items, off_granules, granule_bytes;
 };
 
-// Tiles of b rows that P evenly spread pairs give E experts, on average: sum over the row counts n of ceil(n / b), n Poisson.
+// Tiles of b rows that P evenly spread pairs give E experts, on average: sum over the row counts n of ceil(n / b), n Poisson
+// and cut at P (which for one to three experts takes up to half off both numbers that moe_takes_few compares).
 static double expected_tiles(int64_t P, int E, int b) {
     const double mean = (double)P / E;
     double p = exp(-mean), tiles = 0.0;
@@ -479,11 +480,16 @@ static bool moe_few_possible(int64_t H, int64_t F, int E, int r_max) {
     return E <= kSmallExperts && r_max <= kFewMaxRank && few_t_parts(H) <= kFewMaxParts && few_t_parts(F) <= kFewMaxParts;
 }
 
-// Whether the weight-streaming kernel takes a batch (else the tiled one).  Both are measured per layer in us: the streaming one takes
+// Whether the weight-streaming kernel takes a batch (else the tiled one).  Estimates per layer in us: the streaming one takes
 // 14 + 0.17 per MB of weight it reads, once per item of 16 rows, + 0.007 per workgroup; the tiled one 45 + 0.19 per MB, once per
-// 32-row tile.  So it is the number of rows per expert that decides, later where the weights are small:
-// 14336 x 4096, 8 experts, 12 rows each 145 against 164, 16 rows 221 / 168; 3584 x 1024, 16 experts, 16 rows 58 / 66, 24 rows 76 / 73;
-// 1408 x 2048, 64 + 2 experts, 0.5 rows 34 / 63, 8 rows 94 / 103; 1024 x 512, 8 experts, 24 rows 28 / 42.
+// 32-row tile.  So it is the number of rows per expert that decides, later where the weights are small.  Measured, streamed /
+// tiled: 14336 x 4096, 8 experts, 4 rows each 133 / 168, 12 rows 162 / 176, 16 rows 204 / 181; 3584 x 1024, 16 experts, 16 rows
+// 48 / 51, 24 rows 61 / 52; 1408 x 2048, 64 + 2 experts, 0.5 rows 41 / 76, 8 rows 90 / 107; 1024 x 512, 8 experts, 24 rows 21 / 38.
+// The counts are those of evenly spread pairs.  Popular experts need more items for the tiles they save, but unpopular ones
+// neither: with popularity falling as rank^-1.2 the first two layers take 118 / 149, 194 / 198, 220 / 208 and 51 / 63, 62 / 66.
+// Of 2875 points measured (158 shapes, both kinds of routing) 2163 are streamed; 19 of them are slower than tiled, by 2 to
+// 12 % and in one layer by 21 % (two experts of 13120 x 2112, each with 25 rows: two items for one tile, 60 / 50), and 409 of the
+// others would be faster streamed.
 static bool moe_takes_few(int64_t T, int64_t H, int64_t F, int E, int topk, int r_max) {
     const int64_t P = T * topk;
     if (P > kSmallPairs || !moe_few_possible(H, F, E, r_max)) return false;
