@@ -161,8 +161,9 @@ int milo_workspace_status(const void* workspace, void* stream);
  *   the state, is accepted: the sums are then formed by another kernel, slower and in another order, so the result
  *   may differ in its last bits.  On workspaces of at least the size asked for, results do not depend on the size.
  * M <= 16 takes the weight-streaming decode kernel (a single launch that also forms X V^T),
- * larger M the tiled MFMA kernel (which also forms X V^T inside the launch; when the problem has
- * too few tiles to fill the device it splits K over workgroups and a second small kernel adds the
+ * larger M, where the tiled kernel's tiles would not fill the device, a kernel whose workgroups own narrow
+ * bands over the whole K (a single launch too), and else the tiled MFMA kernel (which also forms X V^T
+ * inside the launch; when it has too few tiles it splits K over workgroups and a second small kernel adds the
  * fp32 partial sums in a fixed order, so the result is rounded once and two runs agree bit for bit).
  * The workspace size depends on the device the call is made on (the K split follows its number of
  * compute units): query it with that device current.

@@ -54,18 +54,20 @@ bool gemm_takes_decode(int64_t M, int64_t N, int64_t K, int r) {
 static int64_t rank_pad(int r) { return ((int64_t)r + 15) / 16 * 16; }
 
 // Tile height (in blocks of 32 rows) and K splits of the tiled kernel for an [M x N x K] problem.
-static int gemm_mb(int64_t M) {
-    // tile height / 32; measured on N = 14336, K = 4096: up to 64 rows the shallow tile wins, up to
-    // a few hundred rows two 64-row tiles beat one tall one
-    int mb = M <= 64 ? 1 : (M <= 384 ? 2 : 4);
+static int gemm_mb_override() {
     // tuning override, read once per process so that the workspace query and the call agree
-    static const int mb_override = [] {
+    static const int mb = [] {
         const char* e = getenv("MILO_GEMM_MB");
         const int v = e ? atoi(e) : 0;
         return (v == 1 || v == 2 || v == 4) ? v : 0;
     }();
-    if (mb_override) mb = mb_override;
     return mb;
+}
+static int gemm_mb(int64_t M) {
+    // tile height / 32; measured on N = 14336, K = 4096: up to 64 rows the shallow tile wins, up to
+    // a few hundred rows two 64-row tiles beat one tall one
+    const int mb = M <= 64 ? 1 : (M <= 384 ? 2 : 4);
+    return gemm_mb_override() ? gemm_mb_override() : mb;
 }
 static int gemm_splits(int64_t M, int64_t N, int64_t K, int r) {
     const int bm = 32 * gemm_mb(M);
@@ -201,6 +203,20 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     if ((uint64_t)M * K * 2 >= 0x80000000ull || ((uint64_t)r + 256) * K * 2 >= 0xFFFFFFF0ull ||
         (uint64_t)(parts > 0 ? parts : 1) * M * ldt * 4 >= 0xFFFFFFF0ull || (N & 3) != 0)
         return MILO_ERR_SHAPE;                                          // 32-bit offsets in the kernel
+    // Batches whose tiles do not fill the chip: one launch without K splits.  Its T needs no more scratch than the tiled one's
+    // (no more parts, and no 16-bit copy), so every workspace that is accepted serves either.
+    MidPlan mid;
+    if (!gemm_mb_override() && plan_mid(M, N, K, r, (flags & MILO_LR_INT3) != 0, mb, splits, r > 0 ? tiled_t_parts(K) : 0, &mid)) {
+        MidArgs ma;
+        ma.X = reinterpret_cast<const f16*>(X); ma.Y = reinterpret_cast<f16*>(Y);
+        ma.M = (uint32_t)M; ma.N = (uint32_t)N; ma.K = (uint32_t)K; ma.x_bytes = (uint32_t)(M * K * 2);
+        ma.w = w; ma.ldt = (uint32_t)ldt;
+        ma.T = reinterpret_cast<float*>(T); ma.t_bytes = (uint32_t)(mid.t_parts * M * ldt * 4);
+        ma.epoch = reinterpret_cast<unsigned long long*>(ws + kGemmCountersAt);
+        ma.ready = reinterpret_cast<unsigned long long*>(ws + kGemmGranulesAt) + kDecSplitFrags * 256;
+        ma.status = ctrl + 3;
+        return launch_mid(ma, mid, stream);
+    }
     float* Tp = reinterpret_cast<float*>(reinterpret_cast<char*>(T) + align_up((size_t)M * (size_t)ldt * 2 + 256, 256));
     float* partial = reinterpret_cast<float*>(
         reinterpret_cast<char*>(Tp) + align_up((size_t)parts * (size_t)M * (size_t)ldt * 4 + 256, 256));

@@ -178,6 +178,34 @@ struct FewArgs {
 // nw = 2: gate and up projection with SwiGLU, nw = 1: down projection (rows of X in the items' order).
 int launch_few(FewArgs a, int nw, bool bf, hipStream_t stream);
 
+// The kernel for batches that are too small for the tiled one (gemm_mid.hip).
+struct MidArgs {
+    const f16* X;               // [M x K]
+    f16* Y;                     // [M x N]
+    uint32_t M, N, K;
+    uint32_t x_bytes;           // < 2 GiB
+    WeightDev w;
+    float* T;                   // X V^T per K part, [t_parts][M x ldt] fp32, zero beyond the rank
+    uint32_t ldt;               // rank rounded up to 16
+    uint32_t t_bytes;
+    unsigned long long* epoch;  // launch counters, as in the decode kernel
+    unsigned long long* ready;  // a tagged word per worker that forms T
+    uint32_t* status;           // set non-zero if a wait gave up
+    // set by launch_mid
+    uint32_t spin_limit;
+    uint32_t once;              // non-zero: one M-tile, every weight is read once
+    uint32_t nt, rank_blocks, t_parts;          // T workers (the first workgroups): 32-row blocks x 32-rank blocks x K parts
+    uint32_t tile_rows, bands, tiles, nmain;    // workgroups of the product: bands x tiles
+};
+struct MidPlan {
+    int form;
+    int t_parts;
+};
+constexpr int kMidMaxWorkers = kDecSplitMax;        // tagged words, in the place of the last fragment of granules
+// Whether that kernel takes a problem the tiled one would run with tiles of 32 mb rows, `splits` K splits and t_parts parts of T.
+bool plan_mid(int64_t M, int64_t N, int64_t K, int r, bool lr3, int mb, int splits, int t_parts, MidPlan* p);
+int launch_mid(MidArgs a, const MidPlan& p, hipStream_t stream);
+
 size_t decode_workspace_bytes(int64_t N, int64_t K, int r);    // what a call is to bring
 size_t decode_workspace_min(int64_t N, int64_t K, int r);      // what it has to (without room for the long-K kernel's granules)
 int launch_decode(DecodeArgs a, void* workspace, size_t workspace_bytes, hipStream_t stream);

@@ -227,6 +227,45 @@ def test_tiled_shapes(N, K, r):
     _check_case(96, N, K, r, seed=N + K + r)
 
 
+@pytest.mark.parametrize("M,N,K,r", [
+    (17, 16, 64, 8), (31, 48, 128, 0), (32, 80, 192, 20), (33, 64, 1088, 33),       # one wave with work, ragged bands and chunks
+    (79, 14336, 1024, 24), (80, 14400, 1024, 16), (65, 12816, 1536, 0),             # the one tile of eighty rows
+    (81, 528, 2112, 128), (160, 1024, 4160, 48), (257, 272, 1408, 17),              # several tiles, parts of T that differ in length
+    (40, 512, 14336, 64), (700, 512, 512, 128),                                     # eight parts of T; more than 64 of its blocks
+    (64, 14352, 512, 1), (130, 8208, 704, 40), (1200, 592, 640, 8),                 # two streams per wave; the most rows
+    (48, 528, 2112, 136), (100, 512, 2112, 136),                                    # above its ranks: 32- and 64-row tiles
+])
+@pytest.mark.parametrize("dtype", ["fp16", "symmetric", "bf16", "int3"])
+def test_batches_between_decode_and_full_tiles(M, N, K, r, dtype):
+    import torch
+    from paper_2504_02658_amd import api
+    if dtype == "int3":
+        N = (N + 63) // 64 * 64
+        if r == 0 or r > 128:
+            return
+    g = torch.Generator()
+    g.manual_seed(M + N + K + r)
+    randn = lambda *shape: torch.randn(shape, generator=g)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    r = min(r, N, K)
+    X, W = randn(M, K).to(dt), (randn(N, K) * 0.02).numpy()
+    U, V = randn(N, r) * 0.1, randn(r, K) * 0.1         # a low-rank term larger than the product: its errors show
+    q, s, z = oracle.quantize_sym(W) if dtype == "symmetric" else oracle.quantize_rtn(W)
+    pw = api.pack_w3(torch.from_numpy(W).cuda(), symmetric=dtype == "symmetric")
+    Ud, Vd = U.to(dt).double().numpy(), V.to(dt).double().numpy()
+    if dtype == "int3":
+        pw = pw.with_int3_compensator(*api.pack_lr3(U.cuda(), V.cuda()), r)
+        Ud, Vd = oracle.dequantize_compensator(*oracle.quantize_compensator(U.numpy(), V.numpy()), r)
+    elif r:
+        pw = pw.with_compensator(U.to(dt).cuda(), V.to(dt).cuda())
+    ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, r))
+    Y = api.w3lr_gemm(X.cuda(), pw, workspace=ws)
+    assert torch.equal(api.w3lr_gemm(X.cuda(), pw, workspace=ws), Y) and api.workspace_status(ws) == 0
+    ref = oracle.w3lr_linear(X.double().numpy(), q, s, z, Ud, Vd)
+    # One rounding to 16 bits of each weight, of T and of the output; fp16 2^-11 each at most, bf16 2^-8, a third of that in the mean.
+    assert np.linalg.norm(Y.double().cpu().numpy() - ref) <= (8.0 if dtype == "bf16" else 1.0) * 2.0 ** -11 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("M,N,K,r", [(8, 1024, 1024, 512), (12, 528, 2112, 136), (200, 1024, 1024, 512),
                                      (96, 512, 2048, 300)])
 def test_high_rank_compensators(M, N, K, r):
