@@ -52,8 +52,11 @@ constexpr int kSmallThreads = 512;            // the one-workgroup factorization
 // an exponential per weight, three quarters of the work) only when that is above the limit (less a margin for the
 // rounding of the power).  The sums keep one order (four in turn, then pairs), with or without the shrinkage: a zero-point
 // that is off by one rounding moves a code at a boundary now and then, and from there on everything that follows.
-// Bound: the vector units, five operations per weight and update.  14336 x 4096, 20 updates: 180 us, with
-// 16 lanes per group and the shrinkage always evaluated 772 us + 48 us for the scales + 71 us for a copy of W.
+// Without the shrinkage an update that returns every zero-point of the wave is a fixed point: the rest of the updates would
+// repeat it (a normal weight takes 7 to 17 of them until the last of a wave's 64 groups is there, 11 in the mean).
+// Bound: the vector units, five operations per weight and update, and HBM (W in, E out: 90 us).  14336 x 4096, 20
+// updates: 143 us (167 when all were carried out); with 16 lanes per group and the shrinkage always evaluated 772 us + 48 us
+// for the scales + 71 us for a copy of W.
 // Sum of 64 values: four in turn, then pairs.  four(k, a) gives values 4 k .. 4 k + 3; the barriers keep the scheduler from
 // forming all of them before the first addition (128 registers hold the group already).
 template <typename F>
@@ -116,14 +119,20 @@ __global__ __launch_bounds__(kRowBlockThreads, 2) void hqq_kernel(const float* _
         t[i] = div_by(t[i], sf, inv_s);
     }
     int it = 0;
+    bool settled = false;
     for (; it < iters; ++it) {
         // largest residual of the group: a rounding, or a clamp at one of its ends
         const float most = fmaxf(0.5f, fmaxf((mx + zf) - 7.0f, -(mn + zf))) * sf;
         if (__builtin_amdgcn_ballot_w64(live && !(most <= edge)) != 0ull) break;
-        zf = group_sum([&](int k, float (&v)[4]) {
+        if (!settled) {
+            const float zn = group_sum([&](int k, float (&v)[4]) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = fminf(fmaxf(__builtin_rintf(t[4 * k + i] + zf), 0.0f), 7.0f) - p[4 * k + i];
-        }) * (1.0f / 64.0f);
+                for (int i = 0; i < 4; ++i) v[i] = fminf(fmaxf(__builtin_rintf(t[4 * k + i] + zf), 0.0f), 7.0f) - p[4 * k + i];
+            }) * (1.0f / 64.0f);
+            // an update that gives every group of the wave its zero-point back, bit for bit, is the last one that does anything
+            settled = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(uint32_t, zn) != __builtin_bit_cast(uint32_t, zf)) == 0ull;
+            zf = zn;
+        }
         beta *= kappa;
         edge *= edge_step;
     }
