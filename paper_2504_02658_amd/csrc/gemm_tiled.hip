@@ -63,7 +63,6 @@ __device__ __forceinline__ int64_t input_row(const RowSpace& rs, int64_t R) {
     return rs.x_rows ? (int64_t)rs.x_rows[R] : R;
 }
 
-__device__ __forceinline__ float silu(float a) { return a / (1.0f + __expf(-a)); }
 
 typedef __attribute__((address_space(3))) void* LdsPtr;
 // Offset that lies outside every activation buffer (they are kept below 2 GiB) and stays outside
