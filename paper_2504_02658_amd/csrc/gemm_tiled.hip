@@ -155,7 +155,7 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
             rank0[s] = MBT != MB ? ((NW == 1) ? 32 * s : 0) : pass0 + ((NW == 1) ? 64 * wave + 32 * s : 32 * wave);
             active[s] = rank0[s] < w.r && (MBT == MB || wave < MB);
             vb[s] = make_rsrc(w.V, (uint64_t)(w.r > 0 ? w.r : 0) * (uint64_t)K * 2u);
-            voff[s] = active[s] ? (uint32_t)(((int64_t)(rank0[s] + i32) * K + 64 * h) * 2) : kOobOffset;
+            voff[s] = active[s] ? (uint32_t)(((int64_t)(rank0[s] + i32) * K + 8 * h) * 2) : kOobOffset;
         }
         f32x16 acc[2][MBT];
 #pragma unroll
@@ -166,11 +166,11 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 for (int v = 0; v < 16; ++v) acc[s][mb][v] = 0.0f;
         // one step of the product: A fragments a0, a1 (streams 0, 1) against the B fragments of this
         // wave's row blocks; xs points at row i32 of block 0 in the stage
-        auto mfma_step = [&](const unsigned char* xs, int sx, int t, f16x8 a0, f16x8 a1) {
+        auto mfma_step = [&](const unsigned char* xs, int sx, int seg, f16x8 a0, f16x8 a1) {
 #pragma unroll
             for (int mb = 0; mb < MBT; ++mb) {
                 const f16x8 b = __builtin_bit_cast(
-                    f16x8, *reinterpret_cast<const u32x4*>(xs + (blk0 + mb) * 32 * 256 + (((8 * h + t) ^ sx) << 4)));
+                    f16x8, *reinterpret_cast<const u32x4*>(xs + (blk0 + mb) * 32 * 256 + ((seg ^ sx) << 4)));
                 if (BF) {       // (bf16 activations: V is bf16 as well, same bits in the fragments)
                     if (active[0])
                         acc[0][mb] = mfma32_bf16(__builtin_bit_cast(bf16x8, a0), __builtin_bit_cast(bf16x8, b), acc[0][mb]);
@@ -219,16 +219,61 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 const int sx = i32 & 15;
                 if (active[0] || active[1]) {
                     dequant_units2_steps<true>(cur[0], cur[1],
-                                               [&](int t, f16x8 a0, f16x8 a1) { mfma_step(xs, sx, t, a0, a1); });
+                                               [&](int t, f16x8 a0, f16x8 a1) { mfma_step(xs, sx, 8 * h + t, a0, a1); });
                 }
                 cur[0] = nxt[0];
                 cur[1] = nxt[1];
             }
+        } else if constexpr (MBT != MB) {
+            // Ranks up to 32: all waves need all of V, so a chunk of it goes through LDS like the activations (per weight [rank][256
+            // bytes], the same swizzle), copied once by whole 256-byte rows, and from there into registers; a second barrier
+            // frees the area for the next chunk.  Read as fragments from memory, 16 bytes of 64 different lines per instruction and
+            // by every wave again, it kept the CU's address path busy for 2.4 us per chunk, also for the workgroup beside.
+            unsigned char* const vlds = smem + 2 * STAGE;
+            auto issue_v = [&](int c) {
+                const bool last_half = ktail && c == nchunks - 1;
+#pragma unroll
+                for (int n = 0; n < 2 * NW; ++n) {
+                    const int s = n >> 1, j = wave + 4 * (n & 1);           // rows 4 j .. 4 j + 3 of weight s
+                    if (4 * j >= ((ti.w[s].r + 15) & ~15)) continue;        // (ranks from the next multiple of 16 on: nobody looks)
+                    const int row = 4 * j + (lane >> 4), seg = (lane & 15) ^ (row & 15);
+                    const uint32_t off = last_half && seg >= 8 ? kOobOffset : (uint32_t)row * (uint32_t)(K * 2) + (uint32_t)c * 256u + (uint32_t)(seg * 16);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(vb[s], (LdsPtr)(vlds + s * 8192 + j * 1024), 16, off, 0, 0, 0);
+                }
+            };
+            __syncthreads();            // a previous pass is done with the stages
+            if (c_lo < c_hi) {
+                issue_x(c_lo);
+                issue_v(c_lo);
+            }
+            for (int c = c_lo; c < c_hi; ++c) {
+                wait_vmem();
+                __syncthreads();
+                f16x8 va[2][8];
+                const int sx = i32 & 15;
+#pragma unroll
+                for (int s = 0; s < NW; ++s)
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        va[s][t] = __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(vlds + s * 8192 + i32 * 256 + (((8 * h + t) ^ sx) << 4)));
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (c + 1 < c_hi) {
+                    issue_x(c + 1);
+                    issue_v(c + 1);
+                }
+                const unsigned char* xs = smem + (c & 1) * STAGE + i32 * 256;
+                if (active[0] || active[1]) {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) mfma_step(xs, sx, 8 * h + t, va[0][t], va[NW - 1][t]);
+                }
+            }
         } else {
-            // V fragment of step t of chunk c; out of range (inactive stream, ragged K tail) reads zero
+            // V fragment of step t of chunk c, 16 neighbouring columns of 32 rows; out of range (inactive stream, ragged K
+            // tail) reads zero
             auto load_v = [&](int c, int s, int t) -> u32x4 {
-                const bool out = !active[s] || c >= c_hi || (ktail && c == nchunks - 1 && h == 1);
-                return buf_load16(vb[s], out ? kOobOffset : voff[s] + (uint32_t)c * 256u + 16u * t);
+                const bool out = !active[s] || c >= c_hi || (ktail && c == nchunks - 1 && t >= 4);
+                return buf_load16(vb[s], out ? kOobOffset : voff[s] + (uint32_t)c * 256u + 32u * t);
             };
             u32x4 va[2][8];
             __syncthreads();            // a previous pass is done with the stages
@@ -252,7 +297,7 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 if (active[0] || active[1]) {
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
-                        mfma_step(xs, sx, t, __builtin_bit_cast(f16x8, va[0][t]), __builtin_bit_cast(f16x8, va[1][t]));
+                        mfma_step(xs, sx, 2 * t + h, __builtin_bit_cast(f16x8, va[0][t]), __builtin_bit_cast(f16x8, va[1][t]));
                         // the registers of this step are free again: fetch the next chunk's fragment into them
                         va[0][t] = load_v(c + 1, 0, t);
                         va[1][t] = load_v(c + 1, 1, t);
@@ -304,7 +349,11 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
         last = atomicAdd(a.flags + 4 * by, 1u) == (uint32_t)a.t_parts - 1u;
         if (a.t_dist) wait_flag(a.flags + 4 * by, (uint32_t)a.t_parts, a.flags_status);
     }
-    if (!__syncthreads_or(last) && !a.t_dist) return;
+    // (through the dead stages: the reduction built into a barrier would take LDS of its own, and two workgroups with all of a
+    // CU's LDS between them would not fit beside each other any more)
+    if (tid == 0) *reinterpret_cast<volatile int*>(smem) = last;
+    __syncthreads();
+    if (!*reinterpret_cast<volatile int*>(smem) && !a.t_dist) return;
 #pragma unroll
     for (int s = 0; s < NW; ++s) {
         const WeightDev& w = ti.w[s];
@@ -876,7 +925,9 @@ static int launch_one(const TiledArgs& a, dim3 grid, hipStream_t stream) {
     constexpr int lds_stages = (MB == 4 ? 2 : kTiledStages) * 32 * MB * 256;
     // room for the U array of an INT3 compensator: 256 band features x (pad16(rank) + 8) fp16
     const int lds_u = a.lr3_rank > 0 ? 256 * (((a.lr3_rank + 15) & ~15) + 8) * 2 : 0;
-    const int lds = lds_u > lds_stages ? lds_u : lds_stages;
+    // the workgroups that form T: two stages, and a chunk of V of up to 32 ranks of two weights
+    const int lds_t = a.v_tiles > 0 && MB > 1 ? 2 * 32 * MB * 256 + 16 * 1024 : 0;
+    const int lds_x = lds_t > lds_stages ? lds_t : lds_stages, lds = lds_u > lds_x ? lds_u : lds_x;
     static bool raised[64] = {false};
     if (lds > 64 * 1024) {
         int dev = 0;
