@@ -39,108 +39,126 @@ struct RouteArgs {
 };
 
 // One workgroup per expert; no workgroup depends on another one, so a single launch suffices.
-// A thread owns a contiguous range of the pairs and counts the ids equal to its expert and the
-// ids below it: the stable position of a pair inside its expert's group is the number of matches
-// in the threads before it (one scan over the workgroup) plus the matches before it in its own
-// range, and the group starts at the number of ids below the expert.  No histogram over all
-// experts is needed (LDS atomics of a whole workgroup on the few popular experts serialize
-// badly): expert e places its tiles from slot floor(start_e / bm) + e of the tile list, which
-// never overlaps the next expert's first slot, and marks the slots up to there as empty.
+// A wave owns a contiguous range of the pairs, 256 of them per step (a lane four neighbours, one 16-byte load) and eight steps
+// of them in registers, and finds its expert's pairs with one ballot per lane slot: the stable position of a pair inside
+// the expert's group is the number of matches in the waves before, in the steps before and, by bit counts, in the lanes before;
+// the group starts at the number of ids below the expert.  No histogram over all experts is needed (LDS atomics of a
+// whole workgroup on the few popular experts serialize badly): expert e places its tiles from slot floor(start_e / bm) + e of
+// the tile list, which never overlaps the next expert's first slot, and marks the slots up to there as empty.
+// Bound by latency (the loads, one exchange between the waves) and by the stores of the popular experts, 4 bytes per lane and two
+// per pair: 32768 pairs of 66 experts 14 us, 1024 of 8 7.9 (20 and 8.7 when a thread walked its range twice, with a
+// division per pair).
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(const RouteArgs a) {
-    __shared__ int32_t s_bad;
-    __shared__ int32_t wsum_eq[kRouteThreads / 64], wsum_less[kRouteThreads / 64];
+    constexpr int kWaves = kRouteThreads / 64, kHeld = 8;
+    __shared__ int32_t s_eq[kWaves], s_less[kWaves], s_bad[kWaves];
 
-    const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid == 0) s_bad = 0;
-    __syncthreads();
-
-    // a thread's range: a multiple of 16 pairs, read 16 at a time with four 16-byte loads in flight
-    // (one id per load would pay the memory latency once per pair)
-    const int per = ((a.P + kRouteThreads - 1) / kRouteThreads + 15) & ~15;
-    const int lo = tid * per < a.P ? tid * per : a.P;
-    const int hi = lo + per < a.P ? lo + per : a.P;
-    int n_eq = 0, n_less = 0, bad = 0;
-    auto load16 = [&](int i0, int32_t (&v)[16]) {
-        if (i0 + 16 <= a.P) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int4 q = *reinterpret_cast<const int4*>(a.ids + i0 + 4 * j);
-                v[4 * j] = q.x; v[4 * j + 1] = q.y; v[4 * j + 2] = q.z; v[4 * j + 3] = q.w;
-            }
+    const int e = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int steps = (a.P + 256 * kWaves - 1) / (256 * kWaves);        // 256 pairs each
+    const int lo = wave * steps * 256 + 4 * lane;
+    // (a pair past the end reads as an id of nobody)
+    auto load = [&](int i0) {
+        int4 v = {-1, -1, -1, -1};
+        if (i0 + 4 <= a.P) {
+            v = *reinterpret_cast<const int4*>(a.ids + i0);
         } else {
+            if (i0 < a.P) v.x = a.ids[i0];
+            if (i0 + 1 < a.P) v.y = a.ids[i0 + 1];
+            if (i0 + 2 < a.P) v.z = a.ids[i0 + 2];
+        }
+        return v;
+    };
+    int n_eq = 0, n_less = 0;
+    bool bad = false;
+    auto count = [&](int i0, const int4& v) {
+        const int id[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int j = 0; j < 16; ++j) v[j] = i0 + j < a.P ? a.ids[i0 + j] : e + 1;   // padding: no match
+        for (int j = 0; j < 4; ++j) {
+            n_eq += __popcll(__builtin_amdgcn_ballot_w64(id[j] == e));
+            n_less += (uint32_t)id[j] < (uint32_t)e;
+        }
+        if (e == 0) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bad = bad || ((uint32_t)id[j] >= (uint32_t)a.E && i0 + j < a.P);
         }
     };
-    for (int i0 = lo; i0 < hi; i0 += 16) {
-        int32_t v[16];
-        load16(i0, v);
+    int4 held[kHeld];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if (i0 + j >= hi) break;
-            const int id = v[j];
-            if (id >= 0 && id < a.E) {
-                n_eq += id == e;
-                n_less += id < e;
-            } else {
-                bad = 1;
-            }
-        }
+    for (int s = 0; s < kHeld; ++s)
+        if (s < steps) held[s] = load(lo + 256 * s);
+#pragma unroll
+    for (int s = 0; s < kHeld; ++s)
+        if (s < steps) count(lo + 256 * s, held[s]);
+    for (int s = kHeld; s < steps; ++s) count(lo + 256 * s, load(lo + 256 * s));
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) n_less += __shfl_xor(n_less, d, 64);
+    const bool any_bad = __builtin_amdgcn_ballot_w64(bad) != 0ull;
+    if (lane == 0) {
+        s_eq[wave] = n_eq;
+        s_less[wave] = n_less;
+        s_bad[wave] = any_bad;
     }
-    // inclusive scan of n_eq within the wave, wave totals to LDS
-    int scan = n_eq;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int v = __shfl_up(scan, d, 64);
-        if (lane >= d) scan += v;
-    }
-    int less = n_less;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) less += __shfl_xor(less, d, 64);
-    if (lane == 63) wsum_eq[wave] = scan;
-    if (lane == 0) wsum_less[wave] = less;
     __syncthreads();
-    int before = 0, off_e = 0, count = 0;
-    for (int w = 0; w < kRouteThreads / 64; ++w) {
-        if (w < wave) before += wsum_eq[w];
-        count += wsum_eq[w];
-        off_e += wsum_less[w];
+    int before = 0, off_e = 0, count_e = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        before += w < wave ? s_eq[w] : 0;
+        count_e += s_eq[w];
+        off_e += s_less[w];
     }
     // stable scatter of the pairs routed to expert e
-    int pos = off_e + before + scan - n_eq;
-    if (n_eq) {
-        for (int i0 = lo; i0 < hi; i0 += 16) {
-            int32_t v[16];
-            load16(i0, v);
+    int at = off_e + before;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    // pair / topk from the upper half of a product: short by at most one for pairs below 2^30
+    const uint32_t magic = a.topk > 1 ? (uint32_t)((1ull << 32) / (uint32_t)a.topk) : 0xffffffffu;
+    auto token_of = [&](int i) {
+        const uint32_t t = __umulhi((uint32_t)i, magic);
+        return (int)(t + ((uint32_t)i - t * (uint32_t)a.topk >= (uint32_t)a.topk ? 1u : 0u));
+    };
+    auto scatter = [&](int i0, const int4& v) {
+        const int id[4] = {v.x, v.y, v.z, v.w};
+        unsigned long long m[4];
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                if (i0 + j < hi && v[j] == e) {
-                    a.sorted[pos] = i0 + j;
-                    a.sorted_token[pos] = (i0 + j) / a.topk;
-                    ++pos;
-                }
-            }
+        for (int j = 0; j < 4; ++j) m[j] = __builtin_amdgcn_ballot_w64(id[j] == e);
+        if ((m[0] | m[1] | m[2] | m[3]) == 0ull) return;
+        int pos = at;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            pos += __popcll(m[j] & below);
+            at += __popcll(m[j]);
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (id[j] == e) {
+                a.sorted[pos] = i0 + j;
+                a.sorted_token[pos] = token_of(i0 + j);
+                ++pos;
+            }
+    };
+    if (n_eq) {
+#pragma unroll
+        for (int s = 0; s < kHeld; ++s)
+            if (s < steps) scatter(lo + 256 * s, held[s]);
+        for (int s = kHeld; s < steps; ++s) scatter(lo + 256 * s, load(lo + 256 * s));
     }
     // this expert's slots of the tile list: its tiles, then empty slots up to the next expert's first
     const int tile0 = off_e / a.bm + e;
-    const int tile1 = (e + 1 < a.E) ? (off_e + count) / a.bm + e + 1 : a.max_tiles;
-    const int nt = (count + a.bm - 1) / a.bm;
+    const int tile1 = (e + 1 < a.E) ? (off_e + count_e) / a.bm + e + 1 : a.max_tiles;
+    const int nt = (count_e + a.bm - 1) / a.bm;
     for (int i = tid; i < tile1 - tile0; i += kRouteThreads) {
         TileDesc td;
         td.expert = e;
         td.row0 = off_e + (i < nt ? i * a.bm : 0);
-        td.rows = i < nt ? ((count - i * a.bm) < a.bm ? (count - i * a.bm) : a.bm) : 0;
+        td.rows = i < nt ? ((count_e - i * a.bm) < a.bm ? (count_e - i * a.bm) : a.bm) : 0;
         td.pad = 0;
         a.tiles[tile0 + i] = td;
     }
     if (e == 0) {
         // every workgroup has looked at all ids; this one reports the ones out of range
-        if (bad) atomicOr(&s_bad, 1);
         for (int i = tid; i < a.n_flags; i += kRouteThreads) a.flags[i] = 0u;
-        __syncthreads();
         if (tid == 0) {
-            a.header[0] = s_bad ? MILO_ERR_ROUTING : MILO_OK;
+            int32_t found = 0;
+            for (int w = 0; w < kWaves; ++w) found |= s_bad[w];
+            a.header[0] = found ? MILO_ERR_ROUTING : MILO_OK;
             a.header[1] = a.max_tiles;
             a.header[3] = 0;
         }
@@ -151,91 +169,86 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(const RouteArgs a)
 // put longest first: a tile costs about what its number of 32-row blocks says, and more with a
 // compensator of high rank, so tiles go by that number, most blocks first, within it those of
 // experts with a rank above 32 first, in expert order within a class.  The dispatcher hands out workgroups
-// in list order, so the launch ends with the short items.  One workgroup; a thread owns a
-// contiguous range of slots and a scan per class gives every tile its place.
+// in list order, so the launch ends with the short items.  One workgroup; a wave owns a contiguous range of slots, counts
+// each class with a ballot, and one scan over (class, wave) gives every wave the place of its first tile of each class.
+// Latency-bound (slots, ranks of their experts, the scan, the stores): 5.4 us, also in a trace that gave the form with a scan
+// per class over all threads and a second pass over the slots 13.
 __global__ __launch_bounds__(kRouteThreads) void order_tiles_kernel(const TileDesc* __restrict__ slots,
                                                                     int n_slots, int bm,
                                                                     TileDesc* __restrict__ tiles,
                                                                     int32_t* __restrict__ header,
                                                                     const milo_w3lr_expert* __restrict__ experts) {
-    constexpr int NC = 8;                               // classes: bm / 32 blocks down to one, x rank
-    __shared__ int32_t wsum[NC][kRouteThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (n_slots + kRouteThreads - 1) / kRouteThreads;
-    const int lo = tid * per < n_slots ? tid * per : n_slots;
-    const int hi = lo + per < n_slots ? lo + per : n_slots;
+    constexpr int NC = 8, kWaves = kRouteThreads / 64;  // classes: bm / 32 blocks down to one, x rank
+    static_assert(NC * kWaves == 128, "two entries per lane of the scan");
+    __shared__ int32_t s_at[NC * kWaves + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int steps = (n_slots + kRouteThreads - 1) / kRouteThreads;
+    const int lo = wave * steps * 64 + lane;
     const int mb = bm / 32;
-    auto cls = [&](const TileDesc& td) {                // 0: as many blocks as a full tile, high rank
+    auto load = [&](int i) {
+        TileDesc td = {0, 0, 0, 0};
+        if (i < n_slots) td = slots[i];
+        return td;
+    };
+    auto cls = [&](const TileDesc& td) {                // 0: as many blocks as a full tile, high rank; -1: no tile
         const int nb = (td.rows + 31) / 32;
         const milo_w3lr_expert& ex = experts[td.expert];
         const int low = (ex.w1.r <= 32 && ex.w3.r <= 32 && ex.w2.r <= 32) ? 1 : 0;
-        return 2 * (mb - (nb < mb ? nb : mb)) + low;
+        return td.rows > 0 ? 2 * (mb - (nb < mb ? nb : mb)) + low : -1;
     };
     int cnt[NC] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = lo; i < hi; ++i) {
-        const TileDesc td0 = slots[i];
-        const int rows = td0.rows;
-        if (rows > 0) {
-            const int c = cls(td0);
+    TileDesc td = load(lo);
+    int c = cls(td);
+    for (int s = 0; s < steps; ++s) {
+        if (s > 0) c = cls(load(lo + 64 * s));
 #pragma unroll
-            for (int k = 0; k < NC; ++k) cnt[k] += c == k;
-        }
+        for (int k = 0; k < NC; ++k) cnt[k] += __popcll(__builtin_amdgcn_ballot_w64(c == k));
     }
-    int scan[NC];                                       // inclusive scans within the wave
+    if (lane == 0) {
 #pragma unroll
-    for (int k = 0; k < NC; ++k) scan[k] = cnt[k];
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-            const int v = __shfl_up(scan[k], d, 64);
-            if (lane >= d) scan[k] += v;
-        }
-    }
-    if (lane == 63) {
-#pragma unroll
-        for (int k = 0; k < NC; ++k) wsum[k][wave] = scan[k];
+        for (int k = 0; k < NC; ++k) s_at[k * kWaves + wave] = cnt[k];
     }
     __syncthreads();
-    int before[NC], total[NC];
+    if (wave == 0) {
+        const int x = s_at[2 * lane], y = s_at[2 * lane + 1];
+        int sum = x + y;
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-        before[k] = 0;
-        total[k] = 0;
-        for (int w = 0; w < kRouteThreads / 64; ++w) {
-            if (w < wave) before[k] += wsum[k][w];
-            total[k] += wsum[k][w];
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(sum, d, 64);
+            if (lane >= d) sum += v;
         }
+        s_at[2 * lane] = sum - x - y;
+        s_at[2 * lane + 1] = sum - y;
+        if (lane == 63) s_at[NC * kWaves] = sum;
     }
+    __syncthreads();
     // From kXcdPlacementTiles tiles on, the tiled kernel reads the list as eight contiguous ranges,
     // one per sequence of workgroups (range k starts at k * (n / 8) + min(k, n % 8)).  Position p of
     // the order goes to range p % 8, place p / 8, so that every range gets the same mix and ends
     // with its short items.
-    int n = 0;
-#pragma unroll
-    for (int k = 0; k < NC; ++k) n += total[k];
-    const int base = n >> 3, rem = n & 7;
+    const int n = s_at[NC * kWaves], base = n >> 3, rem = n & 7;
     auto place = [&](int p) {
         if (n < (int)kXcdPlacementTiles) return p;          // the kernel takes the list in order
         const int k = p & 7;
         return k * base + (k < rem ? k : rem) + (p >> 3);
     };
     int pos[NC];
-    int start = 0;
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-        pos[k] = start + before[k] + scan[k] - cnt[k];
-        start += total[k];
-    }
-    for (int i = lo; i < hi; ++i) {
-        const TileDesc td = slots[i];
-        if (td.rows <= 0) continue;
-        const int c = cls(td);
+    for (int k = 0; k < NC; ++k) pos[k] = s_at[k * kWaves + wave];
+    const unsigned long long below = (1ull << lane) - 1ull;
+    for (int s = 0; s < steps; ++s) {
+        if (steps > 1) {
+            td = load(lo + 64 * s);
+            c = cls(td);
+        }
         int p = 0;
 #pragma unroll
-        for (int k = 0; k < NC; ++k)
-            if (c == k) p = pos[k]++;
-        tiles[place(p)] = td;
+        for (int k = 0; k < NC; ++k) {
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(c == k);
+            if (c == k) p = pos[k] + __popcll(m & below);
+            pos[k] += __popcll(m);
+        }
+        if (c >= 0) tiles[place(p)] = td;
     }
     if (tid == 0) header[1] = n;
 }
