@@ -340,6 +340,39 @@ def test_single_launch_routing_of_many_tiles():
 
 
 @pytest.mark.timeout(900)
+@pytest.mark.parametrize("E,topk,T", [
+    (5, 3, 683), (5, 1, 4095), (66, 2, 2049),           # ids that end within a lane's four; one step of 4096 pairs, and two
+    (40, 8, 4096), (40, 8, 4097), (3, 1, 40001),        # eight steps, which stay in registers, and more
+    (1500, 6, 700),                                     # more slots than a wave of the ordering kernel takes at once
+])
+def test_routing_by_steps(E, topk, T):
+    import torch
+    from paper_2504_02658_amd import api
+    g = torch.Generator(device="cuda")
+    g.manual_seed(E + T)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    kinds = [tuple(api.pack_w3(randn(64, 64) * 0.1) for _ in range(3)) for _ in range(3)]
+    layer = api.MoELayer([kinds[e % 3] for e in range(E)], 64, 64)
+    X = randn(T, 64).half()
+    ids = torch.argsort(torch.rand((T, E), generator=g, device="cuda"), dim=1)[:, :topk].to(torch.int32).contiguous()
+    ids[T // 2, 0], ids[T - 1, topk - 1] = -1, E + 5
+    gates = torch.rand((T, topk), generator=g, device="cuda")
+    Y = layer.forward(X, ids, gates).double()
+    assert layer.routing_status() == 6
+    # the three experts there are, dequantized by the library (tested by itself), in 64 bits; H and each pair's output are 16-bit
+    w = [[api.dequant_w3(p).double() for p in k] for k in kinds]
+    x, ref = X.double(), torch.zeros((T, 64), dtype=torch.float64, device="cuda")
+    out = [(torch.nn.functional.silu(x @ a.T) * (x @ b.T)) @ c.T for a, b, c in w]
+    for j in range(topk):
+        good = (ids[:, j] >= 0) & (ids[:, j] < E)
+        for k in range(3):
+            ref += torch.where((good & (ids[:, j] % 3 == k))[:, None], gates[:, j, None].double() * out[k], 0.0)
+    # every row by itself: a pair that went astray is an error of the size of the row; roundings are 2^-11 of it each
+    err = (Y - ref).norm(dim=1) / ref.norm(dim=1).clamp_min(1e-6)
+    assert float(err[ref.norm(dim=1) > 1e-3].max()) < 6 * 2.0 ** -11
+    assert float(Y[ref.norm(dim=1) == 0].abs().sum()) == 0.0
+
+
 def test_c4_deepseek_layer_full_size():
     _check(wl.C4)
 
