@@ -63,14 +63,14 @@ static int gemm_mb_override() {
     }();
     return mb;
 }
-static int gemm_mb(int64_t M) {
+static int gemm_mb_by_rows(int64_t M) {
     // tile height / 32; measured on N = 14336, K = 4096: up to 64 rows the shallow tile wins, up to
     // a few hundred rows two 64-row tiles beat one tall one
     const int mb = M <= 64 ? 1 : (M <= 384 ? 2 : 4);
     return gemm_mb_override() ? gemm_mb_override() : mb;
 }
-static int gemm_splits(int64_t M, int64_t N, int64_t K, int r) {
-    const int bm = 32 * gemm_mb(M);
+static int gemm_splits(int mb, int64_t M, int64_t N, int64_t K, int r) {
+    const int bm = 32 * mb;
     const int64_t m_tiles = (M + bm - 1) / bm;
     return tiled_k_splits(m_tiles * ((N + 255) / 256), K, r > 0 ? m_tiles * tiled_t_parts(K) : 0);
 }
@@ -78,17 +78,49 @@ static int gemm_splits(int64_t M, int64_t N, int64_t K, int r) {
 // epilogue: a part should take at most half as long as a column tile's share of K.  A part walks its
 // chunks once per 256 ranks, and with K splits a column tile's share is short, so both call for more
 // (shorter) parts than the default of eight chunks each.
-static int gemm_t_parts(int64_t M, int64_t N, int64_t K, int r) {
+static int gemm_t_parts(int mb, int64_t M, int64_t N, int64_t K, int r) {
     if (r <= 0) return 0;
     const int base = tiled_t_parts(K);
     const int64_t nchunks = (K / 64 + 1) / 2;
-    const int64_t cps = (nchunks + gemm_splits(M, N, K, r) - 1) / gemm_splits(M, N, K, r);
+    const int splits = gemm_splits(mb, M, N, K, r);
+    const int64_t cps = (nchunks + splits - 1) / splits;
     const int64_t passes = ((int64_t)r + 255) / 256;
     int64_t cpp = cps / (2 * passes);
     if (cpp < 1) cpp = 1;
     int64_t parts = (nchunks + cpp - 1) / cpp;
     if (parts > 16) parts = 16;
     return parts > base ? (int)parts : base;
+}
+// Time of the tiled kernel (us) with tiles of 64 or 128 rows, fitted to 8000 points each (512 .. 14336 x 512 .. 14336, 129 .. 4096
+// rows, ranks 0 .. 128) with weight on those where the height is the better one: rounds of workgroups at two per CU, each a
+// start and its chunks, a chunk of a partly filled tile (`filled`) costing `fixed` of a full one's time whatever its rows, and
+// the K splits' second kernel with the partial sums it moves.
+static double gemm_tiled_estimate(int mb, int64_t M, int64_t N, int64_t K, int r) {
+    struct Fit { double start, wg, chunk, partly, sum, mb, lr, rank32, fixed; };
+    static const Fit fits[2] = {{5.72, 6.07, 1.758, 0.326, 2.227, 0.194, -1.032, 2.684, 1.486},
+                                {9.766, 6.556, 3.288, 0.207, 3.061, 0.134, -2.008, 3.868, 0.766}};
+    const Fit& f = fits[mb == 4];
+    const int64_t m_tiles = (M + 32 * mb - 1) / (32 * mb), nchunks = (K / 64 + 1) / 2, cap = 2 * (int64_t)device_cus();
+    const int splits = gemm_splits(mb, M, N, K, r);
+    const int64_t wgs = m_tiles * ((N + 255) / 256) * splits + m_tiles * gemm_t_parts(mb, M, N, K, r), full = wgs / cap, rem = wgs - full * cap;
+    const double rounds = (double)full + (rem > 0 ? f.partly + (1.0 - f.partly) * (double)rem / (double)cap : 0.0);
+    const double filled = (double)M / (double)(m_tiles * 32 * mb);
+    double t = f.start + rounds * (f.wg + (double)((nchunks + splits - 1) / splits) * f.chunk * (f.fixed + (1.0 - f.fixed) * filled));
+    if (splits > 1) t += f.sum + f.mb * 4e-6 * (double)M * (double)N * splits;
+    if (r > 0) t += f.lr + f.rank32 * (double)r / 32.0;
+    return t;
+}
+// Tile height of a call: by rows, or the other of 64 and 128 rows where the estimates say that it is clearly the faster one, as
+// how evenly the tiles fill the chip and whether K has to be split depend on the whole shape.  us, by rows / now: 1024 rows of
+// 4096 x 4096 59 / 44, 512 of 14336 x 4096 77 / 71, 512 of 8192 x 8192 89 / 81, 384 of 11008 x 4096 64 / 59.  Of 4726 drawn problems that
+// the tiled kernel takes 1338 change; the geometric mean over all is 5 % faster, 61 are slower by more than 2 % and 19 by more than
+// 5 %, at worst 1.2 times.  (Without the factor 1.13 it is 6 %, and about 60 are slower by more than 5 %.  With a compensator and
+// a very short K the wait for T decides, which the estimates have no part for: 620 rows of 11360 x 576, r = 32, 128-row tiles 21, 64-row
+// tiles 35.)
+static int gemm_mb(int64_t M, int64_t N, int64_t K, int r) {
+    const int mb = gemm_mb_by_rows(M);
+    if (gemm_mb_override() || M < 129 || M > 4096 || r > 128 || (r > 0 && K < 768)) return mb;        // (measured there)
+    return 1.13 * gemm_tiled_estimate(6 - mb, M, N, K, r) < gemm_tiled_estimate(mb, M, N, K, r) ? 6 - mb : mb;
 }
 
 // Adds the fp32 partial sums of the K splits in split order and rounds once.
@@ -114,7 +146,7 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict
 }
 
 size_t milo::gemm_flags_behind(int64_t M) {
-    const int64_t bm = 32 * gemm_mb(M), tiles = (M + bm - 1) / bm;
+    const int64_t bm = 32 * gemm_mb_by_rows(M), tiles = (M + bm - 1) / bm;      // (another height only below 4096 rows, where all fit)
     return tiles > kTiledFlagTiles ? align_up((size_t)tiles * 16, 256) : 0;
 }
 
@@ -122,24 +154,34 @@ static bool gemm_shape_ok(int64_t M, int64_t N, int64_t K) {
     return M >= 1 && M <= (int64_t)0x3fffffff && weight_shape_ok(N, K);
 }
 
-size_t milo::gemm_workspace_min(int64_t M, int64_t N, int64_t K, int r) {
-    if (!gemm_shape_ok(M, N, K) || r < 0) return 0;
-    if (gemm_takes_decode(M, N, K, r)) return decode_workspace_min(N, K, r);
+// What a tiled call needs at a tile height.
+static size_t gemm_tiled_bytes(int mb, int64_t M, int64_t N, int64_t K, int r) {
     // head | flag words that do not fit in it | T = X V^T, fp16 [M x pad16(r)] | its fp32 partials per part of K | with K
     // splits, their fp32 partial sums [M x N] each
-    const size_t parts = (size_t)gemm_t_parts(M, N, K, r);
-    const int splits = gemm_splits(M, N, K, r);
+    const size_t parts = (size_t)gemm_t_parts(mb, M, N, K, r);
+    const int splits = gemm_splits(mb, M, N, K, r);
     return kGemmHeadBytes + gemm_flags_behind(M) +
            align_up((size_t)M * (size_t)rank_pad(r) * 2 + 256, 256) +
            align_up(parts * (size_t)M * (size_t)rank_pad(r) * 4 + 256, 256) +
            (splits > 1 ? align_up((size_t)splits * (size_t)M * (size_t)N * 4, 256) : 0);
 }
 
+// (The height by rows sets the limit: a call with less than its own height asks for takes that one.)
+size_t milo::gemm_workspace_min(int64_t M, int64_t N, int64_t K, int r) {
+    if (!gemm_shape_ok(M, N, K) || r < 0) return 0;
+    if (gemm_takes_decode(M, N, K, r)) return decode_workspace_min(N, K, r);
+    return gemm_tiled_bytes(gemm_mb_by_rows(M), M, N, K, r);
+}
+
 // A workspace sized for a prefill serves decode calls on the same weight at full speed as well: room for either.  (With one
 // sized for 4096 rows of 4096 x 14336, r = 0, a decode of 16 rows took 12.3 us, the other kernel, instead of 10.9.)
 extern "C" size_t milo_w3lr_gemm_workspace(int64_t M, int64_t N, int64_t K, int r) {
-    const size_t need = gemm_workspace_min(M, N, K, r);
+    size_t need = gemm_workspace_min(M, N, K, r);
     if (need == 0) return 0;
+    if (!gemm_takes_decode(M, N, K, r)) {
+        const size_t own = gemm_tiled_bytes(gemm_mb(M, N, K, r), M, N, K, r);
+        if (own > need) need = own;
+    }
     const size_t decode = decode_workspace_bytes(N, K, r);
     return need > decode ? need : decode;
 }
@@ -194,19 +236,23 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     f16* T = reinterpret_cast<f16*>(ws + kGemmHeadBytes + flags_behind);
     const int64_t ldt = rank_pad(r);
 
-    const int mb = gemm_mb(M);
+    // Batches whose tiles do not fill the chip: one launch without K splits.  Its T needs no more scratch than the tiled one's
+    // (no more parts, and no 16-bit copy), so every workspace that is accepted serves either.
+    const int by_rows = gemm_mb_by_rows(M);
+    MidPlan mid;
+    const bool takes_mid = !gemm_mb_override() && plan_mid(M, N, K, r, (flags & MILO_LR_INT3) != 0, by_rows, gemm_splits(by_rows, M, N, K, r),
+                                                           r > 0 ? tiled_t_parts(K) : 0, &mid);
+    int mb = takes_mid ? by_rows : gemm_mb(M, N, K, r);
+    if (mb != by_rows && workspace_bytes < gemm_tiled_bytes(mb, M, N, K, r)) mb = by_rows;
     const int bm = 32 * mb;
     const int64_t m_tiles = (M + bm - 1) / bm;
     if (m_tiles > 65535) return MILO_ERR_SHAPE;
-    const int parts = gemm_t_parts(M, N, K, r);
-    const int splits = gemm_splits(M, N, K, r);
+    const int parts = gemm_t_parts(mb, M, N, K, r);
+    const int splits = gemm_splits(mb, M, N, K, r);
     if ((uint64_t)M * K * 2 >= 0x80000000ull || ((uint64_t)r + 256) * K * 2 >= 0xFFFFFFF0ull ||
         (uint64_t)(parts > 0 ? parts : 1) * M * ldt * 4 >= 0xFFFFFFF0ull || (N & 3) != 0)
         return MILO_ERR_SHAPE;                                          // 32-bit offsets in the kernel
-    // Batches whose tiles do not fill the chip: one launch without K splits.  Its T needs no more scratch than the tiled one's
-    // (no more parts, and no 16-bit copy), so every workspace that is accepted serves either.
-    MidPlan mid;
-    if (!gemm_mb_override() && plan_mid(M, N, K, r, (flags & MILO_LR_INT3) != 0, mb, splits, r > 0 ? tiled_t_parts(K) : 0, &mid)) {
+    if (takes_mid) {
         MidArgs ma;
         ma.X = reinterpret_cast<const f16*>(X); ma.Y = reinterpret_cast<f16*>(Y);
         ma.M = (uint32_t)M; ma.N = (uint32_t)N; ma.K = (uint32_t)K; ma.x_bytes = (uint32_t)(M * K * 2);
