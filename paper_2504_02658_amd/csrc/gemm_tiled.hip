@@ -155,7 +155,7 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
             rank0[s] = MBT != MB ? ((NW == 1) ? 32 * s : 0) : pass0 + ((NW == 1) ? 64 * wave + 32 * s : 32 * wave);
             active[s] = rank0[s] < w.r && (MBT == MB || wave < MB);
             vb[s] = make_rsrc(w.V, (uint64_t)(w.r > 0 ? w.r : 0) * (uint64_t)K * 2u);
-            voff[s] = active[s] ? (uint32_t)(((int64_t)(rank0[s] + i32) * K + 8 * h) * 2) : kOobOffset;
+            voff[s] = active[s] ? (uint32_t)(((int64_t)(rank0[s] + i32) * K + (NW == 2 ? 8 : 64) * h) * 2) : kOobOffset;
         }
         f32x16 acc[2][MBT];
 #pragma unroll
@@ -269,11 +269,13 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 }
             }
         } else {
-            // V fragment of step t of chunk c, 16 neighbouring columns of 32 rows; out of range (inactive stream, ragged K
-            // tail) reads zero
+            // V fragment of step t of chunk c; out of range (inactive stream, ragged K tail) reads zero.  Two weights: 16
+            // neighbouring columns of 32 rows, 32 bytes of a row per pair of lanes; one weight, where few waves have ranks: 16 bytes of
+            // each group (us: two shared experts of rank 128 in a layer 742 / 744, r = 64 of a single linear 81.6 / 81.1).
+            constexpr bool NEAR = NW == 2;
             auto load_v = [&](int c, int s, int t) -> u32x4 {
-                const bool out = !active[s] || c >= c_hi || (ktail && c == nchunks - 1 && t >= 4);
-                return buf_load16(vb[s], out ? kOobOffset : voff[s] + (uint32_t)c * 256u + 32u * t);
+                const bool out = !active[s] || c >= c_hi || (ktail && c == nchunks - 1 && (NEAR ? t >= 4 : h == 1));
+                return buf_load16(vb[s], out ? kOobOffset : voff[s] + (uint32_t)c * 256u + (NEAR ? 32u : 16u) * t);
             };
             u32x4 va[2][8];
             __syncthreads();            // a previous pass is done with the stages
@@ -297,7 +299,7 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 if (active[0] || active[1]) {
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
-                        mfma_step(xs, sx, 2 * t + h, __builtin_bit_cast(f16x8, va[0][t]), __builtin_bit_cast(f16x8, va[1][t]));
+                        mfma_step(xs, sx, NEAR ? 2 * t + h : 8 * h + t, __builtin_bit_cast(f16x8, va[0][t]), __builtin_bit_cast(f16x8, va[1][t]));
                         // the registers of this step are free again: fetch the next chunk's fragment into them
                         va[0][t] = load_v(c + 1, 0, t);
                         va[1][t] = load_v(c + 1, 1, t);
@@ -925,8 +927,9 @@ static int launch_one(const TiledArgs& a, dim3 grid, hipStream_t stream) {
     constexpr int lds_stages = (MB == 4 ? 2 : kTiledStages) * 32 * MB * 256;
     // room for the U array of an INT3 compensator: 256 band features x (pad16(rank) + 8) fp16
     const int lds_u = a.lr3_rank > 0 ? 256 * (((a.lr3_rank + 15) & ~15) + 8) * 2 : 0;
-    // the workgroups that form T: two stages, and a chunk of V of up to 32 ranks of two weights
-    const int lds_t = a.v_tiles > 0 && MB > 1 ? 2 * 32 * MB * 256 + 16 * 1024 : 0;
+    // the workgroups that form T: two stages, and a chunk of V of up to 32 ranks of two weights (larger ranks stay out of LDS)
+    const bool v_staged = a.v_tiles > 0 && MB > 1 && (a.rs.tiles || a.rs.w[0].r <= 32);
+    const int lds_t = v_staged ? 2 * 32 * MB * 256 + 16 * 1024 : 0;
     const int lds_x = lds_t > lds_stages ? lds_t : lds_stages, lds = lds_u > lds_x ? lds_u : lds_x;
     static bool raised[64] = {false};
     if (lds > 64 * 1024) {
