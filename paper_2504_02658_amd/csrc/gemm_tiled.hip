@@ -1,4 +1,4 @@
-// Tiled MFMA kernel for the compensated W3A16 linear at M > 16, single or grouped per expert,
+// Tiled MFMA kernel for the compensated W3A16 linear at larger M, single or grouped per expert,
 // including the workgroups of the same launch that form T = X V^T for the low-rank term.
 //
 // Work split.  A workgroup of four waves owns BM = 32*MB rows of the (expert-sorted) row space
