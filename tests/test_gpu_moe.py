@@ -339,7 +339,6 @@ def test_single_launch_routing_of_many_tiles():
     _check(wl.MoECase("many_small", T=128, H=256, F=192, E=220, topk=4, seed=56, rank_choices=(8, 136), zipf_s=0.4), rows=32)
 
 
-@pytest.mark.timeout(900)
 @pytest.mark.parametrize("E,topk,T", [
     (5, 3, 683), (5, 1, 4095), (66, 2, 2049),           # ids that end within a lane's four; one step of 4096 pairs, and two
     (40, 8, 4096), (40, 8, 4097), (3, 1, 40001),        # eight steps, which stay in registers, and more
@@ -373,6 +372,7 @@ def test_routing_by_steps(E, topk, T):
     assert float(Y[ref.norm(dim=1) == 0].abs().sum()) == 0.0
 
 
+@pytest.mark.timeout(900)
 def test_c4_deepseek_layer_full_size():
     _check(wl.C4)
 
