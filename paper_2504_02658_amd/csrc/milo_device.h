@@ -509,12 +509,14 @@ __device__ __forceinline__ f16x8 load_f16x8(const f16* p) {
     return __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(p));
 }
 
-// a / (1 + exp(-a)).  The quotient from the hardware's reciprocal and one correction by its remainder, which leaves less than
-// the rounding of the result; the compiler's division guards the ends of the range, which a denominator of at least 1 has
-// only one of (infinity, mended by the fixup), with three further instructions and two scalings.
+// a / (1 + exp(-a)).  The quotient from the hardware's reciprocal and one correction by its remainder.  The reciprocal of more than
+// 2^126 would be below the normal numbers and comes out as zero (gates from -88.7 to -87.3, whose quotient is a normal
+// number still), so numerator and denominator are both taken four times smaller, which costs a multiplication and is exact
+// but for gates below 2^-124; an infinite denominator is mended by the fixup.  The compiler's division scales both by tests
+// of their exponents, two instructions and two more in the correction.
 __device__ __forceinline__ float silu(float a) {
-    const float d = 1.0f + __expf(-a), r = __builtin_amdgcn_rcpf(d), q = a * r;
-    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, q, a), r, q), d, a);
+    const float d = __builtin_fmaf(__expf(-a), 0.25f, 0.25f), n = 0.25f * a, r = __builtin_amdgcn_rcpf(d), q = n * r;
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, q, n), r, q), d, n);
 }
 
 // 8 consecutive fp16 of a row of length `len` starting at column k0 (k0 % 8 == 0): one 16-byte

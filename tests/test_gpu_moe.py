@@ -397,6 +397,32 @@ def test_few_rows_per_expert(H, F, E, topk, T, ranks, dtype):
         _check(case, int3=dtype == "int3")
 
 
+@pytest.mark.parametrize("T", [20, 600])      # streamed, 128-row tiles
+def test_swiglu_at_the_ends_of_its_range(T):
+    # Gates from -88.5 to 88.5, up projections of 2^100: below a gate of -87.3 the quotient's denominator is above 2^126, its reciprocal
+    # below the normal numbers and the product a normal number still.  Every feature of the SwiGLU output is copied to the layer's output.
+    import torch
+    from paper_2504_02658_amd import api
+    H = F = 192
+    n, codes = np.arange(F), np.zeros((3, F, H), np.uint8)
+    scales = np.zeros((3, F, 3), np.float16)
+    codes[0, :, 64], scales[0, :, 1] = 1, np.where(n < 177, 0.5 * (n + 1), 1.0)         # gate: X[64] times 0.5 .. 88.5
+    codes[1, :, 0], scales[1, :, 0] = 1, 1.0                                            # up: X[0]
+    codes[2, n, n], scales[2] = 1, 1.0
+    w = [api.PackedWeight(F, H, torch.from_numpy(oracle.pack_w3(c, s, np.zeros((F, 3), np.float16))).cuda()) for c, s in zip(codes, scales)]
+    layer = api.MoELayer([tuple(w)], H, F, bf16=True)
+    X = torch.zeros((T, H), dtype=torch.bfloat16, device="cuda")
+    X[:, 0] = 2.0 ** 100
+    X[:, 64] = torch.tensor([-1.0, 1.0, -0.5, 0.0], device="cuda").repeat((T + 3) // 4)[:T].to(torch.bfloat16)
+    ids, gates = torch.zeros((T, 1), dtype=torch.int32, device="cuda"), torch.ones((T, 1), device="cuda")
+    Y = layer.forward(X, ids, gates).double().cpu()
+    assert_rows_per_tile(layer, ids.cpu().numpy(), STREAMED if T == 20 else 128)
+    a = X[:, 64].double().cpu()[:, None] * torch.from_numpy(scales[0, :, 1].astype(np.float64))
+    ref = a / (1.0 + torch.exp(-a)) * 2.0 ** 100
+    # two roundings to bf16, 2^-9 of the value each; the exponential's argument is rounded to fp32, 88 * 2^-24 of the result
+    assert bool(((Y - ref).abs() <= (2.0 ** -8 + 2.0 ** -16) * ref.abs()).all())
+
+
 def test_few_rows_routing_rejects_and_repeats():
     # ids out of range leave no item behind, and an expert named twice by a token gets both rows
     case = wl.MoECase("few_ids", T=6, H=128, F=192, E=4, topk=3, seed=29, rank_choices=(8,))
