@@ -279,7 +279,7 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     ga.T[0] = ga.T[1] = T; ga.ldt = ldt; ga.t_bytes = (uint64_t)M * ldt * 2;
     ga.Tp[0] = ga.Tp[1] = Tp; ga.tp_bytes = (uint64_t)parts * M * ldt * 4;
     ga.t_part_stride = M * ldt; ga.t_parts = parts; ga.v_tiles = parts; ga.ksplit = splits;
-    ga.flags = tile_flags; ga.flags_status = ctrl + 3; ga.weights_once = m_tiles == 1;
+    ga.flags = tile_flags; ga.flags_spread = flags_behind == 0; ga.flags_status = ctrl + 3; ga.weights_once = m_tiles == 1;
     ga.lr3_rank = (w.flags & MILO_LR_INT3) ? r : 0;
     ga.self_clean = 1;
     ga.act_bf16 = (flags & MILO_ACT_BF16) ? 1 : 0;

@@ -69,6 +69,15 @@ typedef __attribute__((address_space(3))) void* LdsPtr;
 // when a column offset is added to it.
 constexpr uint32_t kOobHalf = 0x80000000u;
 
+// Control words of M-tile t.  A linear spreads them over the cache lines there are: every wave of a tile's column tiles looks at its
+// "ready" word at about the same time, and the workgroups that form T count on the word beside it.  With the words of
+// eight tiles on a line those loads and atomics (which all go to memory, past the L2s) queued up behind each other, and where T is
+// needed soon (short K) that decided the launch: us, eight tiles per line / one: 878 rows of 13952 x 1024, r = 48 50 / 38.5, 444 of
+// 12288 x 832, r = 48 30 / 23.5, 1225 of 13312 x 576, INT3 r = 32 57 / 40; the three words on lines of their own give no more.
+__device__ __forceinline__ uint32_t* tile_words(const TiledArgs& a, uint32_t t) {
+    return a.flags + (a.flags_spread ? (t % kTiledFlagLines) * 32u + t / kTiledFlagLines * 4u : 4u * t);
+}
+
 // Spin until *flag reaches `target`.  The producers never wait and were dispatched earlier, so the
 // wait ends; the bound only turns a broken assumption into an error code instead of a hang.
 __device__ __forceinline__ void wait_flag(const uint32_t* flag, uint32_t target, uint32_t* status) {
@@ -347,9 +356,10 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
     wait_vmem();
     __syncthreads();
     int last = 0;
+    uint32_t* const words = tile_words(a, by);
     if (tid == 0) {
-        last = atomicAdd(a.flags + 4 * by, 1u) == (uint32_t)a.t_parts - 1u;
-        if (a.t_dist) wait_flag(a.flags + 4 * by, (uint32_t)a.t_parts, a.flags_status);
+        last = atomicAdd(words, 1u) == (uint32_t)a.t_parts - 1u;
+        if (a.t_dist) wait_flag(words, (uint32_t)a.t_parts, a.flags_status);
     }
     // (through the dead stages: the reduction built into a barrier would take LDS of its own, and two workgroups with all of a
     // CU's LDS between them would not fit beside each other any more)
@@ -422,8 +432,8 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
     wait_vmem();
     __syncthreads();
     if (tid == 0) {
-        if (a.t_dist) atomicAdd(a.flags + 4 * by + 1, 1u);
-        else __hip_atomic_store(a.flags + 4 * by + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (a.t_dist) atomicAdd(words + 1, 1u);
+        else __hip_atomic_store(words + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -635,6 +645,7 @@ __global__ __launch_bounds__(kTiledThreads, 2) void w3lr_tiled_kernel(const Tile
     // microsecond): the workgroups that form T were dispatched long before, so the answer is nearly
     // always yes, and the wave goes from its last chunk straight to the low-rank term.
     uint32_t early_flag = 0u;
+    uint32_t* const words = tile_words(a, by);
     const bool wants_t = any_rank && bz < (uint32_t)a.lr_splits;
     const uint32_t t_ready = a.t_dist ? (uint32_t)a.t_parts : 1u;     // value of the tile's flag when T is complete
     auto k_loop = [&](auto mbu_c) {
@@ -695,7 +706,7 @@ __global__ __launch_bounds__(kTiledThreads, 2) void w3lr_tiled_kernel(const Tile
                 __syncthreads();        // everyone's copies of chunk c landed; everyone left chunk c-1
                 issue(c + PD - 1, (slot + PD - 1) % PD, ring[(slot + PD - 1) % PD]);
                 if (wants_t && c == c_end - 1 && lane == 0)
-                    early_flag = __hip_atomic_load(a.flags + 4 * by + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    early_flag = __hip_atomic_load(words + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 compute(slot, ring[slot], [](int) {});
             }
         }
@@ -807,7 +818,7 @@ __global__ __launch_bounds__(kTiledThreads, 2) void w3lr_tiled_kernel(const Tile
             load_u(ks_lo, avA);
             if (!waited) {
                 // every wave asks for itself (no barrier: a wave that is done early goes on early)
-                if (lane == 0 && early_flag < t_ready) wait_flag(a.flags + 4 * by + 1, t_ready, a.flags_status);
+                if (lane == 0 && early_flag < t_ready) wait_flag(words + 1, t_ready, a.flags_status);
                 waited = true;
             }
             load_t(ks_lo, bvA);
@@ -825,7 +836,7 @@ __global__ __launch_bounds__(kTiledThreads, 2) void w3lr_tiled_kernel(const Tile
             }
         }
         if (!waited) {          // (not reached: some rank is positive)
-            if (lane == 0 && early_flag < t_ready) wait_flag(a.flags + 4 * by + 1, t_ready, a.flags_status);
+            if (lane == 0 && early_flag < t_ready) wait_flag(words + 1, t_ready, a.flags_status);
         }
         // the last reader of this M-tile's T clears its control words for the next launch (the MoE
         // call clears all of them before every forward instead: the returning atomic is a round
@@ -833,10 +844,10 @@ __global__ __launch_bounds__(kTiledThreads, 2) void w3lr_tiled_kernel(const Tile
         if (a.self_clean) __syncthreads();
         if (a.self_clean && tid == 0) {
             const uint32_t readers = (gx - (uint32_t)a.v_tiles) * (uint32_t)a.lr_splits;
-            if (atomicAdd(a.flags + 4 * by + 2, 1u) == readers - 1u) {
-                __hip_atomic_store(a.flags + 4 * by, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(a.flags + 4 * by + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(a.flags + 4 * by + 2, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (atomicAdd(words + 2, 1u) == readers - 1u) {
+                __hip_atomic_store(words, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(words + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(words + 2, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     }

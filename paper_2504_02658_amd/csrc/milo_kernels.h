@@ -61,7 +61,8 @@ struct TiledArgs {
     int m_tiles;        // upper bound of the number of M-tiles (set by launch_tiled)
     int lr3_rank;       // largest rank an INT3 compensator of this launch may have (0: none can occur)
     int weights_once;   // non-zero: every weight is read by one M-tile only (non-temporal loads)
-    uint32_t* flags;    // per M-tile t: [4t] parts done, [4t+1] T ready, [4t+2] readers done; zero at launch
+    uint32_t* flags;    // four words per M-tile: parts done, T ready, readers done; zero at launch
+    int flags_spread;   // non-zero: the words of kTiledFlagTiles M-tiles at most, spread over that many tiles' bytes; zero: one after the other
     int self_clean;     // non-zero: the last reader of a tile's T clears its words (else the caller does before the next launch)
     int act_bf16;       // non-zero: activations, compensators and outputs are bfloat16 (MILO_ACT_BF16)
     int t_dist;         // non-zero: every part of T adds a share of the rows once all parts are written, and the
@@ -99,6 +100,7 @@ constexpr int kDecDoneBytes = 8192;  // sign-off words: up to 2048 resident work
 // flags behind the head, where other calls have scratch, and clears them itself.
 constexpr int64_t kTiledFlagTiles = 1024;
 constexpr int kTiledFlagBytes = (int)kTiledFlagTiles * 16;
+constexpr uint32_t kTiledFlagLines = kTiledFlagBytes / 128;     // cache lines
 // Hand-over of T in the decode kernel (see gemm_decode.hip): launch counters, one per group of consumers
 // and each on a cache line of its own, and the granules.
 constexpr uint32_t kDecGroups = 32, kDecGroupStride = 8;       // stride in 8-byte counters
