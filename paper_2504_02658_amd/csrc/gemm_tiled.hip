@@ -175,11 +175,11 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 for (int v = 0; v < 16; ++v) acc[s][mb][v] = 0.0f;
         // one step of the product: A fragments a0, a1 (streams 0, 1) against the B fragments of this
         // wave's row blocks; xs points at row i32 of block 0 in the stage
-        auto mfma_step = [&](const unsigned char* xs, int sx, int seg, f16x8 a0, f16x8 a1) {
+        auto mfma_step = [&](const unsigned char* xs, int sx, int t, f16x8 a0, f16x8 a1) {
 #pragma unroll
             for (int mb = 0; mb < MBT; ++mb) {
                 const f16x8 b = __builtin_bit_cast(
-                    f16x8, *reinterpret_cast<const u32x4*>(xs + (blk0 + mb) * 32 * 256 + ((seg ^ sx) << 4)));
+                    f16x8, *reinterpret_cast<const u32x4*>(xs + (blk0 + mb) * 32 * 256 + (((8 * h + t) ^ sx) << 4)));
                 if (BF) {       // (bf16 activations: V is bf16 as well, same bits in the fragments)
                     if (active[0])
                         acc[0][mb] = mfma32_bf16(__builtin_bit_cast(bf16x8, a0), __builtin_bit_cast(bf16x8, b), acc[0][mb]);
@@ -228,7 +228,7 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 const int sx = i32 & 15;
                 if (active[0] || active[1]) {
                     dequant_units2_steps<true>(cur[0], cur[1],
-                                               [&](int t, f16x8 a0, f16x8 a1) { mfma_step(xs, sx, 8 * h + t, a0, a1); });
+                                               [&](int t, f16x8 a0, f16x8 a1) { mfma_step(xs, sx, t, a0, a1); });
                 }
                 cur[0] = nxt[0];
                 cur[1] = nxt[1];
@@ -274,13 +274,15 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 const unsigned char* xs = smem + (c & 1) * STAGE + i32 * 256;
                 if (active[0] || active[1]) {
 #pragma unroll
-                    for (int t = 0; t < 8; ++t) mfma_step(xs, sx, 8 * h + t, va[0][t], va[NW - 1][t]);
+                    for (int t = 0; t < 8; ++t) mfma_step(xs, sx, t, va[0][t], va[NW - 1][t]);
                 }
             }
         } else {
-            // V fragment of step t of chunk c; out of range (inactive stream, ragged K tail) reads zero.  Two weights: 16
-            // neighbouring columns of 32 rows, 32 bytes of a row per pair of lanes; one weight, where few waves have ranks: 16 bytes of
-            // each group (us: two shared experts of rank 128 in a layer 742 / 744, r = 64 of a single linear 81.6 / 81.1).
+            // Piece t of chunk c of V; out of range (inactive stream, ragged K tail) reads zero.  Two weights: 16 neighbouring
+            // columns of 32 rows, 32 bytes of a row per pair of lanes (lanes i and i + 32 exchange pieces t and t + 4 when they are
+            // there, which makes them the fragments of steps 2 t and 2 t + 1); one weight, where few waves have ranks: the fragment of
+            // step t, 16 bytes of each group (us, near / fragments: two shared experts of rank 128 in a layer 745 / 752, r = 64 of a
+            // single linear 81.6 / 81.1).
             constexpr bool NEAR = NW == 2;
             auto load_v = [&](int c, int s, int t) -> u32x4 {
                 const bool out = !active[s] || c >= c_hi || (ktail && c == nchunks - 1 && (NEAR ? t >= 4 : h == 1));
@@ -300,6 +302,18 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
 #pragma unroll
                     for (int t = 0; t < 8; ++t)
                         asm volatile("" : "+v"(va[s][t].x), "+v"(va[s][t].y), "+v"(va[s][t].z), "+v"(va[s][t].w));
+                if constexpr (NEAR) {
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const u32x2 x = __builtin_amdgcn_permlane32_swap(va[s][t][e], va[s][t + 4][e], false, false);
+                                va[s][t][e] = x.x;
+                                va[s][t + 4][e] = x.y;
+                            }
+                }
                 __syncthreads();
                 if (c + 1 < c_hi) issue_x(c + 1);
                 const unsigned char* xs = smem + (c & 1) * STAGE + i32 * 256;
@@ -308,10 +322,11 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
                 if (active[0] || active[1]) {
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
-                        mfma_step(xs, sx, NEAR ? 2 * t + h : 8 * h + t, __builtin_bit_cast(f16x8, va[0][t]), __builtin_bit_cast(f16x8, va[1][t]));
-                        // the registers of this step are free again: fetch the next chunk's fragment into them
-                        va[0][t] = load_v(c + 1, 0, t);
-                        va[1][t] = load_v(c + 1, 1, t);
+                        const int p = NEAR ? t / 2 + 4 * (t & 1) : t;
+                        mfma_step(xs, sx, t, __builtin_bit_cast(f16x8, va[0][p]), __builtin_bit_cast(f16x8, va[1][p]));
+                        // the registers of this step are free again: fetch the next chunk's piece into them
+                        va[0][p] = load_v(c + 1, 0, p);
+                        va[1][p] = load_v(c + 1, 1, p);
                     }
                 }
             }

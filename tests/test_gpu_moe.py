@@ -397,6 +397,30 @@ def test_few_rows_per_expert(H, F, E, topk, T, ranks, dtype):
         _check(case, int3=dtype == "int3")
 
 
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+def test_a_row_does_not_depend_on_the_height_of_its_tile(dtype):
+    # 560 pairs in 32-row tiles, the same tokens among ten times as many in 128-row tiles: T = X V^T is read from memory, or staged
+    # with ranks up to 32, and every sum has one order
+    import torch
+    from paper_2504_02658_amd import api
+    E, H, F, dt = 24, 1088, 384, torch.bfloat16 if dtype == "bf16" else torch.float16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    experts = [tuple(api.pack_w3(randn(n, k) * 0.05).with_compensator((randn(n, r) * 0.1).to(dt), (randn(r, k) * 0.1).to(dt))
+                     for n, k in ((F, H), (F, H), (H, F))) for r in (8, 24, 32, 40) * 6]
+    layer = api.MoELayer(experts, H, F, bf16=dtype == "bf16")
+    X = randn(1400, H).to(dt)
+    ids = torch.rand((1400, E), generator=g, device="cuda").argsort(dim=1)[:, :4].to(torch.int32).contiguous()
+    ids[:40, 0] = 0                                         # more than 32 rows of one expert: several tiles
+    gates = torch.rand((1400, 4), generator=g, device="cuda")
+    tall = layer.forward(X, ids, gates).clone()
+    assert_rows_per_tile(layer, ids.cpu().numpy(), 128)
+    low = layer.forward(X[:140].clone(), ids[:140].clone(), gates[:140].clone())
+    assert_rows_per_tile(layer, ids[:140].cpu().numpy(), 32)
+    assert torch.equal(low, tall[:140])
+
+
 @pytest.mark.parametrize("T", [20, 600])      # streamed, 128-row tiles
 def test_swiglu_at_the_ends_of_its_range(T):
     # Gates from -88.5 to 88.5, up projections of 2^100: below a gate of -87.3 the quotient's denominator is above 2^126, its reciprocal
