@@ -110,17 +110,19 @@ static double gemm_tiled_estimate(int mb, int64_t M, int64_t N, int64_t K, int r
     if (r > 0) t += f.lr + f.rank32 * (double)r / 32.0;
     return t;
 }
-// Tile height of a call: by rows, or the other of 64 and 128 rows where the estimates say that it is clearly the faster one, as
-// how evenly the tiles fill the chip and whether K has to be split depend on the whole shape.  us, by rows / now: 1024 rows of
-// 4096 x 4096 59 / 44, 512 of 14336 x 4096 77 / 71, 512 of 8192 x 8192 89 / 81, 384 of 11008 x 4096 64 / 59.  Of 4726 drawn problems that
-// the tiled kernel takes 1338 change; the geometric mean over all is 5 % faster, 61 are slower by more than 2 % and 19 by more than
-// 5 %, at worst 1.2 times.  (Without the factor 1.13 it is 6 %, and about 60 are slower by more than 5 %.  With a compensator and
-// a very short K the wait for T decides, which the estimates have no part for: 620 rows of 11360 x 576, r = 32, 128-row tiles 21, 64-row
-// tiles 35.)
+// Tile height of a call: by rows, or 64 instead of 128 rows where the estimates say that this is clearly the faster one, as
+// how evenly the tiles fill the chip and whether K has to be split depend on the whole shape.  us, 128-row tiles / now: 512 rows of
+// 14336 x 4096, r = 32 77 / 70, 2048 of 2048 x 2048, r = 32 37 / 27, 1024 of 2048 x 1408, r = 32 27 / 19, 4096 of 1408 x 2048, r = 64
+// 56 / 42.  Not where K would be split less than half as often: few workgroups with a long share of K each were up to 14 % slower (605
+// rows of 8192 x 5504, INT3 r = 20: 3 splits 74, none 84).  Of 3290 drawn problems that change (all types, ranks to 128) the
+// geometric mean is 1.24 times as fast, 27 are slower by more than 2 % and 3 by more than 5 %, at worst by 9 % (2000 rows of
+// 560 x 5312 34 / 37).  (129 to 384 rows in 128-row tiles: 16 of 24 that the estimates
+// chose were slower by more than 2 %, at worst by 14 %.)
 static int gemm_mb(int64_t M, int64_t N, int64_t K, int r) {
     const int mb = gemm_mb_by_rows(M);
-    if (gemm_mb_override() || M < 129 || M > 4096 || r > 128 || (r > 0 && K < 768)) return mb;        // (measured there)
-    return 1.13 * gemm_tiled_estimate(6 - mb, M, N, K, r) < gemm_tiled_estimate(mb, M, N, K, r) ? 6 - mb : mb;
+    if (gemm_mb_override() || mb != 4 || M > 4096 || r > 128 ||         // (measured there)
+        gemm_splits(4, M, N, K, r) > 2 * gemm_splits(2, M, N, K, r)) return mb;
+    return 1.13 * gemm_tiled_estimate(2, M, N, K, r) < gemm_tiled_estimate(4, M, N, K, r) ? 2 : 4;
 }
 
 // Adds the fp32 partial sums of the K splits in split order and rounds once.
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict
 }
 
 size_t milo::gemm_flags_behind(int64_t M) {
-    const int64_t bm = 32 * gemm_mb_by_rows(M), tiles = (M + bm - 1) / bm;      // (another height only below 4096 rows, where all fit)
+    const int64_t bm = 32 * gemm_mb_by_rows(M), tiles = (M + bm - 1) / bm;      // (another height only up to 4096 rows, where all fit)
     return tiles > kTiledFlagTiles ? align_up((size_t)tiles * 16, 256) : 0;
 }
 
@@ -154,10 +156,13 @@ static bool gemm_shape_ok(int64_t M, int64_t N, int64_t K) {
     return M >= 1 && M <= (int64_t)0x3fffffff && weight_shape_ok(N, K);
 }
 
-// What a tiled call needs at a tile height.
-static size_t gemm_tiled_bytes(int mb, int64_t M, int64_t N, int64_t K, int r) {
+size_t milo::gemm_workspace_min(int64_t M, int64_t N, int64_t K, int r) {
+    if (!gemm_shape_ok(M, N, K) || r < 0) return 0;
+    if (gemm_takes_decode(M, N, K, r)) return decode_workspace_min(N, K, r);
     // head | flag words that do not fit in it | T = X V^T, fp16 [M x pad16(r)] | its fp32 partials per part of K | with K
-    // splits, their fp32 partial sums [M x N] each
+    // splits, their fp32 partial sums [M x N] each.  (At the tile height by rows: 64 instead of 128 rows make no fewer tiles, so
+    // no more K splits and no more parts of T, and need no more.)
+    const int mb = gemm_mb_by_rows(M);
     const size_t parts = (size_t)gemm_t_parts(mb, M, N, K, r);
     const int splits = gemm_splits(mb, M, N, K, r);
     return kGemmHeadBytes + gemm_flags_behind(M) +
@@ -166,24 +171,43 @@ static size_t gemm_tiled_bytes(int mb, int64_t M, int64_t N, int64_t K, int r) {
            (splits > 1 ? align_up((size_t)splits * (size_t)M * (size_t)N * 4, 256) : 0);
 }
 
-// (The height by rows sets the limit: a call with less than its own height asks for takes that one.)
-size_t milo::gemm_workspace_min(int64_t M, int64_t N, int64_t K, int r) {
-    if (!gemm_shape_ok(M, N, K) || r < 0) return 0;
-    if (gemm_takes_decode(M, N, K, r)) return decode_workspace_min(N, K, r);
-    return gemm_tiled_bytes(gemm_mb_by_rows(M), M, N, K, r);
-}
-
 // A workspace sized for a prefill serves decode calls on the same weight at full speed as well: room for either.  (With one
 // sized for 4096 rows of 4096 x 14336, r = 0, a decode of 16 rows took 12.3 us, the other kernel, instead of 10.9.)
 extern "C" size_t milo_w3lr_gemm_workspace(int64_t M, int64_t N, int64_t K, int r) {
-    size_t need = gemm_workspace_min(M, N, K, r);
+    const size_t need = gemm_workspace_min(M, N, K, r);
     if (need == 0) return 0;
-    if (!gemm_takes_decode(M, N, K, r)) {
-        const size_t own = gemm_tiled_bytes(gemm_mb(M, N, K, r), M, N, K, r);
-        if (own > need) need = own;
-    }
     const size_t decode = decode_workspace_bytes(N, K, r);
     return need > decode ? need : decode;
+}
+
+// The kernel that a call takes.
+struct GemmPlan {
+    bool decode, mid;
+    MidPlan mid_plan;
+    int mb, splits;     // the tiled kernel: tile height / 32, K splits
+};
+static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int r, unsigned flags) {
+    GemmPlan p = {};
+    p.decode = gemm_takes_decode(M, N, K, r);
+    if (p.decode) return p;
+    // Batches whose tiles do not fill the chip: one launch without K splits.  Its T needs no more scratch than the tiled one's
+    // (no more parts, and no 16-bit copy), so every workspace that is accepted serves either.
+    const int by_rows = gemm_mb_by_rows(M);
+    p.mid = !gemm_mb_override() && plan_mid(M, N, K, r, r > 0 && (flags & MILO_LR_INT3) != 0, by_rows, gemm_splits(by_rows, M, N, K, r),
+                                            r > 0 ? tiled_t_parts(K) : 0, &p.mid_plan);
+    p.mb = p.mid ? by_rows : gemm_mb(M, N, K, r);
+    p.splits = gemm_splits(p.mb, M, N, K, r);
+    return p;
+}
+
+// For tests (not declared in milo.h): the plan of a call that is accepted.  Returns 0 for the decode kernel, 1 for the one of
+// gemm_mid.hip, 2 for the tiled one; *rows: rows of a tile, *parts: feature streams of a wave (1) or K splits (2).
+extern "C" int milo_gemm_route(int64_t M, int64_t N, int64_t K, int r, unsigned flags, int* rows, int* parts) {
+    const GemmPlan p = plan_gemm(M, N, K, r, flags);
+    *rows = p.decode ? 16 : 32 * p.mb;
+    *parts = p.splits;
+    if (p.mid) mid_plan_shape(p.mid_plan, rows, parts);
+    return p.decode ? 0 : p.mid ? 1 : 2;
 }
 
 extern "C" int milo_w3lr_gemm(const milo_half* X, int64_t M, int64_t N, int64_t K, const void* q3,
@@ -206,7 +230,6 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
         if (r > MILO_LR3_MAX_RANK) return MILO_ERR_RANK;
         if ((N % kGroup) != 0) return MILO_ERR_SHAPE;
     }
-    const bool decode = gemm_takes_decode(M, N, K, r);
     if (!workspace || workspace_bytes < gemm_workspace_min(M, N, K, r)) return MILO_ERR_WORKSPACE;
     if (!aligned16(X) || !aligned16(q3) ||
         !aligned16(Y) || !aligned16(workspace) || (r > 0 && (!aligned16(U) || !aligned16(V))))
@@ -219,7 +242,8 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     w.V = reinterpret_cast<const f16*>(V);
     w.r = r;
     w.flags = flags;
-    if (decode) {
+    const GemmPlan plan = plan_gemm(M, N, K, r, flags);
+    if (plan.decode) {
         // 32-bit buffer offsets in the decode kernel
         if ((uint64_t)M * K * 2 >= 0xFFFFFFF0ull || ((uint64_t)r + 128) * K * 2 >= 0xFFFFFFF0ull ||
             (uint64_t)N * (uint64_t)(r > 0 ? r : 1) * 2 >= 0xFFFFFFF0ull)
@@ -236,32 +260,24 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     f16* T = reinterpret_cast<f16*>(ws + kGemmHeadBytes + flags_behind);
     const int64_t ldt = rank_pad(r);
 
-    // Batches whose tiles do not fill the chip: one launch without K splits.  Its T needs no more scratch than the tiled one's
-    // (no more parts, and no 16-bit copy), so every workspace that is accepted serves either.
-    const int by_rows = gemm_mb_by_rows(M);
-    MidPlan mid;
-    const bool takes_mid = !gemm_mb_override() && plan_mid(M, N, K, r, (flags & MILO_LR_INT3) != 0, by_rows, gemm_splits(by_rows, M, N, K, r),
-                                                           r > 0 ? tiled_t_parts(K) : 0, &mid);
-    int mb = takes_mid ? by_rows : gemm_mb(M, N, K, r);
-    if (mb != by_rows && workspace_bytes < gemm_tiled_bytes(mb, M, N, K, r)) mb = by_rows;
+    const int mb = plan.mb, splits = plan.splits;
     const int bm = 32 * mb;
     const int64_t m_tiles = (M + bm - 1) / bm;
     if (m_tiles > 65535) return MILO_ERR_SHAPE;
     const int parts = gemm_t_parts(mb, M, N, K, r);
-    const int splits = gemm_splits(mb, M, N, K, r);
     if ((uint64_t)M * K * 2 >= 0x80000000ull || ((uint64_t)r + 256) * K * 2 >= 0xFFFFFFF0ull ||
         (uint64_t)(parts > 0 ? parts : 1) * M * ldt * 4 >= 0xFFFFFFF0ull || (N & 3) != 0)
         return MILO_ERR_SHAPE;                                          // 32-bit offsets in the kernel
-    if (takes_mid) {
+    if (plan.mid) {
         MidArgs ma;
         ma.X = reinterpret_cast<const f16*>(X); ma.Y = reinterpret_cast<f16*>(Y);
         ma.M = (uint32_t)M; ma.N = (uint32_t)N; ma.K = (uint32_t)K; ma.x_bytes = (uint32_t)(M * K * 2);
         ma.w = w; ma.ldt = (uint32_t)ldt;
-        ma.T = reinterpret_cast<float*>(T); ma.t_bytes = (uint32_t)(mid.t_parts * M * ldt * 4);
+        ma.T = reinterpret_cast<float*>(T); ma.t_bytes = (uint32_t)(plan.mid_plan.t_parts * M * ldt * 4);
         ma.epoch = reinterpret_cast<unsigned long long*>(ws + kGemmCountersAt);
         ma.ready = reinterpret_cast<unsigned long long*>(ws + kGemmGranulesAt) + kDecSplitFrags * 256;
         ma.status = ctrl + 3;
-        return launch_mid(ma, mid, stream);
+        return launch_mid(ma, plan.mid_plan, stream);
     }
     float* Tp = reinterpret_cast<float*>(reinterpret_cast<char*>(T) + align_up((size_t)M * (size_t)ldt * 2 + 256, 256));
     float* partial = reinterpret_cast<float*>(

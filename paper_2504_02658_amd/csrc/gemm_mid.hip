@@ -528,6 +528,11 @@ bool plan_mid(int64_t M, int64_t N, int64_t K, int r, bool lr3, int mb, int spli
     return p->form >= 0;
 }
 
+void mid_plan_shape(const MidPlan& p, int* rows, int* streams) {
+    *rows = kMidForms[p.form].rows;
+    *streams = kMidForms[p.form].streams;
+}
+
 int launch_mid(MidArgs a, const MidPlan& p, hipStream_t stream) {
     const MidForm& f = kMidForms[p.form];
     a.tile_rows = f.rows;

@@ -207,6 +207,7 @@ constexpr int kMidMaxWorkers = kDecSplitMax;        // tagged words, in the plac
 // Whether that kernel takes a problem the tiled one would run with tiles of 32 mb rows, `splits` K splits and t_parts parts of T.
 bool plan_mid(int64_t M, int64_t N, int64_t K, int r, bool lr3, int mb, int splits, int t_parts, MidPlan* p);
 int launch_mid(MidArgs a, const MidPlan& p, hipStream_t stream);
+void mid_plan_shape(const MidPlan& p, int* rows, int* streams);     // rows of a tile, 32-feature streams of a wave
 
 size_t decode_workspace_bytes(int64_t N, int64_t K, int r);    // what a call is to bring
 size_t decode_workspace_min(int64_t N, int64_t K, int r);      // what it has to (without room for the long-K kernel's granules)

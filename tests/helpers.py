@@ -37,6 +37,20 @@ def assert_rows_per_tile(layer, ids, rows):
     assert heights == [rows] or rows == 128 and heights[-1] == rows, (heights, rows, int(n.max()))
 
 
+DECODE, MID, TILED = 0, 1, 2
+
+
+def gemm_route(M, N, K, r, flags=0):
+    """Which kernel a linear takes (the library's own plan of the call, for the current device or, without one, for 256 CUs):
+    (DECODE, 16, 0), (MID, rows of a tile, feature streams of a wave) or (TILED, rows of a tile, K splits)."""
+    import ctypes
+    from paper_2504_02658_amd import api
+    rows, parts = ctypes.c_int(0), ctypes.c_int(0)
+    i64 = ctypes.c_int64
+    kind = api.lib().milo_gemm_route(i64(M), i64(N), i64(K), r, ctypes.c_uint(flags), ctypes.byref(rows), ctypes.byref(parts))
+    return kind, rows.value, parts.value
+
+
 def oracle_weight(W, r, seed=0, exact_svd_limit=1024 * 1024, symmetric=False):
     """Quantize W on the CPU and fit the rank-r compensator to the residual."""
     q, s, z = oracle.quantize_sym(W) if symmetric else oracle.quantize_rtn(W)
