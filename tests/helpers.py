@@ -40,6 +40,16 @@ def assert_rows_per_tile(layer, ids, rows):
 DECODE, MID, TILED = 0, 1, 2
 
 
+# Linears that take the tiled kernel whatever the type: M, N, K, r, rows of a tile, K splits
+TILED_LINEARS = [
+    (33, 11136, 64, 0, 32, 1), (17, 64, 12032, 20, 32, 11), (31, 64, 12224, 40, 32, 12), (31, 256, 14272, 72, 32, 14), (48, 528, 2112, 136, 32, 2),
+    (1201, 128, 64, 32, 64, 1), (1300, 192, 192, 72, 64, 1), (1201, 192, 128, 128, 64, 1), (96, 64, 14272, 20, 64, 14),
+    (1201, 64, 2112, 40, 64, 2), (1300, 240, 2112, 0, 64, 2), (1201, 128, 2112, 72, 64, 2), (100, 512, 2112, 136, 64, 2),
+    (600, 10944, 64, 8, 128, 1), (513, 14272, 64, 64, 128, 1), (600, 13248, 128, 72, 128, 1), (1300, 64, 9152, 8, 128, 9),
+    (1300, 64, 10048, 64, 128, 9), (1201, 128, 12416, 72, 128, 12), (400, 528, 2112, 200, 128, 2), (4200, 272, 1088, 24, 128, 1), (4200, 144, 320, 0, 128, 1),
+]
+
+
 def gemm_route(M, N, K, r, flags=0):
     """Which kernel a linear takes (the library's own plan of the call, for the current device or, without one, for 256 CUs):
     (DECODE, 16, 0), (MID, rows of a tile, feature streams of a wave) or (TILED, rows of a tile, K splits)."""

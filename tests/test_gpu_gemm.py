@@ -1,10 +1,10 @@
-"""GPU parity of milo_w3lr_gemm against the fp64 oracle (decode kernel for M <= 16, tiled above)."""
+"""GPU parity of milo_w3lr_gemm against the fp64 oracle, all three kernels."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2504_02658_amd import workloads as wl
-from helpers import assert_close, oracle_weight, gpu_weight
+from helpers import MID, TILED, TILED_LINEARS, assert_close, gemm_route, oracle_weight, gpu_weight
 
 pytestmark = pytest.mark.gpu
 
@@ -227,29 +227,19 @@ def test_tiled_shapes(N, K, r):
     _check_case(96, N, K, r, seed=N + K + r)
 
 
-@pytest.mark.parametrize("M,N,K,r", [
-    (17, 16, 64, 8), (31, 48, 128, 0), (32, 80, 192, 20), (33, 64, 1088, 33),       # one wave with work, ragged bands and chunks
-    (79, 14336, 1024, 24), (80, 14400, 1024, 16), (65, 12816, 1536, 0),             # the one tile of eighty rows
-    (81, 528, 2112, 128), (160, 1024, 4160, 48), (257, 272, 1408, 17),              # several tiles, parts of T that differ in length
-    (40, 512, 14336, 64), (700, 512, 512, 128),                                     # eight parts of T; more than 64 of its blocks
-    (64, 14352, 512, 1), (130, 8208, 704, 40), (1200, 592, 640, 8),                 # two streams per wave; the most rows
-    (48, 528, 2112, 136), (100, 512, 2112, 136),                                    # above its ranks: 32- and 64-row tiles
-])
-@pytest.mark.parametrize("dtype", ["fp16", "symmetric", "bf16", "int3"])
-def test_batches_between_decode_and_full_tiles(M, N, K, r, dtype):
+FLAGS = {"fp16": 0, "symmetric": 1, "int3": 2, "bf16": 4}       # of milo.h
+
+
+def _typed_case(M, N, K, r, dtype):
+    """Activations, weight and the oracle's result, with a low-rank term larger than the product: its errors show."""
     import torch
     from paper_2504_02658_amd import api
-    if dtype == "int3":
-        N = (N + 63) // 64 * 64
-        if r == 0 or r > 128:
-            return
     g = torch.Generator()
     g.manual_seed(M + N + K + r)
     randn = lambda *shape: torch.randn(shape, generator=g)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float16
-    r = min(r, N, K)
     X, W = randn(M, K).to(dt), (randn(N, K) * 0.02).numpy()
-    U, V = randn(N, r) * 0.1, randn(r, K) * 0.1         # a low-rank term larger than the product: its errors show
+    U, V = randn(N, r) * 0.1, randn(r, K) * 0.1
     q, s, z = oracle.quantize_sym(W) if dtype == "symmetric" else oracle.quantize_rtn(W)
     pw = api.pack_w3(torch.from_numpy(W).cuda(), symmetric=dtype == "symmetric")
     Ud, Vd = U.to(dt).double().numpy(), V.to(dt).double().numpy()
@@ -258,12 +248,77 @@ def test_batches_between_decode_and_full_tiles(M, N, K, r, dtype):
         Ud, Vd = oracle.dequantize_compensator(*oracle.quantize_compensator(U.numpy(), V.numpy()), r)
     elif r:
         pw = pw.with_compensator(U.to(dt).cuda(), V.to(dt).cuda())
-    ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, r))
-    Y = api.w3lr_gemm(X.cuda(), pw, workspace=ws)
-    assert torch.equal(api.w3lr_gemm(X.cuda(), pw, workspace=ws), Y) and api.workspace_status(ws) == 0
-    ref = oracle.w3lr_linear(X.double().numpy(), q, s, z, Ud, Vd)
+    return X.cuda(), pw, oracle.w3lr_linear(X.double().numpy(), q, s, z, Ud, Vd)
+
+
+def _assert_typed_close(Y, ref, dtype):
     # One rounding to 16 bits of each weight, of T and of the output; fp16 2^-11 each at most, bf16 2^-8, a third of that in the mean.
     assert np.linalg.norm(Y.double().cpu().numpy() - ref) <= (8.0 if dtype == "bf16" else 1.0) * 2.0 ** -11 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("M,N,K,r,form", [
+    (17, 16, 64, 8, (32, 1)), (31, 48, 128, 0, (32, 1)), (32, 80, 192, 20, (32, 1)),        # one wave with work, ragged bands and chunks
+    (33, 64, 1088, 33, (32, 1)),
+    (79, 14336, 1024, 24, (80, 2)), (80, 14400, 1024, 16, (80, 2)), (65, 12816, 1536, 0, (80, 2)),      # the one tile of eighty rows
+    (81, 528, 2112, 128, (32, 1)), (160, 1024, 4160, 48, (32, 1)), (257, 272, 1408, 17, (32, 1)),   # several tiles, parts of T that differ in length
+    (40, 512, 14336, 64, (32, 1)), (700, 512, 512, 128, (32, 1)),                           # eight parts of T; more than 64 of its blocks
+    (64, 14352, 512, 1, (64, 2)), (130, 8208, 704, 40, (32, 2)), (1200, 592, 640, 8, (64, 2)),      # two streams per wave; the most rows
+])
+@pytest.mark.parametrize("dtype", ["fp16", "symmetric", "bf16", "int3"])
+def test_batches_between_decode_and_full_tiles(M, N, K, r, form, dtype):
+    import torch
+    from paper_2504_02658_amd import api
+    if dtype == "int3":
+        if r == 0:
+            pytest.skip("no compensator")
+        N = (N + 63) // 64 * 64
+        if (M, N) in ((40, 512), (64, 14400), (130, 8256)):
+            pytest.skip("goes to the tiled kernel")
+    kind, rows, streams = gemm_route(M, N, K, r, FLAGS[dtype])
+    assert kind == MID and ((rows, streams) == form or dtype == "int3")
+    X, pw, ref = _typed_case(M, N, K, r, dtype)
+    ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, r))
+    Y = api.w3lr_gemm(X, pw, workspace=ws)
+    assert torch.equal(api.w3lr_gemm(X, pw, workspace=ws), Y) and api.workspace_status(ws) == 0
+    _assert_typed_close(Y, ref, dtype)
+
+
+@pytest.mark.parametrize("M,N,K,r,rows,splits", TILED_LINEARS)
+@pytest.mark.parametrize("dtype", ["fp16", "symmetric", "bf16", "int3"])
+def test_tiled_linear(M, N, K, r, rows, splits, dtype):
+    # each tile height, with and without K splits, on both sides of the rank limits of the paths that form T (32, 64), odd numbers
+    # of groups, ragged rows; what lies behind the state may hold anything; captured calls replay with eager work in between
+    import torch
+    from paper_2504_02658_amd import api
+    if dtype == "int3" and not 0 < r <= 128:
+        pytest.skip("no such compensator")
+    if dtype == "int3":
+        N = (N + 63) // 64 * 64
+    assert gemm_route(M, N, K, r, FLAGS[dtype]) == (TILED, rows, splits)
+    X, pw, ref = _typed_case(M, N, K, r, dtype)
+    ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, r))
+    Y = api.w3lr_gemm(X, pw, workspace=ws).clone()
+    _assert_typed_close(Y, ref, dtype)
+    ws[59648:].fill_(0xa5)                                      # MILO_WORKSPACE_STATE_BYTES
+    out = torch.empty_like(Y)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        api.w3lr_gemm(X, pw, out=out, workspace=ws)
+        api.w3lr_gemm(X, pw, out=out, workspace=ws)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, Y)
+        assert torch.equal(api.w3lr_gemm(X, pw, workspace=ws), Y)
+    assert api.workspace_status(ws) == 0
+
+
+def test_tiled_linears_on_a_shared_workspace():
+    # split sums, T and partials of tiled calls where others keep theirs; M-tiles on both sides of the 128 lines of their words
+    _shared_workspace_sequence([
+        (31, 64, 12224, 40), (1201, 64, 2112, 40), (77, 256, 1024, 32), (1300, 64, 10048, 64), (16, 1024, 8192, 32), (96, 64, 14272, 20),
+        (8192, 64, 512, 40), (8192 + 40, 64, 512, 40), (1201, 128, 12416, 72), (4, 256, 1024, 32), (16384 + 40, 128, 512, 72), (31, 64, 12224, 40)])
 
 
 @pytest.mark.parametrize("M,N,K,r", [(8, 1024, 1024, 512), (12, 528, 2112, 136), (200, 1024, 1024, 512),
@@ -433,8 +488,8 @@ def test_c2_mixtral_down_projection_prefill():
 
 
 def test_k_splits_and_t_parts_many_chunks():
-    # few tiles and a long K: the tiled kernel splits K over workgroups (partial sums added in
-    # order by a second kernel) and forms X V^T in several parts; odd number of groups as well
+    # few tiles and a long K: the whole of it in each workgroup, X V^T in several parts; odd number of groups as well (K splits
+    # of the tiled kernel: test_tiled_linear)
     _check_case(48, 512, 4096, 24, seed=301)
     _check_case(200, 256, 8256, 72, seed=302)           # 129 groups
 
@@ -501,7 +556,8 @@ def test_workspace_status_reports_a_wait_that_gave_up():
     # stays there until the workspace is prepared again; a clean run reports MILO_OK.
     import torch
     from paper_2504_02658_amd import api
-    for M in (16, 96):                                  # decode and tiled workspaces
+    for M in (16, 96, 1300):                            # workspaces of the three kernels
+        assert gemm_route(M, 512, 1024, 16)[0] == {16: 0, 96: MID, 1300: TILED}[M]
         case = wl.LinearCase("t", M=M, N=512, K=1024, r=16, seed=31)
         X, W = wl.linear_inputs(case)
         ow = oracle_weight(W, 16)

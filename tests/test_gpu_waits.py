@@ -6,7 +6,7 @@ import ctypes
 import numpy as np
 import pytest
 
-from helpers import STREAMED, assert_rows_per_tile
+from helpers import STREAMED, TILED, TILED_LINEARS, assert_rows_per_tile, gemm_route
 from paper_2504_02658_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -44,6 +44,34 @@ def test_counted_waits_equal_full_waits(M, N, K, r):
     b = _gemm(full, X, q3, U, V, r, N)
     assert np.array_equal(a.view(np.uint16), b.view(np.uint16))
     assert np.all(np.isfinite(a)) and np.any(a != 0)
+
+
+@pytest.mark.parametrize("M,N,K,r,rows,splits", TILED_LINEARS)
+@pytest.mark.parametrize("dtype", ["fp16", "symmetric", "bf16", "int3"])
+def test_tiled_linear_counted_waits_equal_full_waits(monkeypatch, M, N, K, r, rows, splits, dtype):
+    # (above sixteen rows the cases further up take a kernel that counts no waits)
+    import torch
+    from paper_2504_02658_amd import api
+    if dtype == "int3":
+        N, r = (N + 63) // 64 * 64, min(r, 128)
+        if r == 0 or gemm_route(M, N, K, r, 2)[0] != TILED:
+            pytest.skip("no compensator, or not the tiled kernel without ranks above 128")
+    else:
+        assert gemm_route(M, N, K, r, {"fp16": 0, "symmetric": 1, "bf16": 4}[dtype]) == (TILED, rows, splits)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K + r)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    pw, X = api.pack_w3(randn(N, K) * 0.02, symmetric=dtype == "symmetric"), randn(M, K).to(dt)
+    if r:
+        U, V = randn(N, r) * 0.1, randn(r, K) * 0.1
+        pw = pw.with_int3_compensator(*api.pack_lr3(U, V), r) if dtype == "int3" else pw.with_compensator(U.to(dt), V.to(dt))
+    call = lambda: api.w3lr_gemm(X, pw, workspace=api.new_workspace(api.gemm_workspace_bytes(M, N, K, r)))
+    Y1 = call()
+    with monkeypatch.context() as m:
+        m.setattr(api, "_lib", api.bind(api.FULLWAITS_LIB_PATH))
+        Y2 = call()
+    assert torch.equal(Y1, Y2) and bool(torch.isfinite(Y1.float()).all()) and bool((Y1 != 0).any())
 
 
 @pytest.mark.parametrize("T,H,F,E,topk,ranks,zipf,rows", [

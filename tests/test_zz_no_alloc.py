@@ -24,10 +24,11 @@ def _weight(N, K, r, seed):
 def test_static_scratch_entry_matches_the_workspace_entry():
     import torch
     from paper_2504_02658_amd import api
-    # two calls in a row, the second with a smaller input; decode kernel, then tiled kernel
+    # two calls in a row, the second with a smaller input; decode kernel, the kernel of small batches, tiled kernel (the last pair)
     for shapes in (((16, 1024, 4096, 32), (4, 272, 1408, 8)),
                    ((96, 512, 2048, 24), (40, 256, 832, 0)),
-                   ((16, 1024, 4096, 32), (48, 512, 4096, 24))):
+                   ((16, 1024, 4096, 32), (48, 512, 4096, 24)),
+                   ((1201, 64, 2112, 40), (17, 64, 12032, 20))):
         outs = []
         for (M, N, K, r) in shapes:
             pw = _weight(N, K, r, seed=M + N + K + r)
