@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kFewThreads, 4) void w3lr_few_kernel(const FewArgs 
     const size_t at = (size_t)orow * a.N + nb16 + 4 * q;
     f32x4 o;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = NW == 2 ? silu(sum[0][e]) * sum[NW - 1][e] : scale * sum[0][e];
+    for (int e = 0; e < 4; ++e) o[e] = NW == 2 ? silu<BF>(sum[0][e]) * sum[NW - 1][e] : scale * sum[0][e];
     if (NW == 2) *reinterpret_cast<u32x2*>(static_cast<f16*>(a.out) + at) = few_pack4<BF>(o);
     else *reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + at) = o;
 }

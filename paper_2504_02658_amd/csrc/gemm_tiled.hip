@@ -889,7 +889,7 @@ __global__ __launch_bounds__(kTiledThreads, 2) void w3lr_tiled_kernel(const Tile
             for (int vq = 0; vq < 4; ++vq) {
                 float g[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) g[e] = silu(acc[0][mb][4 * vq + e]) * acc[1][mb][4 * vq + e];
+                for (int e = 0; e < 4; ++e) g[e] = silu<BF>(acc[0][mb][4 * vq + e]) * acc[1][mb][4 * vq + e];
                 if (BF) {
                     o[vq] = u32x2{pack_bf16(g[0], g[1]), pack_bf16(g[2], g[3])};
                 } else {

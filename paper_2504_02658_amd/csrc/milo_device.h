@@ -509,13 +509,18 @@ __device__ __forceinline__ f16x8 load_f16x8(const f16* p) {
     return __builtin_bit_cast(f16x8, *reinterpret_cast<const u32x4*>(p));
 }
 
-// a / (1 + exp(-a)).  The quotient from the hardware's reciprocal and one correction by its remainder.  The reciprocal of more than
-// 2^126 would be below the normal numbers and comes out as zero (gates from -88.7 to -87.3, whose quotient is a normal
-// number still), so numerator and denominator are both taken four times smaller, which costs a multiplication and is exact
-// but for gates below 2^-124; an infinite denominator is mended by the fixup.  The compiler's division scales both by tests
-// of their exponents, two instructions and two more in the correction.
+// a / (1 + exp(-a)).  The quotient from the hardware's reciprocal and one correction by its remainder; an infinite denominator is
+// mended by the fixup.  (The compiler's division scales numerator and denominator by tests of their exponents, two instructions and
+// two more in the correction.)
+// The reciprocal of more than 2^126 would be below the normal numbers and comes out as zero: gates from -88.7 to -87.3, whose
+// quotient is a normal number still.  For bf16 both are therefore taken four times smaller, which costs a multiplication and is
+// exact but for gates below 2^-124.  In fp16 there is nothing to see of it: an up projection below 2^60 (65504 for activations,
+// weights and factors, K below 2^26) times 2^-119 is zero of the same sign (us, with / without the multiplication: DeepSeek-shaped
+// layer of 4096 tokens 742 / 738, Mixtral-shaped one of 512 477 / 474).
+template <bool BF>
 __device__ __forceinline__ float silu(float a) {
-    const float d = __builtin_fmaf(__expf(-a), 0.25f, 0.25f), n = 0.25f * a, r = __builtin_amdgcn_rcpf(d), q = n * r;
+    const float d = BF ? __builtin_fmaf(__expf(-a), 0.25f, 0.25f) : 1.0f + __expf(-a), n = BF ? 0.25f * a : a;
+    const float r = __builtin_amdgcn_rcpf(d), q = n * r;
     return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, q, n), r, q), d, n);
 }
 
