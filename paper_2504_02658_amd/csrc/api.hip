@@ -180,16 +180,14 @@ extern "C" size_t milo_w3lr_gemm_workspace(int64_t M, int64_t N, int64_t K, int 
     return need > decode ? need : decode;
 }
 
-// The kernel that a call takes.
+// The kernel that a call beyond the decode sizes takes.
 struct GemmPlan {
-    bool decode, mid;
+    bool mid;
     MidPlan mid_plan;
     int mb, splits;     // the tiled kernel: tile height / 32, K splits
 };
 static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int r, unsigned flags) {
-    GemmPlan p = {};
-    p.decode = gemm_takes_decode(M, N, K, r);
-    if (p.decode) return p;
+    GemmPlan p;
     // Batches whose tiles do not fill the chip: one launch without K splits.  Its T needs no more scratch than the tiled one's
     // (no more parts, and no 16-bit copy), so every workspace that is accepted serves either.
     const int by_rows = gemm_mb_by_rows(M);
@@ -203,11 +201,16 @@ static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int r, unsigned flags
 // For tests (not declared in milo.h): the plan of a call that is accepted.  Returns 0 for the decode kernel, 1 for the one of
 // gemm_mid.hip, 2 for the tiled one; *rows: rows of a tile, *parts: feature streams of a wave (1) or K splits (2).
 extern "C" int milo_gemm_route(int64_t M, int64_t N, int64_t K, int r, unsigned flags, int* rows, int* parts) {
+    if (gemm_takes_decode(M, N, K, r)) {
+        *rows = 16;
+        *parts = 0;
+        return 0;
+    }
     const GemmPlan p = plan_gemm(M, N, K, r, flags);
-    *rows = p.decode ? 16 : 32 * p.mb;
+    *rows = 32 * p.mb;
     *parts = p.splits;
     if (p.mid) mid_plan_shape(p.mid_plan, rows, parts);
-    return p.decode ? 0 : p.mid ? 1 : 2;
+    return p.mid ? 1 : 2;
 }
 
 extern "C" int milo_w3lr_gemm(const milo_half* X, int64_t M, int64_t N, int64_t K, const void* q3,
@@ -242,8 +245,7 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
     w.V = reinterpret_cast<const f16*>(V);
     w.r = r;
     w.flags = flags;
-    const GemmPlan plan = plan_gemm(M, N, K, r, flags);
-    if (plan.decode) {
+    if (gemm_takes_decode(M, N, K, r)) {
         // 32-bit buffer offsets in the decode kernel
         if ((uint64_t)M * K * 2 >= 0xFFFFFFF0ull || ((uint64_t)r + 128) * K * 2 >= 0xFFFFFFF0ull ||
             (uint64_t)N * (uint64_t)(r > 0 ? r : 1) * 2 >= 0xFFFFFFF0ull)
@@ -253,6 +255,7 @@ extern "C" int milo_w3lr_gemm_flags(const milo_half* X, int64_t M, int64_t N, in
         da.w = w; da.Y = reinterpret_cast<f16*>(Y);
         return launch_decode(da, workspace, workspace_bytes, stream);
     }
+    const GemmPlan plan = plan_gemm(M, N, K, r, flags);
     char* ws = reinterpret_cast<char*>(workspace);
     uint32_t* ctrl = reinterpret_cast<uint32_t*>(ws);
     const size_t flags_behind = gemm_flags_behind(M);
