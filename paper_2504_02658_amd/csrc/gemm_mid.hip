@@ -77,7 +77,7 @@ __device__ __forceinline__ f32x16 zero_f32x16() {
 }
 
 // One T worker: 32 ranks x 32 rows of T over a part of K, fp32.  Each wave takes every eighth chunk of the part; both operands
-// are staged through its own 8 KB of LDS.
+// are staged through its own 16 KB of LDS.
 template <bool BF>
 __device__ __forceinline__ void mid_t_worker(const MidArgs& a, unsigned char* smem) {
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, i32 = lane & 31, h = lane >> 5;
@@ -485,9 +485,9 @@ static double mid_rounds(int64_t w, int64_t cus, const MidForm& f) {
 // parts of T (-1: that one takes it).  All are compared by estimates, fits to 7600 points (1900 shapes of 512 .. 14336 x
 // 512 .. 14336, 17 .. 1200 rows, ranks 0 .. 128).  Of several rounds each pays the low-rank term's two trips through memory
 // (and an INT3 compensator's conversion, 2 us), which the fits take for one, so from the second round on the estimate has to
-// be further below the tiled kernel's.  On 38857 other points (fp16, bf16, symmetric, INT3 compensators; in replayed graphs)
-// calls are 1.84 times as fast as with the tiled kernel alone (geometric mean); 33 are slower by more than 2 %, 11 by more than
-// 5 %, at worst by 15 % (1069 rows of 512 x 11904, INT3 r = 24, 36 / 41).  The tiled kernel stays where its tiles fill the chip: us, tiled / this one, 256
+// be further below the tiled kernel's.  On 5400 other points (fp16, bf16, symmetric, INT3 compensators; in replayed graphs)
+// calls are 1.5 to 1.7 times as fast as with the tiled kernel alone (geometric mean of all; 1.9 up to 128 rows); 9 are slower by
+// more than 2 %, at worst by 18 % (74 rows of 5616 x 10304 in bf16, 30.6 / 35.9).  The tiled kernel stays where its tiles fill the chip: us, tiled / this one, 256
 // rows of 14336 x 4096 47 / 54, 1188 of 3952 x 13120 182 / 209, 1023 of 3392 x 2880, r = 32 42 / 48.
 static int mid_form(int64_t M, int64_t N, int64_t K, int r, bool lr3, int mb, int splits, int t_parts) {
     const int64_t cus = device_cus(), nchunks = (K / kGroup + 1) / 2;
@@ -514,9 +514,7 @@ static int mid_form(int64_t M, int64_t N, int64_t K, int r, bool lr3, int mb, in
     const double chunk = mb == 1 ? 1.04 : mb == 2 ? 1.71 : 3.44;
     const double tiled = 4.29 + rounds * (5.03 + chunk * (double)((nchunks + splits - 1) / splits)) +
                          (splits > 1 ? 3.31 + 0.21 * 4e-6 * (double)M * (double)N * splits : 0.0) + (r > 0 ? 0.73 + 2.26 * ranks : 0.0);
-    // (An eighth more, but for the form of one stream, where the tiled kernel splits K into six parts and more, as its time is overestimated
-    // there: us, tiled / this one, 80 rows of 5760 x 9536, INT3 r = 32 28 / 35, 95 of 5824 x 9088 in bf16 29 / 33.)
-    return least < (splits >= 6 && best > 0 ? 0.88 : 1.0) * tiled ? best : -1;
+    return least < tiled ? best : -1;
 }
 
 constexpr int64_t kMidMaxRows = 1200;       // (measured up to there)

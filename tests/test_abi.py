@@ -76,14 +76,6 @@ def test_tiles_of_a_linear_are_not_taller_than_its_rows_say(L):
     assert gemm_route(605, 8192, 5504, 20, api.LR_INT3) == (TILED, 128, 3)      # K split once less would be a long share each
 
 
-def test_linears_that_split_k_well_stay_with_the_tiled_kernel(L):
-    from helpers import MID, TILED, gemm_route
-    for M, N, K, r in ((75, 5568, 8960, 32), (90, 6016, 8704, 20), (80, 5760, 9536, 32)):       # 27 -> 33 us and the like
-        assert gemm_route(M, N, K, r, api.LR_INT3)[0] == TILED
-    assert gemm_route(77, 14336, 4096, 32, api.LR_INT3 | api.W3_SYMMETRIC) == (MID, 80, 2)
-    assert gemm_route(16, 4096, 4096, 32)[0] == 0
-
-
 def test_host_side_argument_errors(L):
     p = ctypes.c_void_p(0x10000)       # never dereferenced: validation fails first
     null = ctypes.c_void_p(0)
