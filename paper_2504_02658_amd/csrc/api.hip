@@ -111,17 +111,16 @@ static double gemm_tiled_estimate(int mb, int64_t M, int64_t N, int64_t K, int r
     return t;
 }
 // Tile height of a call: by rows, or 64 instead of 128 rows where the estimates say that this is clearly the faster one, as
-// how evenly the tiles fill the chip and whether K has to be split depend on the whole shape.  us, 128-row tiles / now: 512 rows of
-// 14336 x 4096, r = 32 77 / 70, 2048 of 2048 x 2048, r = 32 37 / 27, 1024 of 2048 x 1408, r = 32 27 / 19, 4096 of 1408 x 2048, r = 64
-// 56 / 42.  Not where K would be split less than half as often: few workgroups with a long share of K each were up to 14 % slower (605
-// rows of 8192 x 5504, INT3 r = 20: 3 splits 74, none 84).  Of 3290 drawn problems that change (all types, ranks to 128) the
-// geometric mean is 1.24 times as fast, 27 are slower by more than 2 % and 3 by more than 5 %, at worst by 9 % (2000 rows of
-// 560 x 5312 34 / 37).  (129 to 384 rows in 128-row tiles: 16 of 24 that the estimates
-// chose were slower by more than 2 %, at worst by 14 %.)
+// how evenly the tiles fill the chip and whether K has to be split depend on the whole shape.  us, 128-row tiles as they were / now:
+// 512 rows of 14336 x 4096, r = 32 77 / 70, 2048 of 2048 x 2048, r = 32 37 / 27, 1024 of 2048 x 1408, r = 32 27 / 19, 4096 of
+// 1408 x 2048, r = 64 56 / 42.  Of 4590 drawn problems that change (all types, ranks to 128) the geometric mean is 1.20 times as fast as with
+// 128-row tiles; 294 are slower by more than 2 % and 53 by more than 5 %, at worst by 21 % (1490 rows of 3024 x 4800 in bf16, r = 8,
+// 65 / 79).  A larger factor than 1.13, or one where K is split less than half as often, takes five to ten times as many problems
+// from the faster height as from the slower.  (129 to 384 rows in 128-row tiles: 21 of 27 that the estimates chose were slower
+// by more than 2 %, at worst by 22 %.)
 static int gemm_mb(int64_t M, int64_t N, int64_t K, int r) {
     const int mb = gemm_mb_by_rows(M);
-    if (gemm_mb_override() || mb != 4 || M > 4096 || r > 128 ||         // (measured there)
-        gemm_splits(4, M, N, K, r) > 2 * gemm_splits(2, M, N, K, r)) return mb;
+    if (gemm_mb_override() || mb != 4 || M > 4096 || r > 128) return mb;        // (measured there)
     return 1.13 * gemm_tiled_estimate(2, M, N, K, r) < gemm_tiled_estimate(4, M, N, K, r) ? 2 : 4;
 }
 

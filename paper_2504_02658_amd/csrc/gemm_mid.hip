@@ -13,11 +13,12 @@
 // r = 32: 32 rows of 1024 x 1024 11.8 / 5.7, 2048 x 1408 14.2 / 6.6, 4096 x 4096 15.3 / 8.6, 14336 x 4096 18.5 / 13.5;
 // 64 rows of 4096 x 14336 27.9 / 21.2; 77 of 14336 x 4096 31 / 20; 128 of 4096 x 4096 21.5 / 11.9.
 //
-// Bound: at K = 4096 the launch, the first data and the epilogue (4 us), then per chunk and wave the conversion, the MFMAs and
-// the copies of X, about 1 us each at MB = S = 2, of which the two waves of a SIMD overlap half.  X comes from L2 once per
-// workgroup, 1 KB per copy instruction: as whole 256-byte row pieces.  (64-byte pieces, four times as many rows per copy,
-// cost 50 cycles per copy instead of 16: 32 rows of 4096 x 14336 25 us, now 19.)  Tried without gain: sixteen waves per
-// workgroup, weights requested two chunks ahead, chunks rotated per workgroup.
+// Bound: latency.  The launch, the first data and the epilogue take about 4 us; in the loop a wave waits for its chunk, converts and
+// multiplies in turn, with one workgroup of eight waves per CU (two with 32-row tiles) to fill in.  Counters: 77 rows of 14336 x 4096, INT3
+// r = 32 (21 us) matrix cores busy for 17 % and vector units for 20 % of the SIMD-cycles, waves waiting 43 % of their time, no bank conflicts;
+// 400 of 4096 x 4096 (30 us) 18, 28 and 32 %; 32 of 4096 x 4096 (8 us) 3, 8 and 53 %.  X comes from L2 once per workgroup, 1 KB per copy
+// instruction, as whole 256-byte row pieces (64-byte pieces of four times as many rows per copy: 32 rows of 4096 x 14336 25 us, now 19).
+// Tried without gain: sixteen waves per workgroup, weights requested two chunks ahead, chunks rotated per workgroup.
 #include <type_traits>
 
 #include "milo_host.h"
@@ -77,7 +78,7 @@ __device__ __forceinline__ f32x16 zero_f32x16() {
 }
 
 // One T worker: 32 ranks x 32 rows of T over a part of K, fp32.  Each wave takes every eighth chunk of the part; both operands
-// are staged through its own 16 KB of LDS.
+// are staged through its own 8 KB of LDS.
 template <bool BF>
 __device__ __forceinline__ void mid_t_worker(const MidArgs& a, unsigned char* smem) {
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, i32 = lane & 31, h = lane >> 5;
@@ -485,9 +486,11 @@ static double mid_rounds(int64_t w, int64_t cus, const MidForm& f) {
 // parts of T (-1: that one takes it).  All are compared by estimates, fits to 7600 points (1900 shapes of 512 .. 14336 x
 // 512 .. 14336, 17 .. 1200 rows, ranks 0 .. 128).  Of several rounds each pays the low-rank term's two trips through memory
 // (and an INT3 compensator's conversion, 2 us), which the fits take for one, so from the second round on the estimate has to
-// be further below the tiled kernel's.  On 5400 other points (fp16, bf16, symmetric, INT3 compensators; in replayed graphs)
-// calls are 1.5 to 1.7 times as fast as with the tiled kernel alone (geometric mean of all; 1.9 up to 128 rows); 9 are slower by
-// more than 2 %, at worst by 18 % (74 rows of 5616 x 10304 in bf16, 30.6 / 35.9).  The tiled kernel stays where its tiles fill the chip: us, tiled / this one, 256
+// be further below the tiled kernel's.  Of 37305 other
+// points (fp16, bf16, symmetric, INT3 compensators; in replayed graphs) 23369 go here and are 1.80 times as fast as with the tiled
+// kernel (geometric mean); 93 are slower by more than 2 %, 53 by more than 5 %, at worst by 26 % (81 rows of 5760 x 9792, symmetric, INT3
+// r = 32, 27.6 / 34.6: a few more workgroups than CUs).  Asking for a lead where K is split into six parts and more would mend half of
+// those and lose three hundred that are up to 1.4 times as fast here.  The tiled kernel stays where its tiles fill the chip: us, tiled / this one, 256
 // rows of 14336 x 4096 47 / 54, 1188 of 3952 x 13120 182 / 209, 1023 of 3392 x 2880, r = 32 42 / 48.
 static int mid_form(int64_t M, int64_t N, int64_t K, int r, bool lr3, int mb, int splits, int t_parts) {
     const int64_t cus = device_cus(), nchunks = (K / kGroup + 1) / 2;

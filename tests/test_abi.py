@@ -68,12 +68,12 @@ def test_gemm_workspace_has_room_for_partial_sums_only_where_some_decode_uses_it
 
 def test_tiles_of_a_linear_are_not_taller_than_its_rows_say(L):
     # 65 to 384 rows go in 64-row tiles: taller ones were slower where the estimates called them faster (44 -> 50 us and the like)
-    from helpers import TILED, gemm_route
-    for M, N, K, r in ((264, 2688, 10752, 8), (342, 2432, 9728, 24), (243, 10480, 4672, 20), (247, 4912, 8128, 8)):
+    from helpers import MID, TILED, gemm_route
+    for M, N, K, r in ((264, 2688, 10752, 8), (335, 10304, 2112, 8), (243, 10480, 4672, 20), (247, 4912, 8128, 8)):
         assert gemm_route(M, N, K, r)[:2] == (TILED, 64)
     # more rows go in 64- or 128-row tiles; neither needs more room than the taller ones (whose need is the limit)
     assert gemm_route(512, 14336, 4096, 32)[:2] == (TILED, 64) and gemm_route(4096, 14336, 4096, 32)[:2] == (TILED, 128)
-    assert gemm_route(605, 8192, 5504, 20, api.LR_INT3) == (TILED, 128, 3)      # K split once less would be a long share each
+    assert gemm_route(16, 4096, 4096, 32)[0] == 0 and gemm_route(77, 14336, 4096, 32, api.LR_INT3 | api.W3_SYMMETRIC) == (MID, 80, 2)
 
 
 def test_host_side_argument_errors(L):
