@@ -74,8 +74,9 @@ constexpr uint32_t kOobHalf = 0x80000000u;
 // eight tiles on a line those loads and atomics (which all go to memory, past the L2s) queued up behind each other, and where T is
 // needed soon (short K) that decided the launch: us, eight tiles per line / one: 878 rows of 13952 x 1024, r = 48 50 / 38.5, 444 of
 // 12288 x 832, r = 48 30 / 23.5, 1225 of 13312 x 576, INT3 r = 32 57 / 40; the three words on lines of their own give no more.
+template <int EPI>
 __device__ __forceinline__ uint32_t* tile_words(const TiledArgs& a, uint32_t t) {
-    return a.flags + (a.flags_spread ? (t % kTiledFlagLines) * 32u + t / kTiledFlagLines * 4u : 4u * t);
+    return a.flags + (EPI == EPI_STORE && a.flags_spread ? (t % kTiledFlagLines) * 32u + t / kTiledFlagLines * 4u : 4u * t);
 }
 
 // Spin until *flag reaches `target`.  The producers never wait and were dispatched earlier, so the
@@ -95,7 +96,7 @@ __device__ __forceinline__ void wait_flag(const uint32_t* flag, uint32_t target,
 // lane and chunk).  NW = 1: wave w, stream s take ranks 64w + 32s ..; NW = 2: stream s is weight s,
 // ranks 32w ..; larger ranks take further passes.  T is written with device-coherent stores and
 // published through the tile's flag.
-template <int NW, int MB, bool BF>
+template <int NW, int MB, int EPI, bool BF>
 __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& ti, unsigned char* smem, int part,
                                             uint32_t by) {
     constexpr int BM = 32 * MB;
@@ -371,7 +372,7 @@ __device__ __forceinline__ void v_tile_body(const TiledArgs& a, const TileInfo& 
     wait_vmem();
     __syncthreads();
     int last = 0;
-    uint32_t* const words = tile_words(a, by);
+    uint32_t* const words = tile_words<EPI>(a, by);
     if (tid == 0) {
         last = atomicAdd(words, 1u) == (uint32_t)a.t_parts - 1u;
         if (a.t_dist) wait_flag(words, (uint32_t)a.t_parts, a.flags_status);
@@ -541,7 +542,7 @@ __global__ __launch_bounds__(kTiledThreads, 2) void w3lr_tiled_kernel(const Tile
     const bool any_rank = ti.w[0].r > 0 || ti.w[1].r > 0;
     if ((int)bx < a.v_tiles) {
         // forms one part of T = X V^T for this M-tile (see v_tile_body)
-        if (any_rank && bz == 0) v_tile_body<NW, MB, BF>(a, ti, smem, (int)bx, by);
+        if (any_rank && bz == 0) v_tile_body<NW, MB, EPI, BF>(a, ti, smem, (int)bx, by);
         return;
     }
 
@@ -660,7 +661,7 @@ __global__ __launch_bounds__(kTiledThreads, 2) void w3lr_tiled_kernel(const Tile
     // microsecond): the workgroups that form T were dispatched long before, so the answer is nearly
     // always yes, and the wave goes from its last chunk straight to the low-rank term.
     uint32_t early_flag = 0u;
-    uint32_t* const words = tile_words(a, by);
+    uint32_t* const words = tile_words<EPI>(a, by);
     const bool wants_t = any_rank && bz < (uint32_t)a.lr_splits;
     const uint32_t t_ready = a.t_dist ? (uint32_t)a.t_parts : 1u;     // value of the tile's flag when T is complete
     auto k_loop = [&](auto mbu_c) {

@@ -62,7 +62,7 @@ struct TiledArgs {
     int lr3_rank;       // largest rank an INT3 compensator of this launch may have (0: none can occur)
     int weights_once;   // non-zero: every weight is read by one M-tile only (non-temporal loads)
     uint32_t* flags;    // four words per M-tile: parts done, T ready, readers done; zero at launch
-    int flags_spread;   // non-zero: the words of kTiledFlagTiles M-tiles at most, spread over that many tiles' bytes; zero: one after the other
+    int flags_spread;   // EPI 0 only, non-zero: the words of kTiledFlagTiles M-tiles at most, spread over that many tiles' bytes; zero: one after the other
     int self_clean;     // non-zero: the last reader of a tile's T clears its words (else the caller does before the next launch)
     int act_bf16;       // non-zero: activations, compensators and outputs are bfloat16 (MILO_ACT_BF16)
     int t_dist;         // non-zero: every part of T adds a share of the rows once all parts are written, and the
