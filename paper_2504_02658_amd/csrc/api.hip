@@ -115,8 +115,8 @@ static double gemm_tiled_estimate(int mb, int64_t M, int64_t N, int64_t K, int r
 // 512 rows of 14336 x 4096, r = 32 77 / 70, 2048 of 2048 x 2048, r = 32 37 / 27, 1024 of 2048 x 1408, r = 32 27 / 19, 4096 of
 // 1408 x 2048, r = 64 56 / 42.  Of 4590 drawn problems that change (all types, ranks to 128) the geometric mean is 1.20 times as fast as with
 // 128-row tiles; 294 are slower by more than 2 % and 53 by more than 5 %, at worst by 21 % (1490 rows of 3024 x 4800 in bf16, r = 8,
-// 65 / 79).  A larger factor than 1.13, or one where K is split less than half as often, takes five to ten times as many problems
-// from the faster height as from the slower.  (129 to 384 rows in 128-row tiles: 21 of 27 that the estimates chose were slower
+// 65 / 79).  A larger factor than 1.13 takes three to seven times as many problems from the faster height as from the slower, and one
+// for problems whose K would be split less than half as often twice as many.  (129 to 384 rows in 128-row tiles: 21 of 27 that the estimates chose were slower
 // by more than 2 %, at worst by 22 %.)
 static int gemm_mb(int64_t M, int64_t N, int64_t K, int r) {
     const int mb = gemm_mb_by_rows(M);
