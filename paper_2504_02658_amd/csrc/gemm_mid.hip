@@ -486,12 +486,12 @@ static double mid_rounds(int64_t w, int64_t cus, const MidForm& f) {
 // parts of T (-1: that one takes it).  All are compared by estimates, fits to 7600 points (1900 shapes of 512 .. 14336 x
 // 512 .. 14336, 17 .. 1200 rows, ranks 0 .. 128).  Of several rounds each pays the low-rank term's two trips through memory
 // (and an INT3 compensator's conversion, 2 us), which the fits take for one, so from the second round on the estimate has to
-// be further below the tiled kernel's.  Of 37305 other
-// points (fp16, bf16, symmetric, INT3 compensators; in replayed graphs) 23369 go here and are 1.80 times as fast as with the tiled
-// kernel (geometric mean); 93 are slower by more than 2 %, 53 by more than 5 %, at worst by 26 % (81 rows of 5760 x 9792, symmetric, INT3
-// r = 32, 27.6 / 34.6: a few more workgroups than CUs).  Asking for a lead of an eighth where K is split into six parts and more
-// would mend fifty and lose four hundred that are up to 1.4 times as fast here.  The tiled kernel stays where its tiles fill the chip: us, tiled / this one, 256
-// rows of 14336 x 4096 47 / 54, 1188 of 3952 x 13120 182 / 209, 1023 of 3392 x 2880, r = 32 42 / 48.
+// be further below the tiled kernel's.  Of 37305 other points (fp16, bf16, symmetric, INT3 compensators; in replayed graphs)
+// 23369 go here and are 1.80 times as fast as with the tiled kernel (geometric mean); 93 are slower by more than 2 %, 53 by more
+// than 5 %, at worst by 26 % (81 rows of 5760 x 9792, symmetric, INT3 r = 32, 27.6 / 34.6: a few more workgroups than CUs).
+// Asking for a lead of an eighth where K is split into six parts and more would mend fifty and lose four hundred that are up to
+// 1.4 times as fast here.  The tiled kernel stays where its tiles fill the chip: us, tiled / this one, 256 rows of 14336 x 4096
+// 47 / 54, 1188 of 3952 x 13120 182 / 209, 1023 of 3392 x 2880, r = 32 42 / 48.
 static int mid_form(int64_t M, int64_t N, int64_t K, int r, bool lr3, int mb, int splits, int t_parts) {
     const int64_t cus = device_cus(), nchunks = (K / kGroup + 1) / 2;
     const int64_t workers = r > 0 ? mid_rank_items(M, r) * mid_t_parts(M, K, r) : 0;
